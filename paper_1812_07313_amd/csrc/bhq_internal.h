@@ -256,6 +256,9 @@ struct TreeParams {
     // offsets.
     int64_t cap_p = 0, cap_c = 0;
     int64_t slot_bytes = 0;  // upper bound on the slot memory of that mode
+    // Cells a group may open in the level walk's LDS (0: unknown; < 0: a
+    // group of an earlier build of this kind opened too many)
+    int cap_o = 0;
     // Depth (levels) and cell count of an earlier build of similar input:
     // the levels are then built without host synchronisation (0: unknown).
     int spec_levels = 0;
@@ -278,6 +281,10 @@ inline int64_t slot_memory_bound(int64_t njp, int64_t njc)
 {
     return 16 * (njp + njc) + ((int64_t)256 << 20);
 }
+
+// Cells a group may open in the level walk, whose LDS holds kOctBytes for
+// each: at a first build, and at most (64 KiB less the kernel's other LDS).
+constexpr int kOctFirst = 1024, kOctMost = 4080, kOctBytes = 16;
 
 // Builder working memory, kept between builds of one context.
 enum TreeBuf {
@@ -306,6 +313,9 @@ struct TreeOut {
     int64_t ng = 0, njp = 0, njc = 0, ncell = 0;
     // longest particle and cell list of a group; whether one walk sufficed
     int64_t max_p = 0, max_c = 0;
+    // most cells opened by a group in the level walk; whether they outgrew it
+    int64_t max_o = 0;
+    bool oct_full = false;
     bool one_walk = false;
     // one walk: jp_idx / jc_idx hold the per-group slots of these sizes
     int64_t slot_p = 0, slot_c = 0;

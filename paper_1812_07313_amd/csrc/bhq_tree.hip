@@ -67,7 +67,7 @@ constexpr int kBboxBlocks = 1024;
 struct alignas(64) WCell {
     double cx, cy, cz, side;
     double mx, my, mz;
-    uint64_t key;
+    double pad;
 };
 struct alignas(16) WLink {
     int32_t first, count, child0, nd;
@@ -513,13 +513,13 @@ __device__ __forceinline__ double abs_min_image(double v, double box)
     return a;
 }
 
-__device__ __forceinline__ bool contains(uint64_t ckey, int cdepth, uint64_t gkey,
-                                         int gdepth)
+// Whether the cell holds the group: no deeper than it, and its particles
+// include the group's (cells of one depth are disjoint, so the cell is then
+// the group's ancestor at that depth, or the group).
+__device__ __forceinline__ bool contains(const WLink &C, const WLink &G)
 {
-    if (cdepth > gdepth) return false;
-    const int sh = 3 * (kMaxDepth - cdepth);
-    if (sh >= 64) return true;
-    return (ckey >> sh) == (gkey >> sh);
+    return (C.nd >> 8) <= (G.nd >> 8) && C.first <= G.first &&
+           C.first + C.count >= G.first + G.count;
 }
 
 __global__ __launch_bounds__(kBlock) void k_walk_cells(Cells C, int32_t ncell,
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(kBlock) void k_walk_cells(Cells C, int32_t ncell,
     w.mx = pc[c].x;
     w.my = pc[c].y;
     w.mz = pc[c].z;
-    w.key = C.key[c];
+    w.pad = 0.0;
     wc[c] = w;
     WLink l;
     l.first = C.first[c];
@@ -561,7 +561,9 @@ struct WalkArgs {
     int64_t *jp_cnt, *jc_cnt;          // count pass
     const int64_t *jp_off, *jc_off;    // fill pass
     int32_t *jp_idx, *jc_idx;
-    int *flag;                         // set if a stack would overflow
+    int *flag;                         // set if a stack (1) or the level walk's
+                                       // octets (2) would overflow
+    int *most;                         // most octets of a group in the level walk
     int64_t cap_p, cap_c;              // slot sizes of the one-walk mode
     int frames;                        // frame stack depth: levels of the tree
     const double *gbox;                // [6 ng] lo, hi of each group's particles
@@ -576,14 +578,13 @@ struct WalkArgs {
 //                                        opened leaf)
 //   opened internal cell                {-2 - child0, nchild}
 __device__ __forceinline__ int2 classify(const WalkArgs &W, int32_t id, const WCell &G,
-                                         int gdepth, const double *gb)
+                                         const WLink &GL, const double *gb)
 {
     const WCell C = W.wc[id];
     const WLink L = W.wl[id];
-    const int cdepth = L.nd >> 8;
     const double box = W.box;
     const double gc[3] = {G.cx, G.cy, G.cz};
-    if (!contains(C.key, cdepth, G.key, gdepth)) {
+    if (!contains(L, GL)) {
         if (W.rcut > 0.0) {
             const double cc[3] = {C.cx, C.cy, C.cz};
             double d2 = 0.0;
@@ -648,6 +649,210 @@ __device__ __forceinline__ int octet_sum(int v)
     return v;
 }
 
+// Centre and half widths of the box (lo, hi) of group gi's particles, with
+// the host builder's operations (zero without a cutoff).
+__device__ __forceinline__ void group_box(const WalkArgs &W, int64_t gi, double gb[6])
+{
+    for (int k = 0; k < 6; ++k) gb[k] = 0.0;
+    if (W.rdrop2 > 0.0)
+        for (int k = 0; k < 3; ++k) {
+            const double lo = W.gbox[6 * gi + k], hi = W.gbox[6 * gi + 3 + k];
+            gb[k] = 0.5 * (lo + hi);
+            gb[3 + k] = 0.5 * (hi - lo);
+        }
+}
+
+// Walk modes: count the entries; fill the lists at exact offsets; or fill
+// fixed slots of cap_p / cap_c entries per group and count (one walk).
+enum WalkMode { kWalkCount = 0, kWalkFill = 1, kWalkSlots = 2 };
+
+// Level walk: a block of NW waves walks one group breadth first.  Every
+// opened cell is an octet of lanes, one per child; all cells that a level
+// opens are classified together, so the chain of dependent loads is as long
+// as the tree is deep (the octet walk's is one per opened cell, some
+// hundreds).  Then two passes over the octets give every entry its place in
+// the depth-first, octant order: totals from the deepest level up, positions
+// from the root down.  Octets are numbered as they come up (LDS counter),
+// those opened by one octet in a row; the lists do not depend on the numbers.
+// LDS keeps 16 B per octet, so that occupancy is not bound by it: the first
+// child's id, the number of the first octet opened (16 bits) over the
+// children's kinds (2 bits each), and the totals, replaced by the octet's
+// position on the way down.  `cap` octets fit: a group that opens more sets
+// *W.flag = 2 (its other cells are left out) and the host walks again with
+// the octet walk.
+// A rebuild's walk took 0.26 ms on the cube of 2^20 (0.75 with the octet
+// walk), 3.3 on the 2^24 lattice at ncrit 128 (4.6) and 0.042 on a Plummer
+// sphere of 16,384 (0.65: 989 groups, each a chain of about 200 openings).
+// What is left is the classification's FP64 arithmetic (VALU) on large inputs
+// and one chain of loads per level on small ones.  Keeping the children as
+// classified (72 B per octet) left two blocks per CU on inputs with a few
+// long groups: the clustered 2^22 walk was slower than the octet walk.
+constexpr uint32_t kNodeNone = 0, kNodeCell = 1, kNodeRun = 2, kNodeOpen = 3;
+
+template <int MODE, int NW>
+__global__ __launch_bounds__(64 * NW) void k_walk_level(const WalkArgs W, int cap)
+{
+    extern __shared__ int2 s_walk[];
+    int2 *s_sum = s_walk;                                // {cells, particles}
+    int32_t *s_c0 = reinterpret_cast<int32_t *>(s_walk + cap);
+    uint32_t *s_kind = reinterpret_cast<uint32_t *>(s_c0 + cap);  // first: nchild
+    __shared__ int s_lev[kFrames + 1];
+    __shared__ int s_cnt;
+    const int t = threadIdx.x;
+    const int k = t & (kOct - 1);
+    const int o = t / kOct;
+    const unsigned per = gridDim.x / kXcds;  // as in k_walk
+    const int64_t gi = (int64_t)(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+    if (gi >= W.ng) return;
+    const int32_t gid = W.groups[gi];
+    const WCell G = W.wc[gid];
+    const WLink GL = W.wl[gid];
+    double gb[6];
+    group_box(W, gi, gb);
+    int64_t pb = 0, cb = 0, pe = 0, ce = 0;  // where this group's entries go
+    if (MODE == kWalkFill) {
+        pb = W.jp_off[gi];
+        cb = W.jc_off[gi];
+        pe = W.jp_off[gi + 1];
+        ce = W.jc_off[gi + 1];
+    } else if (MODE == kWalkSlots) {
+        pb = gi * W.cap_p;
+        cb = gi * W.cap_c;
+        pe = pb + W.cap_p;
+        ce = cb + W.cap_c;
+    }
+    const WLink R = W.wl[W.sys_root[W.cell_sys[gid]]];
+    if (R.child0 < 0) {
+        // a one-leaf tree: the root contains the group and is opened
+        if (MODE != kWalkCount)
+            for (int32_t j = t; j < R.count && pb + j < pe; j += 64 * NW)
+                W.jp_idx[pb + j] = R.first + j;
+        if (MODE != kWalkFill && t == 0) {
+            W.jp_cnt[gi] = R.count;
+            W.jc_cnt[gi] = 0;
+        }
+        return;
+    }
+    if (t == 0) {
+        s_c0[0] = R.child0;
+        s_kind[0] = (uint32_t)R.nd & 0xffu;
+        s_cnt = 1;
+    }
+    __syncthreads();
+    int lo = 0, hi = 1, nl = 0;
+    bool full = false;
+    while (hi > lo) {
+        if (t == 0) s_lev[nl] = lo;
+        for (int q = lo + o; q < hi; q += kOct * NW) {
+            const int32_t c0 = s_c0[q];
+            const int2 e = k < (int)s_kind[q] ? classify(W, c0 + k, G, GL, gb) : make_int2(-1, 0);
+            bool open = e.x <= -2;
+            const uint64_t bal = __ballot(open);
+            int ch = 0;  // octet of this lane's (opened) child, or the next one's
+            if (bal != 0) {
+                const int first = __builtin_ctzll(bal);
+                int base = 0;
+                if ((t & 63) == first) base = atomicAdd(&s_cnt, (int)__popcll(bal));
+                base = __builtin_amdgcn_readlane(base, first);
+                ch = base + (int)__builtin_amdgcn_mbcnt_hi(
+                                (uint32_t)(bal >> 32),
+                                __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+                if (open) {
+                    if (ch < cap) {
+                        s_c0[ch] = -2 - e.x;
+                        s_kind[ch] = (uint32_t)e.y;
+                    } else {
+                        full = true;
+                        open = false;
+                    }
+                }
+            }
+            const bool cell = e.x >= 0 && e.y == 0, run = e.x >= 0 && e.y > 0;
+            const uint32_t kind =
+                (cell ? kNodeCell : run ? kNodeRun : open ? kNodeOpen : kNodeNone) << (2 * k);
+            const int2 own = make_int2(octet_sum(cell ? 1 : 0), octet_sum(run ? e.y : 0));
+            const uint32_t kinds = (uint32_t)octet_sum((int)kind);
+            if (k == 0) {
+                s_kind[q] = kinds | (uint32_t)ch << 16;
+                s_sum[q] = own;
+            }
+        }
+        __syncthreads();
+        lo = hi;
+        hi = s_cnt < cap ? s_cnt : cap;
+        ++nl;
+        __syncthreads();
+    }
+    if (t == 0) s_lev[nl] = hi;
+    if (full) *W.flag = 2;
+    // octet of lane k's child among those opened by an octet of these kinds
+    auto child_octet = [&](uint32_t kinds) -> int {
+        const uint32_t m = kinds & (kinds >> 1) & 0x5555u & ((1u << (2 * k)) - 1u);
+        return (int)(kinds >> 16) + __popc(m);
+    };
+    __syncthreads();
+    for (int l = nl - 2; l >= 0; --l) {  // the deepest level opens nothing
+        const int b = s_lev[l], f = s_lev[l + 1];
+        for (int q = b + o; q < f; q += kOct * NW) {
+            const uint32_t kinds = s_kind[q];
+            int2 v = make_int2(0, 0);
+            if (((kinds >> (2 * k)) & 3u) == kNodeOpen) v = s_sum[child_octet(kinds)];
+            const int2 sum = make_int2(octet_sum(v.x), octet_sum(v.y));
+            if (k == 0) {
+                const int2 own = s_sum[q];
+                s_sum[q] = make_int2(own.x + sum.x, own.y + sum.y);
+            }
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        if (MODE != kWalkFill) {
+            W.jc_cnt[gi] = s_sum[0].x;
+            W.jp_cnt[gi] = s_sum[0].y;
+            // most octets of a group, for the next build's LDS (the plain
+            // read spares most groups the atomic)
+            if (*(volatile int *)W.most < hi) atomicMax(W.most, hi);
+        }
+        s_sum[0] = make_int2(0, 0);
+    }
+    if (MODE == kWalkCount) return;
+    __syncthreads();
+    for (int l = 0; l < nl; ++l) {
+        const int b = s_lev[l], f = s_lev[l + 1];
+        for (int q = b + o; q < f; q += kOct * NW) {
+            const int2 at = s_sum[q];
+            const uint32_t kinds = s_kind[q], kind = (kinds >> (2 * k)) & 3u;
+            const int32_t id = s_c0[q] + k;
+            int32_t first = 0;
+            int2 v = make_int2(kind == kNodeCell ? 1 : 0, 0);
+            int ch = 0;
+            if (kind == kNodeOpen) {
+                ch = child_octet(kinds);
+                v = s_sum[ch];
+            } else if (kind == kNodeRun) {
+                const WLink L = W.wl[id];
+                first = L.first;
+                v.y = L.count;
+            }
+            const int c0 = at.x + octet_scan(v.x, k) - v.x;
+            const int p0 = at.y + octet_scan(v.y, k) - v.y;
+            if (kind == kNodeOpen) {
+                s_sum[ch] = make_int2(c0, p0);
+            } else if (kind == kNodeCell) {
+                if (cb + c0 < ce) W.jc_idx[cb + c0] = id;
+            } else if (kind == kNodeRun) {
+                // the entries that fit in the group's segment (none past
+                // it: a slot overflow is detected from the counts)
+                const int64_t w = pb + p0;
+                const int32_t nw = (int32_t)(pe - w < (int64_t)v.y ? pe - w : v.y);
+                int32_t *dst = W.jp_idx + w;
+                for (int32_t j = 0; j < nw; ++j) dst[j] = first + j;
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // Octet walk: the 8 lanes of an octet walk one group.  Opening an internal
 // cell loads and classifies all of its children at once, one per lane, and
 // pushes them as a frame; a frame is emitted in octant order up to its next
@@ -659,11 +864,9 @@ __device__ __forceinline__ int octet_sum(int v)
 // LDS for the return from a subtree, and the frame's child count and cursor
 // are stored once per octet, written by all 8 lanes with the same value.
 // Control flow is uniform within an octet.  The fill pass writes only
-// inside the group's own segments of the lists.
-// Walk modes: count the entries; fill the lists at exact offsets; or fill
-// fixed slots of cap_p / cap_c entries per group and count (one walk).
-enum WalkMode { kWalkCount = 0, kWalkFill = 1, kWalkSlots = 2 };
-
+// inside the group's own segments of the lists.  Its memory is bounded by
+// the tree's depth alone: it takes the groups that open more cells than the
+// level walk's LDS holds.
 template <int MODE>
 __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
 {
@@ -686,16 +889,9 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
     if (gi >= W.ng) return;  // whole octets leave; no block-wide synchronisation below
     const int32_t gid = W.groups[gi];
     const WCell G = W.wc[gid];
-    const int gdepth = W.wl[gid].nd >> 8;
-    // centre and half widths of the box (lo, hi) of the group's particles,
-    // with the host builder's operations
-    double gb[6] = {0, 0, 0, 0, 0, 0};
-    if (W.rdrop2 > 0.0)
-        for (int k = 0; k < 3; ++k) {
-            const double lo = W.gbox[6 * gi + k], hi = W.gbox[6 * gi + 3 + k];
-            gb[k] = 0.5 * (lo + hi);
-            gb[3 + k] = 0.5 * (hi - lo);
-        }
+    const WLink GL = W.wl[gid];
+    double gb[6];
+    group_box(W, gi, gb);
     int64_t np = 0, nc = 0;
     constexpr bool FILL = MODE != kWalkCount;
     int64_t pb = 0, cb = 0, pe = 0, ce = 0;  // where this group's entries go
@@ -722,7 +918,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
         np = R.count;
     } else {
         nch = R.nd & 0xff;
-        e = k < nch ? classify(W, R.child0 + k, G, gdepth, gb) : make_int2(-1, 0);
+        e = k < nch ? classify(W, R.child0 + k, G, GL, gb) : make_int2(-1, 0);
         s_ent[0][t] = e;
         sp = 1;
     }
@@ -782,7 +978,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
             cur = hdr >> 8;
         }
         if (n2 < 0) break;
-        e = k < n2 ? classify(W, c0 + k, G, gdepth, gb) : make_int2(-1, 0);
+        e = k < n2 ? classify(W, c0 + k, G, GL, gb) : make_int2(-1, 0);
         s_ent[sp][t] = e;
         nch = n2;
         cur = 0;
@@ -846,13 +1042,15 @@ __global__ __launch_bounds__(kBlock) void k_compact(int64_t ng, const int64_t *o
 }
 
 // stats[0], stats[1] = list totals (the scans' last entries), stats[4] =
-// the walk's overflow flag; stats[2], stats[3] hold the longest lists.
+// the walk's overflow flag, stats[5] the most octets of a group in a level
+// walk; stats[2], stats[3] hold the longest lists.
 __global__ void k_list_stats(int64_t ng, const int64_t *jp_off, const int64_t *jc_off,
                              const int *flag, int64_t *stats)
 {
     stats[0] = jp_off[ng];
     stats[1] = jc_off[ng];
-    stats[4] = *flag;
+    stats[4] = flag[0];
+    stats[5] = flag[2];
 }
 
 }  // namespace
@@ -1407,9 +1605,47 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     W.jp_cnt = B[T_JPCNT].as<int64_t>();
     W.jc_cnt = B[T_JCCNT].as<int64_t>();
     W.flag = B[T_FLAG].as<int>();
+    W.most = W.flag + 2;
     // one frame per level below the root: enough for the deepest opened cell
     W.frames = std::max(1, std::min(kFrames, (int)level.size() - 1));
     const size_t walk_lds = (size_t)W.frames * (kWalkBlock * sizeof(int2) + kWalkBlock / kOct * 4);
+    // octets the level walk's LDS holds; 0: octet walk
+    int oct_cap = std::min(P.cap_o > 0 ? P.cap_o : (P.cap_o == 0 ? kOctFirst : 0), kOctMost);
+    // Waves per group of the level walk: two, or four when there are too few
+    // groups to fill the chip (2048: 16 waves per CU either way), where the
+    // time is the chain of one group.  With one, two and four waves a rebuild's
+    // walk took 80, - and 42 us (Plummer sphere of 16,384, 989 groups), and
+    // force evaluations 15.2, 13.8 and 14.2 ms (clustered 2^22, whose longest
+    // groups end last with one wave) and TreePM steps 31.0, 31.1 and 32.3 ms
+    // (2^24 lattice).
+    const bool wide = ng <= 2048;
+    auto walk = [&](int mode) -> bool {
+        if (oct_cap > 0) {
+            const size_t lds = (size_t)oct_cap * kOctBytes;
+            const dim3 g((unsigned)((ng + kXcds - 1) / kXcds * kXcds));
+            auto launch = [&](auto two, auto four) {
+                if (wide)
+                    hipLaunchKernelGGL(four, g, dim3(256), lds, s, W, oct_cap);
+                else
+                    hipLaunchKernelGGL(two, g, dim3(128), lds, s, W, oct_cap);
+            };
+            if (mode == kWalkCount)
+                launch(k_walk_level<kWalkCount, 2>, k_walk_level<kWalkCount, 4>);
+            else if (mode == kWalkFill)
+                launch(k_walk_level<kWalkFill, 2>, k_walk_level<kWalkFill, 4>);
+            else
+                launch(k_walk_level<kWalkSlots, 2>, k_walk_level<kWalkSlots, 4>);
+        } else {
+            const dim3 g(walk_blocks(ng)), b(kWalkBlock);
+            if (mode == kWalkCount)
+                hipLaunchKernelGGL(k_walk<kWalkCount>, g, b, walk_lds, s, W);
+            else if (mode == kWalkFill)
+                hipLaunchKernelGGL(k_walk<kWalkFill>, g, b, walk_lds, s, W);
+            else
+                hipLaunchKernelGGL(k_walk<kWalkSlots>, g, b, walk_lds, s, W);
+        }
+        return hip(hipGetLastError(), "walk");
+    };
     W.gbox = nullptr;
     if (W.rdrop2 > 0.0) {
         STEP(B[T_GBOX].reserve((size_t)ng * 6 * 8), "allocation");
@@ -1429,41 +1665,44 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         W.cap_c = P.cap_c;
         W.jp_idx = B[T_JPSLOT].as<int32_t>();
         W.jc_idx = B[T_JCSLOT].as<int32_t>();
-        hipLaunchKernelGGL(k_walk<kWalkSlots>, dim3(walk_blocks(ng)), dim3(kWalkBlock), walk_lds, s, W);
-        LAUNCHED("walk (slots)");
-    } else {
-        hipLaunchKernelGGL(k_walk<kWalkCount>, dim3(walk_blocks(ng)), dim3(kWalkBlock), walk_lds, s, W);
-        LAUNCHED("walk (count)");
     }
-    for (int pass = 0; pass < 2; ++pass) {
-        int64_t *cnt = pass ? B[T_JCCNT].as<int64_t>() : B[T_JPCNT].as<int64_t>();
-        int64_t *off = pass ? O.jc_off->as<int64_t>() : O.jp_off->as<int64_t>();
-        size_t st = 0;
-        STEP(hipcub::DeviceScan::ExclusiveSum(nullptr, st, cnt, off, (int)(ng + 1), s),
-             "scan size");
-        STEP(B[T_SORT].reserve(std::max(st, B[T_SORT].cap)), "allocation");
-        STEP(hipcub::DeviceScan::ExclusiveSum(B[T_SORT].p, st, cnt, off, (int)(ng + 1), s),
-             "scan");
+    int64_t hstats[6] = {0, 0, 0, 0, 0, 0};
+    for (;;) {
+        if (!walk(slots ? kWalkSlots : kWalkCount)) return fail();
+        for (int pass = 0; pass < 2; ++pass) {
+            int64_t *cnt = pass ? B[T_JCCNT].as<int64_t>() : B[T_JPCNT].as<int64_t>();
+            int64_t *off = pass ? O.jc_off->as<int64_t>() : O.jp_off->as<int64_t>();
+            size_t st = 0;
+            STEP(hipcub::DeviceScan::ExclusiveSum(nullptr, st, cnt, off, (int)(ng + 1), s),
+                 "scan size");
+            STEP(B[T_SORT].reserve(std::max(st, B[T_SORT].cap)), "allocation");
+            STEP(hipcub::DeviceScan::ExclusiveSum(B[T_SORT].p, st, cnt, off, (int)(ng + 1), s),
+                 "scan");
+        }
+        // list totals, longest lists and the walk's overflow flag: the host
+        // needs only these five numbers (the offsets stay on the device)
+        STEP(B[T_STATS].reserve(8 * sizeof(int64_t)), "allocation");
+        int64_t *stats = B[T_STATS].as<int64_t>();
+        for (int pass = 0; pass < 2; ++pass) {
+            const int64_t *cnt = pass ? B[T_JCCNT].as<int64_t>() : B[T_JPCNT].as<int64_t>();
+            size_t st = 0;
+            STEP(hipcub::DeviceReduce::Max(nullptr, st, cnt, stats + 2 + pass, (int)ng, s),
+                 "reduce size");
+            STEP(B[T_SORT].reserve(std::max(st, B[T_SORT].cap)), "allocation");
+            STEP(hipcub::DeviceReduce::Max(B[T_SORT].p, st, cnt, stats + 2 + pass, (int)ng, s),
+                 "reduce");
+        }
+        hipLaunchKernelGGL(k_list_stats, dim3(1), dim3(1), 0, s, ng, O.jp_off->as<int64_t>(),
+                           O.jc_off->as<int64_t>(), B[T_FLAG].as<int>(), stats);
+        LAUNCHED("list totals");
+        STEP(hipMemcpyAsync(hstats, stats, sizeof(hstats), hipMemcpyDeviceToHost, s), "copy");
+        STEP(hipStreamSynchronize(s), "sync");
+        if (hstats[4] != 2) break;
+        // a group opened more cells than the level walk's LDS holds
+        oct_cap = 0;
+        O.oct_full = true;
+        STEP(hipMemsetAsync(B[T_FLAG].p, 0, 64, s), "memset");
     }
-    // list totals, longest lists and the walk's overflow flag: the host
-    // needs only these five numbers (the offsets stay on the device)
-    STEP(B[T_STATS].reserve(8 * sizeof(int64_t)), "allocation");
-    int64_t *stats = B[T_STATS].as<int64_t>();
-    for (int pass = 0; pass < 2; ++pass) {
-        const int64_t *cnt = pass ? B[T_JCCNT].as<int64_t>() : B[T_JPCNT].as<int64_t>();
-        size_t st = 0;
-        STEP(hipcub::DeviceReduce::Max(nullptr, st, cnt, stats + 2 + pass, (int)ng, s),
-             "reduce size");
-        STEP(B[T_SORT].reserve(std::max(st, B[T_SORT].cap)), "allocation");
-        STEP(hipcub::DeviceReduce::Max(B[T_SORT].p, st, cnt, stats + 2 + pass, (int)ng, s),
-             "reduce");
-    }
-    hipLaunchKernelGGL(k_list_stats, dim3(1), dim3(1), 0, s, ng, O.jp_off->as<int64_t>(),
-                       O.jc_off->as<int64_t>(), B[T_FLAG].as<int>(), stats);
-    LAUNCHED("list totals");
-    int64_t hstats[5] = {0, 0, 0, 0, 0};
-    STEP(hipMemcpyAsync(hstats, stats, sizeof(hstats), hipMemcpyDeviceToHost, s), "copy");
-    STEP(hipStreamSynchronize(s), "sync");
     if (hstats[4]) {
         code = BHQ_E_RANGE;
         what = "walk stack overflow";
@@ -1497,9 +1736,10 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         W.jc_off = O.jc_off->as<int64_t>();
         W.jp_idx = O.jp_idx->as<int32_t>();
         W.jc_idx = O.jc_idx->as<int32_t>();
-        hipLaunchKernelGGL(k_walk<kWalkFill>, dim3(walk_blocks(ng)), dim3(kWalkBlock), walk_lds, s, W);
-        LAUNCHED("walk (fill)");
+        if (oct_cap > 0) oct_cap = std::max(1, (int)hstats[5]);
+        if (!walk(kWalkFill)) return fail();
     }
+    O.max_o = hstats[5];
     O.max_p = max_p;
     O.max_c = max_c;
 
