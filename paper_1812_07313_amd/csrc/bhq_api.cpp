@@ -166,9 +166,7 @@ struct bhq_ctx {
     int walk_oct = 0;
     double walk_theta = 0.0;
     int walk_ncrit = 0;
-    // depth and cell count of the last device-built tree
-    int tree_levels = 0;
-    int64_t tree_cells = 0;
+    int tree_levels = 0;  // levels of the last device-built tree
     int64_t build_info[3] = {0, 0, 0};
     uint64_t args_version = 0;  // bumped when device pointers/params change
     hipStream_t cap_stream = nullptr;
@@ -1827,7 +1825,6 @@ static int device_build(bhq_ctx *ctx, int64_t nsys, const int64_t *sys_off,
     const bool same = ctx->walk_theta == theta && ctx->walk_ncrit == ncrit;
     P.cap_o = ctx->walk_oct >= 0 ? ctx->walk_oct : (same ? -1 : 0);
     P.spec_levels = ctx->tree_levels;
-    P.spec_cells = ctx->tree_cells;
     P.slot_bytes = ctx->ng >= 0 ? bhq::slot_memory_bound(ctx->njp, ctx->njc) : 0;
     bhq::TreeOut O;
     O.i_off = &ctx->arr[A_IOFF];
@@ -1873,7 +1870,6 @@ static int device_build(bhq_ctx *ctx, int64_t nsys, const int64_t *sys_off,
     ctx->walk_theta = theta;
     ctx->walk_ncrit = ncrit;
     ctx->tree_levels = O.nlevels;
-    ctx->tree_cells = O.ncell;
     ctx->build_info[0] = O.one_walk ? 1 : 0;
     ctx->build_info[1] = O.max_p;
     ctx->build_info[2] = O.max_c;

@@ -259,10 +259,9 @@ struct TreeParams {
     // Cells a group may open in the level walk's LDS (0: unknown; < 0: a
     // group of an earlier build of this kind opened too many)
     int cap_o = 0;
-    // Depth (levels) and cell count of an earlier build of similar input:
-    // the levels are then built without host synchronisation (0: unknown).
+    // Levels of the tree of an earlier build of similar input: only the key
+    // bits that such a tree reads are sorted (0: unknown).
     int spec_levels = 0;
-    int64_t spec_cells = 0;
 };
 
 // Slot sizing of one-walk rebuilds.  A group's slot holds 1.25 times the
@@ -288,11 +287,10 @@ constexpr int kOctFirst = 1024, kOctMost = 4080, kOctBytes = 16;
 
 // Builder working memory, kept between builds of one context.
 enum TreeBuf {
-    T_KEY, T_KEY2, T_IDX0, T_SORT, T_BBOX, T_FLAG,
-    T_CX, T_CY, T_CZ, T_SIDE, T_FIRST, T_COUNT, T_CHILD0, T_NCHILD, T_PARENT,
-    T_DEPTH, T_CKEY, T_NCH, T_NOFF, T_GSTART, T_GROUPS, T_NSEL, T_WC, T_WL,
-    T_JPCNT, T_JCCNT, T_CSYS, T_SYSOFF, T_SYSOFF32, T_ROOTS, T_SYSROOT, T_LSC, T_PERM,
-    T_JPSLOT, T_JCSLOT, T_GBOX, T_LV, T_STATS,
+    T_KEY, T_KEY2, T_IDX0, T_IDX1, T_INFO, T_SORT, T_BBOX, T_FLAG, T_TABLE,
+    T_NCH, T_NOFF, T_PARENT, T_GSTART, T_GROUPS, T_GROOT, T_NSEL, T_WC, T_WL,
+    T_JPCNT, T_JCCNT, T_SYSOFF, T_SYSOFF32, T_ROOTS, T_LSC, T_LSN, T_SHIFT, T_BYLEVEL,
+    T_JPSLOT, T_JCSLOT, T_GBOX, T_STATS,
     T_COUNT_
 };
 

@@ -8,22 +8,20 @@
 //      independent systems one root per system from that system's box;
 //   2. a 63-bit key per particle by descending 21 levels (upper half along
 //      an axis iff the coordinate is >= the cell centre), then a stable
-//      radix sort by key (ties keep input order), segmented by system;
-//   3. cells breadth-first, one level per pass: a cell with more than nleaf
-//      particles above depth 21 gets one child per non-empty octant, found
-//      by binary search in the sorted keys; children are numbered in the
-//      order of their parents, then octants (the host's breadth-first ids);
-//      particles inside a leaf return to input order; a batch's cells are
-//      then renumbered system by system (each system's cells breadth first,
-//      the host's concatenation of independently built systems);
+//      radix sort by key (ties keep input order), system by system;
+//   3. cells: a cell with more than nleaf particles above depth 21 has one
+//      child per non-empty octant; all levels come from the sorted keys in
+//      one pass, numbered in the order of their parents, then octants (the
+//      host's breadth-first ids; a batch's system by system, the host's
+//      concatenation of independently built systems); particles inside a
+//      leaf return to input order;
 //   4. moments: leaves from their particles, parents from their children
 //      by the parallel-axis shift, deepest level first;
 //   5. groups: the largest cells with at most ncrit particles (or leaves),
 //      in depth-first order, which is the order of their first particle;
-//   6. lists: eight lanes per group walk the tree depth first (children in
-//      octant order, all children of an opened cell classified at once),
-//      once to count and once to fill.  A cell that does not
-//      contain the group is accepted iff side^2 < theta^2 d^2 (d: its
+//   6. lists in depth-first, octant order: a block per group walks the tree
+//      level by level, once to count and once to fill (a rebuild once, into
+//      slots).  A cell that does not contain the group is accepted iff side^2 < theta^2 d^2 (d: its
 //      centre of mass to the group cube; minimum image in a periodic box,
 //      where cells farther than rcut from the group are skipped, and
 //      accepted cells whose centre of mass lies at least rcut (1 + 2^-16)
@@ -37,7 +35,6 @@
 #include <hipcub/hipcub.hpp>
 
 #include <algorithm>
-#include <cmath>
 
 #include "bhq.h"
 #include "bhq_internal.h"
@@ -62,29 +59,61 @@ inline unsigned walk_blocks(int64_t ng)
 constexpr int kBlock = 256;
 constexpr int kBboxBlocks = 1024;
 
-// What the walk reads of a cell: geometry and centre of mass (64 B), then
-// the links (16 B; nchild in bits 0-7 and depth in bits 8-15 of .w).
+// A cell: geometry and centre of mass (64 B), then its particles
+// [first, end) and its children [child0, cend) (child0 < 0: a leaf).
 struct alignas(64) WCell {
     double cx, cy, cz, side;
     double mx, my, mz;
     double pad;
 };
 struct alignas(16) WLink {
-    int32_t first, count, child0, nd;
+    int32_t first, child0, end, cend;
 };
 
-struct Cells {
-    double *cx, *cy, *cz, *side;
-    int32_t *first, *count, *child0, *nchild, *parent, *depth, *sys;
-    uint64_t *key;
-};
+__device__ __forceinline__ int children(const WLink &L)
+{
+    return L.child0 < 0 ? 0 : L.cend - L.child0;
+}
 
 inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-// ---- 1. bounding box ------------------------------------------------------
+// ---- 1. input check, bounding box, root cubes --------------------------------
 
-__global__ __launch_bounds__(kBlock) void k_bbox_partial(const double *x, int64_t n,
-                                                         double *part)
+// Minimum and maximum per axis over the block's threads: lo, hi of thread t
+// in s[0..2][t], s[3..5][t]; the result in s[.][0].
+__device__ __forceinline__ void block_box(double (*s)[kBlock])
+{
+    __syncthreads();
+    for (int h = kBlock / 2; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h)
+            for (int a = 0; a < 3; ++a) {
+                const double l = s[a][threadIdx.x + h], u = s[3 + a][threadIdx.x + h];
+                if (l < s[a][threadIdx.x]) s[a][threadIdx.x] = l;
+                if (u > s[3 + a][threadIdx.x]) s[3 + a][threadIdx.x] = u;
+            }
+        __syncthreads();
+    }
+}
+
+// Root cube of the box s[.][0]: centre and side, with the host builder's
+// operations.
+__device__ __forceinline__ void root_cube(double (*s)[kBlock], double *root)
+{
+    double ext = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        root[a] = 0.5 * (s[a][0] + s[3 + a][0]);
+        const double e = s[3 + a][0] - s[a][0];
+        ext = ext < e ? e : ext;
+    }
+    root[3] = ext > 0.0 ? ext * (1.0 + 0x1p-20) : 1.0;
+}
+
+// Non-finite positions or masses set flag[0]; a softening that is not
+// finite and positive sets flag[1] (vector stores of 1).  The same pass over
+// the positions gives each block's bounding box (one system).
+__global__ __launch_bounds__(kBlock) void k_check(const double *x, const double *m,
+                                                  const double *eps2, int64_t n, int *flag,
+                                                  double *part)
 {
     __shared__ double s[6][kBlock];
     double lo[3], hi[3];
@@ -92,32 +121,34 @@ __global__ __launch_bounds__(kBlock) void k_bbox_partial(const double *x, int64_
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     const int64_t p0 = start < n ? start : 0;  // n >= 1
     for (int a = 0; a < 3; ++a) lo[a] = hi[a] = x[3 * p0 + a];
-    for (int64_t p = start; p < n; p += stride)
+    for (int64_t p = start; p < n; p += stride) {
+        double v[3];
         for (int a = 0; a < 3; ++a) {
-            const double v = x[3 * p + a];
-            lo[a] = v < lo[a] ? v : lo[a];
-            hi[a] = v > hi[a] ? v : hi[a];
+            v[a] = x[3 * p + a];
+            lo[a] = v[a] < lo[a] ? v[a] : lo[a];
+            hi[a] = v[a] > hi[a] ? v[a] : hi[a];
         }
+        if (!isfinite(v[0]) || !isfinite(v[1]) || !isfinite(v[2]) || !isfinite(m[p])) flag[0] = 1;
+        if (eps2 && !(isfinite(eps2[p]) && eps2[p] >= kMinEps2)) flag[1] = 1;
+    }
+    if (!part) return;
     for (int a = 0; a < 3; ++a) {
         s[a][threadIdx.x] = lo[a];
         s[3 + a][threadIdx.x] = hi[a];
     }
-    __syncthreads();
-    for (int h = kBlock / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h)
-            for (int a = 0; a < 3; ++a) {
-                const double l = s[a][threadIdx.x + h], u = s[3 + a][threadIdx.x + h];
-                if (l < s[a][threadIdx.x]) s[a][threadIdx.x] = l;
-                if (u > s[3 + a][threadIdx.x]) s[3 + a][threadIdx.x] = u;
-            }
-        __syncthreads();
-    }
+    block_box(s);
     if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = s[threadIdx.x][0];
 }
 
-__global__ __launch_bounds__(kBlock) void k_bbox_final(double *part, int nb)
+// The one system's root cube from the blocks' boxes, or [0, box)^3.
+__global__ __launch_bounds__(kBlock) void k_root(const double *part, int nb, double box,
+                                                 double *root)
 {
     __shared__ double s[6][kBlock];
+    if (box > 0.0) {
+        if (threadIdx.x < 4) root[threadIdx.x] = threadIdx.x < 3 ? 0.5 * box : box;
+        return;
+    }
     for (int a = 0; a < 6; ++a) s[a][threadIdx.x] = part[a];  // block 0
     for (int b = threadIdx.x; b < nb; b += kBlock)
         for (int a = 0; a < 3; ++a) {
@@ -125,39 +156,15 @@ __global__ __launch_bounds__(kBlock) void k_bbox_final(double *part, int nb)
             if (l < s[a][threadIdx.x]) s[a][threadIdx.x] = l;
             if (u > s[3 + a][threadIdx.x]) s[3 + a][threadIdx.x] = u;
         }
-    __syncthreads();
-    for (int h = kBlock / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h)
-            for (int a = 0; a < 3; ++a) {
-                const double l = s[a][threadIdx.x + h], u = s[3 + a][threadIdx.x + h];
-                if (l < s[a][threadIdx.x]) s[a][threadIdx.x] = l;
-                if (u > s[3 + a][threadIdx.x]) s[3 + a][threadIdx.x] = u;
-            }
-        __syncthreads();
-    }
-    __syncthreads();
-    if (threadIdx.x < 6) part[threadIdx.x] = s[threadIdx.x][0];
+    block_box(s);
+    if (threadIdx.x == 0) root_cube(s, root);
 }
 
-// Non-finite positions or masses set flag[0]; a softening that is not
-// finite and positive sets flag[1] (vector stores of 1).
-__global__ __launch_bounds__(kBlock) void k_check_finite(const double *x, const double *m,
-                                                         const double *eps2, int64_t n,
-                                                         int *flag)
+// Root cube of each system of a batch: one block per system.
+__global__ __launch_bounds__(kBlock) void k_root_sys(const double *x, const int64_t *sys_off,
+                                                     double *roots)
 {
-    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (p >= n) return;
-    if (!isfinite(x[3 * p]) || !isfinite(x[3 * p + 1]) || !isfinite(x[3 * p + 2]) ||
-        !isfinite(m[p]))
-        flag[0] = 1;
-    if (eps2 && !(isfinite(eps2[p]) && eps2[p] >= kMinEps2)) flag[1] = 1;
-}
-
-// Bounding box of each system of a batch: one block per system.
-__global__ __launch_bounds__(kBlock) void k_bbox_sys(const double *x, const int64_t *sys_off,
-                                                     double *bb)
-{
-    __shared__ double sh[6][kBlock];
+    __shared__ double s[6][kBlock];
     const int64_t a = sys_off[blockIdx.x], e = sys_off[blockIdx.x + 1];
     double lo[3], hi[3];
     for (int k = 0; k < 3; ++k) lo[k] = hi[k] = x[3 * a + k];
@@ -168,41 +175,41 @@ __global__ __launch_bounds__(kBlock) void k_bbox_sys(const double *x, const int6
             hi[k] = v > hi[k] ? v : hi[k];
         }
     for (int k = 0; k < 3; ++k) {
-        sh[k][threadIdx.x] = lo[k];
-        sh[3 + k][threadIdx.x] = hi[k];
+        s[k][threadIdx.x] = lo[k];
+        s[3 + k][threadIdx.x] = hi[k];
     }
-    __syncthreads();
-    for (int h = kBlock / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h)
-            for (int k = 0; k < 3; ++k) {
-                const double l = sh[k][threadIdx.x + h], u = sh[3 + k][threadIdx.x + h];
-                if (l < sh[k][threadIdx.x]) sh[k][threadIdx.x] = l;
-                if (u > sh[3 + k][threadIdx.x]) sh[3 + k][threadIdx.x] = u;
-            }
-        __syncthreads();
-    }
-    if (threadIdx.x < 6) bb[6 * blockIdx.x + threadIdx.x] = sh[threadIdx.x][0];
+    block_box(s);
+    if (threadIdx.x == 0) root_cube(s, roots + 4 * blockIdx.x);
 }
 
 // ---- 2. keys ----------------------------------------------------------------
 
-// roots[4 s .. 4 s + 3] = centre and side of system s's root cube.
-__global__ __launch_bounds__(kBlock) void k_keys(const double *x, int64_t n,
-                                                 const int64_t *sys_off, int nsys,
-                                                 const double *roots, uint64_t *key,
-                                                 int32_t *idx)
+// System of particle p (input or sorted index): off[s] <= p < off[s + 1].
+__device__ __forceinline__ int system_of(const int64_t *off, int nsys, int64_t p)
 {
-    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (p >= n) return;
-    int lo = 0, hi = nsys;  // system of p: sys_off[s] <= p < sys_off[s + 1]
+    int lo = 0, hi = nsys;
     while (hi - lo > 1) {
         const int mid = (lo + hi) / 2;
-        if (sys_off[mid] <= p)
+        if (off[mid] <= p)
             lo = mid;
         else
             hi = mid;
     }
-    const double *rt = roots + 4 * lo;
+    return lo;
+}
+
+// roots[4 s .. 4 s + 3] = centre and side of system s's root cube.  The sort
+// key is the particle's 63-bit key or, with lo > 0 and several systems, its
+// bits from lo up below the system's number.
+__global__ __launch_bounds__(kBlock) void k_keys(const double *x, int64_t n,
+                                                 const int64_t *sys_off, int nsys,
+                                                 const double *roots, int lo, uint64_t *key,
+                                                 int32_t *idx)
+{
+    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (p >= n) return;
+    const int sys = nsys > 1 ? system_of(sys_off, nsys, p) : 0;
+    const double *rt = roots + 4 * sys;
     const double xp[3] = {x[3 * p], x[3 * p + 1], x[3 * p + 2]};
     double c[3] = {rt[0], rt[1], rt[2]};
     double s = rt[3];
@@ -221,130 +228,399 @@ __global__ __launch_bounds__(kBlock) void k_keys(const double *x, int64_t n,
         k = (k << 3) | o;
         s = s * 0.5;
     }
-    key[p] = k;
+    key[p] = lo > 0 ? (uint64_t)sys << (3 * kMaxDepth - lo) | k >> lo : k;
     idx[p] = (int32_t)p;
 }
 
 // ---- 3. cells ----------------------------------------------------------------
+//
+// All levels at once, from the sorted keys alone.  Two particles lie in one
+// cell of depth L iff their keys share L digits, and the sorted particles of a
+// cell are consecutive, so with cp(a, b) the number of leading digits that
+// the keys of a and b share:
+//   * particle k is the first of its cell at depth L iff L > D_k = cp(k - 1, k)
+//     (-1 at a system's first particle);
+//   * a cell that holds k and w more particles at least has depth at most
+//     cp(j, j + w) for a j in [k - w, k], and one of that depth exists.  A cell
+//     is split iff it has more than nleaf particles (and depth below 21), so
+//     k's leaf has depth LD_k = min(21, 1 + max_j cp(j, j + nleaf)), and k's
+//     group, the first cell of at most ncrit particles or a leaf, the depth
+//     GD_k that the same formula gives with ncrit.
+// Particle k then starts the cells of depths D_k + 1 .. LD_k, and a group iff
+// D_k < GD_k; a cell's number is the count of cell starts of lower depth plus
+// those of its depth before k: the host's breadth-first ids.  Tiles of
+// particles count their starts per depth (k_split), one scan gives every
+// tile its first numbers, and k_cells writes the cells: the thread of the
+// first particle its geometry and first child, the thread of the first
+// particle past it its ends.
+// One level per pass, each with two binary searches per octant in the keys,
+// a scan and a read by the host, took 0.33 of 1.9 ms on the cube of 2^20
+// (now 0.04) and 0.31 ms on a Plummer sphere of 16,384.
 
-__device__ __forceinline__ int32_t lower_bound(const uint64_t *v, int32_t lo, int32_t hi,
-                                               uint64_t x)
-{
-    while (lo < hi) {
-        const int32_t mid = lo + (hi - lo) / 2;
-        if (v[mid] < x)
-            lo = mid + 1;
-        else
-            hi = mid;
+constexpr int kTile = 1024;            // particles per block of k_split and k_cells
+constexpr int kPer = kTile / kBlock;   // per thread
+constexpr int kChunks = kTile / 64;    // waves' worth of particles per tile
+constexpr int kWinMost = 4096;         // longest window k_split holds in LDS
+constexpr int kRows = kMaxDepth + 2;   // depths 0 .. 21 and the groups
+
+// What the build needs of a sorted key array: key(k) = (v[k] & mask) << lo.
+struct SortedKeys {
+    const uint64_t *v;
+    uint64_t mask;
+    int lo;
+    __device__ __forceinline__ uint64_t operator[](int64_t k) const
+    {
+        return (v[k] & mask) << lo;
     }
-    return lo;
+};
+
+__device__ __forceinline__ int common_digits(uint64_t a, uint64_t b)
+{
+    const uint64_t x = a ^ b;
+    return x == 0 ? kMaxDepth : (__builtin_clzll(x) - 1) / 3;
 }
 
-// Octant boundaries of cell c: b[o] .. b[o+1] holds octant o.
-__device__ __forceinline__ void octant_bounds(const uint64_t *skey, const Cells &C,
-                                              int32_t c, int sh, int32_t b[9])
-{
-    const int32_t f = C.first[c], e = f + C.count[c];
-    const uint64_t k = C.key[c];
-    b[0] = f;
-    for (int o = 1; o < 8; ++o) b[o] = lower_bound(skey, b[o - 1], e, k | ((uint64_t)o << sh));
-    b[8] = e;
-}
+// Depths of a particle's start, leaf and group, in one word.
+__device__ __forceinline__ int info_d(int32_t v) { return (v & 0xff) - 1; }
+__device__ __forceinline__ int info_leaf(int32_t v) { return (v >> 8) & 0xff; }
+__device__ __forceinline__ int info_group(int32_t v) { return (v >> 16) & 0xff; }
 
-// Level passes.  lv[l] is the first cell of level l (level l is cells
-// [lv[l], lv[l+1])), in device memory, so that a rebuild can run its levels
-// without the host reading their sizes.  A pass covers `bound` >= the
-// level's width threads (a host-side upper bound when the width is not
-// known there).
+struct SplitArgs {
+    SortedKeys key;
+    int64_t n;
+    const int64_t *sys_off;  // several systems only
+    int nsys, nleaf;
+    int ncrit;               // 0: no group row
+    int depth;               // digits the sort has ordered
+    int rows;                // depth + 1, the group row is row `rows`
+    int32_t *info;           // [n] D + 1, LD, GD
+    int32_t *count;          // [(rows + 1) nb] starts per depth and tile
+    int *deep;               // set if a cell needs more digits
+};
 
-// nch[t] = number of children of cell lv[L] + t (0 beyond the level).
-// After an overflow (*flag set) the level's cells may be incomplete: they
-// are not read, and the level gets no children.
-__global__ __launch_bounds__(kBlock) void k_level_count(Cells C, const uint64_t *skey,
-                                                        const int32_t *lv, int L, int32_t bound,
-                                                        int nleaf, const int *flag, int32_t *nch)
+// Largest cp(j, j + w) over j in [k - w, k] for the tile's particles k, -1
+// if there is none; in LDS bytes a, b of kTile + w each, by doubling: a
+// window's maximum is that of two windows half as long.
+__device__ __forceinline__ const int8_t *window_max(const SplitArgs &A, int64_t k0, int w,
+                                                    int8_t *a, int8_t *b, int &half)
 {
-    const int32_t t = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    if (t >= bound) return;
-    const int32_t c = lv[L] + t;
-    int32_t n = 0;
-    if (*flag == 0 && c < lv[L + 1] && C.count[c] > nleaf && C.depth[c] < kMaxDepth) {
-        int32_t b[9];
-        octant_bounds(skey, C, c, 3 * (kMaxDepth - 1 - C.depth[c]), b);
-        for (int o = 0; o < 8; ++o) n += b[o + 1] > b[o];
-    }
-    nch[t] = n;
-}
-
-// Children of level L from the exclusive sums noff of nch; thread 0 sets
-// lv[L + 2], the end of level L + 1.  Cells at or beyond `cap` are not
-// written: the end is clamped to cap and *flag is set.
-__global__ __launch_bounds__(kBlock) void k_level_write(Cells C, const uint64_t *skey, int32_t *lv,
-                                                        int L, int32_t bound, const int32_t *nch,
-                                                        const int32_t *noff, int32_t cap,
-                                                        int *flag)
-{
-    const int32_t t = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    const int32_t lo = lv[L], hi = lv[L + 1];
-    if (t == 0) {
-        const int32_t w = hi - lo;
-        const int64_t end = w > 0 ? (int64_t)hi + noff[w - 1] + nch[w - 1] : (int64_t)hi;
-        lv[L + 2] = end > cap ? cap : (int32_t)end;
-        if (end > cap) *flag = 1;
-    }
-    if (t >= bound) return;
-    const int32_t c = lo + t;
-    if (c >= hi) return;
-    if (nch[t] == 0) return;
-    const int32_t child0 = hi + noff[t];
-    if ((int64_t)child0 + nch[t] > cap) return;
-    const int d = C.depth[c];
-    const int sh = 3 * (kMaxDepth - 1 - d);
-    int32_t b[9];
-    octant_bounds(skey, C, c, sh, b);
-    const double qd = C.side[c] * 0.25;
-    const double pc[3] = {C.cx[c], C.cy[c], C.cz[c]};
-    int32_t j = 0;
-    for (int o = 0; o < 8; ++o) {
-        if (b[o + 1] <= b[o]) continue;
-        const int32_t ch = child0 + j++;
-        C.cx[ch] = pc[0] + (((o >> 0) & 1) ? qd : -qd);
-        C.cy[ch] = pc[1] + (((o >> 1) & 1) ? qd : -qd);
-        C.cz[ch] = pc[2] + (((o >> 2) & 1) ? qd : -qd);
-        C.side[ch] = C.side[c] * 0.5;
-        C.first[ch] = b[o];
-        C.count[ch] = b[o + 1] - b[o];
-        C.key[ch] = C.key[c] | ((uint64_t)o << sh);
-        C.depth[ch] = d + 1;
-        C.child0[ch] = -1;
-        C.nchild[ch] = 0;
-        C.parent[ch] = c;
-        C.sys[ch] = C.sys[c];
-    }
-    C.child0[c] = child0;
-    C.nchild[c] = j;
-}
-
-// Leaves put their particles back in input order (insertion sort; a leaf
-// holds at most nleaf particles above depth 21, and at depth 21 its
-// particles share one key and are already in input order).
-__global__ __launch_bounds__(kBlock) void k_leaf_order(Cells C, int32_t ncell, int32_t *idx)
-{
-    const int32_t c = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    if (c >= ncell || C.child0[c] >= 0) return;
-    const int32_t f = C.first[c], e = f + C.count[c];
-    for (int32_t i = f + 1; i < e; ++i) {
-        const int32_t v = idx[i];
-        int32_t j = i - 1;
-        while (j >= f && idx[j] > v) {
-            idx[j + 1] = idx[j];
-            --j;
+    const int len = kTile + w;
+    int q = A.nsys > 1 ? system_of(A.sys_off, A.nsys, k0 > w ? k0 - w : 0) : 0;
+    for (int i = threadIdx.x; i < len; i += kBlock) {
+        const int64_t j = k0 - w + i;
+        int c = -1;
+        if (j >= 0 && j < A.n) {
+            int64_t e = A.n;
+            if (A.nsys > 1) {
+                while (A.sys_off[q + 1] <= j) ++q;
+                e = A.sys_off[q + 1];
+            }
+            if (j + w < e) c = common_digits(A.key[j], A.key[j + w]);
         }
-        idx[j + 1] = v;
+        a[i] = (int8_t)c;
+    }
+    __syncthreads();
+    int p = 1;
+    for (; 2 * p <= w + 1; p *= 2) {
+        for (int i = threadIdx.x; i < len - p; i += kBlock) b[i] = a[i] > a[i + p] ? a[i] : a[i + p];
+        __syncthreads();
+        int8_t *s = a;
+        a = b;
+        b = s;
+    }
+    half = p;
+    return a;
+}
+
+__global__ __launch_bounds__(kBlock) void k_split(const SplitArgs A, int nb)
+{
+    extern __shared__ int8_t s_win[];
+    __shared__ int s_cnt[kBlock / 64][kRows];
+    const int t = threadIdx.x;
+    const int64_t k0 = (int64_t)blockIdx.x * kTile;
+    int leaf[kPer], group[kPer];
+    for (int pass = 0; pass < 2; ++pass) {
+        const int w = pass ? A.ncrit : A.nleaf;
+        if (w <= kWinMost && (!pass || w > 0)) {
+            int p;
+            __syncthreads();
+            const int8_t *m = window_max(A, k0, w, s_win, s_win + kTile + w, p);
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int i = t + u * kBlock;
+                const int c = m[i] > m[i + w + 1 - p] ? m[i] : m[i + w + 1 - p];
+                (pass ? group : leaf)[u] = c;
+            }
+        } else {
+            // a leaf of thousands of particles: the window from memory
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int64_t k = k0 + t + u * kBlock;
+                int c = -1;
+                if (!pass && k < A.n) {
+                    int64_t b = 0, e = A.n;
+                    if (A.nsys > 1) {
+                        const int q = system_of(A.sys_off, A.nsys, k);
+                        b = A.sys_off[q];
+                        e = A.sys_off[q + 1];
+                    }
+                    for (int64_t j = k - w > b ? k - w : b; j <= k && j + w < e; ++j) {
+                        const int d = common_digits(A.key[j], A.key[j + w]);
+                        c = d > c ? d : c;
+                    }
+                }
+                (pass ? group : leaf)[u] = c;
+            }
+        }
+    }
+    int mine = 0;  // lane r: the wave's starts of row r
+    const int lane = t & 63;
+    bool deep = false;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int64_t k = k0 + t + u * kBlock;
+        int d = kMaxDepth, ld = -1, gd = -1;
+        if (k < A.n) {
+            ld = leaf[u] + 1 < kMaxDepth ? leaf[u] + 1 : kMaxDepth;
+            gd = group[u] + 1 < kMaxDepth ? group[u] + 1 : kMaxDepth;
+            deep |= ld > A.depth;
+            d = k == 0 ? -1 : common_digits(A.key[k - 1], A.key[k]);
+            if (A.nsys > 1 && A.sys_off[system_of(A.sys_off, A.nsys, k)] == k) d = -1;
+            A.info[k] = (d + 1) | ld << 8 | gd << 16;
+            if (A.ncrit == 0) gd = -1;
+        }
+        for (int r = 0; r < A.rows; ++r) {
+            const int c = (int)__popcll(__ballot(d < r && r <= ld));
+            mine += lane == r ? c : 0;
+        }
+        const int c = (int)__popcll(__ballot(d < gd));
+        mine += lane == A.rows ? c : 0;
+    }
+    if (deep) *A.deep = 1;
+    if (lane <= A.rows) s_cnt[t / 64][lane] = mine;
+    __syncthreads();
+    if (t <= A.rows) {
+        int c = 0;
+        for (int w = 0; w < kBlock / 64; ++w) c += s_cnt[w][t];
+        A.count[(int64_t)t * nb + blockIdx.x] = c;
     }
 }
 
-// ---- 4. moments ---------------------------------------------------------------
+// Exclusive sums of v[0 .. n - 1] to out[0 .. n] in one block (short arrays).
+__global__ __launch_bounds__(1024) void k_scan_block(const int32_t *v, int n, int32_t *out)
+{
+    typedef hipcub::BlockScan<int, 1024> Scan;
+    __shared__ typename Scan::TempStorage tmp;
+    int before = 0;
+    constexpr int kItems = 4;
+    for (int b = 0; b < n; b += 1024 * kItems) {
+        int c[kItems], total;
+        for (int u = 0; u < kItems; ++u) {
+            const int i = b + (int)threadIdx.x * kItems + u;
+            c[u] = i < n ? v[i] : 0;
+        }
+        Scan(tmp).ExclusiveSum(c, c, total);
+        for (int u = 0; u < kItems; ++u) {
+            const int i = b + (int)threadIdx.x * kItems + u;
+            if (i < n) out[i] = before + c[u];
+        }
+        before += total;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[n] = before;
+}
+
+// For the host: table[r] = first number of row r (r <= rows + 1: the cells of
+// each depth, then the groups, then the end), after the flags.
+__global__ void k_table(const int32_t *first, int rows, int nb, const int *flag, int32_t *table)
+{
+    const int r = threadIdx.x;
+    if (r < 4) table[r] = flag[r];
+    if (r <= rows + 1) table[4 + r] = first[(int64_t)r * nb];
+}
+
+// Several systems: before[q rows + L] = starts of depth L (with those of all
+// lower depths) before system q's first particle, q <= nsys.  One wave per
+// system, over the particles of its tile.
+__global__ __launch_bounds__(64) void k_sys_first(const SplitArgs A, const int32_t *first, int nb,
+                                                  int32_t *before)
+{
+    const int q = blockIdx.x, lane = threadIdx.x;
+    const int64_t e = A.sys_off[q], k0 = e / kTile * kTile;
+    int mine = 0;
+    for (int64_t b = k0; b < e; b += 64) {
+        const int32_t v = b + lane < e ? A.info[b + lane] : (kMaxDepth + 1);
+        for (int r = 0; r < A.rows; ++r) {
+            const int c = (int)__popcll(__ballot(info_d(v) < r && r <= info_leaf(v)));
+            mine += lane == r ? c : 0;
+        }
+    }
+    if (lane < A.rows)
+        before[(int64_t)q * A.rows + lane] = first[(int64_t)lane * nb + k0 / kTile] + mine;
+}
+
+// cells[q rows + L] = cells of system q at depth L.
+__global__ __launch_bounds__(kBlock) void k_sys_cells(const int32_t *before, int64_t n, int rows,
+                                                      int32_t *cells)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) cells[i] = before[i + rows] - before[i];
+}
+
+// A batch numbers its cells system by system: shift[q rows + L] takes a
+// number in the order of all systems' levels to that one (the exclusive sums
+// of the systems' cells less the starts before the system).
+__global__ __launch_bounds__(kBlock) void k_sys_shift(const int32_t *before, int64_t n,
+                                                      int32_t *shift)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) shift[i] -= before[i];
+}
+
+struct CellArgs {
+    SplitArgs s;
+    const int32_t *first;  // [(rows + 1) nb + 1] scanned counts
+    const int32_t *shift;  // several systems: [nsys rows]
+    const double *roots;
+    WCell *wc;
+    WLink *wl;
+    int32_t *parent;       // or NULL
+    int32_t *by_level;     // several systems: cells in the order of all levels
+    int32_t *groups;       // (with a group row)
+    int32_t ngroup0;       // number of the first group start
+};
+
+__global__ __launch_bounds__(kBlock) void k_cells(const CellArgs C, int nb)
+{
+    __shared__ uint64_t s_bal[kChunks][kRows];
+    __shared__ int32_t s_pre[kChunks][kRows];
+    const SplitArgs &A = C.s;
+    const int t = threadIdx.x, lane = t & 63;
+    const int64_t k0 = (int64_t)blockIdx.x * kTile;
+    int32_t info[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int64_t k = k0 + t + u * kBlock;
+        info[u] = k < A.n ? A.info[k] : (kMaxDepth + 1);  // past the end: starts nothing
+        const int d = info_d(info[u]), ld = info_leaf(info[u]), gd = info_group(info[u]);
+        const int c = u * (kBlock / 64) + t / 64;
+        for (int r = 0; r < A.rows; ++r) {
+            const uint64_t b = __ballot(d < r && r <= ld);
+            if (lane == r) s_bal[c][r] = b;
+        }
+        const uint64_t b = __ballot(d < gd);
+        if (lane == A.rows) s_bal[c][lane] = b;
+    }
+    __syncthreads();
+    if (t <= A.rows) {
+        int32_t at = C.first[(int64_t)t * nb + blockIdx.x];
+        for (int c = 0; c < kChunks; ++c) {
+            s_pre[c][t] = at;
+            at += (int32_t)__popcll(s_bal[c][t]);
+        }
+    }
+    __syncthreads();
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int64_t k = k0 + t + u * kBlock;
+        if (k > A.n) break;
+        const int c = u * (kBlock / 64) + t / 64;
+        // starts of row r before particle k
+        auto before = [&](int r) -> int32_t {
+            return s_pre[c][r] + (int32_t)__popcll(s_bal[c][r] & below);
+        };
+        int q = 0;
+        const bool sys_start = k == A.n || info_d(info[u]) < 0;
+        if (A.nsys > 1) q = k < A.n ? system_of(A.sys_off, A.nsys, k) : A.nsys;
+        const int d = k < A.n ? info_d(info[u]) : -1;
+        if (k > 0) {
+            // the cells of particle k - 1 that end here
+            const int ld = info_leaf(A.info[k - 1]);
+            const int32_t *sh =
+                C.shift ? C.shift + (int64_t)(q - (sys_start ? 1 : 0)) * A.rows : nullptr;
+            for (int l = d + 1; l <= ld; ++l) {
+                const int32_t id = before(l) - 1 + (sh ? sh[l] : 0);
+                const int32_t ce = l < ld ? before(l + 1) + (sh ? sh[l + 1] : 0) : -1;
+                *reinterpret_cast<int2 *>(&C.wl[id].end) = make_int2((int32_t)k, ce);
+            }
+        }
+        if (k == A.n) break;
+        const int ld = info_leaf(info[u]);
+        if (d >= ld) continue;
+        const int32_t *sh = C.shift ? C.shift + (int64_t)q * A.rows : nullptr;
+        auto number = [&](int l) -> int32_t { return before(l) + (sh ? sh[l] : 0); };
+        const uint64_t key = A.key[k];
+        const double *rt = C.roots + 4 * q;
+        WCell w;
+        w.cx = rt[0];
+        w.cy = rt[1];
+        w.cz = rt[2];
+        w.side = rt[3];
+        for (int l = 0; l <= ld; ++l) {
+            if (l > 0) {
+                const unsigned o = (unsigned)(key >> (3 * (kMaxDepth - l))) & 7u;
+                const double qd = w.side * 0.25;
+                w.cx = w.cx + ((o & 1u) ? qd : -qd);
+                w.cy = w.cy + ((o & 2u) ? qd : -qd);
+                w.cz = w.cz + ((o & 4u) ? qd : -qd);
+                w.side = w.side * 0.5;
+            }
+            if (l <= d) continue;
+            const int32_t id = number(l);
+            double4 *g = reinterpret_cast<double4 *>(C.wc + id);
+            *g = make_double4(w.cx, w.cy, w.cz, w.side);
+            *reinterpret_cast<int2 *>(&C.wl[id].first) =
+                make_int2((int32_t)k, l < ld ? number(l + 1) : -1);
+            // at depth d a cell started before k holds it
+            if (C.parent)
+                C.parent[id] = l == 0 ? -1 : (l - 1 > d ? number(l - 1) : number(l - 1) - 1);
+            if (C.by_level) C.by_level[before(l)] = id;
+        }
+        const int gd = info_group(info[u]);
+        if (C.groups && d < gd) C.groups[before(A.rows) - C.ngroup0] = number(gd);
+    }
+}
+
+// ---- 4. particles and moments -------------------------------------------------
+
+// Particles in tree order: a leaf's particles are put back in input order (at
+// the depth limit they share one key and are in input order already).  One
+// thread per sorted particle ranks it in its leaf.
+__global__ __launch_bounds__(kBlock) void k_particles_out(const int32_t *sidx,
+                                                          const int32_t *info, int64_t n,
+                                                          const double *x, const double *m,
+                                                          const double *eps2, int32_t *order,
+                                                          PartRec *pool, double *xi, double *yi,
+                                                          double *zi, double *e2i)
+{
+    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (k >= n) return;
+    const int32_t p = sidx[k];
+    const int32_t v = info[k];
+    const int ld = info_leaf(v);
+    int64_t at = k;
+    if (ld < kMaxDepth) {
+        bool start = info_d(v) < ld;
+        for (int64_t j = k; !start;) {
+            --j;
+            at -= sidx[j] > p ? 1 : 0;
+            start = info_d(info[j]) < ld;
+        }
+        for (int64_t j = k + 1; j < n && info_d(info[j]) >= ld; ++j) at += sidx[j] < p ? 1 : 0;
+    }
+    order[at] = p;
+    if (eps2) e2i[at] = eps2[p];
+    PartRec r;
+    r.x = x[3 * (int64_t)p];
+    r.y = x[3 * (int64_t)p + 1];
+    r.z = x[3 * (int64_t)p + 2];
+    r.m = m[p];
+    pool[at] = r;
+    xi[at] = r.x;
+    yi[at] = r.y;
+    zi[at] = r.z;
+}
 
 // Moments of a leaf from its particles, in input order (the host's sums, in
 // the host's order): mass and centre of mass, then the traceless
@@ -400,41 +676,47 @@ __device__ __forceinline__ CellRec leaf_moments(int n, const double ctr[3], Part
     return r;
 }
 
-// One thread per leaf.  A leaf of up to kLeafCache particles loads all of
-// them into registers first (independent loads, all in flight at once)
-// and sums from there; a larger one (a leaf at the depth limit) reads them
-// from memory in each pass.
+// One thread per leaf, over its particles in tree order.  A leaf of up to
+// kLeafCache particles loads all of them into registers first (independent
+// loads, all in flight at once) and sums from there; a larger one (a leaf at
+// the depth limit) reads them from memory in each pass.
 constexpr int kLeafCache = 8;
 
-__global__ __launch_bounds__(kBlock) void k_moments_leaf(Cells C, int32_t ncell,
-                                                         const int32_t *idx, const double *x,
-                                                         const double *m, CellRec *pc)
+__device__ __forceinline__ void store_moments(int32_t c, const CellRec &r, WCell *wc, CellRec *pc)
+{
+    pc[c] = r;
+    wc[c].mx = r.x;
+    wc[c].my = r.y;
+    wc[c].mz = r.z;
+}
+
+__global__ __launch_bounds__(kBlock) void k_moments_leaf(const WLink *wl, int32_t ncell,
+                                                         const PartRec *pool, WCell *wc,
+                                                         CellRec *pc)
 {
     const int32_t c = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    if (c >= ncell || C.child0[c] >= 0) return;
-    const int32_t f = C.first[c], n = C.count[c];
-    const double ctr[3] = {C.cx[c], C.cy[c], C.cz[c]};
-    auto mem = [&](int k) {
-        const int64_t p = idx[f + k];
-        return make_double4(m[p], x[3 * p], x[3 * p + 1], x[3 * p + 2]);
-    };
+    if (c >= ncell) return;
+    const WLink l = wl[c];
+    if (l.child0 >= 0) return;
+    const int32_t n = l.end - l.first;
+    const PartRec *p = pool + l.first;
+    const double ctr[3] = {wc[c].cx, wc[c].cy, wc[c].cz};
+    auto mem = [&](int k) { return make_double4(p[k].m, p[k].x, p[k].y, p[k].z); };
     if (n <= kLeafCache) {
         double4 q[kLeafCache];
 #pragma unroll
         for (int k = 0; k < kLeafCache; ++k)
             if (k < n) q[k] = mem(k);
-        pc[c] = leaf_moments<kLeafCache>(n, ctr, [&](int k) { return q[k]; });
+        store_moments(c, leaf_moments<kLeafCache>(n, ctr, [&](int k) { return q[k]; }), wc, pc);
     } else {
-        pc[c] = leaf_moments<0>(n, ctr, mem);
+        store_moments(c, leaf_moments<0>(n, ctr, mem), wc, pc);
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_moments_level(Cells C, int32_t lo, int32_t hi,
-                                                          CellRec *pc)
+// Moments of an internal cell from its children's, in octant order.
+__device__ __forceinline__ void cell_moments(int32_t c, const WLink &l, WCell *wc, CellRec *pc)
 {
-    const int32_t c = lo + (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    if (c >= hi || C.child0[c] < 0) return;
-    const int32_t c0 = C.child0[c], nc = C.nchild[c];
+    const int32_t c0 = l.child0, nc = l.cend - l.child0;
     double M = 0.0, s[3] = {0.0, 0.0, 0.0};
     for (int32_t k = 0; k < nc; ++k) {
         const CellRec &h = pc[c0 + k];
@@ -443,7 +725,7 @@ __global__ __launch_bounds__(kBlock) void k_moments_level(Cells C, int32_t lo, i
         s[1] += h.m * h.y;
         s[2] += h.m * h.z;
     }
-    const double ctr[3] = {C.cx[c], C.cy[c], C.cz[c]};
+    const double ctr[3] = {wc[c].cx, wc[c].cy, wc[c].cz};
     double cm[3];
     for (int a = 0; a < 3; ++a) cm[a] = M > 0.0 ? s[a] / M : ctr[a];
     double q6[6] = {0, 0, 0, 0, 0, 0}, T = 0.0;
@@ -473,7 +755,40 @@ __global__ __launch_bounds__(kBlock) void k_moments_level(Cells C, int32_t lo, i
     r.q22 = q6[5];
     r.t = T;
     r.pad = 0.0;
-    pc[c] = r;
+    store_moments(c, r, wc, pc);
+}
+
+// Cells of one depth: numbers lo .. hi - 1, or those of by_level.
+__global__ __launch_bounds__(kBlock) void k_moments_level(const WLink *wl, int32_t lo, int32_t hi,
+                                                          const int32_t *by_level, WCell *wc,
+                                                          CellRec *pc)
+{
+    int32_t c = lo + (int32_t)(blockIdx.x * kBlock + threadIdx.x);
+    if (c >= hi) return;
+    if (by_level) c = by_level[c];
+    const WLink l = wl[c];
+    if (l.child0 >= 0) cell_moments(c, l, wc, pc);
+}
+
+// The depths `top` .. 0, few cells each, in one block: a launch per depth
+// costs more than the work.
+struct Depths {
+    int32_t first[kMaxDepth + 2];
+};
+constexpr int kTopCells = 2048;  // cells of a depth that one block takes
+
+__global__ __launch_bounds__(1024) void k_moments_top(const WLink *wl, const Depths D, int top,
+                                                      const int32_t *by_level, WCell *wc,
+                                                      CellRec *pc)
+{
+    for (int d = top; d >= 0; --d) {
+        for (int32_t i = D.first[d] + (int32_t)threadIdx.x; i < D.first[d + 1]; i += 1024) {
+            const int32_t c = by_level ? by_level[i] : i;
+            const WLink l = wl[c];
+            if (l.child0 >= 0) cell_moments(c, l, wc, pc);
+        }
+        __syncthreads();
+    }
 }
 
 // ---- 5. groups ----------------------------------------------------------------
@@ -484,21 +799,50 @@ __global__ __launch_bounds__(kBlock) void k_fill_i32(int32_t *v, int64_t n, int3
     if (k < n) v[k] = val;
 }
 
-// A cell is a group iff it has at most ncrit particles or is a leaf, and
-// its parent (if any) has more than ncrit.  gstart[first] = cell id.
-__global__ __launch_bounds__(kBlock) void k_group_mark(Cells C, int32_t ncell, int ncrit,
-                                                       int32_t *gstart)
+// Groups of more particles than k_split's windows span: a cell is a group iff
+// it has at most ncrit particles or is a leaf, and its parent (if any) has
+// more than ncrit.  gstart[first] = cell id.
+__global__ __launch_bounds__(kBlock) void k_group_mark(const WLink *wl, const int32_t *parent,
+                                                       int32_t ncell, int ncrit, int32_t *gstart)
 {
     const int32_t c = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
     if (c >= ncell) return;
-    const bool cond = C.count[c] <= ncrit || C.child0[c] < 0;
-    const bool top = C.parent[c] < 0 || C.count[C.parent[c]] > ncrit;
-    if (cond && top) gstart[C.first[c]] = c;
+    const WLink l = wl[c];
+    const bool cond = l.end - l.first <= ncrit || l.child0 < 0;
+    const int32_t p = parent[c];
+    const bool top = p < 0 || wl[p].end - wl[p].first > ncrit;
+    if (cond && top) gstart[l.first] = c;
 }
 
 struct NonNegative {
     __host__ __device__ bool operator()(const int32_t &v) const { return v >= 0; }
 };
+
+// Groups in the layout of the force context, and each group's root cell (the
+// number of its system's root: shift[q rows] + q; several systems only).
+__global__ __launch_bounds__(kBlock) void k_groups_out(const WCell *wc, const WLink *wl,
+                                                       const int32_t *groups, int64_t ng,
+                                                       int64_t n, const int64_t *sys_off,
+                                                       int nsys, const int32_t *shift, int rows,
+                                                       int64_t *i_off, double *gcx, double *gcy,
+                                                       double *gcz, int32_t *groot)
+{
+    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (g > ng) return;
+    if (g == ng) {
+        i_off[ng] = n;
+        return;
+    }
+    const int32_t c = groups[g], f = wl[c].first;
+    i_off[g] = f;
+    gcx[g] = wc[c].cx;
+    gcy[g] = wc[c].cy;
+    gcz[g] = wc[c].cz;
+    if (groot) {
+        const int q = system_of(sys_off, nsys, f);
+        groot[g] = q + shift[(int64_t)q * rows];
+    }
+}
 
 // ---- 6. walk -----------------------------------------------------------------
 
@@ -513,43 +857,18 @@ __device__ __forceinline__ double abs_min_image(double v, double box)
     return a;
 }
 
-// Whether the cell holds the group: no deeper than it, and its particles
+// Whether the cell holds the group: no smaller than it, and its particles
 // include the group's (cells of one depth are disjoint, so the cell is then
 // the group's ancestor at that depth, or the group).
-__device__ __forceinline__ bool contains(const WLink &C, const WLink &G)
+__device__ __forceinline__ bool contains(const WCell &C, const WLink &L, const WCell &G,
+                                         const WLink &GL)
 {
-    return (C.nd >> 8) <= (G.nd >> 8) && C.first <= G.first &&
-           C.first + C.count >= G.first + G.count;
-}
-
-__global__ __launch_bounds__(kBlock) void k_walk_cells(Cells C, int32_t ncell,
-                                                       const CellRec *pc, WCell *wc,
-                                                       WLink *wl)
-{
-    const int32_t c = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    if (c >= ncell) return;
-    WCell w;
-    w.cx = C.cx[c];
-    w.cy = C.cy[c];
-    w.cz = C.cz[c];
-    w.side = C.side[c];
-    w.mx = pc[c].x;
-    w.my = pc[c].y;
-    w.mz = pc[c].z;
-    w.pad = 0.0;
-    wc[c] = w;
-    WLink l;
-    l.first = C.first[c];
-    l.count = C.count[c];
-    l.child0 = C.child0[c];
-    l.nd = C.nchild[c] | (C.depth[c] << 8);
-    wl[c] = l;
+    return C.side >= G.side && L.first <= GL.first && L.end >= GL.end;
 }
 
 struct WalkArgs {
     const int32_t *groups;
-    const int32_t *cell_sys;           // system of each cell
-    const int32_t *sys_root;           // root cell of each system
+    const int32_t *groot;              // root cell of each group's tree (NULL: 0)
     int64_t ng;
     const WCell *wc;
     const WLink *wl;
@@ -584,7 +903,7 @@ __device__ __forceinline__ int2 classify(const WalkArgs &W, int32_t id, const WC
     const WLink L = W.wl[id];
     const double box = W.box;
     const double gc[3] = {G.cx, G.cy, G.cz};
-    if (!contains(L, GL)) {
+    if (!contains(C, L, G, GL)) {
         if (W.rcut > 0.0) {
             const double cc[3] = {C.cx, C.cy, C.cz};
             double d2 = 0.0;
@@ -613,11 +932,11 @@ __device__ __forceinline__ int2 classify(const WalkArgs &W, int32_t id, const WC
                 }
                 if (b2 >= W.rdrop2) return make_int2(-1, 0);
             }
-            return L.count == 1 ? make_int2(L.first, 1) : make_int2(id, 0);
+            return L.end - L.first == 1 ? make_int2(L.first, 1) : make_int2(id, 0);
         }
     }
-    if (L.child0 < 0) return L.count > 0 ? make_int2(L.first, L.count) : make_int2(-1, 0);
-    return make_int2(-2 - L.child0, L.nd & 0xff);
+    if (L.child0 < 0) return make_int2(L.first, L.end - L.first);
+    return make_int2(-2 - L.child0, L.cend - L.child0);
 }
 
 // Data movement inside an octet (8 aligned lanes) by DPP, on the VALU:
@@ -721,21 +1040,21 @@ __global__ __launch_bounds__(64 * NW) void k_walk_level(const WalkArgs W, int ca
         pe = pb + W.cap_p;
         ce = cb + W.cap_c;
     }
-    const WLink R = W.wl[W.sys_root[W.cell_sys[gid]]];
+    const WLink R = W.wl[W.groot ? W.groot[gi] : 0];
     if (R.child0 < 0) {
         // a one-leaf tree: the root contains the group and is opened
         if (MODE != kWalkCount)
-            for (int32_t j = t; j < R.count && pb + j < pe; j += 64 * NW)
+            for (int32_t j = t; j < R.end - R.first && pb + j < pe; j += 64 * NW)
                 W.jp_idx[pb + j] = R.first + j;
         if (MODE != kWalkFill && t == 0) {
-            W.jp_cnt[gi] = R.count;
+            W.jp_cnt[gi] = R.end - R.first;
             W.jc_cnt[gi] = 0;
         }
         return;
     }
     if (t == 0) {
         s_c0[0] = R.child0;
-        s_kind[0] = (uint32_t)R.nd & 0xffu;
+        s_kind[0] = (uint32_t)children(R);
         s_cnt = 1;
     }
     __syncthreads();
@@ -832,7 +1151,7 @@ __global__ __launch_bounds__(64 * NW) void k_walk_level(const WalkArgs W, int ca
             } else if (kind == kNodeRun) {
                 const WLink L = W.wl[id];
                 first = L.first;
-                v.y = L.count;
+                v.y = L.end - L.first;
             }
             const int c0 = at.x + octet_scan(v.x, k) - v.x;
             const int p0 = at.y + octet_scan(v.y, k) - v.y;
@@ -906,18 +1225,17 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
         pe = pb + W.cap_p;
         ce = cb + W.cap_c;
     }
-    const int32_t root = W.sys_root[W.cell_sys[gid]];
-    const WLink R = W.wl[root];
+    const WLink R = W.wl[W.groot ? W.groot[gi] : 0];
     int sp = 0, nch = 0, cur = 0;
     int2 e = make_int2(-1, 0);
     if (R.child0 < 0) {
         // a one-leaf tree: the root contains the group and is opened
         if (FILL)
-            for (int32_t j = k; j < R.count && pb + j < pe; j += kOct)
+            for (int32_t j = k; j < R.end - R.first && pb + j < pe; j += kOct)
                 W.jp_idx[pb + j] = R.first + j;
-        np = R.count;
+        np = R.end - R.first;
     } else {
-        nch = R.nd & 0xff;
+        nch = children(R);
         e = k < nch ? classify(W, R.child0 + k, G, GL, gb) : make_int2(-1, 0);
         s_ent[0][t] = e;
         sp = 1;
@@ -991,40 +1309,39 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
 }
 
 // Bounding box (lo[3], hi[3]) of each group's particles, for the cutoff
-// drop; one thread per group over its particles in tree order.
-__global__ __launch_bounds__(kBlock) void k_group_box(Cells C, const int32_t *groups,
-                                                      int64_t ng, const int32_t *idx,
-                                                      const double *x, double *gbox)
+// drop; an octet of lanes per group over its particles in tree order
+// (minimum and maximum do not depend on the order).
+__global__ __launch_bounds__(kBlock) void k_group_box(const WLink *wl, const int32_t *groups,
+                                                      int64_t ng, const double *x, const double *y,
+                                                      const double *z, double *gbox)
 {
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t g = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kOct;
+    const int k = threadIdx.x % kOct;
     if (g >= ng) return;
-    const int32_t c = groups[g];
-    double b[6];
-    for (int k = 0; k < 3; ++k) {
-        b[k] = __builtin_inf();
-        b[3 + k] = -__builtin_inf();
+    const WLink l = wl[groups[g]];
+    const double *xs[3] = {x, y, z};
+    double lo[3], hi[3];
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = __builtin_inf();
+        hi[a] = -__builtin_inf();
     }
-    // chunks of 8 particles: their loads are independent and all in flight
-    // at once (minimum and maximum do not depend on the order)
-    constexpr int kChunk = 8;
-    const int32_t f = C.first[c], e = f + C.count[c];
-    for (int32_t q0 = f; q0 < e; q0 += kChunk) {
-        double v[kChunk][3];
-#pragma unroll
-        for (int j = 0; j < kChunk; ++j)
-            if (q0 + j < e) {
-                const double *xp = x + 3 * (int64_t)idx[q0 + j];
-                for (int k = 0; k < 3; ++k) v[j][k] = xp[k];
-            }
-#pragma unroll
-        for (int j = 0; j < kChunk; ++j)
-            if (q0 + j < e)
-                for (int k = 0; k < 3; ++k) {
-                    b[k] = v[j][k] < b[k] ? v[j][k] : b[k];
-                    b[3 + k] = v[j][k] > b[3 + k] ? v[j][k] : b[3 + k];
-                }
+    for (int32_t p = l.first + k; p < l.end; p += kOct)
+        for (int a = 0; a < 3; ++a) {
+            const double v = xs[a][p];
+            lo[a] = v < lo[a] ? v : lo[a];
+            hi[a] = v > hi[a] ? v : hi[a];
+        }
+    for (int a = 0; a < 3; ++a) {
+        for (int h = kOct / 2; h > 0; h /= 2) {
+            const double u = __shfl_xor(lo[a], h, kOct), v = __shfl_xor(hi[a], h, kOct);
+            lo[a] = u < lo[a] ? u : lo[a];
+            hi[a] = v > hi[a] ? v : hi[a];
+        }
+        if (k == 0) {
+            gbox[6 * g + a] = lo[a];
+            gbox[6 * g + 3 + a] = hi[a];
+        }
     }
-    for (int k = 0; k < 6; ++k) gbox[6 * g + k] = b[k];
 }
 
 // Lists of one-walk builds: group g's entries [0, off[g+1] - off[g]) of
@@ -1064,103 +1381,6 @@ hipError_t launch_compact_lists(int64_t ng, const int64_t *off, const int32_t *s
     return hipGetLastError();
 }
 
-namespace {
-
-// ---- outputs -----------------------------------------------------------------
-
-__global__ __launch_bounds__(kBlock) void k_particles_out(const int32_t *idx, int64_t n,
-                                                          const double *x, const double *m,
-                                                          const double *eps2, PartRec *pool,
-                                                          double *xi, double *yi, double *zi,
-                                                          double *e2i)
-{
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= n) return;
-    const int64_t p = idx[k];
-    if (eps2) e2i[k] = eps2[p];
-    PartRec r;
-    r.x = x[3 * p];
-    r.y = x[3 * p + 1];
-    r.z = x[3 * p + 2];
-    r.m = m[p];
-    pool[k] = r;
-    xi[k] = r.x;
-    yi[k] = r.y;
-    zi[k] = r.z;
-}
-
-__global__ __launch_bounds__(kBlock) void k_groups_out(Cells C, const int32_t *groups,
-                                                       int64_t ng, int64_t n, int64_t *i_off,
-                                                       double *gcx, double *gcy, double *gcz)
-{
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g > ng) return;
-    if (g == ng) {
-        i_off[ng] = n;
-        return;
-    }
-    const int32_t c = groups[g];
-    i_off[g] = C.first[c];
-    gcx[g] = C.cx[c];
-    gcy[g] = C.cy[c];
-    gcz[g] = C.cz[c];
-}
-
-__global__ __launch_bounds__(kBlock) void k_set_roots(Cells C, const double *roots,
-                                                      const int64_t *sys_off, int nsys)
-{
-    const int sidx = blockIdx.x * kBlock + threadIdx.x;
-    if (sidx >= nsys) return;
-    C.cx[sidx] = roots[4 * sidx];
-    C.cy[sidx] = roots[4 * sidx + 1];
-    C.cz[sidx] = roots[4 * sidx + 2];
-    C.side[sidx] = roots[4 * sidx + 3];
-    C.first[sidx] = (int32_t)sys_off[sidx];
-    C.count[sidx] = (int32_t)(sys_off[sidx + 1] - sys_off[sidx]);
-    C.key[sidx] = 0;
-    C.depth[sidx] = 0;
-    C.child0[sidx] = -1;
-    C.nchild[sidx] = 0;
-    C.parent[sidx] = -1;
-    C.sys[sidx] = sidx;
-}
-
-// Cells per (depth, system), for the renumbering of a batch.
-__global__ __launch_bounds__(kBlock) void k_level_sys_count(Cells C, int32_t ncell, int nsys,
-                                                            int32_t *cnt)
-{
-    const int32_t c = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    if (c >= ncell) return;
-    atomicAdd(cnt + C.depth[c] * nsys + C.sys[c], 1);
-}
-
-// New id of cell c: base[l][s] + (c - first[l][s]) for its depth l and
-// system s (device cells of one depth are ordered by system).
-__global__ __launch_bounds__(kBlock) void k_perm(Cells C, int32_t ncell, int nsys,
-                                                 const int32_t *base, const int32_t *first,
-                                                 int32_t *perm)
-{
-    const int32_t c = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    if (c >= ncell) return;
-    const int t = C.depth[c] * nsys + C.sys[c];
-    perm[c] = base[t] + (c - first[t]);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_permute(int32_t ncell, const int32_t *perm,
-                                                    const T *in, T *out, bool ids)
-{
-    const int32_t c = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    if (c >= ncell) return;
-    T v = in[c];
-    if constexpr (sizeof(T) == 4) {
-        if (ids && v >= 0) v = perm[v];
-    }
-    out[perm[c]] = v;
-}
-
-}  // namespace
-
 // ---- host orchestration ---------------------------------------------------------
 
 int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string *err)
@@ -1194,394 +1414,275 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     const int nsys = (int)P.nsys;
     STEP(B[T_FLAG].reserve(64), "allocation");
     STEP(hipMemsetAsync(B[T_FLAG].p, 0, 64, s), "memset");
-    hipLaunchKernelGGL(k_check_finite, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s, P.x, P.m,
-                       P.eps2, n, B[T_FLAG].as<int>());
-    LAUNCHED("finite check");
-    int hflag2[2] = {0, 0};
-    STEP(hipMemcpyAsync(hflag2, B[T_FLAG].p, sizeof(hflag2), hipMemcpyDeviceToHost, s), "copy");
-    STEP(hipStreamSynchronize(s), "sync");
-    if (hflag2[0]) {
-        code = BHQ_E_NONFINITE;
-        what = "non-finite position or mass";
-        return fail();
-    }
-    if (hflag2[1]) {
-        code = BHQ_E_ARG;
-        what = "eps2 must be finite and >= 2^-126";
-        return fail();
-    }
-    STEP(B[T_SYSOFF].reserve((size_t)(nsys + 1) * 8), "allocation");
-    STEP(B[T_SYSOFF32].reserve((size_t)(nsys + 1) * 4), "allocation");
-    STEP(hipMemcpyAsync(B[T_SYSOFF].p, P.sys_off, (size_t)(nsys + 1) * 8,
-                        hipMemcpyHostToDevice, s),
-         "copy");
-    std::vector<double> roots((size_t)nsys * 4);
+    int *flag = B[T_FLAG].as<int>();  // non-finite, softening, too deep; the walk's from 4
+    STEP(B[T_ROOTS].reserve((size_t)nsys * 4 * sizeof(double)), "allocation");
+    double *roots = B[T_ROOTS].as<double>();
+    const int64_t *sys_off = nullptr;
+    std::vector<int32_t> so32;  // read by the copy below until the synchronisation
     {
-        std::vector<int32_t> so32((size_t)nsys + 1);
-        for (int k = 0; k <= nsys; ++k) so32[(size_t)k] = (int32_t)P.sys_off[k];
-        STEP(hipMemcpyAsync(B[T_SYSOFF32].p, so32.data(), (size_t)(nsys + 1) * 4,
-                            hipMemcpyHostToDevice, s),
-             "copy");
-        std::vector<double> bb((size_t)nsys * 6);
-        if (P.box > 0.0) {
-            for (int k = 0; k < 3; ++k) roots[(size_t)k] = 0.5 * P.box;
-            roots[3] = P.box;
+        const bool box1 = nsys == 1 && !(P.box > 0.0);
+        const int nb = (int)std::min<int64_t>(kBboxBlocks, blocks(n, kBlock));
+        STEP(B[T_BBOX].reserve((size_t)nb * 6 * sizeof(double)), "allocation");
+        hipLaunchKernelGGL(k_check, dim3(nb), dim3(kBlock), 0, s, P.x, P.m, P.eps2, n, flag,
+                           box1 ? B[T_BBOX].as<double>() : nullptr);
+        LAUNCHED("finite check");
+        if (nsys == 1) {
+            hipLaunchKernelGGL(k_root, dim3(1), dim3(kBlock), 0, s, B[T_BBOX].as<double>(), nb,
+                               P.box, roots);
+            LAUNCHED("root cube");
         } else {
-            if (nsys == 1) {
-                const int nb = (int)std::min<int64_t>(kBboxBlocks, blocks(n, kBlock));
-                STEP(B[T_BBOX].reserve((size_t)nb * 6 * sizeof(double)), "allocation");
-                hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(kBlock), 0, s, P.x, n,
-                                   B[T_BBOX].as<double>());
-                LAUNCHED("bounding box");
-                hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(kBlock), 0, s,
-                                   B[T_BBOX].as<double>(), nb);
-                LAUNCHED("bounding box");
-            } else {
-                STEP(B[T_BBOX].reserve((size_t)nsys * 6 * sizeof(double)), "allocation");
-                hipLaunchKernelGGL(k_bbox_sys, dim3((unsigned)nsys), dim3(kBlock), 0, s, P.x,
-                                   B[T_SYSOFF].as<int64_t>(), B[T_BBOX].as<double>());
-                LAUNCHED("bounding boxes");
-            }
-            STEP(hipMemcpyAsync(bb.data(), B[T_BBOX].p, bb.size() * sizeof(double),
-                                hipMemcpyDeviceToHost, s),
+            STEP(B[T_SYSOFF].reserve((size_t)(nsys + 1) * 8), "allocation");
+            STEP(B[T_SYSOFF32].reserve((size_t)(nsys + 1) * 4), "allocation");
+            STEP(hipMemcpyAsync(B[T_SYSOFF].p, P.sys_off, (size_t)(nsys + 1) * 8,
+                                hipMemcpyHostToDevice, s),
                  "copy");
-            STEP(hipStreamSynchronize(s), "sync");
-            for (int q = 0; q < nsys; ++q) {
-                const double *b = &bb[(size_t)q * 6];
-                double *rt = &roots[(size_t)q * 4];
-                double ext = 0.0;
-                for (int k = 0; k < 3; ++k) {
-                    rt[k] = 0.5 * (b[k] + b[3 + k]);
-                    ext = std::max(ext, b[3 + k] - b[k]);
-                }
-                rt[3] = ext > 0.0 ? ext * (1.0 + std::ldexp(1.0, -20)) : 1.0;
-            }
+            so32.assign(P.sys_off, P.sys_off + nsys + 1);
+            STEP(hipMemcpyAsync(B[T_SYSOFF32].p, so32.data(), (size_t)(nsys + 1) * 4,
+                                hipMemcpyHostToDevice, s),
+                 "copy");
+            sys_off = B[T_SYSOFF].as<int64_t>();
+            hipLaunchKernelGGL(k_root_sys, dim3((unsigned)nsys), dim3(kBlock), 0, s, P.x, sys_off,
+                               roots);
+            LAUNCHED("root cubes");
         }
-        STEP(B[T_ROOTS].reserve(roots.size() * sizeof(double)), "allocation");
-        STEP(hipMemcpyAsync(B[T_ROOTS].p, roots.data(), roots.size() * sizeof(double),
-                            hipMemcpyHostToDevice, s),
-             "copy");
-        STEP(hipStreamSynchronize(s), "sync");
     }
 
-    // keys, sort
+    // keys, sort, cells per depth
     STEP(B[T_KEY].reserve((size_t)n * 8), "allocation");
     STEP(B[T_KEY2].reserve((size_t)n * 8), "allocation");
     STEP(B[T_IDX0].reserve((size_t)n * 4), "allocation");
-    STEP(O.order->reserve((size_t)n * 4), "allocation");
-    hipLaunchKernelGGL(k_keys, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s, P.x, n,
-                       B[T_SYSOFF].as<int64_t>(), nsys, B[T_ROOTS].as<double>(),
-                       B[T_KEY].as<uint64_t>(), B[T_IDX0].as<int32_t>());
-    LAUNCHED("keys");
-    // Stable sort of (key, input index) on key bits [lo_bit, 63).  Splitting
-    // a cell at depth d reads the key digit at bits 3 (kMaxDepth - 1 - d),
-    // so a tree of L levels needs the bits from 3 (kMaxDepth + 1 - L) up;
-    // the order inside a leaf does not matter (leaves are put back in input
-    // order).  A rebuild sorts the bits its previous depth needs; if the tree
-    // turns out deeper, the keys are sorted again on all bits.
-    auto sort_keys = [&](int lo_bit) -> bool {
-        size_t tmp = 0;
-        if (nsys == 1) {
-            if (!hip(hipcub::DeviceRadixSort::SortPairs(
-                         nullptr, tmp, B[T_KEY].as<uint64_t>(), B[T_KEY2].as<uint64_t>(),
-                         B[T_IDX0].as<int32_t>(), O.order->as<int32_t>(), (int)n, lo_bit,
-                         3 * kMaxDepth, s),
-                     "sort size"))
-                return false;
-            if (!hip(B[T_SORT].reserve(std::max(tmp, B[T_SORT].cap)), "allocation")) return false;
-            return hip(hipcub::DeviceRadixSort::SortPairs(
-                           B[T_SORT].p, tmp, B[T_KEY].as<uint64_t>(), B[T_KEY2].as<uint64_t>(),
-                           B[T_IDX0].as<int32_t>(), O.order->as<int32_t>(), (int)n, lo_bit,
-                           3 * kMaxDepth, s),
-                       "sort");
-        }
+    STEP(B[T_IDX1].reserve((size_t)n * 4), "allocation");
+    STEP(B[T_INFO].reserve((size_t)n * 4), "allocation");
+    int sysbits = 0;
+    while (((int64_t)1 << sysbits) < nsys) ++sysbits;
+    // Stable sort of (key, input index) on key bits [lo, 63).  A tree of L
+    // levels (depths below L) reads L - 1 digits of the keys, so it needs the
+    // bits from 3 (kMaxDepth + 1 - L) up; the order inside a leaf does not
+    // matter (its particles are put back in input order).  A rebuild sorts the
+    // bits its previous depth needs; if the tree turns out deeper, the keys
+    // are sorted again on all bits.  The systems of a batch are sorted in one
+    // go where system and key bits fit 64, else as segments.
+    bool joint = false;
+    auto sort_keys = [&](int lo) -> bool {
+        uint64_t *k0 = B[T_KEY].as<uint64_t>(), *k1 = B[T_KEY2].as<uint64_t>();
+        int32_t *i0 = B[T_IDX0].as<int32_t>(), *i1 = B[T_IDX1].as<int32_t>();
         const int32_t *so = B[T_SYSOFF32].as<int32_t>();
-        if (!hip(hipcub::DeviceSegmentedRadixSort::SortPairs(
-                     nullptr, tmp, B[T_KEY].as<uint64_t>(), B[T_KEY2].as<uint64_t>(),
-                     B[T_IDX0].as<int32_t>(), O.order->as<int32_t>(), (int)n, nsys, so, so + 1,
-                     lo_bit, 3 * kMaxDepth, s),
-                 "sort size"))
-            return false;
+        joint = nsys > 1 && lo > 0 && 3 * kMaxDepth - lo + sysbits <= 64;
+        hipLaunchKernelGGL(k_keys, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s, P.x, n, sys_off,
+                           nsys, roots, joint ? lo : 0, k0, i0);
+        if (!hip(hipGetLastError(), "keys")) return false;
+        const int b0 = joint ? 0 : lo, b1 = joint ? 3 * kMaxDepth - lo + sysbits : 3 * kMaxDepth;
+        auto run = [&](void *tmp, size_t &bytes) -> hipError_t {
+            if (nsys == 1 || joint)
+                return hipcub::DeviceRadixSort::SortPairs(tmp, bytes, k0, k1, i0, i1, (int)n, b0,
+                                                          b1, s);
+            return hipcub::DeviceSegmentedRadixSort::SortPairs(tmp, bytes, k0, k1, i0, i1, (int)n,
+                                                               nsys, so, so + 1, b0, b1, s);
+        };
+        size_t tmp = 0;
+        if (!hip(run(nullptr, tmp), "sort size")) return false;
         if (!hip(B[T_SORT].reserve(std::max(tmp, B[T_SORT].cap)), "allocation")) return false;
-        return hip(hipcub::DeviceSegmentedRadixSort::SortPairs(
-                       B[T_SORT].p, tmp, B[T_KEY].as<uint64_t>(), B[T_KEY2].as<uint64_t>(),
-                       B[T_IDX0].as<int32_t>(), O.order->as<int32_t>(), (int)n, nsys, so,
-                       so + 1, lo_bit, 3 * kMaxDepth, s),
-                   "sort");
+        return hip(run(B[T_SORT].p, tmp), "sort");
     };
-    const bool spec = P.spec_levels > 0 && P.spec_cells > 0;
-    const int sort_lo = spec ? 3 * std::max(0, kMaxDepth + 1 - P.spec_levels) : 0;
-    if (!sort_keys(sort_lo)) return fail();
-    const uint64_t *skey = B[T_KEY2].as<uint64_t>();
-    int32_t *idx = O.order->as<int32_t>();
-
-    // cells, level by level
-    size_t cap = B[T_CX].p ? B[T_CX].cap / 8 : 0;
-    const TreeBuf cbuf8[] = {T_CX, T_CY, T_CZ, T_SIDE, T_CKEY};
-    const TreeBuf cbuf4[] = {T_FIRST, T_COUNT, T_CHILD0, T_NCHILD, T_PARENT, T_DEPTH, T_CSYS};
-    auto cells = [&]() {
-        Cells C;
-        C.cx = B[T_CX].as<double>();
-        C.cy = B[T_CY].as<double>();
-        C.cz = B[T_CZ].as<double>();
-        C.side = B[T_SIDE].as<double>();
-        C.key = B[T_CKEY].as<uint64_t>();
-        C.first = B[T_FIRST].as<int32_t>();
-        C.count = B[T_COUNT].as<int32_t>();
-        C.child0 = B[T_CHILD0].as<int32_t>();
-        C.nchild = B[T_NCHILD].as<int32_t>();
-        C.parent = B[T_PARENT].as<int32_t>();
-        C.depth = B[T_DEPTH].as<int32_t>();
-        C.sys = B[T_CSYS].as<int32_t>();
-        return C;
-    };
-    auto ensure = [&](size_t need, size_t used) -> bool {
-        if (need <= cap) return true;
-        size_t nc = std::max(need, cap + cap / 2);
-        for (TreeBuf b : cbuf8)
-            if (!hip(B[b].grow(nc * 8, used * 8, s), "allocation")) return false;
-        for (TreeBuf b : cbuf4)
-            if (!hip(B[b].grow(nc * 4, used * 4, s), "allocation")) return false;
-        cap = nc;
-        return true;
-    };
-    if (!ensure((size_t)std::max<int64_t>(std::max<int64_t>(1024, n / 2), 2 * nsys), 0))
-        return fail();
-    hipLaunchKernelGGL(k_set_roots, dim3(blocks(nsys, kBlock)), dim3(kBlock), 0, s, cells(),
-                       B[T_ROOTS].as<double>(), B[T_SYSOFF].as<int64_t>(), nsys);
-    LAUNCHED("roots");
-    std::vector<int32_t> level{0, nsys};  // level l is cells [level[l], level[l+1])
-    STEP(B[T_NCH].reserve((size_t)std::max<int64_t>(n, 1) * 4 + 4), "allocation");
-    STEP(B[T_NOFF].reserve((size_t)std::max<int64_t>(n, 1) * 4 + 4), "allocation");
-    // level bounds on the device (kMaxDepth + 2 entries), then a flag
-    STEP(B[T_LV].reserve((size_t)(kMaxDepth + 3) * 4), "allocation");
-    int32_t *lv = B[T_LV].as<int32_t>();
-    int *lvflag = reinterpret_cast<int *>(lv + kMaxDepth + 2);
-    {
-        const int32_t init[3] = {0, nsys, 0};
-        STEP(hipMemcpyAsync(lv, init, 8, hipMemcpyHostToDevice, s), "copy");
-        STEP(hipMemcpyAsync(lvflag, init + 2, 4, hipMemcpyHostToDevice, s), "copy");
-    }
-    auto scan = [&](int32_t bound) -> bool {
-        size_t st = 0;
-        if (!hip(hipcub::DeviceScan::ExclusiveSum(nullptr, st, B[T_NCH].as<int32_t>(),
-                                                  B[T_NOFF].as<int32_t>(), bound, s),
-                 "scan size"))
-            return false;
-        if (!hip(B[T_SORT].reserve(std::max(st, B[T_SORT].cap)), "allocation")) return false;
-        return hip(hipcub::DeviceScan::ExclusiveSum(B[T_SORT].p, st, B[T_NCH].as<int32_t>(),
-                                                    B[T_NOFF].as<int32_t>(), bound, s),
-                   "scan");
-    };
-    auto level_pass = [&](int lev, int32_t bound) -> bool {
-        hipLaunchKernelGGL(k_level_count, dim3(blocks(bound, kBlock)), dim3(kBlock), 0, s,
-                           cells(), skey, (const int32_t *)lv, lev, bound, P.nleaf,
-                           (const int *)lvflag, B[T_NCH].as<int32_t>());
-        if (!hip(hipGetLastError(), "level count")) return false;
-        if (!scan(bound)) return false;
-        hipLaunchKernelGGL(k_level_write, dim3(blocks(bound, kBlock)), dim3(kBlock), 0, s,
-                           cells(), skey, lv, lev, bound, B[T_NCH].as<int32_t>(),
-                           B[T_NOFF].as<int32_t>(),
-                           (int32_t)std::min<size_t>(cap, 0x7fffffff), lvflag);
-        return hip(hipGetLastError(), "level write");
-    };
-    // A rebuild first runs as many levels as the previous build had with no
-    // host synchronisation: widths bounded by 8 times the level above and by
-    // n, cells by a capacity of 1.25 times the previous build's.  If the
-    // cells overflow, the levels are built again below, one at a time; if
-    // the tree goes deeper, the remaining levels are built that way.
-    bool done = false;
-    if (spec) {
-        const size_t want = (size_t)P.spec_cells + (size_t)P.spec_cells / 4 + 1024;
-        if (!ensure(std::min<size_t>(want, 0x7fffffff), (size_t)nsys)) return fail();
-        const int nl = std::min(P.spec_levels, kMaxDepth);
-        int64_t bound = nsys;
-        for (int lev = 0; lev < nl; ++lev) {
-            if (!level_pass(lev, (int32_t)bound)) return fail();
-            bound = std::min<int64_t>(8 * bound, n);
+    const int nb = (int)blocks(n + 1, kTile);
+    const bool group_row = P.ncrit <= kWinMost;
+    STEP(B[T_TABLE].reserve(64 * 4), "allocation");
+    int32_t table[4 + kRows + 2] = {};
+    int lo = P.spec_levels > 0 ? 3 * (kMaxDepth + 1 - std::max(2, P.spec_levels)) : 0;
+    SplitArgs S{};
+    int rows = 0;
+    for (;;) {
+        if (!sort_keys(lo)) return fail();
+        S.key = joint ? SortedKeys{B[T_KEY2].as<uint64_t>(),
+                                   ((uint64_t)1 << (3 * kMaxDepth - lo)) - 1, lo}
+                      : SortedKeys{B[T_KEY2].as<uint64_t>(), ~(uint64_t)0, 0};
+        S.n = n;
+        S.sys_off = sys_off;
+        S.nsys = nsys;
+        S.nleaf = P.nleaf;
+        S.ncrit = group_row ? P.ncrit : 0;
+        S.depth = kMaxDepth - lo / 3;
+        S.rows = rows = S.depth + 1;
+        S.info = B[T_INFO].as<int32_t>();
+        const int ncount = (rows + 1) * nb;
+        STEP(B[T_NCH].reserve((size_t)(ncount + 1) * 4), "allocation");
+        STEP(B[T_NOFF].reserve((size_t)(ncount + 1) * 4), "allocation");
+        S.count = B[T_NCH].as<int32_t>();
+        S.deep = flag + 2;
+        const int win = std::max(P.nleaf <= kWinMost ? P.nleaf : 0, S.ncrit);
+        hipLaunchKernelGGL(k_split, dim3((unsigned)nb), dim3(kBlock), 2 * (size_t)(kTile + win), s,
+                           S, nb);
+        LAUNCHED("cell starts");
+        if (ncount <= 16384) {
+            hipLaunchKernelGGL(k_scan_block, dim3(1), dim3(1024), 0, s, S.count, ncount,
+                               B[T_NOFF].as<int32_t>());
+            LAUNCHED("scan");
+        } else {
+            size_t st = 0;
+            STEP(hipcub::DeviceScan::ExclusiveSum(nullptr, st, S.count, B[T_NOFF].as<int32_t>(),
+                                                  ncount + 1, s),
+                 "scan size");
+            STEP(B[T_SORT].reserve(std::max(st, B[T_SORT].cap)), "allocation");
+            STEP(hipcub::DeviceScan::ExclusiveSum(B[T_SORT].p, st, S.count,
+                                                  B[T_NOFF].as<int32_t>(), ncount + 1, s),
+                 "scan");
         }
-        std::vector<int32_t> hl((size_t)kMaxDepth + 3);
-        STEP(hipMemcpyAsync(hl.data(), lv, hl.size() * 4, hipMemcpyDeviceToHost, s), "copy");
-        STEP(hipStreamSynchronize(s), "sync");
-        if (hl[(size_t)kMaxDepth + 2] == 0) {
-            for (int lev = 0; lev < nl; ++lev) {
-                const int32_t e = hl[(size_t)lev + 2];
-                if (e == level.back()) {  // level lev + 1 is empty: the tree ends
-                    done = true;
-                    break;
-                }
-                level.push_back(e);
-            }
-        }
-        if (!done) {
-            // the cells overflowed, or the tree is deeper than the sorted
-            // bits reach: sort on all bits and start again, level by level
-            level.assign({0, nsys});
-            if (sort_lo > 0 && !sort_keys(0)) return fail();
-            const int32_t zero = 0;
-            STEP(hipMemcpyAsync(lvflag, &zero, 4, hipMemcpyHostToDevice, s), "copy");
-            STEP(hipStreamSynchronize(s), "sync");
-        }
-    }
-    for (int lev = (int)level.size() - 2; !done && lev < kMaxDepth; ++lev) {
-        const int32_t lo = level[(size_t)lev], hi = level[(size_t)lev + 1];
-        const int32_t w = hi - lo;
-        if (w <= 0) break;
-        hipLaunchKernelGGL(k_level_count, dim3(blocks(w, kBlock)), dim3(kBlock), 0, s, cells(),
-                           skey, (const int32_t *)lv, lev, w, P.nleaf, (const int *)lvflag,
-                           B[T_NCH].as<int32_t>());
-        LAUNCHED("level count");
-        if (!scan(w)) return fail();
-        int32_t tail[2];
-        STEP(hipMemcpyAsync(&tail[0], B[T_NOFF].as<int32_t>() + (w - 1), 4,
-                            hipMemcpyDeviceToHost, s),
-             "copy");
-        STEP(hipMemcpyAsync(&tail[1], B[T_NCH].as<int32_t>() + (w - 1), 4,
+        hipLaunchKernelGGL(k_table, dim3(1), dim3(64), 0, s, B[T_NOFF].as<int32_t>(), rows, nb,
+                           flag, B[T_TABLE].as<int32_t>());
+        LAUNCHED("level table");
+        STEP(hipMemcpyAsync(table, B[T_TABLE].p, (size_t)(4 + rows + 2) * 4,
                             hipMemcpyDeviceToHost, s),
              "copy");
         STEP(hipStreamSynchronize(s), "sync");
-        const int64_t total = (int64_t)tail[0] + tail[1];
-        if (total == 0) break;
-        if ((int64_t)hi + total > 0x7fffffffLL) {
+        if (table[0]) {
+            code = BHQ_E_NONFINITE;
+            what = "non-finite position or mass";
+            return fail();
+        }
+        if (table[1]) {
+            code = BHQ_E_ARG;
+            what = "eps2 must be finite and >= 2^-126";
+            return fail();
+        }
+        if (!table[2] || lo == 0) break;
+        lo = 0;
+        STEP(hipMemsetAsync(flag + 2, 0, 4, s), "memset");
+    }
+    Depths level{};  // depth l is cells [first[l], first[l + 1]) (in level order)
+    int nlevels = 0;
+    for (int l = 0; l < rows; ++l) {
+        level.first[l] = table[4 + l];
+        level.first[l + 1] = table[4 + l + 1];
+        if (table[4 + l + 1] < table[4 + l]) {
             code = BHQ_E_RANGE;
             what = "more than 2^31 cells";
             return fail();
         }
-        if (!ensure((size_t)(hi + total), (size_t)hi)) return fail();
-        hipLaunchKernelGGL(k_level_write, dim3(blocks(w, kBlock)), dim3(kBlock), 0, s, cells(),
-                           skey, lv, lev, w, B[T_NCH].as<int32_t>(), B[T_NOFF].as<int32_t>(),
-                           (int32_t)std::min<size_t>(cap, 0x7fffffff), lvflag);
-        LAUNCHED("level write");
-        level.push_back((int32_t)(hi + total));
+        if (table[4 + l + 1] > table[4 + l]) nlevels = l + 1;
     }
-    const int32_t ncell = level.back();
-    hipLaunchKernelGGL(k_leaf_order, dim3(blocks(ncell, kBlock)), dim3(kBlock), 0, s, cells(),
-                       ncell, idx);
-    LAUNCHED("leaf order");
+    const int32_t ncell = table[4 + rows];
 
-    // moments straight into the cell pool
+    // cells
+    STEP(B[T_WC].reserve((size_t)ncell * sizeof(WCell)), "allocation");
+    STEP(B[T_WL].reserve((size_t)ncell * sizeof(WLink)), "allocation");
+    WCell *wc = B[T_WC].as<WCell>();
+    WLink *wl = B[T_WL].as<WLink>();
+    CellArgs CA{};
+    CA.s = S;
+    CA.first = B[T_NOFF].as<int32_t>();
+    CA.roots = roots;
+    CA.wc = wc;
+    CA.wl = wl;
+    CA.ngroup0 = ncell;
+    if (nsys > 1) {
+        // each system's cells in a row
+        const int64_t tab = (int64_t)nsys * rows;
+        STEP(B[T_LSC].reserve((size_t)(tab + rows) * 4), "allocation");
+        STEP(B[T_LSN].reserve((size_t)tab * 4), "allocation");
+        STEP(B[T_SHIFT].reserve((size_t)tab * 4), "allocation");
+        STEP(B[T_BYLEVEL].reserve((size_t)ncell * 4), "allocation");
+        int32_t *before = B[T_LSC].as<int32_t>(), *cnt = B[T_LSN].as<int32_t>();
+        int32_t *shift = B[T_SHIFT].as<int32_t>();
+        hipLaunchKernelGGL(k_sys_first, dim3((unsigned)nsys + 1), dim3(64), 0, s, S, CA.first, nb,
+                           before);
+        LAUNCHED("system cells");
+        hipLaunchKernelGGL(k_sys_cells, dim3(blocks(tab, kBlock)), dim3(kBlock), 0, s, before, tab,
+                           rows, cnt);
+        LAUNCHED("system cells");
+        size_t st = 0;
+        STEP(hipcub::DeviceScan::ExclusiveSum(nullptr, st, cnt, shift, (int)tab, s), "scan size");
+        STEP(B[T_SORT].reserve(std::max(st, B[T_SORT].cap)), "allocation");
+        STEP(hipcub::DeviceScan::ExclusiveSum(B[T_SORT].p, st, cnt, shift, (int)tab, s), "scan");
+        hipLaunchKernelGGL(k_sys_shift, dim3(blocks(tab, kBlock)), dim3(kBlock), 0, s, before, tab,
+                           shift);
+        LAUNCHED("system cells");
+        CA.shift = shift;
+        CA.by_level = B[T_BYLEVEL].as<int32_t>();
+    }
+    STEP(B[T_GROUPS].reserve((size_t)(group_row ? table[4 + rows + 1] - ncell : n) * 4),
+         "allocation");
+    int32_t *groups = B[T_GROUPS].as<int32_t>();
+    if (group_row) {
+        CA.groups = groups;
+    } else {
+        STEP(B[T_PARENT].reserve((size_t)ncell * 4), "allocation");
+        CA.parent = B[T_PARENT].as<int32_t>();
+    }
+    hipLaunchKernelGGL(k_cells, dim3((unsigned)nb), dim3(kBlock), 0, s, CA, nb);
+    LAUNCHED("cells");
+
+    // particles in tree order, in the layout of the force context
+    STEP(O.order->reserve((size_t)n * 4), "allocation");
+    STEP(O.pool_p->reserve((size_t)n * sizeof(PartRec)), "allocation");
+    STEP(O.xi->reserve((size_t)n * 8), "allocation");
+    STEP(O.yi->reserve((size_t)n * 8), "allocation");
+    STEP(O.zi->reserve((size_t)n * 8), "allocation");
+    if (P.eps2) STEP(O.e2i->reserve((size_t)n * 8), "allocation");
+    hipLaunchKernelGGL(k_particles_out, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s,
+                       B[T_IDX1].as<int32_t>(), S.info, n, P.x, P.m, P.eps2,
+                       O.order->as<int32_t>(), O.pool_p->as<PartRec>(), O.xi->as<double>(),
+                       O.yi->as<double>(), O.zi->as<double>(),
+                       P.eps2 ? O.e2i->as<double>() : nullptr);
+    LAUNCHED("particle pool");
+
+    // moments straight into the cell pool (the deepest cells are leaves)
     STEP(O.pool_c->reserve((size_t)ncell * sizeof(CellRec)), "allocation");
     CellRec *pc = O.pool_c->as<CellRec>();
-    hipLaunchKernelGGL(k_moments_leaf, dim3(blocks(ncell, kBlock)), dim3(kBlock), 0, s,
-                       cells(), ncell, idx, P.x, P.m, pc);
+    hipLaunchKernelGGL(k_moments_leaf, dim3(blocks(ncell, kBlock)), dim3(kBlock), 0, s, wl, ncell,
+                       O.pool_p->as<PartRec>(), wc, pc);
     LAUNCHED("leaf moments");
-    for (int l = (int)level.size() - 2; l >= 0; --l) {
-        const int32_t lo = level[(size_t)l], hi = level[(size_t)l + 1];
-        hipLaunchKernelGGL(k_moments_level, dim3(blocks(hi - lo, kBlock)), dim3(kBlock), 0, s,
-                           cells(), lo, hi, pc);
+    int top = -1;
+    while (top + 1 <= nlevels - 2 &&
+           level.first[top + 2] - level.first[top + 1] <= kTopCells)
+        ++top;
+    for (int l = nlevels - 2; l > top; --l) {
+        const int32_t b = level.first[l], e = level.first[l + 1];
+        hipLaunchKernelGGL(k_moments_level, dim3(blocks(e - b, kBlock)), dim3(kBlock), 0, s, wl, b,
+                           e, CA.by_level, wc, pc);
+        LAUNCHED("cell moments");
+    }
+    if (top >= 0) {
+        hipLaunchKernelGGL(k_moments_top, dim3(1), dim3(1024), 0, s, wl, level, top, CA.by_level,
+                           wc, pc);
         LAUNCHED("cell moments");
     }
 
-    // a batch: renumber the cells system by system (each system breadth
-    // first), then the walk starts from each group's own root
-    std::vector<int32_t> sys_root((size_t)nsys, 0);
-    if (nsys > 1) {
-        const int nl = (int)level.size() - 1;
-        const size_t tab = (size_t)kFrames * nsys;
-        STEP(B[T_LSC].reserve(tab * 4 * 3), "allocation");
-        int32_t *cnt = B[T_LSC].as<int32_t>();
-        STEP(hipMemsetAsync(cnt, 0, tab * 4, s), "memset");
-        hipLaunchKernelGGL(k_level_sys_count, dim3(blocks(ncell, kBlock)), dim3(kBlock), 0, s,
-                           cells(), ncell, nsys, cnt);
-        LAUNCHED("level counts");
-        std::vector<int32_t> hc(tab), base(tab, 0), first(tab, 0);
-        STEP(hipMemcpyAsync(hc.data(), cnt, tab * 4, hipMemcpyDeviceToHost, s), "copy");
-        STEP(hipStreamSynchronize(s), "sync");
-        int64_t cb = 0;
-        for (int q = 0; q < nsys; ++q) {
-            sys_root[(size_t)q] = (int32_t)cb;
-            for (int l = 0; l < nl; ++l) {
-                base[(size_t)l * nsys + q] = (int32_t)cb;
-                cb += hc[(size_t)l * nsys + q];
-            }
-        }
-        for (int l = 0; l < nl; ++l) {
-            int64_t f = level[(size_t)l];
-            for (int q = 0; q < nsys; ++q) {
-                first[(size_t)l * nsys + q] = (int32_t)f;
-                f += hc[(size_t)l * nsys + q];
-            }
-        }
-        STEP(hipMemcpyAsync(cnt + tab, base.data(), tab * 4, hipMemcpyHostToDevice, s), "copy");
-        STEP(hipMemcpyAsync(cnt + 2 * tab, first.data(), tab * 4, hipMemcpyHostToDevice, s),
-             "copy");
-        STEP(B[T_PERM].reserve((size_t)ncell * 4), "allocation");
-        int32_t *perm = B[T_PERM].as<int32_t>();
-        hipLaunchKernelGGL(k_perm, dim3(blocks(ncell, kBlock)), dim3(kBlock), 0, s, cells(),
-                           ncell, nsys, cnt + tab, cnt + 2 * tab, perm);
-        LAUNCHED("renumbering");
-        // permute each cell array into a scratch buffer and copy it back (the
-        // arrays keep their allocations; everything is ordered on stream s)
-        const unsigned g = blocks(ncell, kBlock);
-        DevArray nb;
-        if (!hip(nb.reserve((size_t)ncell * sizeof(CellRec)), "allocation")) return fail();
-        auto apply = [&](DevArray &arr, size_t elem, int kind) -> bool {
-            if (kind == 0)
-                hipLaunchKernelGGL((k_permute<double>), dim3(g), dim3(kBlock), 0, s, ncell, perm,
-                                   arr.as<double>(), nb.as<double>(), false);
-            else if (kind == 1)
-                hipLaunchKernelGGL((k_permute<uint64_t>), dim3(g), dim3(kBlock), 0, s, ncell,
-                                   perm, arr.as<uint64_t>(), nb.as<uint64_t>(), false);
-            else if (kind == 2 || kind == 3)
-                hipLaunchKernelGGL((k_permute<int32_t>), dim3(g), dim3(kBlock), 0, s, ncell,
-                                   perm, arr.as<int32_t>(), nb.as<int32_t>(), kind == 3);
-            else
-                hipLaunchKernelGGL((k_permute<CellRec>), dim3(g), dim3(kBlock), 0, s, ncell,
-                                   perm, arr.as<CellRec>(), nb.as<CellRec>(), false);
-            if (!hip(hipGetLastError(), "renumbering")) return false;
-            return hip(hipMemcpyAsync(arr.p, nb.p, (size_t)ncell * elem,
-                                      hipMemcpyDeviceToDevice, s),
-                       "copy");
-        };
-        bool ok = true;
-        for (TreeBuf b : {T_CX, T_CY, T_CZ, T_SIDE}) ok = ok && apply(B[b], 8, 0);
-        ok = ok && apply(B[T_CKEY], 8, 1);
-        for (TreeBuf b : {T_FIRST, T_COUNT, T_NCHILD, T_DEPTH, T_CSYS}) ok = ok && apply(B[b], 4, 2);
-        for (TreeBuf b : {T_CHILD0, T_PARENT}) ok = ok && apply(B[b], 4, 3);
-        ok = ok && apply(*O.pool_c, sizeof(CellRec), 4);
-        (void)hipStreamSynchronize(s);
-        nb.release();
-        if (!ok) return fail();
-    }
-    STEP(B[T_SYSROOT].reserve((size_t)nsys * 4), "allocation");
-    STEP(hipMemcpyAsync(B[T_SYSROOT].p, sys_root.data(), (size_t)nsys * 4,
-                        hipMemcpyHostToDevice, s),
-         "copy");
-
     // groups in depth-first order
-    STEP(B[T_GSTART].reserve((size_t)n * 4), "allocation");
-    STEP(B[T_GROUPS].reserve((size_t)n * 4), "allocation");
-    STEP(B[T_NSEL].reserve(64), "allocation");
-    hipLaunchKernelGGL(k_fill_i32, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s,
-                       B[T_GSTART].as<int32_t>(), n, -1);
-    LAUNCHED("fill");
-    hipLaunchKernelGGL(k_group_mark, dim3(blocks(ncell, kBlock)), dim3(kBlock), 0, s, cells(),
-                       ncell, P.ncrit, B[T_GSTART].as<int32_t>());
-    LAUNCHED("groups");
-    {
+    int64_t ng = table[4 + rows + 1] - ncell;
+    if (!group_row) {
+        STEP(B[T_GSTART].reserve((size_t)n * 4), "allocation");
+        STEP(B[T_NSEL].reserve(64), "allocation");
+        hipLaunchKernelGGL(k_fill_i32, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s,
+                           B[T_GSTART].as<int32_t>(), n, -1);
+        LAUNCHED("fill");
+        hipLaunchKernelGGL(k_group_mark, dim3(blocks(ncell, kBlock)), dim3(kBlock), 0, s, wl,
+                           CA.parent, ncell, P.ncrit, B[T_GSTART].as<int32_t>());
+        LAUNCHED("groups");
         size_t st = 0;
-        STEP(hipcub::DeviceSelect::If(nullptr, st, B[T_GSTART].as<int32_t>(),
-                                      B[T_GROUPS].as<int32_t>(), B[T_NSEL].as<int32_t>(),
-                                      (int)n, NonNegative(), s),
+        STEP(hipcub::DeviceSelect::If(nullptr, st, B[T_GSTART].as<int32_t>(), groups,
+                                      B[T_NSEL].as<int32_t>(), (int)n, NonNegative(), s),
              "select size");
         STEP(B[T_SORT].reserve(std::max(st, B[T_SORT].cap)), "allocation");
-        STEP(hipcub::DeviceSelect::If(B[T_SORT].p, st, B[T_GSTART].as<int32_t>(),
-                                      B[T_GROUPS].as<int32_t>(), B[T_NSEL].as<int32_t>(),
-                                      (int)n, NonNegative(), s),
+        STEP(hipcub::DeviceSelect::If(B[T_SORT].p, st, B[T_GSTART].as<int32_t>(), groups,
+                                      B[T_NSEL].as<int32_t>(), (int)n, NonNegative(), s),
              "select");
+        int32_t ng32 = 0;
+        STEP(hipMemcpyAsync(&ng32, B[T_NSEL].p, 4, hipMemcpyDeviceToHost, s), "copy");
+        STEP(hipStreamSynchronize(s), "sync");
+        ng = ng32;
     }
-    int32_t ng32 = 0;
-    STEP(hipMemcpyAsync(&ng32, B[T_NSEL].p, 4, hipMemcpyDeviceToHost, s), "copy");
-    STEP(hipStreamSynchronize(s), "sync");
-    const int64_t ng = ng32;
-    const int32_t *groups = B[T_GROUPS].as<int32_t>();
+    STEP(O.i_off->reserve((size_t)(ng + 1) * 8), "allocation");
+    STEP(O.gcx->reserve((size_t)ng * 8), "allocation");
+    STEP(O.gcy->reserve((size_t)ng * 8), "allocation");
+    STEP(O.gcz->reserve((size_t)ng * 8), "allocation");
+    if (nsys > 1) STEP(B[T_GROOT].reserve((size_t)ng * 4), "allocation");
+    hipLaunchKernelGGL(k_groups_out, dim3(blocks(ng + 1, kBlock)), dim3(kBlock), 0, s, wc, wl,
+                       groups, ng, n, sys_off, nsys, CA.shift, rows, O.i_off->as<int64_t>(),
+                       O.gcx->as<double>(), O.gcy->as<double>(), O.gcz->as<double>(),
+                       nsys > 1 ? B[T_GROOT].as<int32_t>() : nullptr);
+    LAUNCHED("groups");
 
     // walk: count, offsets, fill
-    STEP(B[T_WC].reserve((size_t)ncell * sizeof(WCell)), "allocation");
-    STEP(B[T_WL].reserve((size_t)ncell * sizeof(WLink)), "allocation");
-    hipLaunchKernelGGL(k_walk_cells, dim3(blocks(ncell, kBlock)), dim3(kBlock), 0, s, cells(),
-                       ncell, pc, B[T_WC].as<WCell>(), B[T_WL].as<WLink>());
-    LAUNCHED("walk cells");
     STEP(B[T_JPCNT].reserve((size_t)(ng + 1) * 8), "allocation");
     STEP(B[T_JCCNT].reserve((size_t)(ng + 1) * 8), "allocation");
     STEP(O.jp_off->reserve((size_t)(ng + 1) * 8), "allocation");
@@ -1590,11 +1691,10 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     STEP(hipMemsetAsync(B[T_JCCNT].as<int64_t>() + ng, 0, 8, s), "memset");
     WalkArgs W{};
     W.groups = groups;
-    W.cell_sys = B[T_CSYS].as<int32_t>();
-    W.sys_root = B[T_SYSROOT].as<int32_t>();
+    W.groot = nsys > 1 ? B[T_GROOT].as<int32_t>() : nullptr;
     W.ng = ng;
-    W.wc = B[T_WC].as<WCell>();
-    W.wl = B[T_WL].as<WLink>();
+    W.wc = wc;
+    W.wl = wl;
     W.theta2 = P.theta * P.theta;
     W.rcut = P.rcut;
     {
@@ -1604,10 +1704,10 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     W.box = P.box;
     W.jp_cnt = B[T_JPCNT].as<int64_t>();
     W.jc_cnt = B[T_JCCNT].as<int64_t>();
-    W.flag = B[T_FLAG].as<int>();
+    W.flag = flag + 4;
     W.most = W.flag + 2;
     // one frame per level below the root: enough for the deepest opened cell
-    W.frames = std::max(1, std::min(kFrames, (int)level.size() - 1));
+    W.frames = std::max(1, std::min(kFrames, nlevels));
     const size_t walk_lds = (size_t)W.frames * (kWalkBlock * sizeof(int2) + kWalkBlock / kOct * 4);
     // octets the level walk's LDS holds; 0: octet walk
     int oct_cap = std::min(P.cap_o > 0 ? P.cap_o : (P.cap_o == 0 ? kOctFirst : 0), kOctMost);
@@ -1649,8 +1749,9 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     W.gbox = nullptr;
     if (W.rdrop2 > 0.0) {
         STEP(B[T_GBOX].reserve((size_t)ng * 6 * 8), "allocation");
-        hipLaunchKernelGGL(k_group_box, dim3(blocks(ng, kBlock)), dim3(kBlock), 0, s, cells(),
-                           groups, ng, idx, P.x, B[T_GBOX].as<double>());
+        hipLaunchKernelGGL(k_group_box, dim3(blocks(ng * kOct, kBlock)), dim3(kBlock), 0, s, wl,
+                           groups, ng, O.xi->as<double>(), O.yi->as<double>(),
+                           O.zi->as<double>(), B[T_GBOX].as<double>());
         LAUNCHED("group boxes");
         W.gbox = B[T_GBOX].as<double>();
     }
@@ -1693,7 +1794,7 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
                  "reduce");
         }
         hipLaunchKernelGGL(k_list_stats, dim3(1), dim3(1), 0, s, ng, O.jp_off->as<int64_t>(),
-                           O.jc_off->as<int64_t>(), B[T_FLAG].as<int>(), stats);
+                           O.jc_off->as<int64_t>(), W.flag, stats);
         LAUNCHED("list totals");
         STEP(hipMemcpyAsync(hstats, stats, sizeof(hstats), hipMemcpyDeviceToHost, s), "copy");
         STEP(hipStreamSynchronize(s), "sync");
@@ -1743,31 +1844,12 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     O.max_p = max_p;
     O.max_c = max_c;
 
-    // particles and groups in the layout of the force context
-    STEP(O.pool_p->reserve((size_t)n * sizeof(PartRec)), "allocation");
-    STEP(O.xi->reserve((size_t)n * 8), "allocation");
-    STEP(O.yi->reserve((size_t)n * 8), "allocation");
-    STEP(O.zi->reserve((size_t)n * 8), "allocation");
-    STEP(O.i_off->reserve((size_t)(ng + 1) * 8), "allocation");
-    STEP(O.gcx->reserve((size_t)ng * 8), "allocation");
-    STEP(O.gcy->reserve((size_t)ng * 8), "allocation");
-    STEP(O.gcz->reserve((size_t)ng * 8), "allocation");
-    if (P.eps2) STEP(O.e2i->reserve((size_t)n * 8), "allocation");
-    hipLaunchKernelGGL(k_particles_out, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s, idx, n,
-                       P.x, P.m, P.eps2, O.pool_p->as<PartRec>(), O.xi->as<double>(),
-                       O.yi->as<double>(), O.zi->as<double>(),
-                       P.eps2 ? O.e2i->as<double>() : nullptr);
-    LAUNCHED("particle pool");
-    hipLaunchKernelGGL(k_groups_out, dim3(blocks(ng + 1, kBlock)), dim3(kBlock), 0, s, cells(),
-                       groups, ng, n, O.i_off->as<int64_t>(), O.gcx->as<double>(),
-                       O.gcy->as<double>(), O.gcz->as<double>());
-    LAUNCHED("groups");
     STEP(hipStreamSynchronize(s), "sync");
     O.ng = ng;
     O.njp = njp;
     O.njc = njc;
     O.ncell = ncell;
-    O.nlevels = (int)level.size() - 1;
+    O.nlevels = nlevels;
 #undef STEP
 #undef LAUNCHED
     return BHQ_OK;

@@ -30,3 +30,67 @@ def test_walk_branches(n, theta, ncrit, nleaf):
             assert bhq.bhq_get_build_info(ctx)[1:] == longest
     finally:
         bhq.bhq_destroy(ctx)
+
+
+def _clumps(n, g):
+    """Clumps of coincident and nearly coincident particles on a sphere."""
+    x, m = synth.plummer(n, g)
+    x[: n // 4] = x[0]
+    x[n // 4: n // 2] = x[n // 4] + 1e-7 * g.random((n // 2 - n // 4, 3))
+    return x, m
+
+
+@pytest.mark.parametrize("n,ncrit,nleaf", [
+    (1, 1, 1), (2, 1, 1),
+    (1022, 32, 8), (1023, 32, 8), (1024, 32, 8), (1025, 33, 7),  # edges of a tile of particles
+    (30000, 64, 8),                    # the scan of the tiles' counts in one block
+    (800000, 256, 8),                  # ... and by several
+    (9000, 4096, 1), (9000, 4097, 8),  # the longest group in windows, and past it
+    (12000, 4097, 4097),               # leaves past it
+])
+def test_cells_from_keys(n, ncrit, nleaf):
+    """Cells, groups, order and moments; a first build and a rebuild."""
+    x, m = synth.plummer(n, synth.rng(41)) if n > 100000 else _clumps(n, synth.rng(41))
+    h = _host(x, m, 0.8, ncrit, nleaf)
+    ctx = bhq.bhq_create(0, bhq.QUAD, bhq.FP32_OFS64)
+    try:
+        for build in range(2):
+            _same(h, _device(ctx, x, m, 0.8, ncrit, nleaf), "cells %d build %d" % (n, build))
+    finally:
+        bhq.bhq_destroy(ctx)
+
+
+@pytest.mark.parametrize("sizes", [
+    (1, 1, 3), (1023, 1, 1024, 5, 2000), (700,) * 9,
+    tuple(range(1, 80)),               # many systems in one tile
+])
+@pytest.mark.parametrize("ncrit,nleaf", [(16, 4), (5000, 8)])
+def test_batch_cells_from_keys(sizes, ncrit, nleaf):
+    """Systems whose particles begin and end inside tiles, one of them of
+    clumps; a first build (sorted as segments) and rebuilds (sorted in one go;
+    the last deeper than the one before)."""
+    g = synth.rng(42)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    shallow = [synth.uniform_cube(k, g) for k in sizes]
+    deep = list(shallow)
+    deep[-1] = _clumps(sizes[-1], g)
+    ctx = bhq.bhq_create(0, bhq.QUAD, bhq.FP32_OFS64)
+    try:
+        for build, parts in enumerate((shallow, shallow, deep, deep)):
+            x = np.concatenate([p[0] for p in parts])
+            m = np.concatenate([p[1] for p in parts])
+            L = bhq.bhq_build_lists_batch(off, x, m, 0.6, ncrit, nleaf)
+            try:
+                h = bhq.bhq_lists_export(L, len(m))
+                h["cells"] = bhq.bhq_lists_cells(L)
+                h["sizes"] = bhq.bhq_lists_sizes(L)
+            finally:
+                bhq.bhq_lists_free(L)
+            bhq.bhq_build_lists_device_batch(ctx, off, torch.from_numpy(x).cuda(),
+                                             torch.from_numpy(m).cuda(), 0.6, ncrit, nleaf)
+            d = bhq.bhq_get_lists(ctx, len(m))
+            d["cells"] = bhq.bhq_get_cells(ctx)
+            d["sizes"] = bhq.bhq_get_lists_sizes(ctx)
+            _same(h, d, "batch %d systems build %d" % (len(sizes), build))
+    finally:
+        bhq.bhq_destroy(ctx)
