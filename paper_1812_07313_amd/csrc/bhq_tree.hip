@@ -713,79 +713,107 @@ __global__ __launch_bounds__(kBlock) void k_moments_leaf(const WLink *wl, int32_
     }
 }
 
-// Moments of an internal cell from its children's, in octant order.
-__device__ __forceinline__ void cell_moments(int32_t c, const WLink &l, WCell *wc, CellRec *pc)
+// Moments of an internal cell from its children's, in octant order, by the
+// parallel-axis shift: the host's sums in the host's order, with an octet of
+// lanes per cell.  Each lane loads one child (contiguous records, all loads in
+// flight at once) into LDS, and each sum is one lane's: mass and first
+// moments, then the traceless quadrupole and the trace about the centre of
+// mass.  With a thread per cell, whose loads followed one another, the depths
+// of a Plummer sphere of 16,384 took 75 us (44 now) and those of the
+// clustered 2^22 241 us (146).  Leaves stay with a thread each, whose loads
+// are all in flight too: with an octet they took 176 us there against 112
+// (the octet's second sums do 2.5 times the work).
+constexpr int kPart = 11;              // m, x, y, z, six moments, trace
+constexpr int kPartStride = kOct + 1;  // (spreads the quantities over banks)
+constexpr int kMomOcts = kBlock / kOct;
+
+// The lanes of an octet are in one wave, whose LDS operations complete in
+// order: this only keeps the compiler from moving them.
+__device__ __forceinline__ void wave_fence()
 {
-    const int32_t c0 = l.child0, nc = l.cend - l.child0;
-    double M = 0.0, s[3] = {0.0, 0.0, 0.0};
-    for (int32_t k = 0; k < nc; ++k) {
-        const CellRec &h = pc[c0 + k];
-        M += h.m;
-        s[0] += h.m * h.x;
-        s[1] += h.m * h.y;
-        s[2] += h.m * h.z;
-    }
-    const double ctr[3] = {wc[c].cx, wc[c].cy, wc[c].cz};
-    double cm[3];
-    for (int a = 0; a < 3; ++a) cm[a] = M > 0.0 ? s[a] / M : ctr[a];
-    double q6[6] = {0, 0, 0, 0, 0, 0}, T = 0.0;
-    for (int32_t k = 0; k < nc; ++k) {
-        const CellRec &h = pc[c0 + k];
-        const double Mc = h.m;
-        const double D[3] = {h.x - cm[0], h.y - cm[1], h.z - cm[2]};
-        const double D2 = D[0] * D[0] + D[1] * D[1] + D[2] * D[2];
-        q6[0] += h.q00 + Mc * (3.0 * D[0] * D[0] - D2);
-        q6[1] += h.q01 + Mc * 3.0 * D[0] * D[1];
-        q6[2] += h.q02 + Mc * 3.0 * D[0] * D[2];
-        q6[3] += h.q11 + Mc * (3.0 * D[1] * D[1] - D2);
-        q6[4] += h.q12 + Mc * 3.0 * D[1] * D[2];
-        q6[5] += h.q22 + Mc * (3.0 * D[2] * D[2] - D2);
-        T += h.t + Mc * D2;
-    }
-    CellRec r;
-    r.x = cm[0];
-    r.y = cm[1];
-    r.z = cm[2];
-    r.m = M;
-    r.q00 = q6[0];
-    r.q01 = q6[1];
-    r.q02 = q6[2];
-    r.q11 = q6[3];
-    r.q12 = q6[4];
-    r.q22 = q6[5];
-    r.t = T;
-    r.pad = 0.0;
-    store_moments(c, r, wc, pc);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
-// Cells of one depth: numbers lo .. hi - 1, or those of by_level.
+__device__ __forceinline__ void cell_moments(int32_t c, const WLink &l, double *sh, WCell *wc,
+                                             CellRec *pc)
+{
+    const int k = threadIdx.x % kOct;
+    const int n = l.cend - l.child0;
+    wave_fence();
+    if (k < n) {
+        const CellRec &q = pc[l.child0 + k];
+        const double v[kPart] = {q.m,   q.x,   q.y,   q.z,   q.q00, q.q01,
+                                 q.q02, q.q11, q.q12, q.q22, q.t};
+#pragma unroll
+        for (int i = 0; i < kPart; ++i) sh[i * kPartStride + k] = v[i];
+    }
+    wave_fence();
+    // lane 0: mass; lanes 1 to 3: first moments (entries past the children
+    // are read but not added)
+    double sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < kOct; ++i) {
+        const double m = sh[i];
+        const double v = sum + (k == 0 ? m : m * sh[(k & 3) * kPartStride + i]);
+        sum = i < n ? v : sum;
+    }
+    const double M = __shfl(sum, 0, kOct);
+    const double ctr = k == 1 ? wc[c].cx : (k == 2 ? wc[c].cy : wc[c].cz);
+    const double mine = M > 0.0 ? sum / M : ctr;
+    const double cm[3] = {__shfl(mine, 1, kOct), __shfl(mine, 2, kOct), __shfl(mine, 3, kOct)};
+    // lanes 0 to 5: q00, q01, q02, q11, q12, q22; lane 6: the trace
+    const int qa = k < 3 ? 0 : (k < 5 ? 1 : 2), qb = k < 3 ? k : (k < 5 ? k - 2 : 2);
+    double q = 0.0;
+#pragma unroll
+    for (int i = 0; i < kOct; ++i) {
+        const double m = sh[i];
+        const double d0 = sh[kPartStride + i] - cm[0], d1 = sh[2 * kPartStride + i] - cm[1],
+                     d2 = sh[3 * kPartStride + i] - cm[2];
+        const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+        const double da = qa == 0 ? d0 : (qa == 1 ? d1 : d2);
+        const double db = qb == 0 ? d0 : (qb == 1 ? d1 : d2);
+        const double v =
+            k >= 6 ? m * r2 : (qa == qb ? m * (3.0 * da * da - r2) : m * 3.0 * da * db);
+        const double u = q + (sh[(k < 7 ? 4 + k : 10) * kPartStride + i] + v);
+        q = i < n ? u : q;
+    }
+    double *r = reinterpret_cast<double *>(pc + c);  // x, y, z, m, moments, trace, 0
+    r[4 + k] = k < 7 ? q : 0.0;
+    if (k < 4) r[(k + 3) & 3] = k == 0 ? M : mine;
+    if (k > 0 && k < 4) (&wc[c].mx)[k - 1] = mine;
+}
+
+// The internal cells of one depth: numbers lo .. hi - 1, or those of by_level.
 __global__ __launch_bounds__(kBlock) void k_moments_level(const WLink *wl, int32_t lo, int32_t hi,
                                                           const int32_t *by_level, WCell *wc,
                                                           CellRec *pc)
 {
-    int32_t c = lo + (int32_t)(blockIdx.x * kBlock + threadIdx.x);
-    if (c >= hi) return;
-    if (by_level) c = by_level[c];
+    __shared__ double sh[kMomOcts][kPart * kPartStride];
+    const int64_t i = lo + ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kOct;
+    if (i >= hi) return;
+    const int32_t c = by_level ? by_level[i] : (int32_t)i;
     const WLink l = wl[c];
-    if (l.child0 >= 0) cell_moments(c, l, wc, pc);
+    if (l.child0 >= 0) cell_moments(c, l, sh[threadIdx.x / kOct], wc, pc);
 }
 
-// The depths `top` .. 0, few cells each, in one block: a launch per depth
-// costs more than the work.
+// The internal cells of depths `top` .. 0, few each, in one block: a launch
+// per depth costs more than the work.
 struct Depths {
     int32_t first[kMaxDepth + 2];
 };
-constexpr int kTopCells = 2048;  // cells of a depth that one block takes
+constexpr int kTopCells = 2 * kMomOcts;  // cells of a depth that one block takes
 
-__global__ __launch_bounds__(1024) void k_moments_top(const WLink *wl, const Depths D, int top,
-                                                      const int32_t *by_level, WCell *wc,
-                                                      CellRec *pc)
+__global__ __launch_bounds__(kBlock) void k_moments_top(const WLink *wl, const Depths D, int top,
+                                                        const int32_t *by_level, WCell *wc,
+                                                        CellRec *pc)
 {
+    __shared__ double sh[kMomOcts][kPart * kPartStride];
+    const int o = threadIdx.x / kOct;
     for (int d = top; d >= 0; --d) {
-        for (int32_t i = D.first[d] + (int32_t)threadIdx.x; i < D.first[d + 1]; i += 1024) {
+        for (int32_t i = D.first[d] + o; i < D.first[d + 1]; i += kMomOcts) {
             const int32_t c = by_level ? by_level[i] : i;
             const WLink l = wl[c];
-            if (l.child0 >= 0) cell_moments(c, l, wc, pc);
+            if (l.child0 >= 0) cell_moments(c, l, sh[o], wc, pc);
         }
         __syncthreads();
     }
@@ -1637,12 +1665,12 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         ++top;
     for (int l = nlevels - 2; l > top; --l) {
         const int32_t b = level.first[l], e = level.first[l + 1];
-        hipLaunchKernelGGL(k_moments_level, dim3(blocks(e - b, kBlock)), dim3(kBlock), 0, s, wl, b,
-                           e, CA.by_level, wc, pc);
+        hipLaunchKernelGGL(k_moments_level, dim3(blocks((int64_t)(e - b) * kOct, kBlock)),
+                           dim3(kBlock), 0, s, wl, b, e, CA.by_level, wc, pc);
         LAUNCHED("cell moments");
     }
     if (top >= 0) {
-        hipLaunchKernelGGL(k_moments_top, dim3(1), dim3(1024), 0, s, wl, level, top, CA.by_level,
+        hipLaunchKernelGGL(k_moments_top, dim3(1), dim3(kBlock), 0, s, wl, level, top, CA.by_level,
                            wc, pc);
         LAUNCHED("cell moments");
     }
