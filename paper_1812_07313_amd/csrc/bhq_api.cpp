@@ -141,6 +141,7 @@ struct bhq_ctx {
     // bhq_build_lists_device).
     bool tree_order = false;
     DevArray tbuf[bhq::T_COUNT_];  // device list builder working memory
+    void *build_host = nullptr;    // pinned: what its kernels write for the host
     bool have_jp_idx = false, have_jc_idx = false;
     int eps_mode = 0;  // 0 none, 1 uniform, 2 per-particle
     double eps2_all = 0.0;
@@ -449,9 +450,12 @@ int bhq_create(bhq_ctx **out, int device, int kernel, int precision)
         return BHQ_E_HIP;
     }
     if (hipEventCreate(&c->ev0) != hipSuccess ||
-        hipEventCreate(&c->ev1) != hipSuccess) {
-        g_create_error = "bhq_create: hipEventCreate failed";
+        hipEventCreate(&c->ev1) != hipSuccess ||
+        hipHostMalloc(&c->build_host, bhq::kBuildHostBytes, hipHostMallocDefault) !=
+            hipSuccess) {
+        g_create_error = "bhq_create: event or pinned memory allocation failed";
         if (c->ev0) (void)hipEventDestroy(c->ev0);
+        if (c->ev1) (void)hipEventDestroy(c->ev1);
         c->arr[A_QUEUE].release();
         delete c;
         return BHQ_E_HIP;
@@ -470,6 +474,7 @@ int bhq_destroy(bhq_ctx *ctx)
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     for (auto &a : ctx->arr) a.release();
     for (auto &a : ctx->tbuf) a.release();
+    if (ctx->build_host) (void)hipHostFree(ctx->build_host);
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
     if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
     delete ctx;
@@ -1547,15 +1552,26 @@ int bhq_set_groups_dev(bhq_ctx *ctx, int64_t ng, const int64_t *i_off,
     if (ctx->order_mode == BHQ_ORDER_XCD &&
         bhq::plan_order_device_supported(ctx->order_window, ctx->order_tail)) {
         // the offsets are on the device: plan the dispatch order there
-        int64_t ns = 0;
         std::string msg;
-        orc = bhq::plan_order_device(ng, ctx->arr[A_IOFF].as<int64_t>(),
-                                     ctx->arr[A_JPOFF].as<int64_t>(),
-                                     ctx->arr[A_JCOFF].as<int64_t>(), ctx->order_window,
-                                     ctx->order_tail, BHQ_XCDS, ctx->arr[A_ORDER],
-                                     ctx->arr[A_OSCRATCH], &ns, s, &msg);
+        bhq::ListPlan L;
+        L.ng = ng;
+        L.i_off = ctx->arr[A_IOFF].as<int64_t>();
+        L.jp_off = ctx->arr[A_JPOFF].as<int64_t>();
+        L.jc_off = ctx->arr[A_JCOFF].as<int64_t>();
+        L.window = ctx->order_window;
+        L.tail = ctx->order_tail;
+        L.xcds = BHQ_XCDS;
+        L.order = &ctx->arr[A_ORDER];
+        L.scratch = &ctx->arr[A_OSCRATCH];
+        L.stats = static_cast<int64_t *>(ctx->build_host);
+        orc = bhq::plan_lists_launch(L, s, &msg);
+        if (orc == BHQ_OK && (e = hipStreamSynchronize(s)) != hipSuccess) {
+            msg = std::string("set_groups_dev: order: ") + hipGetErrorString(e);
+            orc = BHQ_E_HIP;
+        }
+        if (orc == BHQ_OK) orc = bhq::plan_lists_finish(L, s, &msg);
         if (orc == BHQ_OK)
-            ctx->nslots = ns;
+            ctx->nslots = L.stats[bhq::kStatSlots];
         else
             ctx->fail(orc, "%s", msg.c_str());
     } else {
@@ -1812,9 +1828,22 @@ static int device_build(bhq_ctx *ctx, int64_t nsys, const int64_t *sys_off,
     TRY(check_device_range(ctx, m, (size_t)n * sizeof(double), "m"));
     if (eps2) TRY(check_device_range(ctx, eps2, (size_t)n * sizeof(double), "eps2"));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (ctx->launched) (void)hipEventSynchronize(ctx->ev1);
+    // the last compute may still read what the build's kernels write (growing
+    // an array frees the old one, which waits for the device)
+    if (ctx->launched) {
+        hipError_t e = hipStreamWaitEvent(s, ctx->ev1, 0);
+        if (e != hipSuccess) return ctx->hip_fail(e, "hipStreamWaitEvent");
+    }
 
-    bhq::TreeParams P{x, m, eps2, n, nsys, sys_off, theta, ncrit, nleaf, box, rcut};
+    // one softening for all is written with the particles
+    const double eps2_all = !eps2 && ctx->eps_mode == 1 ? ctx->eps2_all : 0.0;
+    bhq::TreeParams P{x, m, eps2, eps2_all, n, nsys, sys_off, theta, ncrit, nleaf, box, rcut};
+    const bool device_order =
+        ctx->order_mode == BHQ_ORDER_XCD &&
+        bhq::plan_order_device_supported(ctx->order_window, ctx->order_tail);
+    P.window = device_order ? ctx->order_window : 0;
+    P.tail = ctx->order_tail;
+    P.xcds = BHQ_XCDS;
     // A rebuild walks once into per-group slots sized from the previous
     // device build's longest lists; the slots may take up to 4 times the
     // previous lists' memory plus 256 MiB.
@@ -1842,7 +1871,10 @@ static int device_build(bhq_ctx *ctx, int64_t nsys, const int64_t *sys_off,
     O.jp_idx = &ctx->arr[A_JPIDX];
     O.jc_idx = &ctx->arr[A_JCIDX];
     O.order = &ctx->arr[A_TORDER];
+    O.slots = &ctx->arr[A_ORDER];
+    O.scratch = &ctx->arr[A_OSCRATCH];
     O.buf = ctx->tbuf;
+    O.host = ctx->build_host;
     ctx->ng = -1;  // no valid lists unless the build completes
     ++ctx->args_version;
     std::string msg;
@@ -1855,8 +1887,8 @@ static int device_build(bhq_ctx *ctx, int64_t nsys, const int64_t *sys_off,
         {A_AZ, (size_t)n * D}, {A_POT, (size_t)n * D},
     };
     for (auto &q : need) {
-        // A_E2I already holds the gathered softening when eps2 was given
-        if (q.a == A_E2I && eps2) continue;
+        // A_E2I already holds the softening when it is known
+        if (q.a == A_E2I && (eps2 || eps2_all > 0.0)) continue;
         hipError_t e = ctx->arr[q.a].reserve(q.bytes);
         if (e != hipSuccess) return ctx->hip_fail(e, "hipMalloc");
     }
@@ -1890,31 +1922,14 @@ static int device_build(bhq_ctx *ctx, int64_t nsys, const int64_t *sys_off,
         ctx->eps_mode = 2;
     else if (ctx->eps_mode == 2)
         ctx->eps_mode = 0;
-    ctx->nslots = 0;
-    int orc;
-    if (ctx->order_mode == BHQ_ORDER_XCD &&
-        bhq::plan_order_device_supported(ctx->order_window, ctx->order_tail)) {
-        // the offsets are on the device already: plan there
-        int64_t ns = 0;
-        orc = bhq::plan_order_device(O.ng, ctx->arr[A_IOFF].as<int64_t>(),
-                                     ctx->arr[A_JPOFF].as<int64_t>(),
-                                     ctx->arr[A_JCOFF].as<int64_t>(), ctx->order_window,
-                                     ctx->order_tail, BHQ_XCDS, ctx->arr[A_ORDER],
-                                     ctx->arr[A_OSCRATCH], &ns, s, &msg);
-        if (orc == BHQ_OK) {
-            ctx->nslots = ns;
-            ++ctx->args_version;
-        } else {
-            ctx->fail(orc, "%s", msg.c_str());
+    ctx->nslots = O.nslots;
+    if (!device_order) {
+        const int orc = ctx->upload_order();
+        if (orc != BHQ_OK) {
+            ctx->ng = -1;
+            return orc;
         }
-    } else {
-        orc = ctx->upload_order();
     }
-    if (orc != BHQ_OK) {
-        ctx->ng = -1;
-        return orc;
-    }
-    if (ctx->eps_mode == 1) TRY(ctx->fill_eps_uniform(s));
     return BHQ_OK;
 }
 

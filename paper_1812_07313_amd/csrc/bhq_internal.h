@@ -224,14 +224,34 @@ hipError_t launch_gather_rows(int64_t n, int words, const void *in, const int32_
                               void *out, hipStream_t s);
 hipError_t launch_iota(int32_t *v, int64_t n, hipStream_t s);
 
-// XCD dispatch order of ng groups whose offsets are in device memory,
-// computed on the GPU; equal to the host planner's table.  Supported for
-// window and tail up to 1024.  The table goes to `order`, its slot count
-// to *nslots; returns a BHQ_* code (message in *what).  Synchronises s.
+// Offsets from list lengths, the XCD dispatch order (the host planner's table,
+// for a window and tail up to 1024) and the numbers the host needs, all on the
+// device.  plan_lists_launch enqueues the work on s; after the caller's
+// synchronisation, stats (host memory that the GPU writes) holds the results,
+// and plan_lists_finish must be called: it runs the order again where the
+// table outgrew its allocation.  Both return a BHQ_* code (message in *what).
+enum ListStat {
+    kStatParts, kStatCells,        // list entries
+    kStatMaxParts, kStatMaxCells,  // longest lists
+    kStatWalk, kStatOpened,        // flag[0], flag[2] of the walk
+    kStatSlots,                    // launch slots
+    kStatCount
+};
+struct ListPlan {
+    int64_t ng = 0;
+    const int64_t *i_off = nullptr;
+    // list lengths, from which the offsets are written; NULL: offsets given
+    const int64_t *jp_cnt = nullptr, *jc_cnt = nullptr;
+    int64_t *jp_off = nullptr, *jc_off = nullptr;
+    int window = 0, tail = 0, xcds = 0;
+    const int *flag = nullptr;     // or NULL
+    int64_t *stats = nullptr;      // [kStatCount]
+    DevArray *order = nullptr;     // NULL: no order
+    DevArray *scratch = nullptr;
+};
 bool plan_order_device_supported(int window, int tail);
-int plan_order_device(int64_t ng, const int64_t *i_off, const int64_t *jp_off,
-                      const int64_t *jc_off, int window, int tail, int xcds, DevArray &order,
-                      DevArray &scratch, int64_t *nslots, hipStream_t s, std::string *what);
+int plan_lists_launch(const ListPlan &P, hipStream_t s, std::string *what);
+int plan_lists_finish(const ListPlan &P, hipStream_t s, std::string *what);
 int energy_partials();  // partial-sum slots (pairs) used by launch_energies
 hipError_t launch_energies(int64_t n, const double *m, const double *v,
                            const double *pot, double eps, double *part,
@@ -243,6 +263,7 @@ struct TreeParams {
     const double *x;
     const double *m;
     const double *eps2;       // [n] per-particle softening squared, or NULL
+    double eps2_all;          // > 0: every particle's, where eps2 is NULL
     int64_t n;
     int64_t nsys;             // independent systems (1: one system)
     const int64_t *sys_off;   // host [nsys + 1]: system s is [sys_off[s], sys_off[s+1])
@@ -259,6 +280,8 @@ struct TreeParams {
     // Cells a group may open in the level walk's LDS (0: unknown; < 0: a
     // group of an earlier build of this kind opened too many)
     int cap_o = 0;
+    // dispatch order planned with the build (window 0: none)
+    int window = 0, tail = 0, xcds = 0;
     // Levels of the tree of an earlier build of similar input: only the key
     // bits that such a tree reads are sorted (0: unknown).
     int spec_levels = 0;
@@ -287,10 +310,10 @@ constexpr int kOctFirst = 1024, kOctMost = 4080, kOctBytes = 16;
 
 // Builder working memory, kept between builds of one context.
 enum TreeBuf {
-    T_KEY, T_KEY2, T_IDX0, T_IDX1, T_INFO, T_SORT, T_BBOX, T_FLAG, T_TABLE,
+    T_KEY, T_KEY2, T_IDX0, T_IDX1, T_INFO, T_SORT, T_BBOX, T_FLAG,
     T_NCH, T_NOFF, T_PARENT, T_GSTART, T_GROUPS, T_GROOT, T_NSEL, T_WC, T_WL,
     T_JPCNT, T_JCCNT, T_SYSOFF, T_SYSOFF32, T_ROOTS, T_LSC, T_LSN, T_SHIFT, T_BYLEVEL,
-    T_JPSLOT, T_JCSLOT, T_GBOX, T_STATS,
+    T_JPSLOT, T_JCSLOT, T_GBOX,
     T_COUNT_
 };
 
@@ -300,13 +323,16 @@ struct TreeOut {
     DevArray *i_off, *jp_off, *jc_off;        // int64 [ng+1]
     DevArray *gcx, *gcy, *gcz;                // FP64 [ng] group centres
     DevArray *xi, *yi, *zi;                   // FP64 [n] i-particles
-    DevArray *e2i;                            // FP64 [n] softening (when given)
+    DevArray *e2i;                            // FP64 [n] softening (when given,
+                                              // per particle or for all)
     DevArray *pool_p;                         // PartRec [n], tree order
     DevArray *pool_c;                         // CellRec [ncell]
     DevArray *jp_idx, *jc_idx;                // int32 list entries
     DevArray *order;                          // int32 [n]: input index of
                                               // tree position k
+    DevArray *slots, *scratch;                // launch slot table, planning memory
     DevArray *buf;                            // [T_COUNT_] working memory
+    void *host;                               // kBuildHostBytes of pinned memory
     // sizes, set on success (the offsets themselves stay on the device)
     int64_t ng = 0, njp = 0, njc = 0, ncell = 0;
     // longest particle and cell list of a group; whether one walk sufficed
@@ -318,7 +344,12 @@ struct TreeOut {
     // one walk: jp_idx / jc_idx hold the per-group slots of these sizes
     int64_t slot_p = 0, slot_c = 0;
     int nlevels = 0;  // levels of the tree (the root's included)
+    int64_t nslots = 0;  // launch slots (where an order was asked for)
 };
+
+// What a build's kernels write for the host: 64 int32 (the level table), then
+// kStatCount int64.
+constexpr size_t kBuildHostBytes = 64 * 4 + 8 * kStatCount;
 
 // Returns a BHQ_* code; on failure *err names the step.
 int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t stream,

@@ -10,11 +10,16 @@
 //   group order);
 //   slot b of the table holds entry b / xcds of piece b % xcds, or -1.
 // So the table is the host planner's, entry for entry.
+//
+// The same passes turn the walk's list lengths into offsets and reduce what
+// the host needs (totals, longest lists, slots), so that a build waits for
+// them once: with library scans and reductions, a read of the pieces by the
+// host and an upload of the windows, these steps took 13 launches and four
+// synchronisations (about 110 us of a 2048-particle build).
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
 
 #include <algorithm>
-#include <vector>
 
 #include "bhq.h"
 #include "bhq_internal.h"
@@ -24,94 +29,240 @@ namespace bhq {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kSortMax = 1024;  // largest window sorted by one block
+constexpr int kItems = 8;
+constexpr int kTile = kBlock * kItems;  // groups per block of the sums
+constexpr int kSortMax = 1024;          // largest window sorted by one block
+constexpr int kMaxXcds = 64;
 
-inline unsigned blocks(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
-
-__global__ __launch_bounds__(kBlock) void k_cost(int64_t ng, const int64_t *i_off,
-                                                 const int64_t *jp_off, const int64_t *jc_off,
-                                                 uint64_t *cost)
-{
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g > ng) return;
-    cost[g] = g < ng ? order_cost(i_off[g + 1] - i_off[g], jp_off[g + 1] - jp_off[g],
-                                  jc_off[g + 1] - jc_off[g])
-                     : 0;  // the exclusive scan then ends with the total
-}
-
-__global__ __launch_bounds__(kBlock) void k_piece(int64_t ng, const uint64_t *cost,
-                                                  const uint64_t *before, int xcds,
-                                                  int32_t *piece)
-{
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g >= ng) return;
-    piece[g] = order_piece(before[g], cost[g], before[ng], xcds, g, ng);
-}
-
-// start[p] = first group of piece p (pieces are contiguous and in order);
-// start[xcds] = ng.
-__global__ __launch_bounds__(kBlock) void k_starts(int64_t ng, const int32_t *piece, int xcds,
-                                                   int64_t *start)
-{
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g >= ng) return;
-    const int x = piece[g];
-    const int xp = g > 0 ? piece[g - 1] : -1;
-    for (int p = xp + 1; p <= x; ++p) start[p] = g;
-    if (g == ng - 1)
-        for (int p = x + 1; p <= xcds; ++p) start[p] = ng;
-}
-
-__global__ __launch_bounds__(kBlock) void k_fill(int32_t *v, int64_t n, int32_t val)
-{
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k < n) v[k] = val;
-}
-
-// One block per window: {first group, length, piece, position of the first
-// group in its piece}.  Bitonic sort in LDS by (cost descending, group
-// ascending), then the groups go to their slots.
-struct Window {
-    int32_t first, len, piece, pos;
+struct Sums {
+    uint64_t p, c, cost;  // list entries, cost
+    uint64_t mp, mc;      // longest lists
 };
 
-__global__ __launch_bounds__(kBlock) void k_window_sort(const Window *win, const uint64_t *cost,
-                                                        int xcds, int32_t *order)
+struct PlanArgs {
+    int64_t ng;
+    const int64_t *i_off;
+    const int64_t *jp_cnt, *jc_cnt;  // list lengths, or NULL: from the offsets
+    int64_t *jp_off, *jc_off;        // written if lengths are given
+    int window, tail, xcds;
+    Sums *tile;                      // [tiles] each tile's sums, then the sums
+                                     // before it; [tiles] the totals
+    uint64_t *cost;                  // [ng]
+    int64_t *start;                  // [xcds + 1] first group of each piece
+    int32_t *order;
+    int64_t cap;                     // entries of order
+    const int *flag;                 // the walk's, or NULL
+    int64_t *stats;
+};
+
+__device__ __forceinline__ void group_terms(const PlanArgs &A, int64_t g, uint64_t &p, uint64_t &c,
+                                            uint64_t &cost)
+{
+    p = c = cost = 0;
+    if (g >= A.ng) return;
+    p = (uint64_t)(A.jp_cnt ? A.jp_cnt[g] : A.jp_off[g + 1] - A.jp_off[g]);
+    c = (uint64_t)(A.jc_cnt ? A.jc_cnt[g] : A.jc_off[g + 1] - A.jc_off[g]);
+    cost = order_cost(A.i_off[g + 1] - A.i_off[g], (int64_t)p, (int64_t)c);
+}
+
+__global__ __launch_bounds__(kBlock) void k_tile_sums(const PlanArgs A)
+{
+    typedef hipcub::BlockReduce<uint64_t, kBlock> Reduce;
+    __shared__ typename Reduce::TempStorage tmp;
+    uint64_t v[5] = {0, 0, 0, 0, 0};
+    for (int u = 0; u < kItems; ++u) {
+        uint64_t p, c, cost;
+        group_terms(A, (int64_t)blockIdx.x * kTile + u * kBlock + threadIdx.x, p, c, cost);
+        v[0] += p;
+        v[1] += c;
+        v[2] += cost;
+        v[3] = p > v[3] ? p : v[3];
+        v[4] = c > v[4] ? c : v[4];
+    }
+    uint64_t r[5];
+    for (int k = 0; k < 5; ++k) {
+        r[k] = k < 3 ? Reduce(tmp).Sum(v[k]) : Reduce(tmp).Reduce(v[k], hipcub::Max());
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) A.tile[blockIdx.x] = Sums{r[0], r[1], r[2], r[3], r[4]};
+}
+
+// Exclusive sums of the tiles' sums, totals after them; one block.
+__global__ __launch_bounds__(kBlock) void k_tile_scan(const PlanArgs A, int tiles)
+{
+    typedef hipcub::BlockScan<uint64_t, kBlock> Scan;
+    typedef hipcub::BlockReduce<uint64_t, kBlock> Reduce;
+    __shared__ union {
+        typename Scan::TempStorage scan;
+        typename Reduce::TempStorage reduce;
+    } tmp;
+    uint64_t at[3] = {0, 0, 0}, m[2] = {0, 0};
+    for (int b = 0; b < tiles; b += kBlock) {
+        const int i = b + (int)threadIdx.x;
+        const Sums t = i < tiles ? A.tile[i] : Sums{0, 0, 0, 0, 0};
+        const uint64_t v[3] = {t.p, t.c, t.cost};
+        uint64_t ex[3], tot[3];
+        for (int k = 0; k < 3; ++k) {
+            Scan(tmp.scan).ExclusiveSum(v[k], ex[k], tot[k]);
+            __syncthreads();
+        }
+        if (i < tiles) A.tile[i] = Sums{at[0] + ex[0], at[1] + ex[1], at[2] + ex[2], 0, 0};
+        for (int k = 0; k < 3; ++k) at[k] += tot[k];
+        m[0] = t.mp > m[0] ? t.mp : m[0];
+        m[1] = t.mc > m[1] ? t.mc : m[1];
+    }
+    for (int k = 0; k < 2; ++k) {
+        m[k] = Reduce(tmp.reduce).Reduce(m[k], hipcub::Max());
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) A.tile[tiles] = Sums{at[0], at[1], at[2], m[0], m[1]};
+}
+
+// A tile's offsets, costs and pieces; the statistics.  ONE: the only tile,
+// whose sums are the block's own.
+template <bool ONE>
+__global__ __launch_bounds__(kBlock) void k_offsets(const PlanArgs A, int tiles)
+{
+    typedef hipcub::BlockScan<uint64_t, kBlock> Scan;
+    typedef hipcub::BlockReduce<uint64_t, kBlock> Reduce;
+    __shared__ union {
+        typename Scan::TempStorage scan;
+        typename Reduce::TempStorage reduce;
+    } tmp;
+    const int64_t g0 = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
+    uint64_t v[3][kItems], cost[kItems], mx[2] = {0, 0};
+    for (int u = 0; u < kItems; ++u) {
+        group_terms(A, g0 + u, v[0][u], v[1][u], v[2][u]);
+        cost[u] = v[2][u];
+        mx[0] = v[0][u] > mx[0] ? v[0][u] : mx[0];
+        mx[1] = v[1][u] > mx[1] ? v[1][u] : mx[1];
+    }
+    Sums before{0, 0, 0, 0, 0}, all;
+    uint64_t tot[3];
+    for (int k = 0; k < 3; ++k) {
+        Scan(tmp.scan).ExclusiveSum(v[k], v[k], tot[k]);
+        __syncthreads();
+    }
+    if constexpr (ONE) {
+        for (int k = 0; k < 2; ++k) {
+            mx[k] = Reduce(tmp.reduce).Reduce(mx[k], hipcub::Max());
+            __syncthreads();
+        }
+        all = Sums{tot[0], tot[1], tot[2], mx[0], mx[1]};  // (maxima: thread 0)
+    } else {
+        before = A.tile[blockIdx.x];
+        all = A.tile[tiles];
+    }
+    // the piece of the group before this thread's first: its cost interval
+    // ends where the first's begins
+    int xp = -1;
+    if (g0 > 0 && g0 < A.ng) {
+        uint64_t p, c, cc;
+        group_terms(A, g0 - 1, p, c, cc);
+        xp = order_piece(before.cost + v[2][0] - cc, cc, all.cost, A.xcds, g0 - 1, A.ng);
+    }
+    for (int u = 0; u < kItems; ++u) {
+        const int64_t g = g0 + u;
+        if (g >= A.ng) break;
+        if (A.jp_cnt) {
+            A.jp_off[g] = (int64_t)(before.p + v[0][u]);
+            A.jc_off[g] = (int64_t)(before.c + v[1][u]);
+        }
+        A.cost[g] = cost[u];
+        const int x = order_piece(before.cost + v[2][u], cost[u], all.cost, A.xcds, g, A.ng);
+        for (int p = xp + 1; p <= x; ++p) A.start[p] = g;
+        xp = x;
+        if (g == A.ng - 1) {
+            for (int p = x + 1; p <= A.xcds; ++p) A.start[p] = A.ng;
+            if (A.jp_cnt) {
+                A.jp_off[A.ng] = (int64_t)all.p;
+                A.jc_off[A.ng] = (int64_t)all.c;
+            }
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        A.stats[kStatParts] = (int64_t)all.p;
+        A.stats[kStatCells] = (int64_t)all.c;
+        A.stats[kStatMaxParts] = (int64_t)all.mp;
+        A.stats[kStatMaxCells] = (int64_t)all.mc;
+        A.stats[kStatWalk] = A.flag ? A.flag[0] : 0;
+        A.stats[kStatOpened] = A.flag ? A.flag[2] : 0;
+    }
+}
+
+// a before b in a window: larger cost, then smaller group index
+__device__ __forceinline__ bool costlier(uint64_t ca, int32_t ga, uint64_t cb, int32_t gb)
+{
+    return ca > cb || (ca == cb && ga < gb);
+}
+
+// One block per window, found from the pieces: piece p has windows of
+// `window` groups from its start and one (perhaps empty) of its last `tail`
+// groups.  Bitonic sort with one group per thread: partners less than a wave
+// apart exchange by shuffles, others through LDS (ten of the 55 exchanges
+// of a tail of 1024; with LDS and a barrier for each, and 256 threads, the
+// cube's windows took 46 us, now 13).  The last window of a piece also marks
+// its empty slots.
+__global__ __launch_bounds__(kSortMax) void k_window_sort(const PlanArgs A)
 {
     __shared__ uint64_t sc[kSortMax];
     __shared__ int32_t sg[kSortMax];
-    const Window w = win[blockIdx.x];
-    int n2 = 1;
-    while (n2 < w.len) n2 <<= 1;
-    for (int i = threadIdx.x; i < n2; i += kBlock) {
-        // padding sorts last: cost 0 and the largest group index
-        sc[i] = i < w.len ? cost[w.first + i] : 0;
-        sg[i] = i < w.len ? w.first + i : 0x7fffffff;
+    const int t = threadIdx.x;
+    int64_t longest = 0;
+    for (int p = 0; p < A.xcds; ++p) {
+        const int64_t k = A.start[p + 1] - A.start[p];
+        longest = k > longest ? k : longest;
     }
-    __syncthreads();
+    if (blockIdx.x == 0 && t == 0) A.stats[kStatSlots] = longest * A.xcds;
+    if (longest * A.xcds > A.cap) return;  // the host allocates and runs this again
+    int64_t b = blockIdx.x, first = 0, pos = 0;
+    int piece = 0, len = -1;
+    bool last = false;
+    for (; piece < A.xcds; ++piece) {
+        const int64_t k = A.start[piece + 1] - A.start[piece];
+        const int64_t body = k > A.tail ? k - A.tail : 0;
+        const int64_t nw = (body + A.window - 1) / A.window;
+        if (b <= nw) {
+            last = b == nw;
+            pos = last ? body : b * A.window;
+            first = A.start[piece] + pos;
+            len = (int)(last ? k - body : (body - pos < A.window ? body - pos : A.window));
+            break;
+        }
+        b -= nw + 1;
+    }
+    if (len < 0) return;
+    int n2 = 1;
+    while (n2 < len) n2 <<= 1;
+    // padding sorts last: cost 0 and the largest group index
+    uint64_t c = t < len ? A.cost[first + t] : 0;
+    int32_t g = t < len ? (int32_t)(first + t) : 0x7fffffff;
     for (int size = 2; size <= n2; size <<= 1) {
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = threadIdx.x; i < n2; i += kBlock) {
-                const int j = i ^ stride;
-                if (j > i) {
-                    // a before b: larger cost, then smaller group index
-                    const bool up = (i & size) == 0;
-                    const bool ab = sc[i] > sc[j] || (sc[i] == sc[j] && sg[i] < sg[j]);
-                    if (ab != up) {
-                        const uint64_t c = sc[i];
-                        sc[i] = sc[j];
-                        sc[j] = c;
-                        const int32_t g = sg[i];
-                        sg[i] = sg[j];
-                        sg[j] = g;
-                    }
-                }
+            uint64_t oc;
+            int32_t og;
+            if (stride >= 64) {
+                __syncthreads();
+                sc[t] = c;
+                sg[t] = g;
+                __syncthreads();
+                oc = sc[t ^ stride];
+                og = sg[t ^ stride];
+            } else {
+                oc = __shfl_xor((unsigned long long)c, stride);
+                og = __shfl_xor(g, stride);
             }
-            __syncthreads();
+            const bool want_first = ((t & stride) == 0) == ((t & size) == 0);
+            if (costlier(c, g, oc, og) != want_first) {
+                c = oc;
+                g = og;
+            }
         }
     }
-    for (int i = threadIdx.x; i < w.len; i += kBlock)
-        order[(int64_t)(w.pos + i) * xcds + w.piece] = sg[i];
+    if (t < len) A.order[(pos + t) * A.xcds + piece] = g;
+    if (last)
+        for (int64_t k = pos + len + t; k < longest; k += kSortMax)
+            A.order[k * A.xcds + piece] = -1;
 }
 
 }  // namespace
@@ -121,90 +272,82 @@ bool plan_order_device_supported(int window, int tail)
     return window >= 1 && window <= kSortMax && tail >= 0 && tail <= kSortMax;
 }
 
-int plan_order_device(int64_t ng, const int64_t *i_off, const int64_t *jp_off,
-                      const int64_t *jc_off, int window, int tail, int xcds, DevArray &order,
-                      DevArray &scratch, int64_t *nslots, hipStream_t s, std::string *what)
+// Scratch layout shared by the two calls below.
+static PlanArgs plan_args(const ListPlan &P)
 {
-    auto fail = [&](hipError_t e, const char *where) {
-        *what = std::string(where) + ": " + hipGetErrorString(e);
+    PlanArgs A{};
+    A.ng = P.ng;
+    A.i_off = P.i_off;
+    A.jp_cnt = P.jp_cnt;
+    A.jc_cnt = P.jc_cnt;
+    A.jp_off = P.jp_off;
+    A.jc_off = P.jc_off;
+    A.window = P.window;
+    A.tail = P.tail;
+    A.xcds = P.xcds;
+    A.flag = P.flag;
+    A.stats = P.stats;
+    char *base = P.scratch->as<char>();
+    A.start = reinterpret_cast<int64_t *>(base);
+    A.cost = reinterpret_cast<uint64_t *>(base + (kMaxXcds + 1) * 8);
+    A.tile = reinterpret_cast<Sums *>(base + (kMaxXcds + 1) * 8 + (size_t)P.ng * 8);
+    A.order = P.order ? P.order->as<int32_t>() : nullptr;
+    A.cap = P.order ? (int64_t)(P.order->cap / 4) : 0;
+    return A;
+}
+
+static hipError_t launch_windows(const ListPlan &P, hipStream_t s)
+{
+    // windows: at most ng / window + 2 per piece
+    const int64_t nwin = P.ng / P.window + 2 * (int64_t)P.xcds;
+    hipLaunchKernelGGL(k_window_sort, dim3((unsigned)nwin), dim3(kSortMax), 0, s, plan_args(P));
+    return hipGetLastError();
+}
+
+int plan_lists_launch(const ListPlan &P, hipStream_t s, std::string *what)
+{
+    auto fail = [&](hipError_t e) {
+        *what = std::string("list plan: ") + hipGetErrorString(e);
         return e == hipErrorOutOfMemory ? BHQ_E_NOMEM : BHQ_E_HIP;
     };
-#define OSTEP(expr, where)                          \
-    do {                                            \
-        hipError_t e_ = (expr);                     \
-        if (e_ != hipSuccess) return fail(e_, where); \
-    } while (0)
-    if (ng < 1 || xcds < 1 || xcds > 64 || !plan_order_device_supported(window, tail)) {
-        *what = "device order: bad argument";
+    if (P.ng < 1 || P.xcds < 1 || P.xcds > kMaxXcds ||
+        (P.order && !plan_order_device_supported(P.window, P.tail))) {
+        *what = "list plan: bad argument";
         return BHQ_E_ARG;
     }
-    // scratch: cost[ng + 1], before[ng + 1] (uint64), piece[ng] (int32),
-    // start[xcds + 1] (int64), scan temporaries
-    const size_t ncost = (size_t)(ng + 1) * 8, npiece = (size_t)ng * 4;
-    const size_t nstart = (size_t)(xcds + 1) * 8;
-    size_t scan_bytes = 0;
-    OSTEP(hipcub::DeviceScan::ExclusiveSum(nullptr, scan_bytes, (uint64_t *)nullptr,
-                                           (uint64_t *)nullptr, (int)(ng + 1), s),
-          "order scan size");
-    auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-    const size_t o_before = up(ncost), o_piece = o_before + up(ncost);
-    const size_t o_start = o_piece + up(npiece), o_scan = o_start + up(nstart);
-    // windows: at most ng / window + 2 per piece
-    const size_t maxwin = (size_t)(ng / window) + 2 * (size_t)xcds + 1;
-    const size_t o_win = o_scan + up(scan_bytes);
-    OSTEP(scratch.reserve(o_win + maxwin * sizeof(Window)), "order scratch");
-    char *base = scratch.as<char>();
-    uint64_t *cost = (uint64_t *)base, *before = (uint64_t *)(base + o_before);
-    int32_t *piece = (int32_t *)(base + o_piece);
-    int64_t *start = (int64_t *)(base + o_start);
-    hipLaunchKernelGGL(k_cost, dim3(blocks(ng + 1)), dim3(kBlock), 0, s, ng, i_off, jp_off,
-                       jc_off, cost);
-    OSTEP(hipGetLastError(), "order cost");
-    OSTEP(hipcub::DeviceScan::ExclusiveSum(base + o_scan, scan_bytes, cost, before,
-                                           (int)(ng + 1), s),
-          "order scan");
-    hipLaunchKernelGGL(k_piece, dim3(blocks(ng)), dim3(kBlock), 0, s, ng, cost, before, xcds,
-                       piece);
-    OSTEP(hipGetLastError(), "order pieces");
-    hipLaunchKernelGGL(k_starts, dim3(blocks(ng)), dim3(kBlock), 0, s, ng, piece, xcds, start);
-    OSTEP(hipGetLastError(), "order pieces");
-    std::vector<int64_t> hs((size_t)xcds + 1);
-    OSTEP(hipMemcpyAsync(hs.data(), start, nstart, hipMemcpyDeviceToHost, s), "order copy");
-    OSTEP(hipStreamSynchronize(s), "order sync");
+    const int64_t tiles = (P.ng + kTile - 1) / kTile;
+    hipError_t e = P.scratch->reserve((kMaxXcds + 1) * 8 + (size_t)P.ng * 8 +
+                                      (size_t)(tiles + 1) * sizeof(Sums));
+    // pieces of equal cost are rarely longer than twice the mean
+    if (e == hipSuccess && P.order)
+        e = P.order->reserve(4 * (size_t)std::max<int64_t>(2 * P.ng, 64 * P.xcds));
+    if (e != hipSuccess) return fail(e);
+    const PlanArgs A = plan_args(P);
+    if (tiles == 1) {
+        hipLaunchKernelGGL(k_offsets<true>, dim3(1), dim3(kBlock), 0, s, A, 1);
+    } else {
+        hipLaunchKernelGGL(k_tile_sums, dim3((unsigned)tiles), dim3(kBlock), 0, s, A);
+        if ((e = hipGetLastError()) != hipSuccess) return fail(e);
+        hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(kBlock), 0, s, A, (int)tiles);
+        if ((e = hipGetLastError()) != hipSuccess) return fail(e);
+        hipLaunchKernelGGL(k_offsets<false>, dim3((unsigned)tiles), dim3(kBlock), 0, s, A,
+                           (int)tiles);
+    }
+    e = hipGetLastError();
+    if (e == hipSuccess && P.order) e = launch_windows(P, s);
+    return e == hipSuccess ? BHQ_OK : fail(e);
+}
 
-    // windows of every piece, as the host planner cuts them
-    std::vector<Window> win;
-    int64_t longest = 0;
-    for (int p = 0; p < xcds; ++p) {
-        const int64_t k = hs[(size_t)p + 1] - hs[(size_t)p];
-        longest = std::max(longest, k);
-        const int64_t body = k > tail ? k - tail : 0;
-        for (int64_t w = 0; w < body; w += window)
-            win.push_back({(int32_t)(hs[(size_t)p] + w), (int32_t)(std::min(body, w + window) - w),
-                           p, (int32_t)w});
-        if (body < k)
-            win.push_back({(int32_t)(hs[(size_t)p] + body), (int32_t)(k - body), p,
-                           (int32_t)body});
-    }
-    const int64_t ns = longest * xcds;
-    if (win.size() > maxwin) {
-        *what = "device order: window table";
-        return BHQ_E_RANGE;
-    }
-    Window *dwin = (Window *)(base + o_win);
-    OSTEP(hipMemcpyAsync(dwin, win.data(), win.size() * sizeof(Window), hipMemcpyHostToDevice, s),
-          "order copy");
-    OSTEP(order.reserve((size_t)ns * 4), "order table");
-    hipLaunchKernelGGL(k_fill, dim3(blocks(ns)), dim3(kBlock), 0, s, order.as<int32_t>(), ns, -1);
-    OSTEP(hipGetLastError(), "order fill");
-    hipLaunchKernelGGL(k_window_sort, dim3((unsigned)win.size()), dim3(kBlock), 0, s, dwin, cost,
-                       xcds, order.as<int32_t>());
-    OSTEP(hipGetLastError(), "order sort");
-    // the window table is host memory read by the copy above
-    OSTEP(hipStreamSynchronize(s), "order sync");
-    *nslots = ns;
-    return BHQ_OK;
-#undef OSTEP
+int plan_lists_finish(const ListPlan &P, hipStream_t s, std::string *what)
+{
+    const int64_t slots = P.stats[kStatSlots];
+    if (slots <= (int64_t)(P.order->cap / 4)) return BHQ_OK;
+    hipError_t e = P.order->reserve((size_t)slots * 4);
+    if (e == hipSuccess) e = launch_windows(P, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) return BHQ_OK;
+    *what = std::string("list plan: ") + hipGetErrorString(e);
+    return e == hipErrorOutOfMemory ? BHQ_E_NOMEM : BHQ_E_HIP;
 }
 
 }  // namespace bhq

@@ -590,9 +590,10 @@ __global__ __launch_bounds__(kBlock) void k_cells(const CellArgs C, int nb)
 __global__ __launch_bounds__(kBlock) void k_particles_out(const int32_t *sidx,
                                                           const int32_t *info, int64_t n,
                                                           const double *x, const double *m,
-                                                          const double *eps2, int32_t *order,
-                                                          PartRec *pool, double *xi, double *yi,
-                                                          double *zi, double *e2i)
+                                                          const double *eps2, double eps2_all,
+                                                          int32_t *order, PartRec *pool,
+                                                          double *xi, double *yi, double *zi,
+                                                          double *e2i)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= n) return;
@@ -610,7 +611,7 @@ __global__ __launch_bounds__(kBlock) void k_particles_out(const int32_t *sidx,
         for (int64_t j = k + 1; j < n && info_d(info[j]) >= ld; ++j) at += sidx[j] < p ? 1 : 0;
     }
     order[at] = p;
-    if (eps2) e2i[at] = eps2[p];
+    if (e2i) e2i[at] = eps2 ? eps2[p] : eps2_all;
     PartRec r;
     r.x = x[3 * (int64_t)p];
     r.y = x[3 * (int64_t)p + 1];
@@ -1386,18 +1387,6 @@ __global__ __launch_bounds__(kBlock) void k_compact(int64_t ng, const int64_t *o
     for (int64_t j = lane; j < n; j += 64) out[o + j] = src[j];
 }
 
-// stats[0], stats[1] = list totals (the scans' last entries), stats[4] =
-// the walk's overflow flag, stats[5] the most octets of a group in a level
-// walk; stats[2], stats[3] hold the longest lists.
-__global__ void k_list_stats(int64_t ng, const int64_t *jp_off, const int64_t *jc_off,
-                             const int *flag, int64_t *stats)
-{
-    stats[0] = jp_off[ng];
-    stats[1] = jc_off[ng];
-    stats[4] = flag[0];
-    stats[5] = flag[2];
-}
-
 }  // namespace
 
 hipError_t launch_compact_lists(int64_t ng, const int64_t *off, const int32_t *slot,
@@ -1514,8 +1503,8 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     };
     const int nb = (int)blocks(n + 1, kTile);
     const bool group_row = P.ncrit <= kWinMost;
-    STEP(B[T_TABLE].reserve(64 * 4), "allocation");
-    int32_t table[4 + kRows + 2] = {};
+    volatile int32_t *table = static_cast<int32_t *>(O.host);
+    static_assert(4 + kRows + 2 <= 64, "level table");
     int lo = P.spec_levels > 0 ? 3 * (kMaxDepth + 1 - std::max(2, P.spec_levels)) : 0;
     SplitArgs S{};
     int rows = 0;
@@ -1556,11 +1545,8 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
                  "scan");
         }
         hipLaunchKernelGGL(k_table, dim3(1), dim3(64), 0, s, B[T_NOFF].as<int32_t>(), rows, nb,
-                           flag, B[T_TABLE].as<int32_t>());
+                           flag, static_cast<int32_t *>(O.host));
         LAUNCHED("level table");
-        STEP(hipMemcpyAsync(table, B[T_TABLE].p, (size_t)(4 + rows + 2) * 4,
-                            hipMemcpyDeviceToHost, s),
-             "copy");
         STEP(hipStreamSynchronize(s), "sync");
         if (table[0]) {
             code = BHQ_E_NONFINITE;
@@ -1645,12 +1631,13 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     STEP(O.xi->reserve((size_t)n * 8), "allocation");
     STEP(O.yi->reserve((size_t)n * 8), "allocation");
     STEP(O.zi->reserve((size_t)n * 8), "allocation");
-    if (P.eps2) STEP(O.e2i->reserve((size_t)n * 8), "allocation");
+    const bool soft = P.eps2 || P.eps2_all > 0.0;
+    if (soft) STEP(O.e2i->reserve((size_t)n * 8), "allocation");
     hipLaunchKernelGGL(k_particles_out, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s,
-                       B[T_IDX1].as<int32_t>(), S.info, n, P.x, P.m, P.eps2,
+                       B[T_IDX1].as<int32_t>(), S.info, n, P.x, P.m, P.eps2, P.eps2_all,
                        O.order->as<int32_t>(), O.pool_p->as<PartRec>(), O.xi->as<double>(),
                        O.yi->as<double>(), O.zi->as<double>(),
-                       P.eps2 ? O.e2i->as<double>() : nullptr);
+                       soft ? O.e2i->as<double>() : nullptr);
     LAUNCHED("particle pool");
 
     // moments straight into the cell pool (the deepest cells are leaves)
@@ -1715,8 +1702,6 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     STEP(B[T_JCCNT].reserve((size_t)(ng + 1) * 8), "allocation");
     STEP(O.jp_off->reserve((size_t)(ng + 1) * 8), "allocation");
     STEP(O.jc_off->reserve((size_t)(ng + 1) * 8), "allocation");
-    STEP(hipMemsetAsync(B[T_JPCNT].as<int64_t>() + ng, 0, 8, s), "memset");
-    STEP(hipMemsetAsync(B[T_JCCNT].as<int64_t>() + ng, 0, 8, s), "memset");
     WalkArgs W{};
     W.groups = groups;
     W.groot = nsys > 1 ? B[T_GROOT].as<int32_t>() : nullptr;
@@ -1795,50 +1780,46 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         W.jp_idx = B[T_JPSLOT].as<int32_t>();
         W.jc_idx = B[T_JCSLOT].as<int32_t>();
     }
-    int64_t hstats[6] = {0, 0, 0, 0, 0, 0};
+    // offsets, dispatch order, and what the host needs of them, with the walk
+    ListPlan L;
+    L.ng = ng;
+    L.i_off = O.i_off->as<int64_t>();
+    L.jp_cnt = W.jp_cnt;
+    L.jc_cnt = W.jc_cnt;
+    L.jp_off = O.jp_off->as<int64_t>();
+    L.jc_off = O.jc_off->as<int64_t>();
+    L.window = P.window;
+    L.tail = P.tail;
+    L.xcds = P.xcds;
+    L.flag = W.flag;
+    L.stats = reinterpret_cast<int64_t *>(static_cast<char *>(O.host) + 64 * 4);
+    L.order = P.window > 0 ? O.slots : nullptr;
+    L.scratch = O.scratch;
+    volatile int64_t *stats = L.stats;
     for (;;) {
         if (!walk(slots ? kWalkSlots : kWalkCount)) return fail();
-        for (int pass = 0; pass < 2; ++pass) {
-            int64_t *cnt = pass ? B[T_JCCNT].as<int64_t>() : B[T_JPCNT].as<int64_t>();
-            int64_t *off = pass ? O.jc_off->as<int64_t>() : O.jp_off->as<int64_t>();
-            size_t st = 0;
-            STEP(hipcub::DeviceScan::ExclusiveSum(nullptr, st, cnt, off, (int)(ng + 1), s),
-                 "scan size");
-            STEP(B[T_SORT].reserve(std::max(st, B[T_SORT].cap)), "allocation");
-            STEP(hipcub::DeviceScan::ExclusiveSum(B[T_SORT].p, st, cnt, off, (int)(ng + 1), s),
-                 "scan");
-        }
-        // list totals, longest lists and the walk's overflow flag: the host
-        // needs only these five numbers (the offsets stay on the device)
-        STEP(B[T_STATS].reserve(8 * sizeof(int64_t)), "allocation");
-        int64_t *stats = B[T_STATS].as<int64_t>();
-        for (int pass = 0; pass < 2; ++pass) {
-            const int64_t *cnt = pass ? B[T_JCCNT].as<int64_t>() : B[T_JPCNT].as<int64_t>();
-            size_t st = 0;
-            STEP(hipcub::DeviceReduce::Max(nullptr, st, cnt, stats + 2 + pass, (int)ng, s),
-                 "reduce size");
-            STEP(B[T_SORT].reserve(std::max(st, B[T_SORT].cap)), "allocation");
-            STEP(hipcub::DeviceReduce::Max(B[T_SORT].p, st, cnt, stats + 2 + pass, (int)ng, s),
-                 "reduce");
-        }
-        hipLaunchKernelGGL(k_list_stats, dim3(1), dim3(1), 0, s, ng, O.jp_off->as<int64_t>(),
-                           O.jc_off->as<int64_t>(), W.flag, stats);
-        LAUNCHED("list totals");
-        STEP(hipMemcpyAsync(hstats, stats, sizeof(hstats), hipMemcpyDeviceToHost, s), "copy");
+        code = plan_lists_launch(L, s, err);
+        if (code != BHQ_OK) return code;
         STEP(hipStreamSynchronize(s), "sync");
-        if (hstats[4] != 2) break;
+        if (stats[kStatWalk] != 2) break;
         // a group opened more cells than the level walk's LDS holds
         oct_cap = 0;
         O.oct_full = true;
-        STEP(hipMemsetAsync(B[T_FLAG].p, 0, 64, s), "memset");
+        STEP(hipMemsetAsync(W.flag, 0, 16, s), "memset");
     }
-    if (hstats[4]) {
+    if (stats[kStatWalk]) {
         code = BHQ_E_RANGE;
         what = "walk stack overflow";
         return fail();
     }
-    const int64_t njp = hstats[0], njc = hstats[1];
-    const int64_t max_p = hstats[2], max_c = hstats[3];
+    if (L.order) {
+        code = plan_lists_finish(L, s, err);
+        if (code != BHQ_OK) return code;
+        O.nslots = stats[kStatSlots];
+    }
+    const int64_t most = stats[kStatOpened];
+    const int64_t njp = stats[kStatParts], njc = stats[kStatCells];
+    const int64_t max_p = stats[kStatMaxParts], max_c = stats[kStatMaxCells];
     O.one_walk = slots && max_p <= P.cap_p && max_c <= P.cap_c;
     O.slot_p = O.slot_c = 0;
     if (O.one_walk) {
@@ -1865,14 +1846,14 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         W.jc_off = O.jc_off->as<int64_t>();
         W.jp_idx = O.jp_idx->as<int32_t>();
         W.jc_idx = O.jc_idx->as<int32_t>();
-        if (oct_cap > 0) oct_cap = std::max(1, (int)hstats[5]);
+        if (oct_cap > 0) oct_cap = std::max(1, (int)most);
         if (!walk(kWalkFill)) return fail();
+        STEP(hipStreamSynchronize(s), "sync");
     }
-    O.max_o = hstats[5];
+    O.max_o = most;
     O.max_p = max_p;
     O.max_c = max_c;
 
-    STEP(hipStreamSynchronize(s), "sync");
     O.ng = ng;
     O.njp = njp;
     O.njc = njc;

@@ -94,3 +94,28 @@ def test_batch_cells_from_keys(sizes, ncrit, nleaf):
             _same(h, d, "batch %d systems build %d" % (len(sizes), build))
     finally:
         bhq.bhq_destroy(ctx)
+
+
+@pytest.mark.parametrize("ng", [1, 9, 2047, 2048, 2049, 9001])
+@pytest.mark.parametrize("window,tail", [(256, 1024), (1024, 0), (1, 1)])
+@pytest.mark.parametrize("skew", [False, True])
+def test_order_plan(ng, window, tail, skew):
+    """Edges of a tile of groups and of windows; skew: one group of nearly all
+    the cost, so that the others share a piece longer than the table's first
+    allocation; groups without i-particles cost nothing."""
+    g = synth.rng(43)
+    cnt = g.integers(0, 60, (3, ng))
+    if skew:
+        cnt[:, 0] = 100000
+    off = [np.concatenate([[0], np.cumsum(c)]).astype(np.int64) for c in cnt]
+    want = bhq.bhq_plan_order(off[0], off[1], off[2], window=window, tail=tail)
+    ctx = bhq.bhq_create(0, bhq.QUAD, bhq.FP32_OFS64)
+    try:
+        bhq.bhq_set_group_order(ctx, bhq.ORDER_XCD, window, tail)
+        t = [torch.from_numpy(o).cuda() for o in off]
+        for _ in range(2):
+            bhq.bhq_set_groups_dev(ctx, t[0], torch.zeros(ng, 3, dtype=torch.float64,
+                                                          device="cuda"), t[1], t[2])
+            assert np.array_equal(bhq.bhq_get_order(ctx), want)
+    finally:
+        bhq.bhq_destroy(ctx)
