@@ -141,7 +141,9 @@ struct bhq_ctx {
     // bhq_build_lists_device).
     bool tree_order = false;
     DevArray tbuf[bhq::T_COUNT_];  // device list builder working memory
-    void *build_host = nullptr;    // pinned: what its kernels write for the host
+    void *build_host = nullptr;    // pinned: what kernels write for the host
+    int flag_at = 0;               // flag word of the next device upload,
+    bool flags_clear = false;      // and whether both words are clear
     bool have_jp_idx = false, have_jc_idx = false;
     int eps_mode = 0;  // 0 none, 1 uniform, 2 per-particle
     double eps2_all = 0.0;
@@ -248,6 +250,15 @@ struct bhq_ctx {
             return fail(BHQ_E_STATE, "lists already given as indices since "
                                      "the last set_groups");
         if (list_mode == 1) return BHQ_OK;
+        const int rc = reserve_materialised();
+        if (rc != BHQ_OK) return rc;
+        list_mode = 1;
+        ++args_version;
+        return BHQ_OK;
+    }
+    int reserve_materialised()
+    {
+        if (list_mode == 1) return BHQ_OK;
         quiesce();
         const size_t D = sizeof(double);
         const Arr jp[] = {A_JPX, A_JPY, A_JPZ, A_JPM};
@@ -261,8 +272,6 @@ struct bhq_ctx {
             hipError_t e = arr[a].reserve((size_t)njc * D);
             if (e != hipSuccess) return hip_fail(e, "hipMalloc");
         }
-        list_mode = 1;
-        ++args_version;
         return BHQ_OK;
     }
     int use_indexed()
@@ -1450,25 +1459,84 @@ static int check_device_range(bhq_ctx *ctx, const void *p, size_t bytes,
  * kernels on `stream`; it returns when the copy is complete.
  * ------------------------------------------------------------------------ */
 
-// Run the validation kernels queued by checks(flag) on s, wait for them and
-// turn the flag into a return code.
-extern "C++" template <typename F>
-static int dev_check(bhq_ctx *ctx, hipStream_t s, const char *what, F checks)
+// The flag word of the next call's checks and the one after it (each call's
+// last kernel clears the next one's), cleared here where that did not happen.
+static int dev_flags(bhq_ctx *ctx, hipStream_t s, unsigned *&flag, unsigned *&next)
 {
     hipError_t e = ctx->arr[A_FLAG].reserve(256);
-    unsigned *flag = ctx->arr[A_FLAG].as<unsigned>();
-    if (e == hipSuccess) e = bhq::launch_clear_flag(flag, s);
-    if (e == hipSuccess) e = checks(flag);
-    unsigned h = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&h, flag, sizeof(h), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return ctx->hip_fail(e, what);
+    unsigned *f = ctx->arr[A_FLAG].as<unsigned>();
+    if (e == hipSuccess && !ctx->flags_clear) {
+        e = bhq::launch_clear_flag(f, s);
+        if (e == hipSuccess) e = bhq::launch_clear_flag(f + 1, s);
+    }
+    if (e != hipSuccess) return ctx->hip_fail(e, "flag");
+    flag = f + ctx->flag_at;
+    next = f + (ctx->flag_at ^ 1);
+    ctx->flag_at ^= 1;
+    ctx->flags_clear = false;  // until the call's kernels have run
+    return BHQ_OK;
+}
+
+static int flag_code(bhq_ctx *ctx, unsigned h, const char *what)
+{
     if (h & bhq::kBadNonFinite) return ctx->fail(BHQ_E_NONFINITE, "%s: NaN or infinity", what);
     if (h & bhq::kBadNonPositive) return ctx->fail(BHQ_E_ARG, "%s: a value below 2^-126", what);
     if (h & bhq::kBadOrder)
         return ctx->fail(BHQ_E_RANGE, "%s: offsets not starting at 0 or not monotone", what);
     if (h & bhq::kBadRange) return ctx->fail(BHQ_E_RANGE, "%s: index outside the pool", what);
     return BHQ_OK;
+}
+
+// Check the arrays, copy their columns if all are good (copy: whether to copy
+// at all), wait, and turn the checks' flag into a return code.
+static int dev_upload(bhq_ctx *ctx, hipStream_t s, const char *what, const bhq::UploadCol *c,
+                      int n, bool copy = true)
+{
+    unsigned *flag, *next;
+    TRY(dev_flags(ctx, s, flag, next));
+    unsigned *host = static_cast<unsigned *>(ctx->build_host);
+    hipError_t e = bhq::launch_check_cols(c, n, flag, s);
+    bhq::UploadCol none{};
+    none.w = 1;
+    if (e == hipSuccess)
+        e = bhq::launch_copy_cols(copy ? c : &none, copy ? n : 1, flag, next, host, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return ctx->hip_fail(e, what);
+    ctx->flags_clear = true;
+    return flag_code(ctx, *static_cast<volatile unsigned *>(host), what);
+}
+
+// The same for checks of another kind (checks(flag) queues them); no copy.
+extern "C++" template <typename F>
+static int dev_check(bhq_ctx *ctx, hipStream_t s, const char *what, F checks)
+{
+    unsigned *flag, *next;
+    TRY(dev_flags(ctx, s, flag, next));
+    unsigned *host = static_cast<unsigned *>(ctx->build_host);
+    hipError_t e = checks(flag);
+    bhq::UploadCol none{};
+    none.w = 1;
+    if (e == hipSuccess) e = bhq::launch_copy_cols(&none, 1, flag, next, host, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return ctx->hip_fail(e, what);
+    ctx->flags_clear = true;
+    return flag_code(ctx, *static_cast<volatile unsigned *>(host), what);
+}
+
+// The same into the materialised list arrays from entry adr on; places(col)
+// sets the columns' places.  The first upload after set_groups allocates the
+// arrays and, if its entries are good, fixes the lists' kind.
+extern "C++" template <typename F>
+static int upload_materialised(bhq_ctx *ctx, hipStream_t s, const char *what, bhq::UploadCol *c,
+                               int n, int64_t adr, F places)
+{
+    const bool other = ctx->list_mode == 2;  // refused below, once checked
+    if (!other) TRY(ctx->reserve_materialised());
+    places([&](Arr a) -> void * {
+        return other ? nullptr : ctx->arr[a].as<double>() + adr;
+    });
+    TRY(dev_upload(ctx, s, what, c, n, !other));
+    return ctx->use_materialised();
 }
 
 static int dev_done(bhq_ctx *ctx, hipError_t e, hipStream_t s, const char *what)
@@ -1494,20 +1562,22 @@ int bhq_set_groups_dev(bhq_ctx *ctx, int64_t ng, const int64_t *i_off,
     TRY(check_device_range(ctx, center, (size_t)ng * 24, "center"));
     hipStream_t s = static_cast<hipStream_t>(stream);
     ctx->quiesce();
-    TRY(dev_check(ctx, s, "set_groups_dev", [&](unsigned *f) {
-        hipError_t e = bhq::launch_check_offsets(i_off, ng, f, s);
-        if (e == hipSuccess) e = bhq::launch_check_offsets(jp_off, ng, f, s);
-        if (e == hipSuccess) e = bhq::launch_check_offsets(jc_off, ng, f, s);
-        if (e == hipSuccess) e = bhq::launch_check_f64(&center[0][0], 3 * ng, false, f, s);
-        return e;
-    }));
-    int64_t tot[3] = {0, 0, 0};
-    const int64_t *offs[3] = {i_off, jp_off, jc_off};
-    hipError_t e = hipSuccess;
-    for (int k = 0; k < 3 && e == hipSuccess; ++k)
-        e = hipMemcpyAsync(&tot[k], offs[k] + ng, 8, hipMemcpyDeviceToHost, s);
-    if ((e = (e == hipSuccess ? hipStreamSynchronize(s) : e)) != hipSuccess)
-        return ctx->hip_fail(e, "set_groups_dev: totals");
+    bhq::UploadCol cols[4] = {{i_off, ng + 1, 1, bhq::kColOffsets, {}},
+                              {jp_off, ng + 1, 1, bhq::kColOffsets, {}},
+                              {jc_off, ng + 1, 1, bhq::kColOffsets, {}},
+                              {&center[0][0], ng, 3, bhq::kColFinite, {}}};
+    unsigned *flag, *next;
+    TRY(dev_flags(ctx, s, flag, next));
+    unsigned *host = static_cast<unsigned *>(ctx->build_host);
+    volatile int64_t *tot = static_cast<int64_t *>(ctx->build_host) + 1;
+    hipError_t e = bhq::launch_check_cols(cols, 4, flag, s);
+    if (e == hipSuccess)
+        e = bhq::launch_publish_groups(cols, flag, next, host,
+                                       static_cast<int64_t *>(ctx->build_host) + 1, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return ctx->hip_fail(e, "set_groups_dev");
+    ctx->flags_clear = true;
+    TRY(flag_code(ctx, *static_cast<volatile unsigned *>(host), "set_groups_dev"));
     const int64_t ni = tot[0], njp = tot[1], njc = tot[2];
     const size_t D = sizeof(double);
     const struct { Arr a; size_t bytes; } need[] = {
@@ -1525,15 +1595,18 @@ int bhq_set_groups_dev(bhq_ctx *ctx, int64_t ng, const int64_t *i_off,
             return ctx->hip_fail(e, "hipMalloc");
         }
     }
-    e = hipMemcpyAsync(ctx->arr[A_IOFF].p, i_off, ob, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(ctx->arr[A_JPOFF].p, jp_off, ob, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(ctx->arr[A_JCOFF].p, jc_off, ob, hipMemcpyDeviceToDevice, s);
-    double *gc[3] = {ctx->arr[A_GCX].as<double>(), ctx->arr[A_GCY].as<double>(),
-                     ctx->arr[A_GCZ].as<double>()};
-    if (e == hipSuccess) e = bhq::launch_unpack(&center[0][0], ng, 3, gc, s);
-    if (dev_done(ctx, e, s, "set_groups_dev: copy") != BHQ_OK) {
+    cols[0].dst[0] = ctx->arr[A_IOFF].p;
+    cols[1].dst[0] = ctx->arr[A_JPOFF].p;
+    cols[2].dst[0] = ctx->arr[A_JCOFF].p;
+    cols[3].dst[0] = ctx->arr[A_GCX].p;
+    cols[3].dst[1] = ctx->arr[A_GCY].p;
+    cols[3].dst[2] = ctx->arr[A_GCZ].p;
+    // next is clear, and stays so for the next call: the copy reads it as its
+    // own flag and clears it again
+    e = bhq::launch_copy_cols(cols, 4, next, next, host, s);
+    if (e != hipSuccess) {
         ctx->ng = -1;
-        return BHQ_E_HIP;
+        return ctx->hip_fail(e, "set_groups_dev: copy");
     }
     ctx->ng = ng;
     ctx->ni = ni;
@@ -1575,7 +1648,8 @@ int bhq_set_groups_dev(bhq_ctx *ctx, int64_t ng, const int64_t *i_off,
         else
             ctx->fail(orc, "%s", msg.c_str());
     } else {
-        orc = ctx->upload_order();
+        e = hipStreamSynchronize(s);
+        orc = e == hipSuccess ? ctx->upload_order() : ctx->hip_fail(e, "set_groups_dev: copy");
     }
     if (orc != BHQ_OK) {
         ctx->ng = -1;
@@ -1601,12 +1675,9 @@ int bhq_set_i_dev(bhq_ctx *ctx, int64_t ni, const double (*x)[3], void *stream)
     TRY(check_device_range(ctx, x, (size_t)ni * 24, "x"));
     hipStream_t s = static_cast<hipStream_t>(stream);
     ctx->quiesce();
-    TRY(dev_check(ctx, s, "set_i_dev", [&](unsigned *f) {
-        return bhq::launch_check_f64(&x[0][0], 3 * ni, false, f, s);
-    }));
-    double *out[3] = {ctx->arr[A_XI].as<double>(), ctx->arr[A_YI].as<double>(),
-                      ctx->arr[A_ZI].as<double>()};
-    TRY(dev_done(ctx, bhq::launch_unpack(&x[0][0], ni, 3, out, s), s, "set_i_dev"));
+    const bhq::UploadCol col = {&x[0][0], ni, 3, bhq::kColFinite,
+                                {ctx->arr[A_XI].p, ctx->arr[A_YI].p, ctx->arr[A_ZI].p}};
+    TRY(dev_upload(ctx, s, "set_i_dev", &col, 1));
     ctx->have_i = true;
     return BHQ_OK;
 }
@@ -1624,12 +1695,8 @@ int bhq_set_eps2_i_dev(bhq_ctx *ctx, int64_t ni, const double *eps2, void *strea
         TRY(check_device_range(ctx, eps2, (size_t)ni * 8, "eps2"));
         hipStream_t s = static_cast<hipStream_t>(stream);
         ctx->quiesce();
-        TRY(dev_check(ctx, s, "set_eps2_i_dev", [&](unsigned *f) {
-            return bhq::launch_check_f64(eps2, ni, true, f, s);
-        }));
-        TRY(dev_done(ctx, hipMemcpyAsync(ctx->arr[A_E2I].p, eps2, (size_t)ni * 8,
-                                         hipMemcpyDeviceToDevice, s),
-                     s, "set_eps2_i_dev"));
+        const bhq::UploadCol col = {eps2, ni, 1, bhq::kColPositive, {ctx->arr[A_E2I].p}};
+        TRY(dev_upload(ctx, s, "set_eps2_i_dev", &col, 1));
     }
     ctx->eps_mode = 2;
     return BHQ_OK;
@@ -1652,19 +1719,12 @@ int bhq_set_jp_dev(bhq_ctx *ctx, int64_t adr, int64_t n, const double (*x)[3],
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     ctx->quiesce();
-    TRY(dev_check(ctx, s, "set_jp_dev", [&](unsigned *f) {
-        hipError_t e = bhq::launch_check_f64(&x[0][0], 3 * n, false, f, s);
-        if (e == hipSuccess) e = bhq::launch_check_f64(m, n, false, f, s);
-        return e;
+    bhq::UploadCol cols[2] = {{x ? &x[0][0] : nullptr, n, 3, bhq::kColFinite, {}},
+                              {m, n, 1, bhq::kColFinite, {}}};
+    TRY(upload_materialised(ctx, s, "set_jp_dev", cols, 2, adr, [&](auto col) {
+        cols[0].dst[0] = col(A_JPX), cols[0].dst[1] = col(A_JPY), cols[0].dst[2] = col(A_JPZ);
+        cols[1].dst[0] = col(A_JPM);
     }));
-    TRY(ctx->use_materialised());
-    double *out[3] = {ctx->arr[A_JPX].as<double>() + adr, ctx->arr[A_JPY].as<double>() + adr,
-                      ctx->arr[A_JPZ].as<double>() + adr};
-    hipError_t e = bhq::launch_unpack(&x[0][0], n, 3, out, s);
-    if (e == hipSuccess && n > 0)
-        e = hipMemcpyAsync(ctx->arr[A_JPM].as<double>() + adr, m, (size_t)n * 8,
-                           hipMemcpyDeviceToDevice, s);
-    TRY(dev_done(ctx, e, s, "set_jp_dev"));
     ctx->have_jp = true;
     return BHQ_OK;
 }
@@ -1688,25 +1748,17 @@ int bhq_set_jc_dev(bhq_ctx *ctx, int64_t adr, int64_t n, const double (*x)[3],
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     ctx->quiesce();
-    TRY(dev_check(ctx, s, "set_jc_dev", [&](unsigned *f) {
-        hipError_t e = bhq::launch_check_f64(&x[0][0], 3 * n, false, f, s);
-        if (e == hipSuccess) e = bhq::launch_check_f64(m, n, false, f, s);
-        if (e == hipSuccess) e = bhq::launch_check_f64(&q[0][0], 6 * n, false, f, s);
-        if (e == hipSuccess && trace) e = bhq::launch_check_f64(trace, n, false, f, s);
-        return e;
+    bhq::UploadCol cols[4] = {{x ? &x[0][0] : nullptr, n, 3, bhq::kColFinite, {}},
+                              {m, n, 1, bhq::kColFinite, {}},
+                              {q ? &q[0][0] : nullptr, n, 6, bhq::kColFinite, {}},
+                              {trace, n, 1, bhq::kColFinite, {}}};
+    TRY(upload_materialised(ctx, s, "set_jc_dev", cols, 4, adr, [&](auto col) {
+        const Arr qa[6] = {A_Q00, A_Q01, A_Q02, A_Q11, A_Q12, A_Q22};
+        cols[0].dst[0] = col(A_JCX), cols[0].dst[1] = col(A_JCY), cols[0].dst[2] = col(A_JCZ);
+        cols[1].dst[0] = col(A_JCM);
+        for (int k = 0; k < 6; ++k) cols[2].dst[k] = col(qa[k]);
+        cols[3].dst[0] = col(A_JCT);
     }));
-    TRY(ctx->use_materialised());
-    auto col = [&](Arr a) { return ctx->arr[a].as<double>() + adr; };
-    double *xo[3] = {col(A_JCX), col(A_JCY), col(A_JCZ)};
-    double *qo[6] = {col(A_Q00), col(A_Q01), col(A_Q02), col(A_Q11), col(A_Q12), col(A_Q22)};
-    hipError_t e = bhq::launch_unpack(&x[0][0], n, 3, xo, s);
-    if (e == hipSuccess) e = bhq::launch_unpack(&q[0][0], n, 6, qo, s);
-    if (e == hipSuccess && n > 0)
-        e = hipMemcpyAsync(col(A_JCM), m, (size_t)n * 8, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess && n > 0)
-        e = trace ? hipMemcpyAsync(col(A_JCT), trace, (size_t)n * 8, hipMemcpyDeviceToDevice, s)
-                  : bhq::launch_fill_f64(col(A_JCT), n, 0.0, s);
-    TRY(dev_done(ctx, e, s, "set_jc_dev"));
     ctx->have_jc = true;
     return BHQ_OK;
 }
@@ -1724,11 +1776,9 @@ int bhq_set_pool_particles_dev(bhq_ctx *ctx, int64_t n, const double (*x)[3],
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     ctx->quiesce();
-    TRY(dev_check(ctx, s, "set_pool_particles_dev", [&](unsigned *f) {
-        hipError_t e = bhq::launch_check_f64(&x[0][0], 3 * n, false, f, s);
-        if (e == hipSuccess) e = bhq::launch_check_f64(m, n, false, f, s);
-        return e;
-    }));
+    const bhq::UploadCol cols[2] = {{x ? &x[0][0] : nullptr, n, 3, bhq::kColFinite, {}},
+                                    {m, n, 1, bhq::kColFinite, {}}};
+    TRY(dev_upload(ctx, s, "set_pool_particles_dev", cols, 2, false));
     hipError_t e = ctx->arr[A_POOLP].reserve((size_t)n * sizeof(bhq::PartRec));
     if (e == hipSuccess)
         e = bhq::launch_pack_particles(&x[0][0], m, n, ctx->arr[A_POOLP].as<bhq::PartRec>(), s);
@@ -1755,13 +1805,11 @@ int bhq_set_pool_cells_dev(bhq_ctx *ctx, int64_t n, const double (*x)[3], const 
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     ctx->quiesce();
-    TRY(dev_check(ctx, s, "set_pool_cells_dev", [&](unsigned *f) {
-        hipError_t e = bhq::launch_check_f64(&x[0][0], 3 * n, false, f, s);
-        if (e == hipSuccess) e = bhq::launch_check_f64(m, n, false, f, s);
-        if (e == hipSuccess) e = bhq::launch_check_f64(&q[0][0], 6 * n, false, f, s);
-        if (e == hipSuccess && trace) e = bhq::launch_check_f64(trace, n, false, f, s);
-        return e;
-    }));
+    const bhq::UploadCol cols[4] = {{x ? &x[0][0] : nullptr, n, 3, bhq::kColFinite, {}},
+                                    {m, n, 1, bhq::kColFinite, {}},
+                                    {q ? &q[0][0] : nullptr, n, 6, bhq::kColFinite, {}},
+                                    {trace, n, 1, bhq::kColFinite, {}}};
+    TRY(dev_upload(ctx, s, "set_pool_cells_dev", cols, 4, false));
     hipError_t e = ctx->arr[A_POOLC].reserve((size_t)n * sizeof(bhq::CellRec));
     if (e == hipSuccess)
         e = bhq::launch_pack_cells(&x[0][0], m, &q[0][0], trace, n,

@@ -194,13 +194,27 @@ constexpr unsigned kBadNonFinite = 1, kBadNonPositive = 2, kBadOrder = 4, kBadRa
 // only normal positive arguments.
 constexpr double kMinEps2 = 0x1p-126;
 hipError_t launch_clear_flag(unsigned *flag, hipStream_t s);
-hipError_t launch_check_f64(const double *v, int64_t n, bool positive, unsigned *flag,
-                            hipStream_t s);
-hipError_t launch_check_offsets(const int64_t *off, int64_t ng, unsigned *flag, hipStream_t s);
+// Arrays of a set call: n rows of w 8-byte columns (1, 3 or 6).  Checks by kind;
+// column c of the copy goes to dst[c] (NULL: skipped).
+enum ColKind { kColFinite, kColPositive, kColOffsets };
+struct UploadCol {
+    const void *src;  // NULL: zeros (copied without a check)
+    int64_t n;
+    int w;
+    ColKind kind;
+    void *dst[6];
+};
+constexpr int kMaxUploadCols = 4;
+hipError_t launch_check_cols(const UploadCol *c, int n, unsigned *flag, hipStream_t s);
+// Copies the columns unless *flag is set, writes *flag to *host (memory the
+// host reads) and clears *next.
+hipError_t launch_copy_cols(const UploadCol *c, int n, const unsigned *flag, unsigned *next,
+                            unsigned *host, hipStream_t s);
+// The same without the copy, and the last elements of the first three arrays.
+hipError_t launch_publish_groups(const UploadCol *c, const unsigned *flag, unsigned *next,
+                                 unsigned *host, int64_t *last, hipStream_t s);
 hipError_t launch_check_idx(const int32_t *idx, int64_t n, int64_t pool, unsigned *flag,
                             hipStream_t s);
-// column c of the AoS array v[n][w] (w <= 6) to out[c] (NULL: skipped)
-hipError_t launch_unpack(const double *v, int64_t n, int w, double *const *out, hipStream_t s);
 hipError_t launch_pack_particles(const double *x, const double *m, int64_t n, PartRec *out,
                                  hipStream_t s);
 hipError_t launch_pack_cells(const double *x, const double *m, const double *q,

@@ -119,3 +119,65 @@ def test_order_plan(ng, window, tail, skew):
             assert np.array_equal(bhq.bhq_get_order(ctx), want)
     finally:
         bhq.bhq_destroy(ctx)
+
+
+def test_upload_after_refusals():
+    """Device set calls refused once, twice and three times in a row leave the
+    context's arrays as they were, and the next good call is accepted (the
+    check flags alternate between two words); parts of a list, with and
+    without the trace; empty uploads."""
+    g = synth.rng(44)
+    n = 700  # entries of one group's lists, more than one block's elements
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float64)).cuda()  # noqa: E731
+    x, m, q, tr = g.random((n, 3)), g.random(n), 0.1 * g.random((n, 6)), g.random(n)
+    off = torch.tensor([0, n], dtype=torch.int64, device="cuda")
+
+    def bad(a, k):
+        b = np.array(a, np.float64)
+        b.reshape(-1)[k] = np.inf
+        return dev(b)
+
+    def result(ctx):
+        bhq.bhq_compute(ctx)
+        return bhq.bhq_get_result(ctx, n)
+
+    ctx = bhq.bhq_create(0, bhq.QUAD_SOFT, bhq.FP64)
+    try:
+        bhq.bhq_set_groups_dev(ctx, off, dev(np.full((1, 3), 0.5)), off, off)
+        bhq.bhq_set_i_dev(ctx, dev(x))
+        bhq.bhq_set_eps2_i_dev(ctx, dev(np.full(n, 1e-2)))
+        bhq.bhq_set_jp_dev(ctx, 0, dev(x), dev(m))
+        bhq.bhq_set_jc_dev(ctx, 0, dev(x[:400] + 2), dev(m[:400]), dev(q[:400]), dev(tr[:400]))
+        bhq.bhq_set_jc_dev(ctx, 400, dev(x[400:] + 2), dev(m[400:]), dev(q[400:]))
+        bhq.bhq_set_jp_dev(ctx, n, dev(x[:0]), dev(m[:0]))
+        before = result(ctx)
+        last = n - 1
+        calls = (lambda: bhq.bhq_set_i_dev(ctx, bad(x, 3 * n - 1)),
+                 lambda: bhq.bhq_set_eps2_i_dev(ctx, dev(np.arange(n) - 1.0)),
+                 lambda: bhq.bhq_set_jp_dev(ctx, 0, dev(x + 1), bad(m, last)),
+                 lambda: bhq.bhq_set_jc_dev(ctx, 0, dev(x), dev(m), bad(q, 6 * n - 1)),
+                 lambda: bhq.bhq_set_jc_dev(ctx, 0, dev(x), dev(m), dev(q), bad(tr, last)))
+        for times in (1, 2, 3):
+            for call in calls:
+                for _ in range(times):
+                    with pytest.raises(bhq.BhqError) as e:
+                        call()
+                    assert e.value.code in (bhq.E_NONFINITE, bhq.E_ARG)
+                after = result(ctx)
+                assert np.array_equal(before[0], after[0]) and np.array_equal(before[1], after[1])
+                bhq.bhq_set_i_dev(ctx, dev(x))
+        # the kernels saw the trace where it was given and zero elsewhere
+        bhq.bhq_set_jc_dev(ctx, 400, dev(x[400:] + 2), dev(m[400:]), dev(q[400:]),
+                           dev(np.zeros(n - 400)))
+        assert np.array_equal(before[0], result(ctx)[0])
+        bhq.bhq_set_jc_dev(ctx, 0, dev(x[:400] + 2), dev(m[:400]), dev(q[:400]))
+        assert not np.array_equal(before[0], result(ctx)[0])
+        with pytest.raises(bhq.BhqError) as e:
+            bhq.bhq_set_groups_dev(ctx, off, bad(np.zeros((1, 3)), 2), off, off)
+        assert e.value.code == bhq.E_NONFINITE
+        with pytest.raises(bhq.BhqError) as e:
+            bhq.bhq_set_groups_dev(ctx, off, dev(np.zeros((1, 3))), off + 1, off)
+        assert e.value.code == bhq.E_RANGE
+        assert not np.array_equal(before[0], result(ctx)[0])  # still the lists above
+    finally:
+        bhq.bhq_destroy(ctx)
