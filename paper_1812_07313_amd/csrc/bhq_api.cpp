@@ -157,6 +157,8 @@ struct bhq_ctx {
     hipStream_t last_stream = nullptr;
 
     bhq::LaunchCfg cfg;
+    bool tuned = false;    // bhq_set_tuning was called: cfg as it is
+    int auto_jsplit = 1;   // of the current lists, where it was not
     int use_graph = 0;
     int order_mode = BHQ_ORDER_XCD, order_window = BHQ_ORDER_WINDOW,
         order_tail = BHQ_ORDER_TAIL;
@@ -312,6 +314,83 @@ struct bhq_ctx {
         off_stale = false;
         return BHQ_OK;
     }
+    // Parts of each group's lists for contexts without a launch shape of their
+    // own, from the groups' costs (total and largest, in order_cost's units)
+    // and number.  A launch of few or uneven groups is as long as its longest
+    // block runs beside idle CUs, and is cut shorter by parts:
+    //   * where the largest group is more than half of a CU's share of the
+    //     work, into as many parts as bring it there;
+    //   * where the groups are fewer than the blocks that run at once (five
+    //     per CU), into as many parts as fill the chip;
+    // but no part below the cost of about 3000 pairs, where the tile and
+    // the sum of the parts outweigh it (244 groups of a Plummer sphere of
+    // 4096: 37 us whole, 25 in four parts, 30 in eight).  Quadrupole kernel,
+    // FP32, ncrit 64: 60 -> 48 us (980 groups, two parts), 30 -> 22 (133,
+    // four); ncrit 256: 213 -> 74 (343, eight); 1944 groups even enough take
+    // 79 us whole and 84 in two parts.  The three constants are the best of a
+    // grid over 110 sets of lists (1000 to 700,000 particles).  The split
+    // kernels have one part: what they compute is the same bits in every
+    // default launch.
+    // The memory for the parts (up to 16 MiB) is taken here, so that a compute
+    // allocates nothing.
+    void plan_jsplit(double total, double largest)
+    {
+        auto_jsplit = 1;
+        if (ng < 1 || ni < 1 || !(total > 0.0)) return;
+        const double tail = 2.0 * largest * cfg.num_cu / total;
+        const double fill = 5.0 * cfg.num_cu / (double)ng;
+        int j = 1;
+        while (j < bhq::kMaxJsplit && (2 * j <= tail || j < fill) &&
+               total / (double)ng / (2 * j) >= 4.5e5 &&
+               (size_t)(2 * j) * (size_t)ni * 32 <= bhq::kScratchPartBytes)
+            j *= 2;
+        if (j > 1) {
+            const size_t bytes = (size_t)j * (size_t)ni * 32;
+            if (bytes > arr[A_PART].cap) {
+                quiesce();
+                if (arr[A_PART].reserve(bytes) != hipSuccess) {
+                    (void)hipGetLastError();
+                    j = 1;
+                }
+                ++args_version;
+            }
+        }
+        auto_jsplit = j;
+    }
+    // The launch shape of a compute: the caller's (bhq_set_tuning), or one
+    // chosen by kernel, precision and mean group size.  One i-particle per
+    // thread fills blocks of small groups better (less padding, fewer slices),
+    // two feed two interactions from each LDS broadcast.  Measured (us, two
+    // per thread against one, registers capped for 6 waves in FP32):
+    //   FP32 quadrupole: mean 16 per group 4525 / 4090 (clustered 2^21),
+    //     31 3799 / 3680, 32 2369 / 2232 (128 systems), 58 1376 / 1335 (cube
+    //     2^20), 64 274 / 277 (cube 2^18);
+    //   FP32 monopole (8 waves): 16 2824 / 2394, 58 903 / 849, 64 182 / 173;
+    //   FP64 quadrupole: 15 574 / 538, 16 4575 / 4294, 31 7083 / 7156.
+    // The split kernels keep two (in FP64 one per thread is half as fast); in
+    // FP32 their six waves (80 registers) take 749 us against 807 (lattice
+    // 96^3) and 4244 against 4550 (160^3).
+    bhq::LaunchCfg shape() const
+    {
+        bhq::LaunchCfg c = cfg;
+        if (tuned) return c;
+        const double mean = ng > 0 ? (double)ni / (double)ng : 0.0;
+        if (kernel == BHQ_SPLIT_QUAD || kernel == BHQ_SPLIT_MONO) {
+            c.waves_per_eu = 6;
+            return c;
+        }
+        c.jsplit = auto_jsplit;
+        if (precision == BHQ_FP64) {
+            c.i_per_thread = mean <= 32.0 ? 1 : 2;
+        } else if (kernel == BHQ_MONO) {
+            c.i_per_thread = mean <= 64.0 ? 1 : 2;
+            c.waves_per_eu = c.jsplit > 1 ? 6 : 8;
+        } else if (mean <= 60.0) {
+            c.i_per_thread = 1;
+            c.waves_per_eu = 6;
+        }
+        return c;
+    }
     // Compute the slot table for the current groups and order mode and
     // upload it.
     int upload_order()
@@ -333,6 +412,15 @@ struct bhq_ctx {
         if (e != hipSuccess) return hip_fail(e, "order upload");
         nslots = (int64_t)order.size();
         ++args_version;
+        double total = 0.0, largest = 0.0;
+        for (int64_t g = 0; g < ng; ++g) {
+            const double c = (double)bhq::order_cost(i_off[(size_t)g + 1] - i_off[(size_t)g],
+                                                     jp_off[(size_t)g + 1] - jp_off[(size_t)g],
+                                                     jc_off[(size_t)g + 1] - jc_off[(size_t)g]);
+            total += c;
+            largest = std::max(largest, c);
+        }
+        plan_jsplit(total, largest);
         return BHQ_OK;
     }
     // Turn lists kept in per-group slots into compact lists at the offsets
@@ -789,10 +877,11 @@ int bhq_compute(bhq_ctx *ctx, void *stream)
     CHECK_CTX(ctx);
     bhq::ForceArgs A;
     TRY(prepare_compute(ctx, A));
+    const bhq::LaunchCfg cfg = ctx->shape();
 
-    if (ctx->cfg.jsplit > 1) {
+    if (cfg.jsplit > 1) {
         // parts of every i-particle's sums (32 B per entry covers FP64)
-        const size_t bytes = (size_t)ctx->cfg.jsplit * (size_t)ctx->ni * 32;
+        const size_t bytes = (size_t)cfg.jsplit * (size_t)ctx->ni * 32;
         if (bytes > ctx->arr[A_PART].cap) {
             ctx->quiesce();
             hipError_t e = ctx->arr[A_PART].reserve(bytes);
@@ -808,12 +897,12 @@ int bhq_compute(bhq_ctx *ctx, void *stream)
         const bool same =
             ctx->graph_exec && ctx->graph_key.kernel == ctx->kernel &&
             ctx->graph_key.precision == ctx->precision &&
-            ctx->graph_key.block == ctx->cfg.block &&
-            ctx->graph_key.i_per_thread == ctx->cfg.i_per_thread &&
-            ctx->graph_key.persistent == ctx->cfg.persistent &&
-            ctx->graph_key.blocks_per_cu == ctx->cfg.blocks_per_cu &&
-            ctx->graph_key.jsplit == ctx->cfg.jsplit &&
-            ctx->graph_key.waves_per_eu == ctx->cfg.waves_per_eu &&
+            ctx->graph_key.block == cfg.block &&
+            ctx->graph_key.i_per_thread == cfg.i_per_thread &&
+            ctx->graph_key.persistent == cfg.persistent &&
+            ctx->graph_key.blocks_per_cu == cfg.blocks_per_cu &&
+            ctx->graph_key.jsplit == cfg.jsplit &&
+            ctx->graph_key.waves_per_eu == cfg.waves_per_eu &&
             ctx->graph_key.version == ctx->args_version;
         if (!same) {
             if (ctx->launched) (void)hipEventSynchronize(ctx->ev1);
@@ -825,7 +914,7 @@ int bhq_compute(bhq_ctx *ctx, void *stream)
             e = hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return ctx->hip_fail(e, "hipStreamBeginCapture");
             const hipError_t le =
-                bhq::launch_force(ctx->kernel, ctx->precision, A, ctx->cfg,
+                bhq::launch_force(ctx->kernel, ctx->precision, A, cfg,
                                   ctx->cap_stream);
             e = hipStreamEndCapture(ctx->cap_stream, &ctx->graph);
             if (le != hipSuccess) {
@@ -840,12 +929,12 @@ int bhq_compute(bhq_ctx *ctx, void *stream)
             }
             ctx->graph_key.kernel = ctx->kernel;
             ctx->graph_key.precision = ctx->precision;
-            ctx->graph_key.block = ctx->cfg.block;
-            ctx->graph_key.i_per_thread = ctx->cfg.i_per_thread;
-            ctx->graph_key.persistent = ctx->cfg.persistent;
-            ctx->graph_key.blocks_per_cu = ctx->cfg.blocks_per_cu;
-            ctx->graph_key.jsplit = ctx->cfg.jsplit;
-            ctx->graph_key.waves_per_eu = ctx->cfg.waves_per_eu;
+            ctx->graph_key.block = cfg.block;
+            ctx->graph_key.i_per_thread = cfg.i_per_thread;
+            ctx->graph_key.persistent = cfg.persistent;
+            ctx->graph_key.blocks_per_cu = cfg.blocks_per_cu;
+            ctx->graph_key.jsplit = cfg.jsplit;
+            ctx->graph_key.waves_per_eu = cfg.waves_per_eu;
             ctx->graph_key.version = ctx->args_version;
         }
         e = hipEventRecord(ctx->ev0, s);
@@ -855,7 +944,7 @@ int bhq_compute(bhq_ctx *ctx, void *stream)
     } else {
         e = hipEventRecord(ctx->ev0, s);
         if (e != hipSuccess) return ctx->hip_fail(e, "hipEventRecord");
-        e = bhq::launch_force(ctx->kernel, ctx->precision, A, ctx->cfg, s);
+        e = bhq::launch_force(ctx->kernel, ctx->precision, A, cfg, s);
         if (e != hipSuccess) return ctx->hip_fail(e, "force kernel launch");
     }
     e = hipEventRecord(ctx->ev1, s);
@@ -873,13 +962,16 @@ int bhq_compute_noalloc(bhq_ctx *ctx, double *a, double *pot, void *stream)
     if (!a) return ctx->fail(BHQ_E_ARG, "compute_noalloc: a is NULL");
     bhq::ForceArgs A;
     TRY(prepare_compute(ctx, A));
+    const bhq::LaunchCfg cfg = ctx->shape();
     const size_t entry = ctx->precision == BHQ_FP64 ? 32 : 16;
-    if (ctx->cfg.jsplit > 1 &&
-        (size_t)ctx->cfg.jsplit * (size_t)ctx->ni * entry > bhq::kScratchPartBytes)
+    // parts that the context chose are in its own memory, taken with the lists
+    const bool own = !ctx->tuned && cfg.jsplit > 1;
+    if (!own && cfg.jsplit > 1 &&
+        (size_t)cfg.jsplit * (size_t)ctx->ni * entry > bhq::kScratchPartBytes)
         return ctx->fail(BHQ_E_RANGE,
                          "compute_noalloc: jsplit %d x %lld i-particles x %zu B of parts "
                          "exceed the static %zu B (use a smaller jsplit, or bhq_compute)",
-                         ctx->cfg.jsplit, (long long)ctx->ni, entry, bhq::kScratchPartBytes);
+                         cfg.jsplit, (long long)ctx->ni, entry, bhq::kScratchPartBytes);
     if (ctx->ni > 0) {
         TRY(check_device_range(ctx, a, (size_t)ctx->ni * 3 * sizeof(double), "a"));
         if (pot) TRY(check_device_range(ctx, pot, (size_t)ctx->ni * sizeof(double), "pot"));
@@ -892,11 +984,11 @@ int bhq_compute_noalloc(bhq_ctx *ctx, double *a, double *pot, void *stream)
     A.pot = pot;
     A.out_stride = 3;
     A.queue = reinterpret_cast<unsigned int *>(sp);
-    A.part = sp + bhq::kScratchQueueBytes;
+    A.part = own ? ctx->arr[A_PART].p : sp + bhq::kScratchQueueBytes;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = hipEventRecord(ctx->ev0, s);
     if (e != hipSuccess) return ctx->hip_fail(e, "hipEventRecord");
-    e = bhq::launch_force(ctx->kernel, ctx->precision, A, ctx->cfg, s);
+    e = bhq::launch_force(ctx->kernel, ctx->precision, A, cfg, s);
     if (e != hipSuccess) return ctx->hip_fail(e, "force kernel launch");
     e = hipEventRecord(ctx->ev1, s);
     if (e != hipSuccess) return ctx->hip_fail(e, "hipEventRecord");
@@ -984,6 +1076,7 @@ int bhq_set_tuning(bhq_ctx *ctx, int block, int i_per_thread, int blocks_per_cu,
         return ctx->fail(BHQ_E_ARG, "waves_per_eu must be 0, 6 or 8");
     if (waves_per_eu != 0 && block != 256)
         return ctx->fail(BHQ_E_ARG, "waves_per_eu 6 and 8 exist for block 256 only");
+    ctx->tuned = true;
     ctx->cfg.block = block;
     ctx->cfg.waves_per_eu = waves_per_eu;
     ctx->cfg.i_per_thread = i_per_thread;
@@ -1647,6 +1740,8 @@ int bhq_set_groups_dev(bhq_ctx *ctx, int64_t ng, const int64_t *i_off,
             ctx->nslots = L.stats[bhq::kStatSlots];
         else
             ctx->fail(orc, "%s", msg.c_str());
+        if (orc == BHQ_OK)
+            ctx->plan_jsplit((double)L.stats[bhq::kStatCost], (double)L.stats[bhq::kStatMaxCost]);
     } else {
         e = hipStreamSynchronize(s);
         orc = e == hipSuccess ? ctx->upload_order() : ctx->hip_fail(e, "set_groups_dev: copy");
@@ -1971,6 +2066,7 @@ static int device_build(bhq_ctx *ctx, int64_t nsys, const int64_t *sys_off,
     else if (ctx->eps_mode == 2)
         ctx->eps_mode = 0;
     ctx->nslots = O.nslots;
+    ctx->plan_jsplit(O.cost, O.max_cost);
     if (!device_order) {
         const int orc = ctx->upload_order();
         if (orc != BHQ_OK) {

@@ -248,6 +248,7 @@ enum ListStat {
     kStatParts, kStatCells,        // list entries
     kStatMaxParts, kStatMaxCells,  // longest lists
     kStatWalk, kStatOpened,        // flag[0], flag[2] of the walk
+    kStatCost, kStatMaxCost,       // order_cost: all groups', the largest
     kStatSlots,                    // launch slots
     kStatCount
 };
@@ -358,6 +359,7 @@ struct TreeOut {
     // one walk: jp_idx / jc_idx hold the per-group slots of these sizes
     int64_t slot_p = 0, slot_c = 0;
     int nlevels = 0;  // levels of the tree (the root's included)
+    double cost = 0.0, max_cost = 0.0;  // order_cost of all groups, the largest
     int64_t nslots = 0;  // launch slots (where an order was asked for)
 };
 

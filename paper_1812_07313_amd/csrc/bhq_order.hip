@@ -36,7 +36,7 @@ constexpr int kMaxXcds = 64;
 
 struct Sums {
     uint64_t p, c, cost;  // list entries, cost
-    uint64_t mp, mc;      // longest lists
+    uint64_t mp, mc, mcost;  // longest lists, largest cost
 };
 
 struct PlanArgs {
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kBlock) void k_tile_sums(const PlanArgs A)
 {
     typedef hipcub::BlockReduce<uint64_t, kBlock> Reduce;
     __shared__ typename Reduce::TempStorage tmp;
-    uint64_t v[5] = {0, 0, 0, 0, 0};
+    uint64_t v[6] = {0, 0, 0, 0, 0, 0};
     for (int u = 0; u < kItems; ++u) {
         uint64_t p, c, cost;
         group_terms(A, (int64_t)blockIdx.x * kTile + u * kBlock + threadIdx.x, p, c, cost);
@@ -78,13 +78,14 @@ __global__ __launch_bounds__(kBlock) void k_tile_sums(const PlanArgs A)
         v[2] += cost;
         v[3] = p > v[3] ? p : v[3];
         v[4] = c > v[4] ? c : v[4];
+        v[5] = cost > v[5] ? cost : v[5];
     }
-    uint64_t r[5];
-    for (int k = 0; k < 5; ++k) {
+    uint64_t r[6];
+    for (int k = 0; k < 6; ++k) {
         r[k] = k < 3 ? Reduce(tmp).Sum(v[k]) : Reduce(tmp).Reduce(v[k], hipcub::Max());
         __syncthreads();
     }
-    if (threadIdx.x == 0) A.tile[blockIdx.x] = Sums{r[0], r[1], r[2], r[3], r[4]};
+    if (threadIdx.x == 0) A.tile[blockIdx.x] = Sums{r[0], r[1], r[2], r[3], r[4], r[5]};
 }
 
 // Exclusive sums of the tiles' sums, totals after them; one block.
@@ -96,26 +97,27 @@ __global__ __launch_bounds__(kBlock) void k_tile_scan(const PlanArgs A, int tile
         typename Scan::TempStorage scan;
         typename Reduce::TempStorage reduce;
     } tmp;
-    uint64_t at[3] = {0, 0, 0}, m[2] = {0, 0};
+    uint64_t at[3] = {0, 0, 0}, m[3] = {0, 0, 0};
     for (int b = 0; b < tiles; b += kBlock) {
         const int i = b + (int)threadIdx.x;
-        const Sums t = i < tiles ? A.tile[i] : Sums{0, 0, 0, 0, 0};
+        const Sums t = i < tiles ? A.tile[i] : Sums{0, 0, 0, 0, 0, 0};
         const uint64_t v[3] = {t.p, t.c, t.cost};
         uint64_t ex[3], tot[3];
         for (int k = 0; k < 3; ++k) {
             Scan(tmp.scan).ExclusiveSum(v[k], ex[k], tot[k]);
             __syncthreads();
         }
-        if (i < tiles) A.tile[i] = Sums{at[0] + ex[0], at[1] + ex[1], at[2] + ex[2], 0, 0};
+        if (i < tiles) A.tile[i] = Sums{at[0] + ex[0], at[1] + ex[1], at[2] + ex[2], 0, 0, 0};
         for (int k = 0; k < 3; ++k) at[k] += tot[k];
         m[0] = t.mp > m[0] ? t.mp : m[0];
         m[1] = t.mc > m[1] ? t.mc : m[1];
+        m[2] = t.mcost > m[2] ? t.mcost : m[2];
     }
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < 3; ++k) {
         m[k] = Reduce(tmp.reduce).Reduce(m[k], hipcub::Max());
         __syncthreads();
     }
-    if (threadIdx.x == 0) A.tile[tiles] = Sums{at[0], at[1], at[2], m[0], m[1]};
+    if (threadIdx.x == 0) A.tile[tiles] = Sums{at[0], at[1], at[2], m[0], m[1], m[2]};
 }
 
 // A tile's offsets, costs and pieces; the statistics.  ONE: the only tile,
@@ -130,25 +132,24 @@ __global__ __launch_bounds__(kBlock) void k_offsets(const PlanArgs A, int tiles)
         typename Reduce::TempStorage reduce;
     } tmp;
     const int64_t g0 = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
-    uint64_t v[3][kItems], cost[kItems], mx[2] = {0, 0};
+    uint64_t v[3][kItems], cost[kItems], mx[3] = {0, 0, 0};
     for (int u = 0; u < kItems; ++u) {
         group_terms(A, g0 + u, v[0][u], v[1][u], v[2][u]);
         cost[u] = v[2][u];
-        mx[0] = v[0][u] > mx[0] ? v[0][u] : mx[0];
-        mx[1] = v[1][u] > mx[1] ? v[1][u] : mx[1];
+        for (int k = 0; k < 3; ++k) mx[k] = v[k][u] > mx[k] ? v[k][u] : mx[k];
     }
-    Sums before{0, 0, 0, 0, 0}, all;
+    Sums before{0, 0, 0, 0, 0, 0}, all;
     uint64_t tot[3];
     for (int k = 0; k < 3; ++k) {
         Scan(tmp.scan).ExclusiveSum(v[k], v[k], tot[k]);
         __syncthreads();
     }
     if constexpr (ONE) {
-        for (int k = 0; k < 2; ++k) {
+        for (int k = 0; k < 3; ++k) {
             mx[k] = Reduce(tmp.reduce).Reduce(mx[k], hipcub::Max());
             __syncthreads();
         }
-        all = Sums{tot[0], tot[1], tot[2], mx[0], mx[1]};  // (maxima: thread 0)
+        all = Sums{tot[0], tot[1], tot[2], mx[0], mx[1], mx[2]};  // (maxima: thread 0)
     } else {
         before = A.tile[blockIdx.x];
         all = A.tile[tiles];
@@ -185,6 +186,8 @@ __global__ __launch_bounds__(kBlock) void k_offsets(const PlanArgs A, int tiles)
         A.stats[kStatCells] = (int64_t)all.c;
         A.stats[kStatMaxParts] = (int64_t)all.mp;
         A.stats[kStatMaxCells] = (int64_t)all.mc;
+        A.stats[kStatCost] = (int64_t)all.cost;
+        A.stats[kStatMaxCost] = (int64_t)all.mcost;
         A.stats[kStatWalk] = A.flag ? A.flag[0] : 0;
         A.stats[kStatOpened] = A.flag ? A.flag[2] : 0;
     }

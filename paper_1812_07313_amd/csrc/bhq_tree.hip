@@ -1818,6 +1818,8 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         O.nslots = stats[kStatSlots];
     }
     const int64_t most = stats[kStatOpened];
+    O.cost = (double)stats[kStatCost];
+    O.max_cost = (double)stats[kStatMaxCost];
     const int64_t njp = stats[kStatParts], njc = stats[kStatCells];
     const int64_t max_p = stats[kStatMaxParts], max_c = stats[kStatMaxCells];
     O.one_walk = slots && max_p <= P.cap_p && max_c <= P.cap_c;

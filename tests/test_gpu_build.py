@@ -181,3 +181,92 @@ def test_upload_after_refusals():
         assert not np.array_equal(before[0], result(ctx)[0])  # still the lists above
     finally:
         bhq.bhq_destroy(ctx)
+
+
+@pytest.mark.parametrize("kernel", [bhq.QUAD, bhq.MONO, bhq.QUAD_SOFT])
+@pytest.mark.parametrize("dist,n,ncrit", [
+    ("plummer", 60, 64),       # one group
+    ("plummer", 2048, 64),     # few groups: parts
+    ("plummer", 16384, 256),   # uneven groups: eight parts
+    ("cube", 65536, 128),      # mean group sizes across the choices of
+    ("cube", 30000, 128),      # i-particles per thread: 16, 58, 128
+    ("cube", 524288, 256),
+])
+def test_default_launch_shapes(kernel, dist, n, ncrit):
+    """The launch shape that a context without bhq_set_tuning chooses, against
+    the shape (256, 2) of one part in FP64; the same through
+    bhq_compute_noalloc, after a rebuild, and on lists set from the host."""
+    x, m = (synth.plummer if dist == "plummer" else synth.uniform_cube)(n, synth.rng(45))
+    xt, mt = torch.from_numpy(x).cuda(), torch.from_numpy(m).cuda()
+    ctx = bhq.bhq_create(0, kernel, bhq.FP64)
+    try:
+        bhq.bhq_set_eps(ctx, 0.01)
+        bhq.bhq_set_tuning(ctx, 256, 2)
+        bhq.bhq_build_lists_device(ctx, xt, mt, 0.7, ncrit)
+        bhq.bhq_compute(ctx)
+        ref = bhq.bhq_get_result(ctx, n)
+    finally:
+        bhq.bhq_destroy(ctx)
+    for precision, rms, top in ((bhq.FP32_OFS64, 2e-6, 1e-4), (bhq.FP64, 1e-12, 1e-10)):
+        ctx = bhq.bhq_create(0, kernel, precision)
+        host = bhq.bhq_create(0, kernel, precision)
+        try:
+            shape = bhq.bhq_get_tuning(ctx)
+            for c in (ctx, host):
+                bhq.bhq_set_eps(c, 0.01)
+            first = None
+            for build in range(2):
+                bhq.bhq_build_lists_device(ctx, xt, mt, 0.7, ncrit)
+                bhq.bhq_compute(ctx)
+                a, p = bhq.bhq_get_result(ctx, n)
+                e = np.sqrt(((a - ref[0]) ** 2).sum(1) / (ref[0] ** 2).sum(1))
+                assert np.sqrt(np.mean(e ** 2)) <= rms and e.max() <= top, (precision, e.max())
+                assert (np.abs(p / ref[1] - 1)).max() <= top
+                first = first or (a, p)
+                assert np.array_equal(first[0], a) and np.array_equal(first[1], p)
+            at = torch.empty(n, 3, dtype=torch.float64, device="cuda")
+            pt = torch.empty(n, dtype=torch.float64, device="cuda")
+            bhq.bhq_compute_noalloc(ctx, at, pt)
+            assert np.array_equal(at.cpu().numpy(), a) and np.array_equal(pt.cpu().numpy(), p)
+            L = bhq.bhq_build_lists(x, m, 0.7, ncrit)
+            try:
+                bhq.bhq_set_lists_indexed(host, L, x, m)
+            finally:
+                bhq.bhq_lists_free(L)
+            bhq.bhq_set_eps(host, 0.01)
+            bhq.bhq_compute(host)
+            b, q = bhq.bhq_get_result(host, n)
+            assert np.array_equal(a, b) and np.array_equal(p, q)
+            assert bhq.bhq_get_tuning(ctx) == shape  # what the caller asked for
+        finally:
+            bhq.bhq_destroy(ctx)
+            bhq.bhq_destroy(host)
+
+
+def test_default_shape_captures():
+    """A compute in parts that the context chose allocates nothing: it can be
+    captured in a graph, whose replays give the eager result."""
+    n = 4096
+    x, m = synth.plummer(n, synth.rng(46))
+    ctx = bhq.bhq_create(0, bhq.QUAD, bhq.FP32_OFS64)
+    try:
+        bhq.bhq_set_eps(ctx, 0.01)
+        bhq.bhq_build_lists_device(ctx, torch.from_numpy(x).cuda(), torch.from_numpy(m).cuda(),
+                                   0.6, 64)
+        a = torch.zeros(n, 3, dtype=torch.float64, device="cuda")
+        s = torch.cuda.Stream()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            bhq.bhq_compute_noalloc(ctx, a, None, stream=s)
+        bhq.bhq_compute(ctx)
+        want, _ = bhq.bhq_get_result(ctx, n)
+        for _ in range(3):
+            a.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(a.cpu().numpy(), want)
+            bhq.bhq_compute(ctx)
+    finally:
+        torch.cuda.synchronize()
+        bhq.bhq_destroy(ctx)
