@@ -81,10 +81,11 @@ inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 // Minimum and maximum per axis over the block's threads: lo, hi of thread t
 // in s[0..2][t], s[3..5][t]; the result in s[.][0].
-__device__ __forceinline__ void block_box(double (*s)[kBlock])
+template <int BS>
+__device__ __forceinline__ void block_box(double (*s)[BS])
 {
     __syncthreads();
-    for (int h = kBlock / 2; h > 0; h >>= 1) {
+    for (int h = BS / 2; h > 0; h >>= 1) {
         if ((int)threadIdx.x < h)
             for (int a = 0; a < 3; ++a) {
                 const double l = s[a][threadIdx.x + h], u = s[3 + a][threadIdx.x + h];
@@ -97,7 +98,8 @@ __device__ __forceinline__ void block_box(double (*s)[kBlock])
 
 // Root cube of the box s[.][0]: centre and side, with the host builder's
 // operations.
-__device__ __forceinline__ void root_cube(double (*s)[kBlock], double *root)
+template <int BS>
+__device__ __forceinline__ void root_cube(double (*s)[BS], double *root)
 {
     double ext = 0.0;
     for (int a = 0; a < 3; ++a) {
@@ -110,15 +112,26 @@ __device__ __forceinline__ void root_cube(double (*s)[kBlock], double *root)
 
 // Non-finite positions or masses set flag[0]; a softening that is not
 // finite and positive sets flag[1] (vector stores of 1).  The same pass over
-// the positions gives each block's bounding box (one system).
-__global__ __launch_bounds__(kBlock) void k_check(const double *x, const double *m,
-                                                  const double *eps2, int64_t n, int *flag,
-                                                  double *part)
+// the positions gives each block's bounding box (one system), in part.
+// ONE: the only block, which clears the flags itself and writes the root cube
+// to part (box > 0: of [0, box)^3).  Up to kSmallCheck particles that saves
+// two launches of 4 us each.
+constexpr int64_t kSmallCheck = 8192;
+constexpr int kFlags = 16;
+
+template <int BS, bool ONE>
+__global__ __launch_bounds__(BS) void k_check(const double *x, const double *m,
+                                              const double *eps2, int64_t n, double box,
+                                              int *flag, double *part)
 {
-    __shared__ double s[6][kBlock];
+    __shared__ double s[6][BS];
+    if (ONE) {
+        if (threadIdx.x < kFlags) flag[threadIdx.x] = 0;
+        __syncthreads();
+    }
     double lo[3], hi[3];
-    const int64_t start = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    const int64_t start = (int64_t)blockIdx.x * BS + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * BS;
     const int64_t p0 = start < n ? start : 0;  // n >= 1
     for (int a = 0; a < 3; ++a) lo[a] = hi[a] = x[3 * p0 + a];
     for (int64_t p = start; p < n; p += stride) {
@@ -132,12 +145,20 @@ __global__ __launch_bounds__(kBlock) void k_check(const double *x, const double 
         if (eps2 && !(isfinite(eps2[p]) && eps2[p] >= kMinEps2)) flag[1] = 1;
     }
     if (!part) return;
+    if (ONE && box > 0.0) {
+        if (threadIdx.x < 4) part[threadIdx.x] = threadIdx.x < 3 ? 0.5 * box : box;
+        return;
+    }
     for (int a = 0; a < 3; ++a) {
         s[a][threadIdx.x] = lo[a];
         s[3 + a][threadIdx.x] = hi[a];
     }
-    block_box(s);
-    if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = s[threadIdx.x][0];
+    block_box<BS>(s);
+    if (ONE) {
+        if (threadIdx.x == 0) root_cube<BS>(s, part);
+    } else {
+        if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = s[threadIdx.x][0];
+    }
 }
 
 // The one system's root cube from the blocks' boxes, or [0, box)^3.
@@ -156,8 +177,8 @@ __global__ __launch_bounds__(kBlock) void k_root(const double *part, int nb, dou
             if (l < s[a][threadIdx.x]) s[a][threadIdx.x] = l;
             if (u > s[3 + a][threadIdx.x]) s[3 + a][threadIdx.x] = u;
         }
-    block_box(s);
-    if (threadIdx.x == 0) root_cube(s, root);
+    block_box<kBlock>(s);
+    if (threadIdx.x == 0) root_cube<kBlock>(s, root);
 }
 
 // Root cube of each system of a batch: one block per system.
@@ -178,8 +199,8 @@ __global__ __launch_bounds__(kBlock) void k_root_sys(const double *x, const int6
         s[k][threadIdx.x] = lo[k];
         s[3 + k][threadIdx.x] = hi[k];
     }
-    block_box(s);
-    if (threadIdx.x == 0) root_cube(s, roots + 4 * blockIdx.x);
+    block_box<kBlock>(s);
+    if (threadIdx.x == 0) root_cube<kBlock>(s, roots + 4 * blockIdx.x);
 }
 
 // ---- 2. keys ----------------------------------------------------------------
@@ -257,9 +278,12 @@ __global__ __launch_bounds__(kBlock) void k_keys(const double *x, int64_t n,
 // a scan and a read by the host, took 0.33 of 1.9 ms on the cube of 2^20
 // (now 0.04) and 0.31 ms on a Plummer sphere of 16,384.
 
-constexpr int kTile = 1024;            // particles per block of k_split and k_cells
-constexpr int kPer = kTile / kBlock;   // per thread
-constexpr int kChunks = kTile / 64;    // waves' worth of particles per tile
+// Particles per thread of k_split and k_cells (a tile is a block's particles):
+// four share the windows' ends and the scan's entries; up to kSmallTree
+// particles one, whose chain is shorter where the blocks do not fill the
+// chip (Plummer spheres of 2048 and 16,384: 28 and 31 us for both with four).
+constexpr int kPerLarge = 4;
+constexpr int64_t kSmallTree = 65536;
 constexpr int kWinMost = 4096;         // longest window k_split holds in LDS
 constexpr int kRows = kMaxDepth + 2;   // depths 0 .. 21 and the groups
 
@@ -299,8 +323,9 @@ struct SplitArgs {
 };
 
 // Largest cp(j, j + w) over j in [k - w, k] for the tile's particles k, -1
-// if there is none; in LDS bytes a, b of kTile + w each, by doubling: a
+// if there is none; in LDS bytes a, b of a tile + w each, by doubling: a
 // window's maximum is that of two windows half as long.
+template <int kTile>
 __device__ __forceinline__ const int8_t *window_max(const SplitArgs &A, int64_t k0, int w,
                                                     int8_t *a, int8_t *b, int &half)
 {
@@ -332,8 +357,10 @@ __device__ __forceinline__ const int8_t *window_max(const SplitArgs &A, int64_t 
     return a;
 }
 
+template <int kPer>
 __global__ __launch_bounds__(kBlock) void k_split(const SplitArgs A, int nb)
 {
+    constexpr int kTile = kPer * kBlock;
     extern __shared__ int8_t s_win[];
     __shared__ int s_cnt[kBlock / 64][kRows];
     const int t = threadIdx.x;
@@ -344,7 +371,7 @@ __global__ __launch_bounds__(kBlock) void k_split(const SplitArgs A, int nb)
         if (w <= kWinMost && (!pass || w > 0)) {
             int p;
             __syncthreads();
-            const int8_t *m = window_max(A, k0, w, s_win, s_win + kTile + w, p);
+            const int8_t *m = window_max<kTile>(A, k0, w, s_win, s_win + kTile + w, p);
 #pragma unroll
             for (int u = 0; u < kPer; ++u) {
                 const int i = t + u * kBlock;
@@ -443,10 +470,10 @@ __global__ void k_table(const int32_t *first, int rows, int nb, const int *flag,
 // lower depths) before system q's first particle, q <= nsys.  One wave per
 // system, over the particles of its tile.
 __global__ __launch_bounds__(64) void k_sys_first(const SplitArgs A, const int32_t *first, int nb,
-                                                  int32_t *before)
+                                                  int tile, int32_t *before)
 {
     const int q = blockIdx.x, lane = threadIdx.x;
-    const int64_t e = A.sys_off[q], k0 = e / kTile * kTile;
+    const int64_t e = A.sys_off[q], k0 = e / tile * tile;
     int mine = 0;
     for (int64_t b = k0; b < e; b += 64) {
         const int32_t v = b + lane < e ? A.info[b + lane] : (kMaxDepth + 1);
@@ -456,7 +483,7 @@ __global__ __launch_bounds__(64) void k_sys_first(const SplitArgs A, const int32
         }
     }
     if (lane < A.rows)
-        before[(int64_t)q * A.rows + lane] = first[(int64_t)lane * nb + k0 / kTile] + mine;
+        before[(int64_t)q * A.rows + lane] = first[(int64_t)lane * nb + k0 / tile] + mine;
 }
 
 // cells[q rows + L] = cells of system q at depth L.
@@ -490,8 +517,11 @@ struct CellArgs {
     int32_t ngroup0;       // number of the first group start
 };
 
+template <int kPer>
 __global__ __launch_bounds__(kBlock) void k_cells(const CellArgs C, int nb)
 {
+    constexpr int kTile = kPer * kBlock;
+    constexpr int kChunks = kTile / 64;  // waves' worth of particles per tile
     __shared__ uint64_t s_bal[kChunks][kRows];
     __shared__ int32_t s_pre[kChunks][kRows];
     const SplitArgs &A = C.s;
@@ -1429,8 +1459,7 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
 
     // input check, systems, root cubes
     const int nsys = (int)P.nsys;
-    STEP(B[T_FLAG].reserve(64), "allocation");
-    STEP(hipMemsetAsync(B[T_FLAG].p, 0, 64, s), "memset");
+    STEP(B[T_FLAG].reserve(kFlags * 4), "allocation");
     int *flag = B[T_FLAG].as<int>();  // non-finite, softening, too deep; the walk's from 4
     STEP(B[T_ROOTS].reserve((size_t)nsys * 4 * sizeof(double)), "allocation");
     double *roots = B[T_ROOTS].as<double>();
@@ -1439,15 +1468,22 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     {
         const bool box1 = nsys == 1 && !(P.box > 0.0);
         const int nb = (int)std::min<int64_t>(kBboxBlocks, blocks(n, kBlock));
-        STEP(B[T_BBOX].reserve((size_t)nb * 6 * sizeof(double)), "allocation");
-        hipLaunchKernelGGL(k_check, dim3(nb), dim3(kBlock), 0, s, P.x, P.m, P.eps2, n, flag,
-                           box1 ? B[T_BBOX].as<double>() : nullptr);
+        const bool one = nsys == 1 && n <= kSmallCheck;
+        if (one) {
+            hipLaunchKernelGGL((k_check<1024, true>), dim3(1), dim3(1024), 0, s, P.x, P.m, P.eps2,
+                               n, P.box, flag, roots);
+        } else {
+            STEP(hipMemsetAsync(flag, 0, kFlags * 4, s), "memset");
+            STEP(B[T_BBOX].reserve((size_t)nb * 6 * sizeof(double)), "allocation");
+            hipLaunchKernelGGL((k_check<kBlock, false>), dim3(nb), dim3(kBlock), 0, s, P.x, P.m,
+                               P.eps2, n, P.box, flag, box1 ? B[T_BBOX].as<double>() : nullptr);
+        }
         LAUNCHED("finite check");
-        if (nsys == 1) {
+        if (nsys == 1 && !one) {
             hipLaunchKernelGGL(k_root, dim3(1), dim3(kBlock), 0, s, B[T_BBOX].as<double>(), nb,
                                P.box, roots);
             LAUNCHED("root cube");
-        } else {
+        } else if (nsys > 1) {
             STEP(B[T_SYSOFF].reserve((size_t)(nsys + 1) * 8), "allocation");
             STEP(B[T_SYSOFF32].reserve((size_t)(nsys + 1) * 4), "allocation");
             STEP(hipMemcpyAsync(B[T_SYSOFF].p, P.sys_off, (size_t)(nsys + 1) * 8,
@@ -1501,7 +1537,9 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         if (!hip(B[T_SORT].reserve(std::max(tmp, B[T_SORT].cap)), "allocation")) return false;
         return hip(run(B[T_SORT].p, tmp), "sort");
     };
-    const int nb = (int)blocks(n + 1, kTile);
+    const bool small = n <= kSmallTree;
+    const int tile = (small ? 1 : kPerLarge) * kBlock;
+    const int nb = (int)blocks(n + 1, tile);
     const bool group_row = P.ncrit <= kWinMost;
     volatile int32_t *table = static_cast<int32_t *>(O.host);
     static_assert(4 + kRows + 2 <= 64, "level table");
@@ -1527,8 +1565,12 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         S.count = B[T_NCH].as<int32_t>();
         S.deep = flag + 2;
         const int win = std::max(P.nleaf <= kWinMost ? P.nleaf : 0, S.ncrit);
-        hipLaunchKernelGGL(k_split, dim3((unsigned)nb), dim3(kBlock), 2 * (size_t)(kTile + win), s,
-                           S, nb);
+        const size_t lds = 2 * (size_t)(tile + win);
+        if (small)
+            hipLaunchKernelGGL(k_split<1>, dim3((unsigned)nb), dim3(kBlock), lds, s, S, nb);
+        else
+            hipLaunchKernelGGL(k_split<kPerLarge>, dim3((unsigned)nb), dim3(kBlock), lds, s, S,
+                               nb);
         LAUNCHED("cell starts");
         if (ncount <= 16384) {
             hipLaunchKernelGGL(k_scan_block, dim3(1), dim3(1024), 0, s, S.count, ncount,
@@ -1598,7 +1640,7 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         int32_t *before = B[T_LSC].as<int32_t>(), *cnt = B[T_LSN].as<int32_t>();
         int32_t *shift = B[T_SHIFT].as<int32_t>();
         hipLaunchKernelGGL(k_sys_first, dim3((unsigned)nsys + 1), dim3(64), 0, s, S, CA.first, nb,
-                           before);
+                           tile, before);
         LAUNCHED("system cells");
         hipLaunchKernelGGL(k_sys_cells, dim3(blocks(tab, kBlock)), dim3(kBlock), 0, s, before, tab,
                            rows, cnt);
@@ -1622,7 +1664,10 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         STEP(B[T_PARENT].reserve((size_t)ncell * 4), "allocation");
         CA.parent = B[T_PARENT].as<int32_t>();
     }
-    hipLaunchKernelGGL(k_cells, dim3((unsigned)nb), dim3(kBlock), 0, s, CA, nb);
+    if (small)
+        hipLaunchKernelGGL(k_cells<1>, dim3((unsigned)nb), dim3(kBlock), 0, s, CA, nb);
+    else
+        hipLaunchKernelGGL(k_cells<kPerLarge>, dim3((unsigned)nb), dim3(kBlock), 0, s, CA, nb);
     LAUNCHED("cells");
 
     // particles in tree order, in the layout of the force context

@@ -42,7 +42,11 @@ def _clumps(n, g):
 
 @pytest.mark.parametrize("n,ncrit,nleaf", [
     (1, 1, 1), (2, 1, 1),
-    (1022, 32, 8), (1023, 32, 8), (1024, 32, 8), (1025, 33, 7),  # edges of a tile of particles
+    (254, 32, 8), (255, 32, 8), (256, 32, 8), (257, 33, 7),  # edges of a tile of particles
+    (1022, 32, 8), (1023, 32, 8), (1024, 32, 8), (1025, 33, 7),
+    (8192, 64, 8), (8193, 64, 8),      # checked and bounded in one launch, in two
+    (65536, 64, 8), (65537, 64, 8),    # one and four particles per thread
+    (66559, 64, 8), (66560, 64, 8),    # edges of a tile of 1024
     (30000, 64, 8),                    # the scan of the tiles' counts in one block
     (800000, 256, 8),                  # ... and by several
     (9000, 4096, 1), (9000, 4097, 8),  # the longest group in windows, and past it
