@@ -433,8 +433,21 @@ __global__ __launch_bounds__(kBlock) void k_split(const SplitArgs A, int nb)
     }
 }
 
-// Exclusive sums of v[0 .. n - 1] to out[0 .. n] in one block (short arrays).
-__global__ __launch_bounds__(1024) void k_scan_block(const int32_t *v, int n, int32_t *out)
+// For the host: table[r] = first number of row r (r <= rows + 1: the cells of
+// each depth, then the groups, then the end), after the flags.
+__device__ __forceinline__ void write_table(const int32_t *first, int rows, int nb,
+                                            const int *flag, int32_t *table)
+{
+    const int r = threadIdx.x;
+    if (r < 4) table[r] = flag[r];
+    if (r <= rows + 1) table[4 + r] = first[(int64_t)r * nb];
+}
+
+// Exclusive sums of v[0 .. n - 1] to out[0 .. n] in one block (short arrays),
+// and the table.
+__global__ __launch_bounds__(1024) void k_scan_block(const int32_t *v, int n, int32_t *out,
+                                                     int rows, int nb, const int *flag,
+                                                     int32_t *table)
 {
     typedef hipcub::BlockScan<int, 1024> Scan;
     __shared__ typename Scan::TempStorage tmp;
@@ -455,15 +468,13 @@ __global__ __launch_bounds__(1024) void k_scan_block(const int32_t *v, int n, in
         __syncthreads();
     }
     if (threadIdx.x == 0) out[n] = before;
+    __syncthreads();
+    write_table(out, rows, nb, flag, table);
 }
 
-// For the host: table[r] = first number of row r (r <= rows + 1: the cells of
-// each depth, then the groups, then the end), after the flags.
 __global__ void k_table(const int32_t *first, int rows, int nb, const int *flag, int32_t *table)
 {
-    const int r = threadIdx.x;
-    if (r < 4) table[r] = flag[r];
-    if (r <= rows + 1) table[4 + r] = first[(int64_t)r * nb];
+    write_table(first, rows, nb, flag, table);
 }
 
 // Several systems: before[q rows + L] = starts of depth L (with those of all
@@ -513,8 +524,12 @@ struct CellArgs {
     WLink *wl;
     int32_t *parent;       // or NULL
     int32_t *by_level;     // several systems: cells in the order of all levels
-    int32_t *groups;       // (with a group row)
-    int32_t ngroup0;       // number of the first group start
+    // with a group row: the groups in the layout of the force context, and
+    // each one's cell and root cell (several systems)
+    int32_t *groups, *groot;
+    int64_t *i_off;
+    double *gcx, *gcy, *gcz;
+    int32_t ngroup0, ng;   // number of the first group start, groups
 };
 
 template <int kPer>
@@ -575,12 +590,16 @@ __global__ __launch_bounds__(kBlock) void k_cells(const CellArgs C, int nb)
                 *reinterpret_cast<int2 *>(&C.wl[id].end) = make_int2((int32_t)k, ce);
             }
         }
-        if (k == A.n) break;
+        if (k == A.n) {
+            if (C.groups) C.i_off[C.ng] = k;
+            break;
+        }
         const int ld = info_leaf(info[u]);
         if (d >= ld) continue;
         const int32_t *sh = C.shift ? C.shift + (int64_t)q * A.rows : nullptr;
         auto number = [&](int l) -> int32_t { return before(l) + (sh ? sh[l] : 0); };
         const uint64_t key = A.key[k];
+        const int gd = info_group(info[u]);
         const double *rt = C.roots + 4 * q;
         WCell w;
         w.cx = rt[0];
@@ -606,9 +625,16 @@ __global__ __launch_bounds__(kBlock) void k_cells(const CellArgs C, int nb)
             if (C.parent)
                 C.parent[id] = l == 0 ? -1 : (l - 1 > d ? number(l - 1) : number(l - 1) - 1);
             if (C.by_level) C.by_level[before(l)] = id;
+            if (C.groups && l == gd) {
+                const int32_t g = before(A.rows) - C.ngroup0;
+                C.groups[g] = id;
+                C.i_off[g] = k;
+                C.gcx[g] = w.cx;
+                C.gcy[g] = w.cy;
+                C.gcz[g] = w.cz;
+                if (C.groot) C.groot[g] = q + sh[0];  // its system's root
+            }
         }
-        const int gd = info_group(info[u]);
-        if (C.groups && d < gd) C.groups[before(A.rows) - C.ngroup0] = number(gd);
     }
 }
 
@@ -877,8 +903,9 @@ struct NonNegative {
     __host__ __device__ bool operator()(const int32_t &v) const { return v >= 0; }
 };
 
-// Groups in the layout of the force context, and each group's root cell (the
-// number of its system's root: shift[q rows] + q; several systems only).
+// The same from the groups' cells (groups that k_cells did not find): their
+// layout in the force context, and each group's root cell (the number of its
+// system's root: shift[q rows] + q; several systems only).
 __global__ __launch_bounds__(kBlock) void k_groups_out(const WCell *wc, const WLink *wl,
                                                        const int32_t *groups, int64_t ng,
                                                        int64_t n, const int64_t *sys_off,
@@ -1574,7 +1601,8 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         LAUNCHED("cell starts");
         if (ncount <= 16384) {
             hipLaunchKernelGGL(k_scan_block, dim3(1), dim3(1024), 0, s, S.count, ncount,
-                               B[T_NOFF].as<int32_t>());
+                               B[T_NOFF].as<int32_t>(), rows, nb, flag,
+                               static_cast<int32_t *>(O.host));
             LAUNCHED("scan");
         } else {
             size_t st = 0;
@@ -1585,10 +1613,10 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
             STEP(hipcub::DeviceScan::ExclusiveSum(B[T_SORT].p, st, S.count,
                                                   B[T_NOFF].as<int32_t>(), ncount + 1, s),
                  "scan");
+            hipLaunchKernelGGL(k_table, dim3(1), dim3(64), 0, s, B[T_NOFF].as<int32_t>(), rows,
+                               nb, flag, static_cast<int32_t *>(O.host));
+            LAUNCHED("level table");
         }
-        hipLaunchKernelGGL(k_table, dim3(1), dim3(64), 0, s, B[T_NOFF].as<int32_t>(), rows, nb,
-                           flag, static_cast<int32_t *>(O.host));
-        LAUNCHED("level table");
         STEP(hipStreamSynchronize(s), "sync");
         if (table[0]) {
             code = BHQ_E_NONFINITE;
@@ -1655,11 +1683,25 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         CA.shift = shift;
         CA.by_level = B[T_BYLEVEL].as<int32_t>();
     }
-    STEP(B[T_GROUPS].reserve((size_t)(group_row ? table[4 + rows + 1] - ncell : n) * 4),
-         "allocation");
+    int64_t ng = group_row ? table[4 + rows + 1] - ncell : 0;
+    STEP(B[T_GROUPS].reserve((size_t)(group_row ? ng : n) * 4), "allocation");
     int32_t *groups = B[T_GROUPS].as<int32_t>();
+    auto group_arrays = [&]() -> bool {
+        return hip(O.i_off->reserve((size_t)(ng + 1) * 8), "allocation") &&
+               hip(O.gcx->reserve((size_t)ng * 8), "allocation") &&
+               hip(O.gcy->reserve((size_t)ng * 8), "allocation") &&
+               hip(O.gcz->reserve((size_t)ng * 8), "allocation") &&
+               (nsys == 1 || hip(B[T_GROOT].reserve((size_t)ng * 4), "allocation"));
+    };
     if (group_row) {
+        if (!group_arrays()) return fail();
         CA.groups = groups;
+        CA.groot = nsys > 1 ? B[T_GROOT].as<int32_t>() : nullptr;
+        CA.i_off = O.i_off->as<int64_t>();
+        CA.gcx = O.gcx->as<double>();
+        CA.gcy = O.gcy->as<double>();
+        CA.gcz = O.gcz->as<double>();
+        CA.ng = (int32_t)ng;
     } else {
         STEP(B[T_PARENT].reserve((size_t)ncell * 4), "allocation");
         CA.parent = B[T_PARENT].as<int32_t>();
@@ -1707,9 +1749,8 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         LAUNCHED("cell moments");
     }
 
-    // groups in depth-first order
-    int64_t ng = table[4 + rows + 1] - ncell;
     if (!group_row) {
+        // groups in depth-first order
         STEP(B[T_GSTART].reserve((size_t)n * 4), "allocation");
         STEP(B[T_NSEL].reserve(64), "allocation");
         hipLaunchKernelGGL(k_fill_i32, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s,
@@ -1730,17 +1771,13 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         STEP(hipMemcpyAsync(&ng32, B[T_NSEL].p, 4, hipMemcpyDeviceToHost, s), "copy");
         STEP(hipStreamSynchronize(s), "sync");
         ng = ng32;
+        if (!group_arrays()) return fail();
+        hipLaunchKernelGGL(k_groups_out, dim3(blocks(ng + 1, kBlock)), dim3(kBlock), 0, s, wc, wl,
+                           groups, ng, n, sys_off, nsys, CA.shift, rows, O.i_off->as<int64_t>(),
+                           O.gcx->as<double>(), O.gcy->as<double>(), O.gcz->as<double>(),
+                           nsys > 1 ? B[T_GROOT].as<int32_t>() : nullptr);
+        LAUNCHED("groups");
     }
-    STEP(O.i_off->reserve((size_t)(ng + 1) * 8), "allocation");
-    STEP(O.gcx->reserve((size_t)ng * 8), "allocation");
-    STEP(O.gcy->reserve((size_t)ng * 8), "allocation");
-    STEP(O.gcz->reserve((size_t)ng * 8), "allocation");
-    if (nsys > 1) STEP(B[T_GROOT].reserve((size_t)ng * 4), "allocation");
-    hipLaunchKernelGGL(k_groups_out, dim3(blocks(ng + 1, kBlock)), dim3(kBlock), 0, s, wc, wl,
-                       groups, ng, n, sys_off, nsys, CA.shift, rows, O.i_off->as<int64_t>(),
-                       O.gcx->as<double>(), O.gcy->as<double>(), O.gcz->as<double>(),
-                       nsys > 1 ? B[T_GROOT].as<int32_t>() : nullptr);
-    LAUNCHED("groups");
 
     // walk: count, offsets, fill
     STEP(B[T_JPCNT].reserve((size_t)(ng + 1) * 8), "allocation");
