@@ -8,24 +8,20 @@
 // removed, G = 1) on an n^3 mesh of spacing h = L / n:
 //   1. triangular-shaped-cloud (TSC) assignment of the masses (mesh points
 //      at integer multiples of h): the particles are radix-sorted by their
-//      nearest mesh point, and one thread per mesh point sums, in a fixed
-//      order, the particles of the 27 cells around it (no atomics: the
-//      result is the same bits every run).  A block takes a tile of
-//      2 x 8 x 16 mesh points and first copies the particles of the tile's
-//      cells and their neighbours (720 cells) to LDS, so that each particle
-//      is read from memory about twice instead of 27 times;
+//      nearest mesh point, and a thread per column of mesh points sums, in a
+//      fixed order, the particles of the 27 cells around each (no atomics:
+//      the result is the same bits every run);
 //   2. forward real-to-complex FFT (hipFFT);
 //   3. one thread per complex mode: phi(k) = G(k) rho(k) with
 //      G = -4 pi exp(-k^2 r_s^2) / k^2 / W(k)^2, W = prod_a sinc(k_a h/2)^3
 //      (TSC window, assignment and interpolation), G(0) = 0, and the three
 //      components -i k_a phi(k) (zero on the Nyquist planes);
-//   4. four inverse complex-to-real FFTs (potential and acceleration);
-//   5. the four meshes are interleaved into one (a_x, a_y, a_z, phi) record
-//      per mesh point, and one thread per particle, in the sorted order,
-//      interpolates them with the same TSC weights and writes its result
-//      at the particle's input position.  A block takes the particles of a
-//      tile of 2 x 8 x 16 cells, with the records of the tile's mesh points
-//      and their neighbours in LDS.
+//   4. four inverse complex-to-real FFTs (acceleration and potential);
+//   5. one thread per particle, in the sorted order, interpolates the four
+//      meshes with the same TSC weights and writes its result at the
+//      particle's input position.  A block takes the particles of a tile of
+//      2 x 8 x 16 cells, with the fields at the tile's mesh points and their
+//      neighbours in LDS.
 // All FP64.
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
@@ -101,14 +97,13 @@ __device__ __forceinline__ int pmod(int i, int n)
     return r < 0 ? r + n : r;
 }
 
-// Tiles of the mesh (points for the assignment, cells for the
-// interpolation): kTX x kTY x kTZ per block of kBlock threads, z fastest;
-// with their neighbours, kHX x kHY x kHZ.
+// Tiles of the mesh (cells of the interpolation): kTX x kTY x kTZ per block
+// of kBlock threads, z fastest; with their neighbours, kHX x kHY x kHZ.
 constexpr int kTX = 2, kTY = 8, kTZ = 16;
 constexpr int kHX = kTX + 2, kHY = kTY + 2, kHZ = kTZ + 2;
 constexpr int kHalo = kHX * kHY * kHZ;
-constexpr int kGatherCap = 896;  // particles of a tile's neighbourhood held in LDS
-static_assert(kTX * kTY * kTZ == kBlock, "one tile point per thread");
+constexpr int kRows = kTX * kTY;
+static_assert(kRows <= 64, "a wave scans the rows");
 
 inline unsigned ntiles(int n)
 {
@@ -145,138 +140,119 @@ __global__ __launch_bounds__(kBlock) void k_cell_keys(int64_t np, const double *
     idx[p] = (int32_t)p;
 }
 
-// Sorted particle records (x, y, z, m) and each cell's range [start, end).
-__global__ __launch_bounds__(kBlock) void k_sorted(int64_t np, const uint32_t *key,
+// Sorted particle records (x, y, z, m) and first[c] = first sorted particle of
+// cell c or later (first[n3] = np), written by the particle at whose key the
+// range of cells ends.  Long ranges of empty cells are written by the whole
+// wave.
+__global__ __launch_bounds__(kBlock) void k_sorted(int64_t np, int64_t n3, const uint32_t *key,
                                                    const int32_t *idx, const double *x,
                                                    const double *m, double4 *xs,
-                                                   int32_t *start, int32_t *end)
+                                                   int32_t *first)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= np) return;
-    const int64_t p = idx[k];
-    xs[k] = make_double4(x[3 * p], x[3 * p + 1], x[3 * p + 2], m[p]);
-    const uint32_t c = key[k];
-    if (k == 0 || key[k - 1] != c) start[c] = (int32_t)k;
-    if (k == np - 1 || key[k + 1] != c) end[c] = (int32_t)(k + 1);
-}
-
-// TSC weight for offset o (-1, 0, +1) with o known only at run time; the
-// same operations as tsc_w (negating d is exact).
-__device__ __forceinline__ double tsc_w_var(double d, int o)
-{
-    const double s = o < 0 ? -d : d;
-    return o == 0 ? 0.75 - d * d : 0.5 * (0.5 + s) * (0.5 + s);
-}
-
-// Sum over the neighbourhood of tile point (tx, ty, tz), row by row: for
-// each (ox, oy) the cells at z offsets +1, 0, -1 (neighbourhood z indices
-// tz .. tz + 2), each cell's particles in the sorted order.
-// LDS: the three cells' particles are contiguous in sp, as (offsets from
-// the nearest mesh point, m), with their neighbourhood z index in sz, so
-// that a row is one loop.  Memory: cell by cell from xs, the same order.
-__device__ __forceinline__ void gather_point_lds(int tx, int ty, int tz, const double4 *sp,
-                                                 const uint8_t *sz, const int32_t *first,
-                                                 const int32_t *count, double &sum)
-{
-#pragma unroll
-    for (int ox = -1; ox <= 1; ++ox) {
-#pragma unroll
-        for (int oy = -1; oy <= 1; ++oy) {
-            const int h0 = ((tx + 1 - ox) * kHY + (ty + 1 - oy)) * kHZ + tz;
-            const int32_t k0 = first[h0], k1 = first[h0 + 2] + count[h0 + 2];
-            for (int32_t k = k0; k < k1; ++k) {
-                const double4 r = sp[k];
-                const int oz = tz + 1 - sz[k];
-                sum += r.w * tsc_w(r.x, ox) * tsc_w(r.y, oy) * tsc_w_var(r.z, oz);
-            }
-        }
+    int64_t lo = 0, hi = -1;  // cells lo .. hi begin at k
+    if (k <= np) {
+        lo = k > 0 ? (int64_t)key[k - 1] + 1 : 0;
+        hi = k < np ? (int64_t)key[k] : n3;
+    }
+    if (k < np) {
+        const int64_t p = idx[k];
+        xs[k] = make_double4(x[3 * p], x[3 * p + 1], x[3 * p + 2], m[p]);
+    }
+    constexpr int64_t kOwn = 8;
+    const bool small = hi - lo < kOwn;
+    if (small)
+        for (int64_t c = lo; c <= hi; ++c) first[c] = (int32_t)k;
+    uint64_t left = __ballot(!small);
+    while (left) {
+        const int l = __builtin_ctzll(left);
+        left &= left - 1;
+        const int64_t a = __shfl(lo, l), b = __shfl(hi, l), v = __shfl(k, l);
+        for (int64_t c = a + (threadIdx.x & 63); c <= b; c += 64) first[c] = (int32_t)v;
     }
 }
 
-__device__ __forceinline__ void gather_point_mem(int tx, int ty, int tz, double ih,
-                                                 const double4 *xs, const int32_t *start,
-                                                 const int32_t *count, double &sum)
+// rho at a mesh point: the particles whose nearest point is one of the 27
+// around it, each with its TSC weight, in a fixed order: plane by plane in
+// x, row by row in y, and the three z-cells of a row (whose particles are
+// contiguous) in the sorted order.
+// A block takes kRY x kRZ columns of mesh points, a thread each, and `len` of
+// their points: it goes over the planes of cells, keeping the sums of the
+// three points that a plane's particles reach, so that a particle is visited
+// once for all three.  A plane's particles (of the tile's cells and their
+// neighbours, 324 cells) go to LDS with their weights, computed once per
+// plane, in parts of kPlaneCap.  A thread per mesh point that visited a
+// particle and formed its weights for each of the 27 took 1.18 ms on 2^24
+// particles and 256^3 points and 0.156 on 2,000,003 and 128^3 (VALU); this
+// takes 0.60 and 0.079.
+constexpr int kRY = 16, kRZ = 16;
+constexpr int kPY = kRY + 2, kPZ = kRZ + 2;
+constexpr int kPlane = kPY * kPZ;
+constexpr int kPlaneCap = 448;
+static_assert(kRY * kRZ == kBlock, "a column per thread");
+
+inline unsigned rho_blocks(int n, int len)
 {
-#pragma unroll
-    for (int ox = -1; ox <= 1; ++ox) {
-#pragma unroll
-        for (int oy = -1; oy <= 1; ++oy) {
-#pragma unroll
-            for (int oz = 1; oz >= -1; --oz) {
-                const int h = ((tx + 1 - ox) * kHY + (ty + 1 - oy)) * kHZ + (tz + 1 - oz);
-                const double4 *p = xs + start[h];
-                const int32_t cnt = count[h];
-                for (int32_t k = 0; k < cnt; ++k) {
-                    const double4 r = p[k];
-                    double i0;
-                    const double dx = tsc_d(r.x, ih, i0), dy = tsc_d(r.y, ih, i0),
-                                 dz = tsc_d(r.z, ih, i0);
-                    sum += r.w * tsc_w(dx, ox) * tsc_w(dy, oy) * tsc_w_var(dz, oz);
-                }
-            }
-        }
-    }
+    return (unsigned)(((n + kRY - 1) / kRY) * ((n + kRZ - 1) / kRZ) * ((n + len - 1) / len));
 }
 
-// rho at mesh point q: the particles whose nearest point is q - o,
-// o in {-1, 0, 1}^3, each with its TSC weight for offset o, summed in a
-// fixed order: o_x, then o_y, then o_z = +1, 0, -1, and within a cell the
-// sorted order.
-// One thread per mesh point of the block's tile.  The particles of the
-// tile's neighbourhood go to LDS first (cell by cell, in neighbourhood
-// order, with their offsets from the nearest mesh point); a neighbourhood
-// with more than kGatherCap particles is read from memory instead, in the
-// same order.
-__global__ __launch_bounds__(kBlock) void k_gather_rho(int n, double ih, const double4 *xs,
-                                                       const int32_t *start,
-                                                       const int32_t *end, double *rho)
+__global__ __launch_bounds__(kBlock) void k_rho(int n, double ih, int len, const double4 *xs,
+                                                const int32_t *first, double *rho)
 {
     typedef hipcub::BlockScan<int, kBlock> Scan;
-    __shared__ double4 sp[kGatherCap];
-    __shared__ uint8_t sz[kGatherCap];  // neighbourhood z index (< kHZ) of each particle
-    __shared__ int32_t sfirst[kHalo], scount[kHalo], sstart[kHalo];
+    __shared__ double mwx[3][kPlaneCap], wy[3][kPlaneCap], wz[3][kPlaneCap];
+    __shared__ int32_t sfirst[kPlane + 1], sstart[kPlane];
     __shared__ typename Scan::TempStorage scan_tmp;
-    __shared__ int stotal;
-    int x0, y0, z0;
-    tile_origin(n, x0, y0, z0);
-    const int t = threadIdx.x;
-    // counts of the neighbourhood's cells; thread t takes entries 3t .. 3t+2
-    constexpr int kPer = (kHalo + kBlock - 1) / kBlock;
-    int part = 0;
-    for (int u = 0; u < kPer; ++u) {
-        const int h = kPer * t + u;
-        if (h < kHalo) {
-            const int64_t c = halo_point(h, n, x0, y0, z0);
-            const int32_t s0 = start[c], c0 = end[c] - s0;
-            sstart[h] = s0;
-            scount[h] = c0;
-            part += c0;
-        }
-    }
-    int excl = 0, total = 0;
-    Scan(scan_tmp).ExclusiveSum(part, excl, total);
-    for (int u = 0; u < kPer; ++u) {
-        const int h = kPer * t + u;
-        if (h < kHalo) {
-            sfirst[h] = excl;
-            excl += scount[h];
-        }
-    }
-    if (t == 0) stotal = total;
-    __syncthreads();
-    const int ntot = stotal;
-    const bool local = ntot <= kGatherCap;
-    if (local) {
-        // entry j of the LDS copy belongs to the last cell h with
-        // sfirst[h] <= j (cells before it that are empty share its first
-        // entry; cells after it start beyond j); the threads' loads are
-        // independent, so they are all in flight at once
-        constexpr int kIter = (kGatherCap + kBlock - 1) / kBlock;
+    const int nz = (n + kRZ - 1) / kRZ, ny = (n + kRY - 1) / kRY;
+    int b = (int)blockIdx.x;
+    const int z0 = (b % nz) * kRZ;
+    b /= nz;
+    const int y0 = (b % ny) * kRY, x0 = (b / ny) * len;
+    const int t = threadIdx.x, tz = t % kRZ, ty = t / kRZ;
+    const int xe = x0 + len < n ? x0 + len : n;
+    constexpr int kPer = (kPlane + kBlock - 1) / kBlock;
+    // mesh row and column of the cells that this thread counts (row < 0: none;
+    // on a mesh smaller than the tile those around its points are enough)
+    int row[kPer], col[kPer];
 #pragma unroll
-        for (int u = 0; u < kIter; ++u) {
-            const int j = t + u * kBlock;
-            if (j < ntot) {
-                int lo = 0, hi = kHalo;  // sfirst[lo] <= j; hi: past the answer
+    for (int u = 0; u < kPer; ++u) {
+        const int h = kPer * t + u, hy = h / kPZ, hz = h % kPZ;
+        const bool use = h < kPlane && hy < n + 2 && hz < n + 2;
+        row[u] = use ? pmod(y0 - 1 + hy, n) : -1;
+        col[u] = use ? pmod(z0 - 1 + hz, n) : 0;
+    }
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;  // points px - 1, px, px + 1
+    for (int px = x0 - 1; px <= xe; ++px) {
+        const int64_t plane = (int64_t)pmod(px, n) * n;
+        int cnt[kPer], part = 0;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int h = kPer * t + u;
+            cnt[u] = 0;
+            if (row[u] >= 0) {
+                const int64_t c = (plane + row[u]) * n + col[u];
+                const int32_t f = first[c];
+                cnt[u] = first[c + 1] - f;
+                sstart[h] = f;
+            }
+            part += cnt[u];
+        }
+        int at = 0, total = 0;
+        Scan(scan_tmp).ExclusiveSum(part, at, total);
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int h = kPer * t + u;
+            if (h < kPlane) sfirst[h] = at;
+            at += cnt[u];
+        }
+        if (t == 0) sfirst[kPlane] = total;
+        __syncthreads();
+        for (int c0 = 0; c0 < total; c0 += kPlaneCap) {
+            const int c1 = total - c0 < kPlaneCap ? total : c0 + kPlaneCap;
+            if (c0 > 0) __syncthreads();
+            for (int j = c0 + t; j < c1; j += kBlock) {
+                // the last cell whose first entry is j or before
+                int lo = 0, hi = kPlane;
                 while (hi - lo > 1) {
                     const int mid = (lo + hi) >> 1;
                     if (sfirst[mid] <= j)
@@ -288,21 +264,39 @@ __global__ __launch_bounds__(kBlock) void k_gather_rho(int n, double ih, const d
                 double i0;
                 const double dx = tsc_d(r.x, ih, i0), dy = tsc_d(r.y, ih, i0),
                              dz = tsc_d(r.z, ih, i0);
-                sp[j] = make_double4(dx, dy, dz, r.w);
-                sz[j] = (uint8_t)(lo % kHZ);
+#pragma unroll
+                for (int o = -1; o <= 1; ++o) {
+                    mwx[o + 1][j - c0] = r.w * tsc_w(dx, o);
+                    wy[o + 1][j - c0] = tsc_w(dy, o);
+                    wz[o + 1][j - c0] = tsc_w(dz, o);
+                }
+            }
+            __syncthreads();
+            // rows of cells below, at and above the thread's points in y are at
+            // offsets +1, 0, -1 from their particles; in z the same
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const int h0 = (ty + q) * kPZ + tz;
+                const int f0 = sfirst[h0], f1 = sfirst[h0 + 1], f2 = sfirst[h0 + 2],
+                          f3 = sfirst[h0 + 3];
+                const int ka = f0 > c0 ? f0 : c0, kb = f3 < c1 ? f3 : c1;
+                for (int k = ka; k < kb; ++k) {
+                    const int o = 2 - (k >= f1 ? 1 : 0) - (k >= f2 ? 1 : 0);
+                    const int j = k - c0;
+                    const double w = wy[2 - q][j] * wz[o][j];
+                    s0 = fma(mwx[0][j], w, s0);
+                    s1 = fma(mwx[1][j], w, s1);
+                    s2 = fma(mwx[2][j], w, s2);
+                }
             }
         }
+        const int qy = y0 + ty, qz = z0 + tz;
+        if (px > x0 && qy < n && qz < n) rho[((int64_t)(px - 1) * n + qy) * n + qz] = s0;
+        s0 = s1;
+        s1 = s2;
+        s2 = 0.0;
+        __syncthreads();
     }
-    __syncthreads();
-    const int tz = t % kTZ, ty = (t / kTZ) % kTY, tx = t / (kTZ * kTY);
-    const int qx = x0 + tx, qy = y0 + ty, qz = z0 + tz;
-    if (qx >= n || qy >= n || qz >= n) return;
-    double sum = 0.0;
-    if (local)
-        gather_point_lds(tx, ty, tz, sp, sz, sfirst, scount, sum);
-    else
-        gather_point_mem(tx, ty, tz, ih, xs, sstart, scount, sum);
-    rho[((int64_t)qx * n + qy) * n + qz] = sum;
 }
 
 __device__ __forceinline__ double sinc_half(double kh)
@@ -312,15 +306,14 @@ __device__ __forceinline__ double sinc_half(double kh)
     return t == 0.0 ? 1.0 : sin(t) / t;
 }
 
-// rk: n x n x (n/2+1) complex; writes phik and the three gradient arrays.
+// rk: n x n x (n/2+1) complex; writes the three gradient arrays and phi, nc
+// apart.
 __global__ __launch_bounds__(kBlock) void k_green(const hipfftDoubleComplex *rk, int n,
                                                   double L, double rs, double scale,
-                                                  hipfftDoubleComplex *phik,
-                                                  hipfftDoubleComplex *axk,
-                                                  hipfftDoubleComplex *ayk,
-                                                  hipfftDoubleComplex *azk)
+                                                  hipfftDoubleComplex *fk)
 {
     const int nz = n / 2 + 1;
+    const int64_t nc = (int64_t)n * n * nz;
     const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (e >= (int64_t)n * n * nz) return;
     const int iz = (int)(e % nz);
@@ -340,23 +333,28 @@ __global__ __launch_bounds__(kBlock) void k_green(const hipfftDoubleComplex *rk,
     }
     const hipfftDoubleComplex r = rk[e];
     const double pr = g * r.x, pi = g * r.y;
-    phik[e] = make_hipDoubleComplex(pr, pi);
+    fk[3 * nc + e] = make_hipDoubleComplex(pr, pi);
     // -i k phi = (k phi_i, -k phi_r)
     const double gx = ix == n / 2 ? 0.0 : kxs;
     const double gy = iy == n / 2 ? 0.0 : kys;
     const double gz = iz == n / 2 ? 0.0 : kz;
-    axk[e] = make_hipDoubleComplex(gx * pi, -gx * pr);
-    ayk[e] = make_hipDoubleComplex(gy * pi, -gy * pr);
-    azk[e] = make_hipDoubleComplex(gz * pi, -gz * pr);
+    fk[e] = make_hipDoubleComplex(gx * pi, -gx * pr);
+    fk[nc + e] = make_hipDoubleComplex(gy * pi, -gy * pr);
+    fk[2 * nc + e] = make_hipDoubleComplex(gz * pi, -gz * pr);
 }
 
-__global__ __launch_bounds__(kBlock) void k_interleave(int64_t n3, const double *axm,
-                                                       const double *aym, const double *azm,
-                                                       const double *phim, double4 *m4)
+// TSC weight for offset o (-1, 0, +1) with o known only at run time; the
+// same operations as tsc_w (negating d is exact).
+__device__ __forceinline__ double tsc_w_var(double d, int o)
 {
-    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (q >= n3) return;
-    m4[q] = make_double4(axm[q], aym[q], azm[q], phim[q]);
+    const double s = o < 0 ? -d : d;
+    return o == 0 ? 0.75 - d * d : 0.5 * (0.5 + s) * (0.5 + s);
+}
+
+__device__ __forceinline__ double tsc_offset(double x, double ih)
+{
+    double i0;
+    return tsc_d(x, ih, i0);
 }
 
 // One term of the 27-point interpolation, in the order of the points.
@@ -364,67 +362,79 @@ __device__ __forceinline__ void interp_add(const Tsc &w, int a0, int b, int c, c
                                            double *s4)
 {
     const double wt = w.w[a0][0] * w.w[b][1] * w.w[c][2];
-    s4[0] += wt * v.x;
-    s4[1] += wt * v.y;
-    s4[2] += wt * v.z;
-    s4[3] += wt * v.w;
+    s4[0] = fma(wt, v.x, s4[0]);
+    s4[1] = fma(wt, v.y, s4[1]);
+    s4[2] = fma(wt, v.z, s4[2]);
+    s4[3] = fma(wt, v.w, s4[3]);
 }
 
 // The particles of the block's tile of cells (nearest mesh point in the
 // tile; a row of the tile along z is a contiguous range of the sorted
-// order): 27-point TSC interpolation of the interleaved mesh, whose records
-// around the tile are in LDS; each result goes to the particle's input
-// index.
+// order): 27-point TSC interpolation of the four meshes (a_x, a_y, a_z, phi,
+// n3 apart), whose values around the tile are in LDS as one record per point;
+// each result goes to the particle's input index.
+// A block is one chain of loads (rows, particles, fields): each wave finds
+// the rows' ranges itself, by shuffles, and the particles are loaded before
+// the fields, so that only the fields are waited for together.  With ranges
+// from LDS atomics, a serial sum of them and a separate pass that interleaved
+// the meshes this took 1.17 ms on 2^24 particles and 256^3 points, now 0.99
+// (0.157 and 0.138 on 2,000,003 unsorted particles and 128^3).  What is left
+// are the results' scattered stores.
 __global__ __launch_bounds__(kBlock) void k_interp(int n, const double4 *xs, const int32_t *idx,
-                                                   const int32_t *start, const int32_t *end,
-                                                   double ih, const double4 *m4, double *a,
+                                                   const int32_t *first, double ih,
+                                                   const double *mesh, int64_t n3, double *a,
                                                    double *pot, int accumulate)
 {
-    constexpr int kRows = kTX * kTY;
     __shared__ double4 sm[kHalo];
-    __shared__ int32_t rlo[kRows], rhi[kRows], rpre[kRows + 1];
     int x0, y0, z0;
     tile_origin(n, x0, y0, z0);
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int u = 0; u < (kHalo + kBlock - 1) / kBlock; ++u) {
-        const int h = t + u * kBlock;
-        if (h < kHalo) sm[h] = m4[halo_point(h, n, x0, y0, z0)];
+    const int t = threadIdx.x, lane = t & 63;
+    // lane r: range and inclusive count of row r's particles
+    int32_t lo = 0, incl = 0;
+    {
+        const int cx = x0 + lane / kTY, cy = y0 + lane % kTY;
+        if (lane < kRows && cx < n && cy < n) {
+            const int64_t c = ((int64_t)cx * n + cy) * n + z0;
+            lo = first[c];
+            incl = first[c + (n - z0 < kTZ ? n - z0 : kTZ)] - lo;
+        }
+        for (int h = 1; h < kRows; h *= 2) {
+            const int v = __shfl_up(incl, h);
+            if (lane >= h) incl += v;
+        }
     }
-    if (t < kRows) {
-        rlo[t] = 0x7fffffff;
-        rhi[t] = 0;
+    const int total = __shfl(incl, kRows - 1);
+    // sorted index of the tile's particle j
+    auto sorted_index = [&](int j) -> int64_t {
+        int r = 0;  // rows that end at or before j
+        for (int h = kRows / 2; h > 0; h /= 2)
+            if (__shfl(incl, r + h - 1) <= j) r += h;
+        const int before = __shfl(incl, r > 0 ? r - 1 : 0);
+        return (int64_t)__shfl(lo, r) + (j - (r > 0 ? before : 0));
+    };
+    double4 rec = make_double4(0.0, 0.0, 0.0, 0.0);
+    int64_t p = 0;
+    {
+        const int64_t k = sorted_index(t < total ? t : 0);
+        if (t < total) {
+            rec = xs[k];
+            p = idx[k];
+        }
+    }
+    for (int h = t; h < kHalo; h += kBlock) {
+        const int64_t q = halo_point(h, n, x0, y0, z0);
+        sm[h] = make_double4(mesh[q], mesh[n3 + q], mesh[2 * n3 + q], mesh[3 * n3 + q]);
     }
     __syncthreads();
-    {
-        // row r = (tx, ty): its particles are those of its non-empty cells
-        const int tz = t % kTZ, ty = (t / kTZ) % kTY, tx = t / (kTZ * kTY);
-        const int cx = x0 + tx, cy = y0 + ty, cz = z0 + tz;
-        if (cx < n && cy < n && cz < n) {
-            const int64_t c = ((int64_t)cx * n + cy) * n + cz;
-            const int32_t s0 = start[c], e0 = end[c];
-            if (e0 > s0) {
-                atomicMin(&rlo[tx * kTY + ty], s0);
-                atomicMax(&rhi[tx * kTY + ty], e0);
+    for (int j = t; j - lane < total; j += kBlock) {
+        if (j >= kBlock) {
+            const int64_t k = sorted_index(j < total ? j : 0);
+            if (j < total) {
+                rec = xs[k];
+                p = idx[k];
             }
         }
-    }
-    __syncthreads();
-    if (t == 0) {
-        int acc = 0;
-        for (int r = 0; r < kRows; ++r) {
-            rpre[r] = acc;
-            acc += rhi[r] > rlo[r] ? rhi[r] - rlo[r] : 0;
-        }
-        rpre[kRows] = acc;
-    }
-    __syncthreads();
-    const int total = rpre[kRows];
-    for (int j = t; j < total; j += kBlock) {
-        int r = 0;
-        while (rpre[r + 1] <= j) ++r;
-        const int64_t k = rlo[r] + (j - rpre[r]);
-        const double4 rec = xs[k];
+        if (j >= total) break;
         const double xp[3] = {rec.x, rec.y, rec.z};
         const Tsc w = tsc(xp, ih, n);
         // the particle's cell is in the tile (its sort key was computed by
@@ -444,18 +454,18 @@ __global__ __launch_bounds__(kBlock) void k_interp(int n, const double4 *xs, con
                         interp_add(w, a0, b, c,
                                    sm[((hx0 + a0) * kHY + (hy0 + b)) * kHZ + (hz0 + c)], s4);
         } else {
-#pragma unroll
             for (int a0 = 0; a0 < 3; ++a0)
-#pragma unroll
                 for (int b = 0; b < 3; ++b)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c)
-                        interp_add(w, a0, b, c,
-                                   m4[((int64_t)wrap(w.i[0] + a0 - 1, n) * n +
-                                       wrap(w.i[1] + b - 1, n)) * n + wrap(w.i[2] + c - 1, n)],
-                                   s4);
+                    for (int c = 0; c < 3; ++c) {
+                        const int64_t q = ((int64_t)wrap(w.i[0] + a0 - 1, n) * n +
+                                           wrap(w.i[1] + b - 1, n)) * n +
+                                          wrap(w.i[2] + c - 1, n);
+                        const double wt = tsc_w_var(tsc_offset(xp[0], ih), a0 - 1) *
+                                          tsc_w_var(tsc_offset(xp[1], ih), b - 1) *
+                                          tsc_w_var(tsc_offset(xp[2], ih), c - 1);
+                        for (int f = 0; f < 4; ++f) s4[f] = fma(wt, mesh[f * n3 + q], s4[f]);
+                    }
         }
-        const int64_t p = idx[k];
         if (accumulate) {
             a[3 * p] += s4[0];
             a[3 * p + 1] += s4[1];
@@ -472,15 +482,19 @@ __global__ __launch_bounds__(kBlock) void k_interp(int n, const double4 *xs, con
 
 }  // namespace
 
+// Largest mesh whose inverse transforms are batched.
+constexpr int kBatchMesh = 128;
+
 struct bhq_pm {
     int device = 0;
     int n = 0;
     double box = 0.0, rs = 0.0;
     std::string err;
-    bhq::DevArray rho, rk, phik, axk, ayk, azk, phim, axm, aym, azm, m4;
+    bhq::DevArray rho, rk, fk, mesh;  // fk, mesh: four fields each
     // per-particle sorting (grown to the largest n seen)
-    bhq::DevArray key, key2, idx, idx2, xs, sort_tmp, start, end;
+    bhq::DevArray key, key2, idx, idx2, xs, sort_tmp, first;
     hipfftHandle fwd = 0, inv = 0;
+    int batch = 1;  // fields per inverse transform
     bool have_fwd = false, have_inv = false;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool launched = false;
@@ -505,9 +519,8 @@ void pm_free(bhq_pm *p)
 {
     if (p->have_fwd) (void)hipfftDestroy(p->fwd);
     if (p->have_inv) (void)hipfftDestroy(p->inv);
-    for (bhq::DevArray *a : {&p->rho, &p->rk, &p->phik, &p->axk, &p->ayk, &p->azk, &p->phim,
-                             &p->axm, &p->aym, &p->azm, &p->m4, &p->key, &p->key2, &p->idx,
-                             &p->idx2, &p->xs, &p->sort_tmp, &p->start, &p->end})
+    for (bhq::DevArray *a : {&p->rho, &p->rk, &p->fk, &p->mesh, &p->key, &p->key2, &p->idx,
+                             &p->idx2, &p->xs, &p->sort_tmp, &p->first})
         a->release();
     if (p->ev0) (void)hipEventDestroy(p->ev0);
     if (p->ev1) (void)hipEventDestroy(p->ev1);
@@ -563,13 +576,11 @@ int bhq_pm_create(bhq_pm **out, int device, int nmesh, double box, double rs)
     const size_t n3 = (size_t)nmesh * nmesh * nmesh;
     const size_t nc = (size_t)nmesh * nmesh * (nmesh / 2 + 1);
     hipError_t e = hipSuccess;
-    for (bhq::DevArray *a : {&p->rho, &p->phim, &p->axm, &p->aym, &p->azm})
-        if (e == hipSuccess) e = a->reserve(n3 * sizeof(double));
-    for (bhq::DevArray *a : {&p->rk, &p->phik, &p->axk, &p->ayk, &p->azk})
-        if (e == hipSuccess) e = a->reserve(nc * sizeof(hipfftDoubleComplex));
-    if (e == hipSuccess) e = p->m4.reserve(n3 * sizeof(double4));
-    if (e == hipSuccess) e = p->start.reserve(n3 * sizeof(int32_t));
-    if (e == hipSuccess) e = p->end.reserve(n3 * sizeof(int32_t));
+    e = p->rho.reserve(n3 * sizeof(double));
+    if (e == hipSuccess) e = p->rk.reserve(nc * sizeof(hipfftDoubleComplex));
+    if (e == hipSuccess) e = p->fk.reserve(4 * nc * sizeof(hipfftDoubleComplex));
+    if (e == hipSuccess) e = p->mesh.reserve(4 * n3 * sizeof(double));
+    if (e == hipSuccess) e = p->first.reserve((n3 + 1) * sizeof(int32_t));
     if (e == hipSuccess) e = hipEventCreate(&p->ev0);
     if (e == hipSuccess) e = hipEventCreate(&p->ev1);
     if (e != hipSuccess) {
@@ -584,7 +595,14 @@ int bhq_pm_create(bhq_pm **out, int device, int nmesh, double box, double rs)
         return BHQ_E_HIP;
     }
     p->have_fwd = true;
-    if (hipfftPlan3d(&p->inv, nmesh, nmesh, nmesh, HIPFFT_Z2D) != HIPFFT_SUCCESS) {
+    // The four inverse transforms go in one batch where their fields (67 MB
+    // at 128^3) stay in the caches between its passes: 145 us one after
+    // another at 128^3, 93 together, 53 and 17 at 60^3.  Larger ones run one
+    // after another.
+    p->batch = nmesh <= kBatchMesh ? 4 : 1;
+    int dims[3] = {nmesh, nmesh, nmesh};
+    if (hipfftPlanMany(&p->inv, 3, dims, nullptr, 1, 0, nullptr, 1, 0, HIPFFT_Z2D, p->batch) !=
+        HIPFFT_SUCCESS) {
         g_pm_create_error = "bhq_pm_create: hipFFT inverse plan failed";
         pm_free(p);
         return BHQ_E_HIP;
@@ -657,16 +675,16 @@ int bhq_pm_compute(bhq_pm *pm, int64_t np, const double *x, const double *m, dou
                                                   pm->idx2.as<int32_t>(), (int)np, 0, bits, s),
                "sort"))
         return BHQ_E_HIP;
-    if (!hipok(hipMemsetAsync(pm->start.p, 0, n3 * sizeof(int32_t), s), "memset") ||
-        !hipok(hipMemsetAsync(pm->end.p, 0, n3 * sizeof(int32_t), s), "memset"))
-        return BHQ_E_HIP;
-    hipLaunchKernelGGL(k_sorted, dim3(nblocks(np)), dim3(kBlock), 0, s, np,
+    hipLaunchKernelGGL(k_sorted, dim3(nblocks(np + 1)), dim3(kBlock), 0, s, np, (int64_t)n3,
                        pm->key2.as<uint32_t>(), pm->idx2.as<int32_t>(), x, m,
-                       pm->xs.as<double4>(), pm->start.as<int32_t>(), pm->end.as<int32_t>());
+                       pm->xs.as<double4>(), pm->first.as<int32_t>());
     if (!hipok(hipGetLastError(), "sorted records")) return BHQ_E_HIP;
-    hipLaunchKernelGGL(k_gather_rho, dim3(ntiles(n)), dim3(kBlock), 0, s, n, ih,
-                       pm->xs.as<double4>(), pm->start.as<int32_t>(), pm->end.as<int32_t>(),
-                       pm->rho.as<double>());
+    // points per column and block: eight, or fewer where the blocks would not
+    // fill the chip (each costs two planes more than it has points)
+    int len = 8;
+    while (len > 2 && rho_blocks(n, len) < 1024) len /= 2;
+    hipLaunchKernelGGL(k_rho, dim3(rho_blocks(n, len)), dim3(kBlock), 0, s, n, ih, len,
+                       pm->xs.as<double4>(), pm->first.as<int32_t>(), pm->rho.as<double>());
     if (!hipok(hipGetLastError(), "assignment")) return BHQ_E_HIP;
     if (!fftok(hipfftSetStream(pm->fwd, s), "set stream") ||
         !fftok(hipfftSetStream(pm->inv, s), "set stream"))
@@ -677,23 +695,16 @@ int bhq_pm_compute(bhq_pm *pm, int64_t np, const double *x, const double *m, dou
         return BHQ_E_HIP;
     hipLaunchKernelGGL(k_green, dim3(nblocks(nc)), dim3(kBlock), 0, s,
                        pm->rk.as<hipfftDoubleComplex>(), n, pm->box, pm->rs, scale,
-                       pm->phik.as<hipfftDoubleComplex>(), pm->axk.as<hipfftDoubleComplex>(),
-                       pm->ayk.as<hipfftDoubleComplex>(), pm->azk.as<hipfftDoubleComplex>());
+                       pm->fk.as<hipfftDoubleComplex>());
     if (!hipok(hipGetLastError(), "green function")) return BHQ_E_HIP;
-    const struct { bhq::DevArray *in, *out; } inv[] = {
-        {&pm->phik, &pm->phim}, {&pm->axk, &pm->axm}, {&pm->ayk, &pm->aym}, {&pm->azk, &pm->azm}};
-    for (auto &t : inv)
-        if (!fftok(hipfftExecZ2D(pm->inv, t.in->as<hipfftDoubleComplex>(),
-                                 t.out->as<hipfftDoubleReal>()),
+    for (int f = 0; f < 4; f += pm->batch)
+        if (!fftok(hipfftExecZ2D(pm->inv, pm->fk.as<hipfftDoubleComplex>() + f * nc,
+                                 pm->mesh.as<hipfftDoubleReal>() + f * (int64_t)n3),
                    "inverse FFT"))
             return BHQ_E_HIP;
-    hipLaunchKernelGGL(k_interleave, dim3(nblocks((int64_t)n3)), dim3(kBlock), 0, s,
-                       (int64_t)n3, pm->axm.as<double>(), pm->aym.as<double>(),
-                       pm->azm.as<double>(), pm->phim.as<double>(), pm->m4.as<double4>());
-    if (!hipok(hipGetLastError(), "interleave")) return BHQ_E_HIP;
     hipLaunchKernelGGL(k_interp, dim3(ntiles(n)), dim3(kBlock), 0, s, n, pm->xs.as<double4>(),
-                       pm->idx2.as<int32_t>(), pm->start.as<int32_t>(), pm->end.as<int32_t>(), ih,
-                       pm->m4.as<double4>(), a, pot, accumulate);
+                       pm->idx2.as<int32_t>(), pm->first.as<int32_t>(), ih,
+                       pm->mesh.as<double>(), (int64_t)n3, a, pot, accumulate);
     if (!hipok(hipGetLastError(), "interpolation")) return BHQ_E_HIP;
     if (!hipok(hipEventRecord(pm->ev1, s), "event")) return BHQ_E_HIP;
     pm->launched = true;
