@@ -16,19 +16,35 @@ constexpr int kEnergyBlocks = 512;
 
 inline unsigned blocks(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-// a_in[k] (group order) -> a_out[order[k]] (input order).
+// a_in[k] (group order) -> a_out[order[k]] (input order).  Bound by the lines
+// that the scattered stores touch: a lane that stores its particle's three
+// words touches its line in three instructions, so the block turns its
+// results over in LDS and neighbouring lanes store a particle's words.  On
+// 2^22 particles in random input order 357 us became 217 (2^20: 55 and 33),
+// on 2^24 in nearly their input's order 225 became 208.
 __global__ __launch_bounds__(kBlock) void k_scatter(const int32_t *order, int64_t n,
                                                     const double *ax, const double *ay,
                                                     const double *az, const double *pot,
                                                     double *a_out, double *pot_out)
 {
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= n) return;
-    const int64_t p = order ? order[k] : k;
-    a_out[3 * p] = ax[k];
-    a_out[3 * p + 1] = ay[k];
-    a_out[3 * p + 2] = az[k];
-    if (pot_out) pot_out[p] = pot[k];
+    __shared__ double s_a[3 * kBlock];
+    __shared__ int64_t s_p[kBlock];
+    const int t = threadIdx.x;
+    const int64_t k0 = (int64_t)blockIdx.x * kBlock, k = k0 + t;
+    if (k < n) {
+        const int64_t p = order ? order[k] : k;
+        s_p[t] = p;
+        s_a[3 * t] = ax[k];
+        s_a[3 * t + 1] = ay[k];
+        s_a[3 * t + 2] = az[k];
+        if (pot_out) pot_out[p] = pot[k];
+    }
+    __syncthreads();
+    const int words = 3 * (int)(n - k0 < kBlock ? n - k0 : kBlock);
+    for (int i = t; i < words; i += kBlock) {
+        const int q = i / 3;
+        a_out[3 * s_p[q] + (i - 3 * q)] = s_a[i];
+    }
 }
 
 // v += dtk a, then x += dtd v.
