@@ -99,7 +99,11 @@ __device__ __forceinline__ int pmod(int i, int n)
 
 // Tiles of the mesh (cells of the interpolation): kTX x kTY x kTZ per block
 // of kBlock threads, z fastest; with their neighbours, kHX x kHY x kHZ.
-constexpr int kTX = 2, kTY = 8, kTZ = 16;
+// Interpolation on 256^3 / 128^3 points by tile: 2 x 8 x 16 1.10 / 0.134 ms,
+// 2 x 8 x 32 1.25 / 0.131, 4 x 4 x 32 1.04 / 0.127, 4 x 8 x 16 1.03 / 0.130
+// (under the tracer).
+constexpr int kXcds = 8;
+constexpr int kTX = 4, kTY = 8, kTZ = 16;
 constexpr int kHX = kTX + 2, kHY = kTY + 2, kHZ = kTZ + 2;
 constexpr int kHalo = kHX * kHY * kHZ;
 constexpr int kRows = kTX * kTY;
@@ -107,14 +111,18 @@ static_assert(kRows <= 64, "a wave scans the rows");
 
 inline unsigned ntiles(int n)
 {
-    return (unsigned)(((n + kTX - 1) / kTX) * ((n + kTY - 1) / kTY) * ((n + kTZ - 1) / kTZ));
+    const int t = ((n + kTX - 1) / kTX) * ((n + kTY - 1) / kTY) * ((n + kTZ - 1) / kTZ);
+    return (unsigned)((t + kXcds - 1) / kXcds * kXcds);
 }
 
-// Origin of block b's tile.
+// Origin of the block's tile (x0 >= n: none).  Blocks go to the XCDs round
+// robin; each takes a run of consecutive tiles, whose neighbourhoods overlap
+// in its L2.
 __device__ __forceinline__ void tile_origin(int n, int &x0, int &y0, int &z0)
 {
     const int nz = (n + kTZ - 1) / kTZ, ny = (n + kTY - 1) / kTY;
-    int b = (int)blockIdx.x;
+    const int per = (int)(gridDim.x / kXcds);
+    int b = (int)(blockIdx.x % kXcds) * per + (int)(blockIdx.x / kXcds);
     z0 = (b % nz) * kTZ;
     b /= nz;
     y0 = (b % ny) * kTY;
@@ -377,9 +385,10 @@ __device__ __forceinline__ void interp_add(const Tsc &w, int a0, int b, int c, c
 // the rows' ranges itself, by shuffles, and the particles are loaded before
 // the fields, so that only the fields are waited for together.  With ranges
 // from LDS atomics, a serial sum of them and a separate pass that interleaved
-// the meshes this took 1.17 ms on 2^24 particles and 256^3 points, now 0.99
-// (0.157 and 0.138 on 2,000,003 unsorted particles and 128^3).  What is left
-// are the results' scattered stores.
+// the meshes this took 1.17 ms on 2^24 particles and 256^3 points, now 0.92
+// (0.157 and 0.130 on 2,000,003 unsorted particles and 128^3).  What is left
+// are the neighbourhoods (2.1 mesh points read per point of the tile) and
+// their reads from LDS.
 __global__ __launch_bounds__(kBlock) void k_interp(int n, const double4 *xs, const int32_t *idx,
                                                    const int32_t *first, double ih,
                                                    const double *mesh, int64_t n3, double *a,
@@ -388,6 +397,7 @@ __global__ __launch_bounds__(kBlock) void k_interp(int n, const double4 *xs, con
     __shared__ double4 sm[kHalo];
     int x0, y0, z0;
     tile_origin(n, x0, y0, z0);
+    if (x0 >= n) return;
     const int t = threadIdx.x, lane = t & 63;
     // lane r: range and inclusive count of row r's particles
     int32_t lo = 0, incl = 0;
