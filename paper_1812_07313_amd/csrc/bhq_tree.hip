@@ -33,6 +33,7 @@
 // bit.
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
+#include <rocprim/rocprim.hpp>
 
 #include <algorithm>
 
@@ -636,6 +637,24 @@ __global__ __launch_bounds__(kBlock) void k_cells(const CellArgs C, int nb)
             }
         }
     }
+}
+
+// Radix sort digit by digit at any size (by itself the library merges up to
+// 2^20 keys).  A digit of 8 bits costs about 25 us and little more with n up
+// to 2^20; the merge sort's passes grow with n and do not depend on the bits.
+// Measured (us, digits / merge), 21 bits: 131,072 78 / 58, 262,144 82 / 101,
+// 524,288 88 / 137, 10^6 96 / 183; 30 bits: 262,144 108 / 103, 524,288
+// 115 / 139; 45 bits: 524,288 170 / 144, 10^6 181 / 193; 63 bits: 10^6
+// 240 / 199.  So one digit more pays with each doubling of n.
+typedef rocprim::radix_sort_config<rocprim::default_config, rocprim::default_config,
+                                   rocprim::default_config, 0>
+    DigitSort;
+
+inline bool sort_by_digits(int64_t n, int bits)
+{
+    int lg = 0;
+    while (((int64_t)2 << lg) <= n) ++lg;
+    return (bits + 7) / 8 <= lg - 15;
 }
 
 // ---- 4. particles and moments -------------------------------------------------
@@ -1553,6 +1572,10 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         if (!hip(hipGetLastError(), "keys")) return false;
         const int b0 = joint ? 0 : lo, b1 = joint ? 3 * kMaxDepth - lo + sysbits : 3 * kMaxDepth;
         auto run = [&](void *tmp, size_t &bytes) -> hipError_t {
+            if ((nsys == 1 || joint) && sort_by_digits(n, b1 - b0))
+                return rocprim::radix_sort_pairs<DigitSort>(tmp, bytes, k0, k1, i0, i1,
+                                                            (unsigned)n, (unsigned)b0,
+                                                            (unsigned)b1, s);
             if (nsys == 1 || joint)
                 return hipcub::DeviceRadixSort::SortPairs(tmp, bytes, k0, k1, i0, i1, (int)n, b0,
                                                           b1, s);
