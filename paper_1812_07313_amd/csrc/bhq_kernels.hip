@@ -61,24 +61,6 @@ __device__ __forceinline__ double wrap(double v, double box, double ibox)
 
 constexpr int kMono = 0, kQuad = 1, kSplitQuad = 2, kSplitMono = 3, kQuadSoft = 4;
 
-// Constants of the Gaussian split, uniform over a launch: u = r i2rs with
-// i2rs = 1 / (2 r_s); the FP32 table variable is t = r ct = u N / U.
-template <typename R>
-struct SplitK {
-    R i2rs;
-    R ct;
-};
-
-template <typename R>
-__device__ __forceinline__ SplitK<R> split_k(double rs)
-{
-    SplitK<R> K;
-    const double i2rs = 0.5 / rs;
-    K.i2rs = R(i2rs);
-    K.ct = R(i2rs * ((double)kSplitIntervals / (double)kSplitDomain));
-    return K;
-}
-
 // The FP32 table of the split radial functions (split_table.h) in device
 // memory, one V4 {c0, c1, c2, c3} per function and interval; each block of
 // a split kernel copies it to LDS, where lanes read their own intervals.
@@ -98,21 +80,77 @@ constexpr SplitTab make_split_tab()
 
 __device__ const SplitTab kSplitTabDev = make_split_tab();
 
-// The FP64 kernels' table of exp(-u^2) and erfcx (split_table64.h),
-// likewise copied to LDS by each block of an FP64 split kernel.
+// The FP64 kernels' table of erfc(u), likewise copied to LDS by each block of
+// an FP64 split kernel: on 128 intervals of 0 <= u < 4 a polynomial of degree
+// 9 in f = t - q, t = 32 u, whose derivative gives exp(-u^2) as well.  It is
+// made from split_table64.h (exp(-u^2) of degree 9 and erfcx on 64 intervals):
+// the integral of the exp polynomial from the interval's start, where erfc is
+// exp(-u^2) erfcx, taken about the start of each half and lowered from degree
+// 10 to 9 by the Chebyshev polynomial (the last coefficient over 2^19, below
+// 1e-16 of erfc everywhere).
+// A pair then reads 80 B from LDS in place of the 144 of the two polynomials;
+// LDS bound the kernel (busy 66 % of the time and 15 % more in bank
+// conflicts, VALU 72 %): the force kernel of a 60^3 lattice took 0.64 ms, now
+// 0.56.
+constexpr int kErfcDegree = 9;
+constexpr int kErfcIntervals = 2 * kTab64Intervals;
+constexpr int kErfcStride = kErfcDegree + 1;
+
 struct Tab64 {
-    double v[kTab64Intervals * kTab64Stride];
+    double v[kErfcIntervals * kErfcStride];
 };
 
 constexpr Tab64 make_tab64()
 {
+    constexpr double rsqpi2 = 1.12837916709551257389615890312;  // 2 / sqrt(pi)
+    constexpr double w = kTab64Domain / kTab64Intervals;
+    // T_10(2 s - 1)
+    constexpr double cheb[kErfcDegree + 2] = {1.0,        -200.0,    6600.0,   -84480.0,
+                                              549120.0,   -2050048.0, 4659200.0, -6553600.0,
+                                              5570560.0,  -2621440.0, 524288.0};
+    static_assert(kExpDegree == kErfcDegree, "the integral is one degree higher");
     Tab64 t{};
-    for (int q = 0; q < kTab64Intervals; ++q)
-        for (int k = 0; k < kTab64Stride; ++k) t.v[q * kTab64Stride + k] = kTab64[q][k];
+    for (int q = 0; q < kTab64Intervals; ++q) {
+        double c[kErfcDegree + 2] = {};
+        c[0] = kTab64[q][0] * kTab64[q][kExpDegree + 1];
+        for (int k = 0; k <= kExpDegree; ++k) c[k + 1] = -rsqpi2 * w * kTab64[q][k] / (k + 1);
+        for (int b = 0; b < 2; ++b) {
+            double d[kErfcDegree + 2] = {};
+            for (int k = 0; k < kErfcDegree + 2; ++k) d[k] = c[k];
+            if (b == 1)  // about f = 1/2
+                for (int i = 0; i < kErfcDegree + 1; ++i)
+                    for (int k = kErfcDegree; k >= i; --k) d[k] += 0.5 * d[k + 1];
+            double scale = 1.0;
+            for (int k = 0; k < kErfcDegree + 2; ++k, scale *= 0.5) d[k] *= scale;
+            const double top = d[kErfcDegree + 1] / cheb[kErfcDegree + 1];
+            for (int k = 0; k < kErfcStride; ++k)
+                t.v[(2 * q + b) * kErfcStride + k] = d[k] - top * cheb[k];
+        }
+    }
     return t;
 }
 
 __device__ const Tab64 kTab64Dev = make_tab64();
+
+// Constants of the Gaussian split, uniform over a launch: u = r i2rs with
+// i2rs = 1 / (2 r_s); the table variable is t = r ct = u N / U.
+template <typename R>
+struct SplitK {
+    R i2rs;
+    R ct;
+};
+
+template <typename R>
+__device__ __forceinline__ SplitK<R> split_k(double rs)
+{
+    SplitK<R> K;
+    const double i2rs = 0.5 / rs;
+    K.i2rs = R(i2rs);
+    K.ct = std::is_same<R, float>::value
+               ? R(i2rs * ((double)kSplitIntervals / (double)kSplitDomain))
+               : R(i2rs * (kErfcIntervals / kTab64Domain));
+    return K;
+}
 
 // Element type of the LDS table of a precision.
 template <typename R>
@@ -130,11 +168,10 @@ using TabT = typename SplitTabT<R>::type;
 //   ec = erfc(u), g = erfc(u) + (2u/sqrt(pi)) e^{-u^2},
 //   G2 = 3g + h, G3 = 15g + 5h + k, with h = (4u^3/sqrt(pi)) e^{-u^2} and
 //   k = 2 u^2 h (G2, G3 only for cells with the quadrupole).
-// FP64 takes E = exp(-u^2) and erfcx(u) from the polynomials of
-// split_table64.h (interval q = floor(t), t = u 64 / 4, f = t - q, Horner's
-// rule; degree 9 for E, 7 for erfcx) and forms erfc(u) = E erfcx(u); past
-// u = 4, that is for cutoffs beyond 8 r_s, it calls the library's exp and
-// erfc.  FP32 reads the
+// FP64 takes erfc(u) and its derivative in t from one polynomial (interval
+// q = floor(t), t = 32 u, f = t - q, Horner's rule for both): t times the
+// derivative is u erfc'(u) = -(2u/sqrt(pi)) e^{-u^2}.  Past u = 4, that is for
+// cutoffs beyond 8 r_s, it calls the library's exp and erfc.  FP32 reads the
 // piecewise cubics of the table at t = r ct: interval q = floor(t), local
 // variable f = t - q, Horner's rule (valid for u up to kSplitDomain and one
 // interval beyond; the host refuses FP32 split kernels with a longer
@@ -164,33 +201,32 @@ __device__ __forceinline__ SplitG<R> split_g(R r, const SplitK<R> &K, const TabT
             s.g3 = horner(tab[3 * kSplitEntries + q], f);
         }
     } else {
-        const R rsqpi = R(0.56418958354775628694807945156);
-        const R u = r * K.i2rs;
-        const R u2 = u * u;
-        R E;
-        if (u < R(kTab64Domain)) {
-            // t < 64 exactly: the scale 64 / 4 is a power of two
-            const R t = u * R(kTab64Intervals / kTab64Domain);
+        const R t = r * K.ct;
+        R w;  // (2u/sqrt(pi)) e^{-u^2} = -u erfc'(u)
+        if (t < R(kErfcIntervals)) {
             const int q = (int)t;
             const R f = t - R(q);
-            const double *c = tab + q * kTab64Stride;
-            E = c[kExpDegree];
+            const double *c = tab + q * kErfcStride;
+            R d = c[kErfcDegree];
+            s.ec = fma(d, f, c[kErfcDegree - 1]);
 #pragma unroll
-            for (int k = kExpDegree - 1; k >= 0; --k) E = fma(E, f, c[k]);
-            const double *cx = c + kExpDegree + 1;
-            R x = cx[kErfcxDegree];
-#pragma unroll
-            for (int k = kErfcxDegree - 1; k >= 0; --k) x = fma(x, f, cx[k]);
-            s.ec = E * x;
+            for (int k = kErfcDegree - 2; k >= 0; --k) {
+                d = fma(d, f, s.ec);
+                s.ec = fma(s.ec, f, c[k]);
+            }
+            w = -t * d;
+            s.g = fma(-t, d, s.ec);
         } else {
-            E = exp_r(-u2);
+            const R u = r * K.i2rs;
             s.ec = erfc_r(u);
+            w = R(1.12837916709551257389615890312) * u * exp_r(-u * u);
+            s.g = s.ec + w;
         }
-        const R e = E * rsqpi;
-        s.g = fma(R(2) * u, e, s.ec);
         if (CELL) {
-            const R h = R(4) * u * u2 * e;
-            const R k = R(2) * u2 * h;
+            const R u = r * K.i2rs;
+            const R u2 = R(2) * u * u;
+            const R h = u2 * w;
+            const R k = u2 * h;
             s.g2 = fma(R(3), s.g, h);
             s.g3 = fma(R(15), s.g, fma(R(5), h, k));
         }
@@ -738,14 +774,13 @@ __device__ __forceinline__ void process_group(const ForceArgs &A, int64_t g, int
 }
 
 // The split kinds keep the table of their radial functions in LDS (FP32:
-// split_table.h; FP64: the exp(-u^2) and erfcx polynomials of
-// split_table64.h).
+// split_table.h; FP64: the erfc polynomials made from split_table64.h).
 template <typename R, int KIND>
 constexpr int split_tab_size()
 {
     return KIND != kSplitQuad && KIND != kSplitMono ? 1
            : std::is_same<R, float>::value          ? kSplitFuncs * kSplitEntries
-                                                    : kTab64Intervals * kTab64Stride;
+                                                    : kErfcIntervals * kErfcStride;
 }
 
 template <typename R, int KIND, int BS>
@@ -756,7 +791,7 @@ __device__ __forceinline__ void load_split_tab(TabT<R> *tab)
             for (int k = threadIdx.x; k < kSplitFuncs * kSplitEntries; k += BS)
                 tab[k] = kSplitTabDev.v[k];
         } else {
-            for (int k = threadIdx.x; k < kTab64Intervals * kTab64Stride; k += BS)
+            for (int k = threadIdx.x; k < kErfcIntervals * kErfcStride; k += BS)
                 tab[k] = kTab64Dev.v[k];
         }
         __syncthreads();
