@@ -36,6 +36,7 @@
 #include <rocprim/rocprim.hpp>
 
 #include <algorithm>
+#include <climits>
 
 #include "bhq.h"
 #include "bhq_internal.h"
@@ -1001,39 +1002,41 @@ struct WalkArgs {
 //                                        accepted one-particle cell or an
 //                                        opened leaf)
 //   opened internal cell                {-2 - child0, nchild}
+// CUT: with a cutoff or a periodic box.
+template <bool CUT>
 __device__ __forceinline__ int2 classify(const WalkArgs &W, int32_t id, const WCell &G,
                                          const WLink &GL, const double *gb)
 {
     const WCell C = W.wc[id];
     const WLink L = W.wl[id];
-    const double box = W.box;
+    const double box = CUT ? W.box : 0.0;
     const double gc[3] = {G.cx, G.cy, G.cz};
     if (!contains(C, L, G, GL)) {
-        if (W.rcut > 0.0) {
+        if (CUT && W.rcut > 0.0) {
             const double cc[3] = {C.cx, C.cy, C.cz};
             double d2 = 0.0;
             for (int k = 0; k < 3; ++k) {
-                const double v = abs_min_image(cc[k] - gc[k], box) -
-                                 0.5 * (C.side + G.side);
-                if (v > 0.0) d2 += v * v;
+                const double v = ::fmax(abs_min_image(cc[k] - gc[k], box) -
+                                            0.5 * (C.side + G.side), 0.0);
+                d2 += v * v;
             }
             if (d2 > W.rcut * W.rcut) return make_int2(-1, 0);
         }
         const double cm[3] = {C.mx, C.my, C.mz};
         double d2 = 0.0;
         for (int k = 0; k < 3; ++k) {
-            const double v = abs_min_image(cm[k] - gc[k], box) - 0.5 * G.side;
-            if (v > 0.0) d2 += v * v;
+            const double v = ::fmax(abs_min_image(cm[k] - gc[k], box) - 0.5 * G.side, 0.0);
+            d2 += v * v;
         }
         if (C.side * C.side < W.theta2 * d2) {
             // beyond the cutoff for every particle of the group
-            if (W.rdrop2 > 0.0) {
+            if (CUT && W.rdrop2 > 0.0) {
                 // distance to the box of the group's particles (centre
                 // gb[0..2], half widths gb[3..5])
                 double b2 = 0.0;
                 for (int k = 0; k < 3; ++k) {
-                    const double v = abs_min_image(cm[k] - gb[k], box) - gb[3 + k];
-                    if (v > 0.0) b2 += v * v;
+                    const double v = ::fmax(abs_min_image(cm[k] - gb[k], box) - gb[3 + k], 0.0);
+                    b2 += v * v;
                 }
                 if (b2 >= W.rdrop2) return make_int2(-1, 0);
             }
@@ -1054,15 +1057,15 @@ __device__ __forceinline__ int dpp(int v)
     return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
 }
 
-__device__ __forceinline__ int octet_scan(int v, int k)
+// Exclusive prefix sum; m: per distance 1, 2, 4 all ones in the lanes that
+// have a lane of their octet so far below (k >= 1, 2, 4), else zero.
+__device__ __forceinline__ int octet_scan(int v, const int *m)
 {
-    int u = dpp<0x111>(v);  // row_shr:1
-    v += k >= 1 ? u : 0;
-    u = dpp<0x112>(v);      // row_shr:2
-    v += k >= 2 ? u : 0;
-    u = dpp<0x114>(v);      // row_shr:4
-    v += k >= 4 ? u : 0;
-    return v;
+    const int own = v;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true) & m[0];  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true) & m[1];  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true) & m[2];  // row_shr:4
+    return v - own;
 }
 
 __device__ __forceinline__ int octet_sum(int v)
@@ -1071,6 +1074,22 @@ __device__ __forceinline__ int octet_sum(int v)
     v += dpp<0xB1>(v);   // quad_perm [1, 0, 3, 2]: lane k ^ 1
     v += dpp<0x4E>(v);   // quad_perm [2, 3, 0, 1]: lane k ^ 2
     return v;
+}
+
+// dst[0 .. n - 1] = first, first + 1, ...  A leaf's run is a few entries at any
+// alignment, and its lane's stores each touch a line of their own: four
+// entries per store.
+struct alignas(4) Ids4 {
+    int32_t v[4];
+};
+
+__device__ __forceinline__ void put_run(int32_t *dst, int32_t first, int32_t n)
+{
+    int32_t j = 0;
+    for (; j + 4 <= n; j += 4)
+        *reinterpret_cast<Ids4 *>(dst + j) = {{first + j, first + j + 1, first + j + 2,
+                                               first + j + 3}};
+    for (; j < n; ++j) dst[j] = first + j;
 }
 
 // Centre and half widths of the box (lo, hi) of group gi's particles, with
@@ -1100,20 +1119,24 @@ enum WalkMode { kWalkCount = 0, kWalkFill = 1, kWalkSlots = 2 };
 // those opened by one octet in a row; the lists do not depend on the numbers.
 // LDS keeps 16 B per octet, so that occupancy is not bound by it: the first
 // child's id, the number of the first octet opened (16 bits) over the
-// children's kinds (2 bits each), and the totals, replaced by the octet's
-// position on the way down.  `cap` octets fit: a group that opens more sets
+// children's kinds (2 bits each), and the totals (summed by one lane per
+// octet), replaced by the octet's position on the way down.  `cap` octets fit: a group that opens more sets
 // *W.flag = 2 (its other cells are left out) and the host walks again with
 // the octet walk.
-// A rebuild's walk took 0.26 ms on the cube of 2^20 (0.75 with the octet
-// walk), 3.3 on the 2^24 lattice at ncrit 128 (4.6) and 0.042 on a Plummer
-// sphere of 16,384 (0.65: 989 groups, each a chain of about 200 openings).
-// What is left is the classification's FP64 arithmetic (VALU) on large inputs
-// and one chain of loads per level on small ones.  Keeping the children as
-// classified (72 B per octet) left two blocks per CU on inputs with a few
-// long groups: the clustered 2^22 walk was slower than the octet walk.
+// A rebuild's walk took 0.75 ms on the cube of 10^6, 4.6 on the 2^24 lattice
+// at ncrit 128 and 0.65 on a Plummer sphere of 16,384 (989 groups, each a
+// chain of about 200 openings) with the octet walk, and 0.20, 3.3 and 0.042
+// with this one; with the totals by a lane per octet, four entries per store
+// of a run and no cutoff terms without a cutoff 0.18, 3.15 and 0.040 (1.30 ->
+// 1.11 on 256 systems, 1.36 -> 1.24 on the clustered 2^22).
+// What is left is the classification's arithmetic (VALU busy 88 % of the time
+// on the lattice, 71 % on the cube) and one chain of loads per level on small
+// inputs.  Keeping the children as classified (72 B per octet) left two blocks
+// per CU on inputs with a few long groups: the clustered 2^22 walk was slower
+// than the octet walk.
 constexpr uint32_t kNodeNone = 0, kNodeCell = 1, kNodeRun = 2, kNodeOpen = 3;
 
-template <int MODE, int NW>
+template <int MODE, int NW, bool CUT>
 __global__ __launch_bounds__(64 * NW) void k_walk_level(const WalkArgs W, int cap)
 {
     extern __shared__ int2 s_walk[];
@@ -1169,7 +1192,8 @@ __global__ __launch_bounds__(64 * NW) void k_walk_level(const WalkArgs W, int ca
         if (t == 0) s_lev[nl] = lo;
         for (int q = lo + o; q < hi; q += kOct * NW) {
             const int32_t c0 = s_c0[q];
-            const int2 e = k < (int)s_kind[q] ? classify(W, c0 + k, G, GL, gb) : make_int2(-1, 0);
+            const int2 e = k < (int)s_kind[q] ? classify<CUT>(W, c0 + k, G, GL, gb)
+                                              : make_int2(-1, 0);
             bool open = e.x <= -2;
             const uint64_t bal = __ballot(open);
             int ch = 0;  // octet of this lane's (opened) child, or the next one's
@@ -1194,11 +1218,11 @@ __global__ __launch_bounds__(64 * NW) void k_walk_level(const WalkArgs W, int ca
             const bool cell = e.x >= 0 && e.y == 0, run = e.x >= 0 && e.y > 0;
             const uint32_t kind =
                 (cell ? kNodeCell : run ? kNodeRun : open ? kNodeOpen : kNodeNone) << (2 * k);
-            const int2 own = make_int2(octet_sum(cell ? 1 : 0), octet_sum(run ? e.y : 0));
+            const int own = octet_sum(run ? e.y : 0);
             const uint32_t kinds = (uint32_t)octet_sum((int)kind);
             if (k == 0) {
                 s_kind[q] = kinds | (uint32_t)ch << 16;
-                s_sum[q] = own;
+                s_sum[q].y = own;
             }
         }
         __syncthreads();
@@ -1209,23 +1233,20 @@ __global__ __launch_bounds__(64 * NW) void k_walk_level(const WalkArgs W, int ca
     }
     if (t == 0) s_lev[nl] = hi;
     if (full) *W.flag = 2;
-    // octet of lane k's child among those opened by an octet of these kinds
-    auto child_octet = [&](uint32_t kinds) -> int {
-        const uint32_t m = kinds & (kinds >> 1) & 0x5555u & ((1u << (2 * k)) - 1u);
-        return (int)(kinds >> 16) + __popc(m);
-    };
     __syncthreads();
-    for (int l = nl - 2; l >= 0; --l) {  // the deepest level opens nothing
+    // totals, one lane per octet over the octets it opened
+    for (int l = nl - 1; l >= 0; --l) {
         const int b = s_lev[l], f = s_lev[l + 1];
-        for (int q = b + o; q < f; q += kOct * NW) {
-            const uint32_t kinds = s_kind[q];
-            int2 v = make_int2(0, 0);
-            if (((kinds >> (2 * k)) & 3u) == kNodeOpen) v = s_sum[child_octet(kinds)];
-            const int2 sum = make_int2(octet_sum(v.x), octet_sum(v.y));
-            if (k == 0) {
-                const int2 own = s_sum[q];
-                s_sum[q] = make_int2(own.x + sum.x, own.y + sum.y);
+        for (int q = b + t; q < f; q += 64 * NW) {
+            const uint32_t kinds = s_kind[q], up = kinds >> 1;
+            int2 v = make_int2(__popc(kinds & ~up & 0x5555u), s_sum[q].y);
+            const int c = (int)(kinds >> 16), e = c + __popc(kinds & up & 0x5555u);
+            for (int j = c; j < e; ++j) {
+                const int2 u = s_sum[j];
+                v.x += u.x;
+                v.y += u.y;
             }
+            s_sum[q] = v;
         }
         __syncthreads();
     }
@@ -1241,6 +1262,13 @@ __global__ __launch_bounds__(64 * NW) void k_walk_level(const WalkArgs W, int ca
     }
     if (MODE == kWalkCount) return;
     __syncthreads();
+    // entries left in the group's segments; a slot overflow is detected from
+    // the counts
+    const int cleft = (int)(ce - cb < INT_MAX ? ce - cb : INT_MAX);
+    const int pleft = (int)(pe - pb < INT_MAX ? pe - pb : INT_MAX);
+    int32_t *const jc = W.jc_idx + cb, *const jp = W.jp_idx + pb;
+    const int below[3] = {k >= 1 ? -1 : 0, k >= 2 ? -1 : 0, k >= 4 ? -1 : 0};
+    const uint32_t lower = 0x5555u & ((1u << (2 * k)) - 1u);
     for (int l = 0; l < nl; ++l) {
         const int b = s_lev[l], f = s_lev[l + 1];
         for (int q = b + o; q < f; q += kOct * NW) {
@@ -1251,26 +1279,22 @@ __global__ __launch_bounds__(64 * NW) void k_walk_level(const WalkArgs W, int ca
             int2 v = make_int2(kind == kNodeCell ? 1 : 0, 0);
             int ch = 0;
             if (kind == kNodeOpen) {
-                ch = child_octet(kinds);
+                // its number among those that the octet opened
+                ch = (int)(kinds >> 16) + __popc(kinds & (kinds >> 1) & lower);
                 v = s_sum[ch];
             } else if (kind == kNodeRun) {
                 const WLink L = W.wl[id];
                 first = L.first;
                 v.y = L.end - L.first;
             }
-            const int c0 = at.x + octet_scan(v.x, k) - v.x;
-            const int p0 = at.y + octet_scan(v.y, k) - v.y;
+            const int c0 = at.x + octet_scan(v.x, below);
+            const int p0 = at.y + octet_scan(v.y, below);
             if (kind == kNodeOpen) {
                 s_sum[ch] = make_int2(c0, p0);
             } else if (kind == kNodeCell) {
-                if (cb + c0 < ce) W.jc_idx[cb + c0] = id;
+                if (c0 < cleft) jc[c0] = id;
             } else if (kind == kNodeRun) {
-                // the entries that fit in the group's segment (none past
-                // it: a slot overflow is detected from the counts)
-                const int64_t w = pb + p0;
-                const int32_t nw = (int32_t)(pe - w < (int64_t)v.y ? pe - w : v.y);
-                int32_t *dst = W.jp_idx + w;
-                for (int32_t j = 0; j < nw; ++j) dst[j] = first + j;
+                put_run(jp + p0, first, pleft - p0 < v.y ? pleft - p0 : v.y);
             }
         }
         __syncthreads();
@@ -1331,6 +1355,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
         ce = cb + W.cap_c;
     }
     const WLink R = W.wl[W.groot ? W.groot[gi] : 0];
+    const int below[3] = {k >= 1 ? -1 : 0, k >= 2 ? -1 : 0, k >= 4 ? -1 : 0};
     int sp = 0, nch = 0, cur = 0;
     int2 e = make_int2(-1, 0);
     if (R.child0 < 0) {
@@ -1341,7 +1366,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
         np = R.end - R.first;
     } else {
         nch = children(R);
-        e = k < nch ? classify(W, R.child0 + k, G, GL, gb) : make_int2(-1, 0);
+        e = k < nch ? classify<true>(W, R.child0 + k, G, GL, gb) : make_int2(-1, 0);
         s_ent[0][t] = e;
         sp = 1;
     }
@@ -1364,18 +1389,17 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
             const int vp = em ? e.y : 0;            // particles
             const int vc = em && e.y == 0 ? 1 : 0;  // cells
             if (FILL) {
-                const int ip = octet_scan(vp, k), ic = octet_scan(vc, k);
+                const int ip = octet_scan(vp, below), ic = octet_scan(vc, below);
                 if (em) {
                     if (e.y == 0) {
-                        const int64_t q = cb + nc + ic - 1;
+                        const int64_t q = cb + nc + ic;
                         if (q < ce) W.jc_idx[q] = e.x;
                     } else {
                         // the entries that fit in the group's segment (none
                         // past it: a slot overflow is detected from the counts)
-                        const int64_t q = pb + np + ip - e.y;
-                        const int32_t nw = (int32_t)(pe - q < (int64_t)e.y ? pe - q : e.y);
-                        int32_t *dst = W.jp_idx + q;
-                        for (int32_t j = 0; j < nw; ++j) dst[j] = e.x + j;
+                        const int64_t q = pb + np + ip;
+                        put_run(W.jp_idx + q, e.x,
+                                (int32_t)(pe - q < (int64_t)e.y ? pe - q : e.y));
                     }
                 }
             }
@@ -1401,7 +1425,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
             cur = hdr >> 8;
         }
         if (n2 < 0) break;
-        e = k < n2 ? classify(W, c0 + k, G, GL, gb) : make_int2(-1, 0);
+        e = k < n2 ? classify<true>(W, c0 + k, G, GL, gb) : make_int2(-1, 0);
         s_ent[sp][t] = e;
         nch = n2;
         cur = 0;
@@ -1841,18 +1865,23 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         if (oct_cap > 0) {
             const size_t lds = (size_t)oct_cap * kOctBytes;
             const dim3 g((unsigned)((ng + kXcds - 1) / kXcds * kXcds));
-            auto launch = [&](auto two, auto four) {
+            const bool cut = W.rcut > 0.0 || W.box > 0.0;
+            auto launch = [&](auto two, auto four, auto two_cut, auto four_cut) {
                 if (wide)
-                    hipLaunchKernelGGL(four, g, dim3(256), lds, s, W, oct_cap);
+                    hipLaunchKernelGGL(cut ? four_cut : four, g, dim3(256), lds, s, W, oct_cap);
                 else
-                    hipLaunchKernelGGL(two, g, dim3(128), lds, s, W, oct_cap);
+                    hipLaunchKernelGGL(cut ? two_cut : two, g, dim3(128), lds, s, W, oct_cap);
             };
+#define BHQ_WALKS(mode)                                                   \
+    launch(k_walk_level<mode, 2, false>, k_walk_level<mode, 4, false>,    \
+           k_walk_level<mode, 2, true>, k_walk_level<mode, 4, true>)
             if (mode == kWalkCount)
-                launch(k_walk_level<kWalkCount, 2>, k_walk_level<kWalkCount, 4>);
+                BHQ_WALKS(kWalkCount);
             else if (mode == kWalkFill)
-                launch(k_walk_level<kWalkFill, 2>, k_walk_level<kWalkFill, 4>);
+                BHQ_WALKS(kWalkFill);
             else
-                launch(k_walk_level<kWalkSlots, 2>, k_walk_level<kWalkSlots, 4>);
+                BHQ_WALKS(kWalkSlots);
+#undef BHQ_WALKS
         } else {
             const dim3 g(walk_blocks(ng)), b(kWalkBlock);
             if (mode == kWalkCount)
