@@ -35,6 +35,7 @@
 
 #include "bhq.h"
 #include "bhq_internal.h"
+#include "bhq_sort.h"
 
 // No contraction into fused multiply-adds: every kernel that locates a
 // particle's mesh cell must get the bits the sort keys were made with.
@@ -137,14 +138,26 @@ __device__ __forceinline__ int64_t halo_point(int h, int n, int x0, int y0, int 
     return ((int64_t)cx * n + cy) * n + cz;
 }
 
-// Cell of the nearest mesh point of each particle, and the identity order.
-__global__ __launch_bounds__(kBlock) void k_cell_keys(int64_t np, const double *x, double ih,
-                                                      int n, uint32_t *key, int32_t *idx)
+// Cell of the particle's nearest mesh point.
+struct CellKeys {
+    const double *x;
+    double ih;
+    int n;
+
+    __device__ __forceinline__ uint32_t operator()(int64_t p) const
+    {
+        const Tsc t = tsc(x + 3 * p, ih, n);
+        return (uint32_t)(((int64_t)t.i[0] * n + t.i[1]) * n + t.i[2]);
+    }
+};
+
+// The cells, and the identity order.
+__global__ __launch_bounds__(kBlock) void k_cell_keys(int64_t np, const CellKeys keys,
+                                                      uint32_t *key, int32_t *idx)
 {
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (p >= np) return;
-    const Tsc t = tsc(x + 3 * p, ih, n);
-    key[p] = (uint32_t)(((int64_t)t.i[0] * n + t.i[1]) * n + t.i[2]);
+    key[p] = keys(p);
     idx[p] = (int32_t)p;
 }
 
@@ -670,21 +683,26 @@ int bhq_pm_compute(bhq_pm *pm, int64_t np, const double *x, const double *m, dou
     if (!hipok(pm->xs.reserve((size_t)np * sizeof(double4)), "allocation")) return BHQ_E_NOMEM;
     int bits = 1;
     while (((uint64_t)1 << bits) < (uint64_t)n3) ++bits;
-    size_t tmp = 0;
-    if (!hipok(hipcub::DeviceRadixSort::SortPairs(nullptr, tmp, pm->key.as<uint32_t>(),
-                                                  pm->key2.as<uint32_t>(), pm->idx.as<int32_t>(),
-                                                  pm->idx2.as<int32_t>(), (int)np, 0, bits, s),
-               "sort size"))
-        return BHQ_E_HIP;
-    if (!hipok(pm->sort_tmp.reserve(tmp), "allocation")) return BHQ_E_NOMEM;
-    hipLaunchKernelGGL(k_cell_keys, dim3(nblocks(np)), dim3(kBlock), 0, s, np, x, ih, n,
-                       pm->key.as<uint32_t>(), pm->idx.as<int32_t>());
-    if (!hipok(hipGetLastError(), "cell keys")) return BHQ_E_HIP;
-    if (!hipok(hipcub::DeviceRadixSort::SortPairs(pm->sort_tmp.p, tmp, pm->key.as<uint32_t>(),
-                                                  pm->key2.as<uint32_t>(), pm->idx.as<int32_t>(),
-                                                  pm->idx2.as<int32_t>(), (int)np, 0, bits, s),
-               "sort"))
-        return BHQ_E_HIP;
+    const CellKeys keys{x, ih, n};
+    uint32_t *k0 = pm->key.as<uint32_t>(), *k1 = pm->key2.as<uint32_t>();
+    int32_t *i0 = pm->idx.as<int32_t>(), *i1 = pm->idx2.as<int32_t>();
+    if (np <= bhq::kRankSortMost && bits < 32) {
+        if (!hipok(bhq::rank_sort(keys, np, 0, bits, k0, i0, k1, i1, s), "sort"))
+            return BHQ_E_HIP;
+    } else {
+        size_t tmp = 0;
+        if (!hipok(hipcub::DeviceRadixSort::SortPairs(nullptr, tmp, k0, k1, i0, i1, (int)np, 0,
+                                                      bits, s),
+                   "sort size"))
+            return BHQ_E_HIP;
+        if (!hipok(pm->sort_tmp.reserve(tmp), "allocation")) return BHQ_E_NOMEM;
+        hipLaunchKernelGGL(k_cell_keys, dim3(nblocks(np)), dim3(kBlock), 0, s, np, keys, k0, i0);
+        if (!hipok(hipGetLastError(), "cell keys")) return BHQ_E_HIP;
+        if (!hipok(hipcub::DeviceRadixSort::SortPairs(pm->sort_tmp.p, tmp, k0, k1, i0, i1,
+                                                      (int)np, 0, bits, s),
+                   "sort"))
+            return BHQ_E_HIP;
+    }
     hipLaunchKernelGGL(k_sorted, dim3(nblocks(np + 1)), dim3(kBlock), 0, s, np, (int64_t)n3,
                        pm->key2.as<uint32_t>(), pm->idx2.as<int32_t>(), x, m,
                        pm->xs.as<double4>(), pm->first.as<int32_t>());

@@ -40,6 +40,7 @@
 
 #include "bhq.h"
 #include "bhq_internal.h"
+#include "bhq_sort.h"
 
 #pragma clang fp contract(off)
 
@@ -224,34 +225,45 @@ __device__ __forceinline__ int system_of(const int64_t *off, int nsys, int64_t p
 // roots[4 s .. 4 s + 3] = centre and side of system s's root cube.  The sort
 // key is the particle's 63-bit key or, with lo > 0 and several systems, its
 // bits from lo up below the system's number.
-__global__ __launch_bounds__(kBlock) void k_keys(const double *x, int64_t n,
-                                                 const int64_t *sys_off, int nsys,
-                                                 const double *roots, int lo, uint64_t *key,
+struct TreeKeys {
+    const double *x;
+    const int64_t *sys_off;
+    int nsys;
+    const double *roots;
+    int lo;  // > 0: (system, key from bit lo up)
+
+    __device__ __forceinline__ uint64_t operator()(int64_t p) const
+    {
+        const int sys = nsys > 1 ? system_of(sys_off, nsys, p) : 0;
+        const double *rt = roots + 4 * sys;
+        const double xp[3] = {x[3 * p], x[3 * p + 1], x[3 * p + 2]};
+        double c[3] = {rt[0], rt[1], rt[2]};
+        double s = rt[3];
+        uint64_t k = 0;
+        for (int lev = 0; lev < kMaxDepth; ++lev) {
+            const double qd = s * 0.25;
+            unsigned o = 0;
+            for (int a = 0; a < 3; ++a) {
+                if (xp[a] >= c[a]) {
+                    o |= 1u << a;
+                    c[a] = c[a] + qd;
+                } else {
+                    c[a] = c[a] - qd;
+                }
+            }
+            k = (k << 3) | o;
+            s = s * 0.5;
+        }
+        return lo > 0 ? (uint64_t)sys << (3 * kMaxDepth - lo) | k >> lo : k;
+    }
+};
+
+__global__ __launch_bounds__(kBlock) void k_keys(const TreeKeys keys, int64_t n, uint64_t *key,
                                                  int32_t *idx)
 {
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (p >= n) return;
-    const int sys = nsys > 1 ? system_of(sys_off, nsys, p) : 0;
-    const double *rt = roots + 4 * sys;
-    const double xp[3] = {x[3 * p], x[3 * p + 1], x[3 * p + 2]};
-    double c[3] = {rt[0], rt[1], rt[2]};
-    double s = rt[3];
-    uint64_t k = 0;
-    for (int lev = 0; lev < kMaxDepth; ++lev) {
-        const double qd = s * 0.25;
-        unsigned o = 0;
-        for (int a = 0; a < 3; ++a) {
-            if (xp[a] >= c[a]) {
-                o |= 1u << a;
-                c[a] = c[a] + qd;
-            } else {
-                c[a] = c[a] - qd;
-            }
-        }
-        k = (k << 3) | o;
-        s = s * 0.5;
-    }
-    key[p] = lo > 0 ? (uint64_t)sys << (3 * kMaxDepth - lo) | k >> lo : k;
+    key[p] = keys(p);
     idx[p] = (int32_t)p;
 }
 
@@ -640,13 +652,13 @@ __global__ __launch_bounds__(kBlock) void k_cells(const CellArgs C, int nb)
     }
 }
 
-// Radix sort digit by digit at any size (by itself the library merges up to
-// 2^20 keys).  A digit of 8 bits costs about 25 us and little more with n up
-// to 2^20; the merge sort's passes grow with n and do not depend on the bits.
-// Measured (us, digits / merge), 21 bits: 131,072 78 / 58, 262,144 82 / 101,
-// 524,288 88 / 137, 10^6 96 / 183; 30 bits: 262,144 108 / 103, 524,288
-// 115 / 139; 45 bits: 524,288 170 / 144, 10^6 181 / 193; 63 bits: 10^6
-// 240 / 199.  So one digit more pays with each doubling of n.
+// Radix sort digit by digit above kRankSortMost (by itself the library merges
+// up to 2^20 keys).  A digit of 8 bits costs about 25 us and little more with n
+// up to 2^20; the merge sort's passes grow with n and do not depend on the
+// bits.  Measured (us, digits / merge), 21 bits: 524,288 88 / 137, 10^6
+// 96 / 183; 30 bits: 524,288 115 / 139; 45 bits: 524,288 170 / 144, 10^6
+// 181 / 193; 63 bits: 10^6 240 / 199.  So one digit more pays with each
+// doubling of n.
 typedef rocprim::radix_sort_config<rocprim::default_config, rocprim::default_config,
                                    rocprim::default_config, 0>
     DigitSort;
@@ -1591,10 +1603,14 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         int32_t *i0 = B[T_IDX0].as<int32_t>(), *i1 = B[T_IDX1].as<int32_t>();
         const int32_t *so = B[T_SYSOFF32].as<int32_t>();
         joint = nsys > 1 && lo > 0 && 3 * kMaxDepth - lo + sysbits <= 64;
-        hipLaunchKernelGGL(k_keys, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s, P.x, n, sys_off,
-                           nsys, roots, joint ? lo : 0, k0, i0);
-        if (!hip(hipGetLastError(), "keys")) return false;
+        const TreeKeys keys{P.x, sys_off, nsys, roots, joint ? lo : 0};
         const int b0 = joint ? 0 : lo, b1 = joint ? 3 * kMaxDepth - lo + sysbits : 3 * kMaxDepth;
+        // (a key's 21 levels are too much arithmetic for the few blocks that
+        // sort the tiles: formed there they cost 5 to 9 us more)
+        hipLaunchKernelGGL(k_keys, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s, keys, n, k0, i0);
+        if (!hip(hipGetLastError(), "keys")) return false;
+        if ((nsys == 1 || joint) && n <= kRankSortMost && b1 < 64)
+            return hip(rank_sort(StoredKeys<uint64_t>{k0}, n, b0, b1, k0, i0, k1, i1, s), "sort");
         auto run = [&](void *tmp, size_t &bytes) -> hipError_t {
             if ((nsys == 1 || joint) && sort_by_digits(n, b1 - b0))
                 return rocprim::radix_sort_pairs<DigitSort>(tmp, bytes, k0, k1, i0, i1,

@@ -64,6 +64,29 @@ def test_cells_from_keys(n, ncrit, nleaf):
         bhq.bhq_destroy(ctx)
 
 
+@pytest.mark.parametrize("n", [
+    2047, 2048, 2049, 4096, 4097,      # one tile, two tiles and one merge
+    16384, 16385,                      # eight tiles; seventeen of 1024 and two merges
+    65535, 65536, 65537,               # eight runs of eight; tiles of 2048
+    131072, 131073,                    # tiles of 4096
+    262143, 262144, 262145,            # the largest; the library's sort
+])
+def test_sorted_tiles(n):
+    """The order of the keys' sort: all bits on a first build, those of the
+    last depth on a rebuild, with coincident particles (equal keys, which keep
+    their input order) in different tiles."""
+    g = synth.rng(42)
+    x, m = synth.plummer(n, g)
+    x[g.integers(0, n, 400)] = x[0]
+    h = _host(x, m, 0.8, 256, 16)
+    ctx = bhq.bhq_create(0, bhq.QUAD, bhq.FP32_OFS64)
+    try:
+        for build in range(2):
+            _same(h, _device(ctx, x, m, 0.8, 256, 16), "tiles %d build %d" % (n, build))
+    finally:
+        bhq.bhq_destroy(ctx)
+
+
 @pytest.mark.parametrize("sizes", [
     (1, 1, 3), (1023, 1, 1024, 5, 2000), (700,) * 9,
     tuple(range(1, 80)),               # many systems in one tile
