@@ -113,30 +113,22 @@ __device__ __forceinline__ void root_cube(double (*s)[BS], double *root)
     root[3] = ext > 0.0 ? ext * (1.0 + 0x1p-20) : 1.0;
 }
 
-// Non-finite positions or masses set flag[0]; a softening that is not
-// finite and positive sets flag[1] (vector stores of 1).  The same pass over
-// the positions gives each block's bounding box (one system), in part.
-// ONE: the only block, which clears the flags itself and writes the root cube
-// to part (box > 0: of [0, box)^3).  Up to kSmallCheck particles that saves
-// two launches of 4 us each.
-constexpr int64_t kSmallCheck = 8192;
+// Per block: bad[b] bit 0 if a position or mass is not finite, bit 1 if a
+// softening is not finite and positive, and with part the bounding box (one
+// system).
 constexpr int kFlags = 16;
 
-template <int BS, bool ONE>
-__global__ __launch_bounds__(BS) void k_check(const double *x, const double *m,
-                                              const double *eps2, int64_t n, double box,
-                                              int *flag, double *part)
+__global__ __launch_bounds__(kBlock) void k_check(const double *x, const double *m,
+                                                  const double *eps2, int64_t n, int *bad,
+                                                  double *part)
 {
-    __shared__ double s[6][BS];
-    if (ONE) {
-        if (threadIdx.x < kFlags) flag[threadIdx.x] = 0;
-        __syncthreads();
-    }
+    __shared__ double s[6][kBlock];
     double lo[3], hi[3];
-    const int64_t start = (int64_t)blockIdx.x * BS + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * BS;
+    const int64_t start = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
     const int64_t p0 = start < n ? start : 0;  // n >= 1
     for (int a = 0; a < 3; ++a) lo[a] = hi[a] = x[3 * p0 + a];
+    bool input = false, soft = false;
     for (int64_t p = start; p < n; p += stride) {
         double v[3];
         for (int a = 0; a < 3; ++a) {
@@ -144,55 +136,77 @@ __global__ __launch_bounds__(BS) void k_check(const double *x, const double *m,
             lo[a] = v[a] < lo[a] ? v[a] : lo[a];
             hi[a] = v[a] > hi[a] ? v[a] : hi[a];
         }
-        if (!isfinite(v[0]) || !isfinite(v[1]) || !isfinite(v[2]) || !isfinite(m[p])) flag[0] = 1;
-        if (eps2 && !(isfinite(eps2[p]) && eps2[p] >= kMinEps2)) flag[1] = 1;
+        if (!isfinite(v[0]) || !isfinite(v[1]) || !isfinite(v[2]) || !isfinite(m[p])) input = true;
+        if (eps2 && !(isfinite(eps2[p]) && eps2[p] >= kMinEps2)) soft = true;
     }
+    const int f0 = __syncthreads_or(input), f1 = __syncthreads_or(soft);
+    if (threadIdx.x == 0) bad[blockIdx.x] = (f0 ? 1 : 0) | (f1 ? 2 : 0);
     if (!part) return;
-    if (ONE && box > 0.0) {
-        if (threadIdx.x < 4) part[threadIdx.x] = threadIdx.x < 3 ? 0.5 * box : box;
-        return;
-    }
     for (int a = 0; a < 3; ++a) {
         s[a][threadIdx.x] = lo[a];
         s[3 + a][threadIdx.x] = hi[a];
     }
-    block_box<BS>(s);
-    if (ONE) {
-        if (threadIdx.x == 0) root_cube<BS>(s, part);
-    } else {
-        if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = s[threadIdx.x][0];
-    }
+    block_box<kBlock>(s);
+    if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = s[threadIdx.x][0];
 }
 
-// The one system's root cube from the blocks' boxes, or [0, box)^3.
-__global__ __launch_bounds__(kBlock) void k_root(const double *part, int nb, double box,
-                                                 double *root)
+// The build's flags from the checking blocks' (one block): flag[0], flag[1]
+// as bad's bits, the others cleared.
+__device__ __forceinline__ void set_flags(const int *bad, int nb, int *flag)
 {
-    __shared__ double s[6][kBlock];
+    int f = 0;
+    for (int b = threadIdx.x; b < nb; b += (int)blockDim.x) f |= bad[b];
+    const int f0 = __syncthreads_or(f & 1), f1 = __syncthreads_or(f & 2);
+    if (threadIdx.x < kFlags)
+        flag[threadIdx.x] = threadIdx.x == 0 ? (f0 ? 1 : 0) : threadIdx.x == 1 && f1 ? 1 : 0;
+}
+
+// The one system's root cube (by a block, in its LDS) from the checking
+// blocks' boxes, or [0, box)^3.
+__device__ __forceinline__ void one_root(const double *part, int nb, double box,
+                                         double (*s)[kBlock], double *root)
+{
+    const int t = threadIdx.x;
     if (box > 0.0) {
-        if (threadIdx.x < 4) root[threadIdx.x] = threadIdx.x < 3 ? 0.5 * box : box;
+        if (t < 4) root[t] = t < 3 ? 0.5 * box : box;
+        __syncthreads();
         return;
     }
-    for (int a = 0; a < 6; ++a) s[a][threadIdx.x] = part[a];  // block 0
-    for (int b = threadIdx.x; b < nb; b += kBlock)
+    const int b0 = t < nb ? t : 0;
+    for (int a = 0; a < 6; ++a) s[a][t] = part[6 * b0 + a];
+    for (int b = t + kBlock; b < nb; b += kBlock)
         for (int a = 0; a < 3; ++a) {
             const double l = part[6 * b + a], u = part[6 * b + 3 + a];
-            if (l < s[a][threadIdx.x]) s[a][threadIdx.x] = l;
-            if (u > s[3 + a][threadIdx.x]) s[3 + a][threadIdx.x] = u;
+            if (l < s[a][t]) s[a][t] = l;
+            if (u > s[3 + a][t]) s[3 + a][t] = u;
         }
     block_box<kBlock>(s);
-    if (threadIdx.x == 0) root_cube<kBlock>(s, root);
+    if (t == 0) root_cube<kBlock>(s, root);
+    __syncthreads();
 }
 
-// Root cube of each system of a batch: one block per system.
-__global__ __launch_bounds__(kBlock) void k_root_sys(const double *x, const int64_t *sys_off,
-                                                     double *roots)
+__global__ __launch_bounds__(kBlock) void k_root(const double *part, const int *bad, int nb,
+                                                 double box, int *flag, double *root)
 {
-    __shared__ double s[6][kBlock];
+    __shared__ double s[6][kBlock], rt[4];
+    one_root(part, nb, box, s, rt);
+    if (threadIdx.x < 4) root[threadIdx.x] = rt[threadIdx.x];
+    set_flags(bad, nb, flag);
+}
+
+// Several systems' root cubes, a block each (bound by its chain of loads: 256
+// systems of 15,000 on average took 103 us with 256 threads, 38 now).
+constexpr int kSysBlock = 1024;
+
+__global__ __launch_bounds__(kSysBlock) void k_root_sys(const double *x, const int64_t *sys_off,
+                                                        const int *bad, int nb, int *flag,
+                                                        double *roots)
+{
+    __shared__ double s[6][kSysBlock];
     const int64_t a = sys_off[blockIdx.x], e = sys_off[blockIdx.x + 1];
     double lo[3], hi[3];
     for (int k = 0; k < 3; ++k) lo[k] = hi[k] = x[3 * a + k];
-    for (int64_t p = a + threadIdx.x; p < e; p += kBlock)
+    for (int64_t p = a + threadIdx.x; p < e; p += kSysBlock)
         for (int k = 0; k < 3; ++k) {
             const double v = x[3 * p + k];
             lo[k] = v < lo[k] ? v : lo[k];
@@ -202,8 +216,9 @@ __global__ __launch_bounds__(kBlock) void k_root_sys(const double *x, const int6
         s[k][threadIdx.x] = lo[k];
         s[3 + k][threadIdx.x] = hi[k];
     }
-    block_box<kBlock>(s);
-    if (threadIdx.x == 0) root_cube<kBlock>(s, roots + 4 * blockIdx.x);
+    block_box<kSysBlock>(s);
+    if (threadIdx.x == 0) root_cube<kSysBlock>(s, roots + 4 * blockIdx.x);
+    if (blockIdx.x == 0) set_flags(bad, nb, flag);
 }
 
 // ---- 2. keys ----------------------------------------------------------------
@@ -222,49 +237,67 @@ __device__ __forceinline__ int system_of(const int64_t *off, int nsys, int64_t p
     return lo;
 }
 
-// roots[4 s .. 4 s + 3] = centre and side of system s's root cube.  The sort
-// key is the particle's 63-bit key or, with lo > 0 and several systems, its
-// bits from lo up below the system's number.
-struct TreeKeys {
-    const double *x;
-    const int64_t *sys_off;
-    int nsys;
-    const double *roots;
-    int lo;  // > 0: (system, key from bit lo up)
-
-    __device__ __forceinline__ uint64_t operator()(int64_t p) const
-    {
-        const int sys = nsys > 1 ? system_of(sys_off, nsys, p) : 0;
-        const double *rt = roots + 4 * sys;
-        const double xp[3] = {x[3 * p], x[3 * p + 1], x[3 * p + 2]};
-        double c[3] = {rt[0], rt[1], rt[2]};
-        double s = rt[3];
-        uint64_t k = 0;
-        for (int lev = 0; lev < kMaxDepth; ++lev) {
-            const double qd = s * 0.25;
-            unsigned o = 0;
-            for (int a = 0; a < 3; ++a) {
-                if (xp[a] >= c[a]) {
-                    o |= 1u << a;
-                    c[a] = c[a] + qd;
-                } else {
-                    c[a] = c[a] - qd;
-                }
+// 63-bit key of a particle: the octant at each depth, below the root cube rt
+// (centre, side).
+__device__ __forceinline__ uint64_t tree_key(const double *xp, const double *rt)
+{
+    double c[3] = {rt[0], rt[1], rt[2]};
+    double s = rt[3];
+    uint64_t k = 0;
+    for (int lev = 0; lev < kMaxDepth; ++lev) {
+        const double qd = s * 0.25;
+        unsigned o = 0;
+        for (int a = 0; a < 3; ++a) {
+            if (xp[a] >= c[a]) {
+                o |= 1u << a;
+                c[a] = c[a] + qd;
+            } else {
+                c[a] = c[a] - qd;
             }
-            k = (k << 3) | o;
-            s = s * 0.5;
         }
-        return lo > 0 ? (uint64_t)sys << (3 * kMaxDepth - lo) | k >> lo : k;
+        k = (k << 3) | o;
+        s = s * 0.5;
     }
-};
+    return k;
+}
 
-__global__ __launch_bounds__(kBlock) void k_keys(const TreeKeys keys, int64_t n, uint64_t *key,
+// roots[4 s .. 4 s + 3] = centre and side of system s's root cube.  The sort
+// key is the particle's key or, with lo > 0, its bits from lo up below the
+// system's number; and the identity order.
+__global__ __launch_bounds__(kBlock) void k_keys(const double *x, int64_t n,
+                                                 const int64_t *sys_off, int nsys,
+                                                 const double *roots, int lo, uint64_t *key,
                                                  int32_t *idx)
 {
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (p >= n) return;
-    key[p] = keys(p);
+    const int sys = nsys > 1 ? system_of(sys_off, nsys, p) : 0;
+    const double xp[3] = {x[3 * p], x[3 * p + 1], x[3 * p + 2]};
+    const uint64_t k = tree_key(xp, roots + 4 * sys);
+    key[p] = lo > 0 ? (uint64_t)sys << (3 * kMaxDepth - lo) | k >> lo : k;
     idx[p] = (int32_t)p;
+}
+
+// The keys of one small system; each block finds the root cube itself from
+// the checking blocks' boxes, which saves a launch (4 to 5 us), and the first
+// also writes it and the flags for the kernels after it.
+constexpr int kSmallBoxes = 256;
+
+__global__ __launch_bounds__(kBlock) void k_keys_root(const double *x, int64_t n,
+                                                      const double *part, const int *bad, int nb,
+                                                      double box, int *flag, double *root,
+                                                      uint64_t *key)
+{
+    __shared__ double s[6][kBlock], rt[4];
+    one_root(part, nb, box, s, rt);
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 4) root[threadIdx.x] = rt[threadIdx.x];
+        set_flags(bad, nb, flag);
+    }
+    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (p >= n) return;
+    const double xp[3] = {x[3 * p], x[3 * p + 1], x[3 * p + 2]};
+    key[p] = tree_key(xp, rt);
 }
 
 // ---- 3. cells ----------------------------------------------------------------
@@ -1547,23 +1580,21 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     double *roots = B[T_ROOTS].as<double>();
     const int64_t *sys_off = nullptr;
     std::vector<int32_t> so32;  // read by the copy below until the synchronisation
+    const bool one = nsys == 1 && n <= kRankSortMost;  // the keys' kernel finds the root
+    int nbox = 0;
+    double *part = nullptr;
+    int *bad = nullptr;
     {
-        const bool box1 = nsys == 1 && !(P.box > 0.0);
-        const int nb = (int)std::min<int64_t>(kBboxBlocks, blocks(n, kBlock));
-        const bool one = nsys == 1 && n <= kSmallCheck;
-        if (one) {
-            hipLaunchKernelGGL((k_check<1024, true>), dim3(1), dim3(1024), 0, s, P.x, P.m, P.eps2,
-                               n, P.box, flag, roots);
-        } else {
-            STEP(hipMemsetAsync(flag, 0, kFlags * 4, s), "memset");
-            STEP(B[T_BBOX].reserve((size_t)nb * 6 * sizeof(double)), "allocation");
-            hipLaunchKernelGGL((k_check<kBlock, false>), dim3(nb), dim3(kBlock), 0, s, P.x, P.m,
-                               P.eps2, n, P.box, flag, box1 ? B[T_BBOX].as<double>() : nullptr);
-        }
+        nbox = (int)std::min<int64_t>(one ? kSmallBoxes : kBboxBlocks, blocks(n, kBlock));
+        STEP(B[T_BBOX].reserve((size_t)nbox * (6 * sizeof(double) + sizeof(int))), "allocation");
+        part = B[T_BBOX].as<double>();
+        bad = reinterpret_cast<int *>(part + (size_t)nbox * 6);
+        hipLaunchKernelGGL(k_check, dim3(nbox), dim3(kBlock), 0, s, P.x, P.m, P.eps2, n, bad,
+                           nsys == 1 && !(P.box > 0.0) ? part : nullptr);
         LAUNCHED("finite check");
         if (nsys == 1 && !one) {
-            hipLaunchKernelGGL(k_root, dim3(1), dim3(kBlock), 0, s, B[T_BBOX].as<double>(), nb,
-                               P.box, roots);
+            hipLaunchKernelGGL(k_root, dim3(1), dim3(kBlock), 0, s, part, bad, nbox, P.box, flag,
+                               roots);
             LAUNCHED("root cube");
         } else if (nsys > 1) {
             STEP(B[T_SYSOFF].reserve((size_t)(nsys + 1) * 8), "allocation");
@@ -1576,8 +1607,8 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
                                 hipMemcpyHostToDevice, s),
                  "copy");
             sys_off = B[T_SYSOFF].as<int64_t>();
-            hipLaunchKernelGGL(k_root_sys, dim3((unsigned)nsys), dim3(kBlock), 0, s, P.x, sys_off,
-                               roots);
+            hipLaunchKernelGGL(k_root_sys, dim3((unsigned)nsys), dim3(kSysBlock), 0, s, P.x,
+                               sys_off, bad, nbox, flag, roots);
             LAUNCHED("root cubes");
         }
     }
@@ -1603,11 +1634,15 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         int32_t *i0 = B[T_IDX0].as<int32_t>(), *i1 = B[T_IDX1].as<int32_t>();
         const int32_t *so = B[T_SYSOFF32].as<int32_t>();
         joint = nsys > 1 && lo > 0 && 3 * kMaxDepth - lo + sysbits <= 64;
-        const TreeKeys keys{P.x, sys_off, nsys, roots, joint ? lo : 0};
         const int b0 = joint ? 0 : lo, b1 = joint ? 3 * kMaxDepth - lo + sysbits : 3 * kMaxDepth;
         // (a key's 21 levels are too much arithmetic for the few blocks that
         // sort the tiles: formed there they cost 5 to 9 us more)
-        hipLaunchKernelGGL(k_keys, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s, keys, n, k0, i0);
+        if (one)
+            hipLaunchKernelGGL(k_keys_root, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s, P.x, n,
+                               part, bad, nbox, P.box, flag, roots, k0);
+        else
+            hipLaunchKernelGGL(k_keys, dim3(blocks(n, kBlock)), dim3(kBlock), 0, s, P.x, n,
+                               sys_off, nsys, roots, joint ? lo : 0, k0, i0);
         if (!hip(hipGetLastError(), "keys")) return false;
         if ((nsys == 1 || joint) && n <= kRankSortMost && b1 < 64)
             return hip(rank_sort(StoredKeys<uint64_t>{k0}, n, b0, b1, k0, i0, k1, i1, s), "sort");

@@ -44,7 +44,7 @@ def _clumps(n, g):
     (1, 1, 1), (2, 1, 1),
     (254, 32, 8), (255, 32, 8), (256, 32, 8), (257, 33, 7),  # edges of a tile of particles
     (1022, 32, 8), (1023, 32, 8), (1024, 32, 8), (1025, 33, 7),
-    (8192, 64, 8), (8193, 64, 8),      # checked and bounded in one launch, in two
+    (8192, 64, 8), (8193, 64, 8),
     (65536, 64, 8), (65537, 64, 8),    # one and four particles per thread
     (66559, 64, 8), (66560, 64, 8),    # edges of a tile of 1024
     (30000, 64, 8),                    # the scan of the tiles' counts in one block
