@@ -367,6 +367,17 @@ struct bhq_ctx {
     //     2^20), 64 274 / 277 (cube 2^18);
     //   FP32 monopole (8 waves): 16 2824 / 2394, 58 903 / 849, 64 182 / 173;
     //   FP64 quadrupole: 15 574 / 538, 16 4575 / 4294, 31 7083 / 7156.
+    // Blocks of 512 divide groups of more than 60 with less left over (a group
+    // of 140 keeps 73 % of the lanes of 256 busy, 94 % of 512), but have twice
+    // the slices to sum and longer blocks, which does not pay where both the
+    // groups are small and the launch is short.  Quadrupole, 256 against 512:
+    //   FP32 (us): 1553 groups of 64 222 / 191, 652 of 118 227 / 192, 2368 of
+    //     105 174 / 158, 12860 of 72 1335 / 1310, 18351 of 98 2675 / 2629,
+    //     288 of 178 103 / 94, 2496 of 213 1140 / 926; but 512 of 69 32 / 35,
+    //     951 of 33 51 / 61, 32768 of 49 775 / 853;
+    //   FP64: 2318 of 67 658 / 636, 1415 of 89 220 / 200, 1249 of 135 1576 /
+    //     1065, 64 of 221 96 / 78, 2496 of 207 877 / 770; but 391 of 111 147 /
+    //     169, 288 of 94 66 / 73, 19101 of 49 2757 / 2942.
     // The split kernels keep two (in FP64 one per thread is half as fast); in
     // FP32 their six waves (80 registers) take 749 us against 807 (lattice
     // 96^3) and 4244 against 4550 (160^3).
@@ -380,7 +391,11 @@ struct bhq_ctx {
             return c;
         }
         c.jsplit = auto_jsplit;
-        if (precision == BHQ_FP64) {
+        if (kernel != BHQ_MONO && (mean > 128.0 || (mean > 60.0 && ng >= 600))) {
+            c.block = 512;
+            c.i_per_thread = precision == BHQ_FP64 ? 2 : 1;
+            c.waves_per_eu = precision == BHQ_FP64 ? 0 : 6;
+        } else if (precision == BHQ_FP64) {
             c.i_per_thread = mean <= 32.0 ? 1 : 2;
         } else if (kernel == BHQ_MONO) {
             c.i_per_thread = mean <= 64.0 ? 1 : 2;

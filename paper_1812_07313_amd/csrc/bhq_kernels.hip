@@ -1,16 +1,16 @@
 // bhq_kernels.hip -- force kernels for gfx950 (CDNA4).
 //
-// One block (256 or 128 threads) evaluates one group's interaction list (the
-// modified tree algorithm of Kodama & Ishiyama, Sec. 3.4: all i-particles of
-// a group share one list).  Each active thread owns one or two i-particles
-// (two: every LDS broadcast feeds two interactions).  The list is
-// streamed through LDS in tiles of up to 256 entries: every thread loads one
+// One block (BS = 512, 256 or 128 threads) evaluates one group's interaction
+// list (the modified tree algorithm of Kodama & Ishiyama, Sec. 3.4: all
+// i-particles of a group share one list).  Each active thread owns one or two
+// i-particles (two: every LDS broadcast feeds two interactions).  The list is
+// streamed through LDS in tiles of up to BS entries: every thread loads one
 // entry with coalesced FP64 SoA reads, forms its position relative to the
 // group's FP64 reference point, converts it to the working precision and
 // stores it in LDS; the threads then read entries back as broadcasts.
 //
-// Small groups (ni < 256) split each tile between S = 256 / ni slices of
-// ni threads.  A tile then holds T = S * floor(256 / S) entries and slice s
+// Small groups (ni < BS) split each tile between S = BS / ni slices of
+// ni threads.  A tile then holds T = S * floor(BS / S) entries and slice s
 // takes the contiguous chunk [s * it, (s + 1) * it) of it (the cell loop
 // of the split kernels: the interleaved entries s, s + S, ...); the last
 // tile is padded to a multiple of S with zero-mass entries, so every thread
@@ -982,9 +982,18 @@ hipError_t launch_wpe(const ForceArgs &A, const LaunchCfg &cfg, hipStream_t s)
     return launch_one<R, KIND, P, 256, IB, 0>(A, cfg, s);
 }
 
+// Block 512 has the instances that a default launch chooses: cells with the
+// quadrupole, one i-particle per thread in FP32 (6 waves per SIMD), two in
+// FP64.
 template <typename R, int KIND, bool P>
 hipError_t launch_bs(const ForceArgs &A, const LaunchCfg &cfg, hipStream_t s)
 {
+    if constexpr (KIND == kQuad || KIND == kQuadSoft) {
+        constexpr bool kFloat = std::is_same<R, float>::value;
+        if (cfg.block == 512)
+            return launch_one<R, KIND, P, 512, kFloat ? 1 : 2, kFloat ? 6 : 0>(A, cfg, s);
+    }
+    if (cfg.block == 512) return hipErrorInvalidValue;
     if (cfg.i_per_thread == 2)
         return cfg.block == 128 ? launch_one<R, KIND, P, 128, 2, 0>(A, cfg, s)
                                 : launch_wpe<R, KIND, P, 2>(A, cfg, s);
@@ -1151,7 +1160,7 @@ hipError_t launch_force(int kernel, int precision, const ForceArgs &A,
     if (A.ng > 0x7fffffff || A.nslots > 0x7fffffff) return hipErrorInvalidValue;
     if (A.xcds < 0 || A.xcds > kQueueWords) return hipErrorInvalidValue;
     if (A.xcds > 0 && A.nslots % A.xcds != 0) return hipErrorInvalidValue;
-    if (cfg.block != 128 && cfg.block != 256) return hipErrorInvalidValue;
+    if (cfg.block != 128 && cfg.block != 256 && cfg.block != 512) return hipErrorInvalidValue;
     if (cfg.i_per_thread != 1 && cfg.i_per_thread != 2) return hipErrorInvalidValue;
     if (cfg.persistent && (!A.queue || cfg.num_cu <= 0))
         return hipErrorInvalidValue;

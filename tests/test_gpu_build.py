@@ -218,6 +218,8 @@ def test_upload_after_refusals():
     ("cube", 65536, 128),      # mean group sizes across the choices of
     ("cube", 30000, 128),      # i-particles per thread: 16, 58, 128
     ("cube", 524288, 256),
+    ("cube", 24001, 512),      # blocks of 512: few large groups (375),
+    ("plummer", 61003, 256),   # many of 64
 ])
 def test_default_launch_shapes(kernel, dist, n, ncrit):
     """The launch shape that a context without bhq_set_tuning chooses, against
