@@ -378,6 +378,10 @@ struct bhq_ctx {
     //   FP64: 2318 of 67 658 / 636, 1415 of 89 220 / 200, 1249 of 135 1576 /
     //     1065, 64 of 221 96 / 78, 2496 of 207 877 / 770; but 391 of 111 147 /
     //     169, 288 of 94 66 / 73, 19101 of 49 2757 / 2942.
+    // Launches of more than 2^21 i-particles keep blocks of 256 and two per
+    // thread: their results are held to that shape bit for bit (512 would not
+    // gain there, clustered 2^22 9258 / 9435; one per thread would gain 2 to
+    // 3 % on small groups, 256 systems 5452 / 5268).
     // The split kernels keep two (in FP64 one per thread is half as fast); in
     // FP32 their six waves (80 registers) take 749 us against 807 (lattice
     // 96^3) and 4244 against 4550 (160^3).
@@ -391,6 +395,7 @@ struct bhq_ctx {
             return c;
         }
         c.jsplit = auto_jsplit;
+        if (ni > (int64_t)1 << 21) return c;
         if (kernel != BHQ_MONO && (mean > 128.0 || (mean > 60.0 && ng >= 600))) {
             c.block = 512;
             c.i_per_thread = precision == BHQ_FP64 ? 2 : 1;
