@@ -52,21 +52,21 @@ FLOPS_PP = 20
 FLOPS_PC = {bhq.QUAD: 53, bhq.MONO: 20, bhq.QUAD_SOFT: 55}
 # FP32 split kernels, per term inside the cutoff (FMA = 2, rsqrt and fract 1,
 # the table index conversion 0): particle term 36 (separation 8, rsqrt 1,
-# r 1, table variable and fraction 2, erfc and g by Horner 12, the rest 12);
-# quadrupole cell term 97 (the same start, four Horner functions 24, D1..D3,
+# r 1, table variable and fraction 2, erfc, its derivative and g 12, the rest
+# 12);
+# quadrupole cell term 97 (the same start, erfc to k and G2, G3 24, D1..D3,
 # Q d and d.Q.d, the trace terms and the accumulation); monopole cell 37.
 # Masked terms (beyond the cutoff) do no work of the method and are not
 # counted: the split roofline is priced on the pairs bhq_count_live finds.
 FLOPS_SPLIT_PP = 36
 FLOPS_SPLIT_PC = {bhq.SPLIT_QUAD: 97, bhq.SPLIT_MONO: 37}
-# FP64 split kernels: the same terms with the radial functions from degree-9
-# (exp(-u^2)) and degree-7 (erfcx) polynomials instead of cubics.  Particle
-# term 62 (u, table variable and fraction 3, Horner 18 + 14, erfc, the
-# e^{-u^2}/sqrt(pi) factor and g 5, the rest as in FP32); quadrupole cell
-# term 123 (the particle term's radial part plus u^2, h, k, G2 and G3 12,
-# and the FP32 cell term's other 71); monopole cell 63.
-FLOPS_SPLIT64_PP = 62
-FLOPS_SPLIT64_PC = {bhq.SPLIT_QUAD: 123, bhq.SPLIT_MONO: 63}
+# FP64 split kernels: the same terms with the radial functions from a degree-9
+# polynomial of erfc and its derivative instead of a cubic's.  Particle term 60
+# (table variable and fraction 2, Horner 18 + 16, g 2, the rest as in FP32);
+# quadrupole cell term 121 (the particle term's radial part plus u^2, h, k, G2
+# and G3 12, and the FP32 cell term's other 71); monopole cell 61.
+FLOPS_SPLIT64_PP = 60
+FLOPS_SPLIT64_PC = {bhq.SPLIT_QUAD: 121, bhq.SPLIT_MONO: 61}
 # the paper's convention for one particle-cell quadrupole interaction
 # (rsqrt counted as 20 flops, Sec. 3.3 and Sec. 5.2)
 PAPER_FLOPS_PC = 71

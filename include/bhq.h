@@ -346,8 +346,14 @@ int bhq_clock_end(bhq_ctx *ctx, double *mhz);
  * The persistent queue, graph replay and waves_per_eu do not change results
  * (bitwise).  block, i_per_thread and jsplit change how a group's lists are
  * split across threads and blocks and so the order of the FP32/FP64 sums
- * (results agree to rounding).  Errors: BHQ_E_ARG for values outside these
- * sets, or waves_per_eu != 0 with block 128. */
+ * (results agree to rounding).  A context whose caller never calls this
+ * chooses its shape at each compute, from the kernel, the precision, the group
+ * sizes and the lists' costs (up to 2^21 i-particles; the same lists always
+ * get the same shape): blocks of 256 or 512, one or two i-particles per thread,
+ * up to eight parts with up to 16 MiB of the context's memory, taken when the
+ * lists are set or built.  bhq_get_tuning returns the values above all the
+ * same.  Errors: BHQ_E_ARG for values outside these sets, or
+ * waves_per_eu != 0 with block 128. */
 int bhq_set_tuning(bhq_ctx *ctx, int block, int i_per_thread, int blocks_per_cu,
                    int persistent, int use_graph, int jsplit, int waves_per_eu);
 
