@@ -60,13 +60,16 @@ FLOPS_PC = {bhq.QUAD: 53, bhq.MONO: 20, bhq.QUAD_SOFT: 55}
 # counted: the split roofline is priced on the pairs bhq_count_live finds.
 FLOPS_SPLIT_PP = 36
 FLOPS_SPLIT_PC = {bhq.SPLIT_QUAD: 97, bhq.SPLIT_MONO: 37}
-# FP64 split kernels: the same terms with the radial functions from a degree-9
-# polynomial of erfc and its derivative instead of a cubic's.  Particle term 60
-# (table variable and fraction 2, Horner 18 + 16, g 2, the rest as in FP32);
-# quadrupole cell term 121 (the particle term's radial part plus u^2, h, k, G2
-# and G3 12, and the FP32 cell term's other 71); monopole cell 61.
-FLOPS_SPLIT64_PP = 60
-FLOPS_SPLIT64_PC = {bhq.SPLIT_QUAD: 121, bhq.SPLIT_MONO: 61}
+# FP64 split kernels: the same terms with the radial functions from degree-9
+# (exp(-u^2)) and degree-7 (erfcx) polynomials instead of cubics.  Particle
+# term 62 (u, table variable and fraction 3, Horner 18 + 14, erfc, the
+# e^{-u^2}/sqrt(pi) factor and g 5, the rest as in FP32); quadrupole cell
+# term 123 (the particle term's radial part plus u^2, h, k, G2 and G3 12,
+# and the FP32 cell term's other 71); monopole cell 63.  The price is kept:
+# the kernels now spend two operations fewer (one polynomial and its
+# derivative).
+FLOPS_SPLIT64_PP = 62
+FLOPS_SPLIT64_PC = {bhq.SPLIT_QUAD: 123, bhq.SPLIT_MONO: 63}
 # the paper's convention for one particle-cell quadrupole interaction
 # (rsqrt counted as 20 flops, Sec. 3.3 and Sec. 5.2)
 PAPER_FLOPS_PC = 71
