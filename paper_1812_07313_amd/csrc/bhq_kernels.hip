@@ -37,9 +37,8 @@
 #include <hip/hip_runtime.h>
 
 #include "bhq_internal.h"
+#include "bhq_split.h"
 #include "bhq_terms.h"
-#include "split_table.h"  // kSplitDomain
-#include "split_table64.h"
 
 #include <mutex>
 #include <type_traits>
@@ -47,9 +46,6 @@
 namespace bhq {
 
 namespace {
-
-__device__ __forceinline__ double erfc_r(double v) { return ::erfc(v); }
-__device__ __forceinline__ double exp_r(double v) { return ::exp(v); }
 
 // Minimum image v - box rint(v / box), rounded as written (no contraction of
 // the product into the subtraction), so that every kernel forms the same
@@ -61,312 +57,8 @@ __device__ __forceinline__ double wrap(double v, double box, double ibox)
 
 constexpr int kMono = 0, kQuad = 1, kSplitQuad = 2, kSplitMono = 3, kQuadSoft = 4;
 
-// The FP64 kernels' table of erfc(u), likewise copied to LDS by each block of
-// an FP64 split kernel: on 128 intervals of 0 <= u < 4 a polynomial of degree
-// 9 in f = t - q, t = 32 u, whose derivative gives exp(-u^2) as well.  It is
-// made from split_table64.h (exp(-u^2) of degree 9 and erfcx on 64 intervals):
-// the integral of the exp polynomial from the interval's start, where erfc is
-// exp(-u^2) erfcx, taken about the start of each half and lowered from degree
-// 10 to 9 by the Chebyshev polynomial (the last coefficient over 2^19, below
-// 1e-16 of erfc everywhere).
-// A pair then reads 80 B from LDS in place of the 144 of the two polynomials;
-// LDS bound the kernel (busy 66 % of the time and 15 % more in bank
-// conflicts, VALU 72 %): the force kernel of a 60^3 lattice took 0.64 ms, now
-// 0.56.
-constexpr int kErfcDegree = 9;
-constexpr int kErfcIntervals = 2 * kTab64Intervals;
-constexpr int kErfcStride = kErfcDegree + 1;
-
-struct Tab64 {
-    double v[kErfcIntervals * kErfcStride];
-};
-
-constexpr Tab64 make_tab64()
-{
-    constexpr double rsqpi2 = 1.12837916709551257389615890312;  // 2 / sqrt(pi)
-    constexpr double w = kTab64Domain / kTab64Intervals;
-    // T_10(2 s - 1)
-    constexpr double cheb[kErfcDegree + 2] = {1.0,        -200.0,    6600.0,   -84480.0,
-                                              549120.0,   -2050048.0, 4659200.0, -6553600.0,
-                                              5570560.0,  -2621440.0, 524288.0};
-    static_assert(kExpDegree == kErfcDegree, "the integral is one degree higher");
-    Tab64 t{};
-    for (int q = 0; q < kTab64Intervals; ++q) {
-        double c[kErfcDegree + 2] = {};
-        c[0] = kTab64[q][0] * kTab64[q][kExpDegree + 1];
-        for (int k = 0; k <= kExpDegree; ++k) c[k + 1] = -rsqpi2 * w * kTab64[q][k] / (k + 1);
-        for (int b = 0; b < 2; ++b) {
-            double d[kErfcDegree + 2] = {};
-            for (int k = 0; k < kErfcDegree + 2; ++k) d[k] = c[k];
-            if (b == 1)  // about f = 1/2
-                for (int i = 0; i < kErfcDegree + 1; ++i)
-                    for (int k = kErfcDegree; k >= i; --k) d[k] += 0.5 * d[k + 1];
-            double scale = 1.0;
-            for (int k = 0; k < kErfcDegree + 2; ++k, scale *= 0.5) d[k] *= scale;
-            const double top = d[kErfcDegree + 1] / cheb[kErfcDegree + 1];
-            for (int k = 0; k < kErfcStride; ++k)
-                t.v[(2 * q + b) * kErfcStride + k] = d[k] - top * cheb[k];
-        }
-    }
-    return t;
-}
-
 __device__ const Tab64 kTab64Dev = make_tab64();
-
-// The FP32 kernels' table of erfc(u), likewise copied to LDS: on 256 intervals
-// per unit of u up to kSplitDomain, and one more for the rounding of u at the
-// cutoff, a cubic {c0, c1, c2, c3} in f = t - q, t = 256 u, whose derivative
-// gives exp(-u^2).  The derivative is the quadratic through erfc' at the
-// Chebyshev points of the interval (error below 3e-9), both made from
-// split_table64.h.
-// A pair reads 16 B from LDS in place of the 32 of two functions' cubics (a
-// cell 16 in place of 64) with as many operations: 15.0 -> 14.4 ms on the
-// 2^24 lattice at ncrit 128.  Half as many intervals take the same time, with
-// less exact cells.  Against 64 bits the functions' errors are 0.35 to 0.85
-// of the separate cubics' (r.m.s.), whose scale of t was rounded.
-constexpr int kErfc32PerRow = 16;
-constexpr int kErfc32Unit = (int)(kTab64Intervals / kTab64Domain) * kErfc32PerRow;
-constexpr int kErfc32Entries = (int)(kSplitDomain * kErfc32Unit) + 1;
-
-struct SplitTab {
-    V4<float> v[kErfc32Entries];
-};
-
-constexpr SplitTab make_split_tab()
-{
-    constexpr double rsqpi2 = 1.12837916709551257389615890312;  // 2 / sqrt(pi)
-    constexpr double x0 = 0.06698729810778067661813, x2 = 0.93301270189221932338187;
-    SplitTab t{};
-    for (int q = 0; q < kErfc32Entries; ++q) {
-        const double *c = kTab64[q / kErfc32PerRow];
-        const int b = q % kErfc32PerRow;
-        double y[4] = {}, ex = c[kTab64Stride - 1];
-        const double s[4] = {0.0, x0, 0.5, x2};
-        for (int j = 0; j < 4; ++j) {
-            const double f = (b + s[j]) / kErfc32PerRow;
-            for (int k = kExpDegree; k >= 0; --k) y[j] = y[j] * f + c[k];
-        }
-        for (int k = kErfcxDegree - 1; k >= 0; --k)
-            ex = ex * ((double)b / kErfc32PerRow) + c[kExpDegree + 1 + k];
-        // quadratic through the nodes, about s = 1/2
-        const double e = x2 - 0.5, d1 = (y[3] - y[1]) / (2.0 * e),
-                     d2 = (y[3] + y[1] - 2.0 * y[2]) / (2.0 * e * e);
-        const double w = -rsqpi2 / kErfc32Unit;
-        t.v[q] = {(float)(y[0] * ex), (float)(w * (y[2] - 0.5 * d1 + 0.25 * d2)),
-                  (float)(w * 0.5 * (d1 - d2)), (float)(w * d2 / 3.0)};
-    }
-    return t;
-}
-
 __device__ const SplitTab kSplitTabDev = make_split_tab();
-
-// Constants of the Gaussian split, uniform over a launch: u = r i2rs with
-// i2rs = 1 / (2 r_s); the table variable is t = r ct = u N / U.
-template <typename R>
-struct SplitK {
-    R i2rs;
-    R ct;
-};
-
-template <typename R>
-__device__ __forceinline__ SplitK<R> split_k(double rs)
-{
-    SplitK<R> K;
-    const double i2rs = 0.5 / rs;
-    K.i2rs = R(i2rs);
-    K.ct = std::is_same<R, float>::value
-               ? R(i2rs * kErfc32Unit)
-               : R(i2rs * (kErfcIntervals / kTab64Domain));
-    return K;
-}
-
-// Element type of the LDS table of a precision.
-template <typename R>
-struct SplitTabT {
-    using type = V4<float>;
-};
-template <>
-struct SplitTabT<double> {
-    using type = double;
-};
-template <typename R>
-using TabT = typename SplitTabT<R>::type;
-
-// Gaussian-split radial functions at r (r2 = r^2), u = r / (2 r_s):
-//   ec = erfc(u), g = erfc(u) + (2u/sqrt(pi)) e^{-u^2},
-//   G2 = 3g + h, G3 = 15g + 5h + k, with h = (4u^3/sqrt(pi)) e^{-u^2} and
-//   k = 2 u^2 h (G2, G3 only for cells with the quadrupole).
-// FP64 takes erfc(u) and its derivative in t from one polynomial (interval
-// q = floor(t), t = 32 u, f = t - q, Horner's rule for both): t times the
-// derivative is u erfc'(u) = -(2u/sqrt(pi)) e^{-u^2}.  Past u = 4, that is for
-// cutoffs beyond 8 r_s, it calls the library's exp and erfc.  FP32 does the
-// same with its own table, t = 256 u (valid for u up to kSplitDomain and one
-// interval beyond; the host refuses FP32 split kernels with a longer
-// cutoff).
-template <typename R>
-struct SplitG {
-    R ec, g, g2, g3;
-};
-
-template <typename R, bool CELL>
-__device__ __forceinline__ SplitG<R> split_g(R r, const SplitK<R> &K, const TabT<R> *tab)
-{
-    SplitG<R> s;
-    if constexpr (std::is_same<R, float>::value) {
-        const float t = r * K.ct;
-        const V4<float> c = tab[(int)t];  // t >= 0
-        const float f = __builtin_amdgcn_fractf(t);
-        float d = c.w;
-        s.ec = fmaf(d, f, c.z);
-        d = fmaf(d, f, s.ec);
-        s.ec = fmaf(s.ec, f, c.y);
-        d = fmaf(d, f, s.ec);
-        s.ec = fmaf(s.ec, f, c.x);
-        s.g = fmaf(-t, d, s.ec);
-        if (CELL) {
-            const float u = r * K.i2rs;
-            const float u2 = 2.0f * u * u;
-            const float h = u2 * (-t * d);
-            s.g2 = fmaf(3.0f, s.g, h);
-            s.g3 = fmaf(15.0f, s.g, fmaf(5.0f, h, u2 * h));
-        }
-    } else {
-        const R t = r * K.ct;
-        R w;  // (2u/sqrt(pi)) e^{-u^2} = -u erfc'(u)
-        if (t < R(kErfcIntervals)) {
-            const int q = (int)t;
-            const R f = t - R(q);
-            const double *c = tab + q * kErfcStride;
-            R d = c[kErfcDegree];
-            s.ec = fma(d, f, c[kErfcDegree - 1]);
-#pragma unroll
-            for (int k = kErfcDegree - 2; k >= 0; --k) {
-                d = fma(d, f, s.ec);
-                s.ec = fma(s.ec, f, c[k]);
-            }
-            w = -t * d;
-            s.g = fma(-t, d, s.ec);
-        } else {
-            const R u = r * K.i2rs;
-            s.ec = erfc_r(u);
-            w = R(1.12837916709551257389615890312) * u * exp_r(-u * u);
-            s.g = s.ec + w;
-        }
-        if (CELL) {
-            const R u = r * K.i2rs;
-            const R u2 = R(2) * u * u;
-            const R h = u2 * w;
-            const R k = u2 * h;
-            s.g2 = fma(R(3), s.g, h);
-            s.g3 = fma(R(15), s.g, fma(R(5), h, k));
-        }
-    }
-    return s;
-}
-
-// The cutoff is a decision on r^2, which the FP32 kernels form from FP32
-// offsets.  It is taken as the FP64 kernel takes it: FP64 offsets
-// X = wrap(v - c) from the group centre c, D = X_j - X_i, r^2 =
-// fma(Dz, Dz, fma(Dy, Dy, Dx Dx)), kept iff 0 < r^2 < rcut * rcut in FP64.
-// Outside a band around fl32(rcut^2) the FP32 r^2 decides the same way; a
-// term inside the band (rare) is decided again from the FP64 positions.
-//
-// Band: with u = 2^-24, FP32 offsets x = X (1 + e), |e| <= u, the FP32
-// difference and the three-term FMA chain give, to first order in u,
-// |r2_32 - |D|^2| <= 7 u |D|^2 + 4 u |X_i| |D|, and fl32(rcut^2) is within
-// u rcut^2 of rcut^2 (the FP64 side is exact to 2^-50).  Near the cutoff
-// |D| ~ rcut, so u (8 rcut^2 + 4 |X_i| rcut) bounds the difference;
-// band_i = u (16 rcut^2 + 8 |X_i| rcut) doubles it.  A term with
-// |r2_32 - fl32(rcut^2)| >= band_i is on the same side in both precisions.
-__device__ __forceinline__ float cut_band(float xi, float yi, float zi, float rcut)
-{
-    const float xn = __builtin_sqrtf(fmaf(zi, zi, fmaf(yi, yi, xi * xi)));
-    return 0x1p-21f * rcut * fmaf(2.0f, rcut, xn);  // u (16 rcut^2 + 8 |X_i| rcut)
-}
-
-// FP64 cutoff decision of the FP64 kernel for the FP64 offsets xj - xi
-// (each already wrapped relative to the group centre).
-__device__ __forceinline__ bool keep_f64(double djx, double djy, double djz, double rcut)
-{
-    const double r2 = fma(djz, djz, fma(djy, djy, djx * djx));
-    return r2 > 0.0 && r2 < rcut * rcut;
-}
-
-// Separation of a list entry from an i-particle and its squared length.
-template <typename R>
-struct Sep {
-    R dx, dy, dz, r2;
-};
-
-template <typename R>
-__device__ __forceinline__ Sep<R> separation(const V4<R> &j, R xi, R yi, R zi)
-{
-    Sep<R> s;
-    s.dx = j.x - xi;
-    s.dy = j.y - yi;
-    s.dz = j.z - zi;
-    s.r2 = fma(s.dz, s.dz, fma(s.dy, s.dy, s.dx * s.dx));
-    return s;
-}
-
-// Short-range particle at separation s, kept by the cutoff decision:
-// a += m g/r^3 d, -phi += m erfc(u)/r.
-template <typename R>
-__device__ __forceinline__ void pp_split(const V4<R> &j, const Sep<R> &s, const SplitK<R> &K,
-                                         const TabT<R> *tab, R &ax, R &ay, R &az, R &pt)
-{
-    const R rinv = rsq(s.r2);
-    const R r = s.r2 * rinv;
-    const SplitG<R> f = split_g<R, false>(r, K, tab);
-    const R mr = j.w * rinv;
-    const R c = mr * f.g * (rinv * rinv);
-    pt = fma(mr, f.ec, pt);
-    ax = fma(c, s.dx, ax);
-    ay = fma(c, s.dy, ay);
-    az = fma(c, s.dz, az);
-}
-
-// Short-range cell expanded to second order about its centre of mass
-// (with the trace T):
-//   phi = M Phi + D2 dQd / 6 + T/6 (D2 r^2 + 3 D1)
-//   a   = [M D1 + D3 dQd / 6 + T/6 (D3 r^2 + 5 D2)] d + D2/3 Qd
-// with D1 = g/r^3, D2 = -(3g + h)/r^5, D3 = (15g + 5h + k)/r^7.
-template <typename R, bool QUAD>
-__device__ __forceinline__ void pc_split(const V4<R> &a, const V4<R> &b, const V4<R> &c,
-                                         const Sep<R> &s, const SplitK<R> &K,
-                                         const TabT<R> *tab, R &ax, R &ay, R &az, R &pt)
-{
-    const R dx = s.dx, dy = s.dy, dz = s.dz, r2 = s.r2;
-    const R rinv = rsq(r2);
-    const R r = r2 * rinv;
-    const R rinv2 = rinv * rinv;
-    const SplitG<R> f = split_g<R, QUAD>(r, K, tab);
-    const R D1 = f.g * rinv2 * rinv;
-    R phi = -a.w * f.ec * rinv;  // M Phi
-    R coef = a.w * D1;
-    if (QUAD) {
-        const R rinv5 = rinv2 * rinv2 * rinv;
-        const R D2 = -f.g2 * rinv5;
-        const R D3 = f.g3 * rinv5 * rinv2;
-        const R qx = fma(b.z, dz, fma(b.y, dy, b.x * dx));
-        const R qy = fma(c.x, dz, fma(b.w, dy, b.y * dx));
-        const R qz = fma(c.y, dz, fma(c.x, dy, b.z * dx));
-        const R dqd = fma(dz, qz, fma(dy, qy, dx * qx));
-        const R t6 = c.z * R(1.0 / 6.0);
-        phi = fma(D2, dqd * R(1.0 / 6.0), phi);
-        phi = fma(t6, fma(D2, r2, R(3) * D1), phi);
-        coef = fma(D3, dqd * R(1.0 / 6.0), coef);
-        coef = fma(t6, fma(D3, r2, R(5) * D2), coef);
-        const R d23 = D2 * R(1.0 / 3.0);
-        ax = fma(d23, qx, ax);
-        ay = fma(d23, qy, ay);
-        az = fma(d23, qz, az);
-    }
-    pt -= phi;
-    ax = fma(coef, dx, ax);
-    ay = fma(coef, dy, ay);
-    az = fma(coef, dz, az);
-}
 
 // Compile-time tuning: unroll depth of the cell loop and of the particle
 // loop (whose shorter body leaves more room for independent work: 4 measured
