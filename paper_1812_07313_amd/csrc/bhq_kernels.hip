@@ -321,7 +321,8 @@ __device__ __forceinline__ void process_group(const ForceArgs &A, int64_t g, int
                                 const Sep<R> sp = separation(jv, xi[u], yi[u], zi[u]);
                                 if (sp.r2 >= lim[u] && sp.r2 < hi[u] &&
                                     exact(u, p0 + base, slice * it + k, false))
-                                    pp_split(jv, sp, K, tab, bx[u], by[u], bz[u], bp[u]);
+                                    pp_split(jv, within_cutoff(sp, rcut2), K, tab, bx[u],
+                                             by[u], bz[u], bp[u]);
                             }
                         }
                     }
@@ -436,8 +437,9 @@ __device__ __forceinline__ void process_group(const ForceArgs &A, int64_t g, int
                                 const Sep<R> sp = separation(ja, xi[u], yi[u], zi[u]);
                                 if (sp.r2 >= lim[u] && sp.r2 < hi[u] &&
                                     exact(u, c0 + base, e, true))
-                                    pc_split<R, KIND == kSplitQuad>(ja, jb, jc, sp, K, tab,
-                                                                    bx[u], by[u], bz[u], bp[u]);
+                                    pc_split<R, KIND == kSplitQuad>(
+                                        ja, jb, jc, within_cutoff(sp, rcut2), K, tab, bx[u],
+                                        by[u], bz[u], bp[u]);
                             }
                         }
                     }

@@ -261,6 +261,17 @@ __device__ __forceinline__ Sep<R> separation(const V4<R> &j, R xi, R yi, R zi)
     return s;
 }
 
+// A separation that the FP64 decision kept: its FP32 r^2 may still exceed
+// rcut^2 (by the rounding of the offsets, which is as large as the
+// i-particle is far from the group's centre), and with r_cut at the end of the
+// table's domain it would lead out of the table.
+template <typename R>
+__device__ __forceinline__ Sep<R> within_cutoff(Sep<R> s, R rcut2)
+{
+    s.r2 = s.r2 < rcut2 ? s.r2 : rcut2;
+    return s;
+}
+
 // Short-range particle at separation s, kept by the cutoff decision:
 // a += m g/r^3 d, -phi += m erfc(u)/r.
 template <typename R>

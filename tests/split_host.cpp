@@ -1,0 +1,66 @@
+// The split kernels' operations (csrc/bhq_split.h) compiled for the host, for
+// test_split_host.py.
+#include <cstring>
+#include <limits>
+#include <random>
+#include <vector>
+
+#include "bhq_split.h"
+
+using namespace bhq;
+
+namespace {
+
+// An FP32 table as a block of a split kernel holds it, with NaN behind it.
+const V4<float> *guarded_table()
+{
+    static std::vector<V4<float>> v;
+    if (v.empty()) {
+        static const SplitTab t = make_split_tab();
+        const float nan = std::numeric_limits<float>::quiet_NaN();
+        const size_t n = sizeof(t.v) / sizeof(t.v[0]);
+        v.assign(t.v, t.v + n);
+        v.resize(2 * n, V4<float>{nan, nan, nan, nan});
+    }
+    return v.data();
+}
+
+}  // namespace
+
+extern "C" {
+
+// n pairs, offsets xi, xj (FP64, from the group centre): the FP32 split
+// kernels' acceleration (a[4k .. 4k + 2]) and potential (negative, a[4k + 3])
+// of a unit mass at xj on xi, as a particle (cell 0) or as a cell without
+// moments (cell 1); kept[k]: 0 outside the cutoff, 1 inside, 2 inside by the
+// FP64 decision.
+void split_pairs_f32(int n, const double *xi, const double *xj, double rs, double rcut, int cell,
+                     float *a, int *kept)
+{
+    const V4<float> *tab = guarded_table();
+    const SplitK<float> K = split_k<float>(rs);
+    const float rcut2 = (float)(rcut * rcut);
+    for (int k = 0; k < n; ++k) {
+        const double *p = xi + 3 * k, *q = xj + 3 * k;
+        const V4<float> j = {(float)q[0], (float)q[1], (float)q[2], 1.0f};
+        const float x = (float)p[0], y = (float)p[1], z = (float)p[2];
+        const float band = cut_band(x, y, z, (float)rcut);
+        Sep<float> s = separation(j, x, y, z);
+        kept[k] = s.r2 > 0.0f && s.r2 < rcut2 - band ? 1 : 0;
+        if (s.r2 >= rcut2 - band && s.r2 < rcut2 + band &&
+            keep_f64(q[0] - p[0], q[1] - p[1], q[2] - p[2], rcut)) {
+            s = within_cutoff(s, rcut2);
+            kept[k] = 2;
+        }
+        float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (kept[k] && cell) {
+            const V4<float> zero = {0.0f, 0.0f, 0.0f, 0.0f};
+            pc_split<float, true>(j, zero, zero, s, K, tab, o[0], o[1], o[2], o[3]);
+        } else if (kept[k]) {
+            pp_split(j, s, K, tab, o[0], o[1], o[2], o[3]);
+        }
+        std::memcpy(a + 4 * k, o, sizeof(o));
+    }
+}
+
+}  // extern "C"
