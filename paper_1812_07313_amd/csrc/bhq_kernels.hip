@@ -497,12 +497,12 @@ __device__ __forceinline__ void process_group(const ForceArgs &A, int64_t g, int
     }
 }
 
-// The split kinds keep their precision's table of erfc in LDS.
+// The split kinds keep their precision's table of radial functions in LDS.
 template <typename R, int KIND>
 constexpr int split_tab_size()
 {
     return KIND != kSplitQuad && KIND != kSplitMono ? 1
-           : std::is_same<R, float>::value          ? kErfc32Entries
+           : std::is_same<R, float>::value          ? kSplitFuncs * kSplitEntries
                                                     : kErfcIntervals * kErfcStride;
 }
 
@@ -511,7 +511,7 @@ __device__ __forceinline__ void load_split_tab(TabT<R> *tab)
 {
     if constexpr (split_tab_size<R, KIND>() > 1) {
         if constexpr (std::is_same<R, float>::value) {
-            for (int k = threadIdx.x; k < kErfc32Entries; k += BS)
+            for (int k = threadIdx.x; k < kSplitFuncs * kSplitEntries; k += BS)
                 tab[k] = kSplitTabDev.v[k];
         } else {
             for (int k = threadIdx.x; k < kErfcIntervals * kErfcStride; k += BS)

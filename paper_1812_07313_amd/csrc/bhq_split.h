@@ -9,7 +9,7 @@
 #include <type_traits>
 
 #include "bhq_terms.h"
-#include "split_table.h"  // kSplitDomain
+#include "split_table.h"
 #include "split_table64.h"
 
 namespace bhq {
@@ -67,48 +67,24 @@ constexpr Tab64 make_tab64()
     return t;
 }
 
-// The FP32 kernels' table of erfc(u), likewise copied to LDS: on 256 intervals
-// per unit of u up to kSplitDomain, and one more for the rounding of u at the
-// cutoff, a cubic {c0, c1, c2, c3} in f = t - q, t = 256 u, whose derivative
-// gives exp(-u^2).  The derivative is the quadratic through erfc' at the
-// Chebyshev points of the interval (error below 3e-9), both made from
-// split_table64.h.
-// A pair reads 16 B from LDS in place of the 32 of two functions' cubics (a
-// cell 16 in place of 64) with as many operations: 15.0 -> 14.4 ms on the
-// 2^24 lattice at ncrit 128.  Half as many intervals take the same time, with
-// less exact cells.  Against 64 bits the functions' errors are 0.35 to 0.85
-// of the separate cubics' (r.m.s.), whose scale of t was rounded.
-constexpr int kErfc32PerRow = 16;
-constexpr int kErfc32Unit = (int)(kTab64Intervals / kTab64Domain) * kErfc32PerRow;
-constexpr int kErfc32Entries = (int)(kSplitDomain * kErfc32Unit) + 1;
-
+// The FP32 table of the split radial functions (split_table.h) in device
+// memory, one V4 {c0, c1, c2, c3} per function and interval; each block of
+// a split kernel copies it to LDS, where lanes read their own intervals.  One
+// cubic of erfc on 641 intervals whose derivative gives the other functions
+// reads half as much from LDS (a cell a quarter) and was 2 to 4 % faster, but
+// its errors were larger: 1.1 (erfc) to 1.25 (G3) times these cubics' r.m.s.
+// over random r_s.
 struct SplitTab {
-    V4<float> v[kErfc32Entries];
+    V4<float> v[kSplitFuncs * kSplitEntries];
 };
 
 constexpr SplitTab make_split_tab()
 {
-    constexpr double rsqpi2 = 1.12837916709551257389615890312;  // 2 / sqrt(pi)
-    constexpr double x0 = 0.06698729810778067661813, x2 = 0.93301270189221932338187;
     SplitTab t{};
-    for (int q = 0; q < kErfc32Entries; ++q) {
-        const double *c = kTab64[q / kErfc32PerRow];
-        const int b = q % kErfc32PerRow;
-        double y[4] = {}, ex = c[kTab64Stride - 1];
-        const double s[4] = {0.0, x0, 0.5, x2};
-        for (int j = 0; j < 4; ++j) {
-            const double f = (b + s[j]) / kErfc32PerRow;
-            for (int k = kExpDegree; k >= 0; --k) y[j] = y[j] * f + c[k];
-        }
-        for (int k = kErfcxDegree - 1; k >= 0; --k)
-            ex = ex * ((double)b / kErfc32PerRow) + c[kExpDegree + 1 + k];
-        // quadratic through the nodes, about s = 1/2
-        const double e = x2 - 0.5, d1 = (y[3] - y[1]) / (2.0 * e),
-                     d2 = (y[3] + y[1] - 2.0 * y[2]) / (2.0 * e * e);
-        const double w = -rsqpi2 / kErfc32Unit;
-        t.v[q] = {(float)(y[0] * ex), (float)(w * (y[2] - 0.5 * d1 + 0.25 * d2)),
-                  (float)(w * 0.5 * (d1 - d2)), (float)(w * d2 / 3.0)};
-    }
+    for (int f = 0; f < kSplitFuncs; ++f)
+        for (int q = 0; q < kSplitEntries; ++q)
+            t.v[f * kSplitEntries + q] = {kSplitTable[f][q][0], kSplitTable[f][q][1],
+                                          kSplitTable[f][q][2], kSplitTable[f][q][3]};
     return t;
 }
 
@@ -127,7 +103,7 @@ __device__ __forceinline__ SplitK<R> split_k(double rs)
     const double i2rs = 0.5 / rs;
     K.i2rs = R(i2rs);
     K.ct = std::is_same<R, float>::value
-               ? R(i2rs * kErfc32Unit)
+               ? R(i2rs * (kSplitIntervals / (double)kSplitDomain))
                : R(i2rs * (kErfcIntervals / kTab64Domain));
     return K;
 }
@@ -151,8 +127,9 @@ using TabT = typename SplitTabT<R>::type;
 // FP64 takes erfc(u) and its derivative in t from one polynomial (interval
 // q = floor(t), t = 32 u, f = t - q, Horner's rule for both): t times the
 // derivative is u erfc'(u) = -(2u/sqrt(pi)) e^{-u^2}.  Past u = 4, that is for
-// cutoffs beyond 8 r_s, it calls the library's exp and erfc.  FP32 does the
-// same with its own table, t = 256 u (valid for u up to kSplitDomain and one
+// cutoffs beyond 8 r_s, it calls the library's exp and erfc.  FP32 reads the
+// piecewise cubics of its table at t = r ct: interval q = floor(t), local
+// variable f = t - q, Horner's rule (valid for u up to kSplitDomain and one
 // interval beyond; the host refuses FP32 split kernels with a longer
 // cutoff).
 template <typename R>
@@ -160,27 +137,24 @@ struct SplitG {
     R ec, g, g2, g3;
 };
 
+__device__ __forceinline__ float horner(const V4<float> &c, float f)
+{
+    return fmaf(fmaf(fmaf(c.w, f, c.z), f, c.y), f, c.x);
+}
+
 template <typename R, bool CELL>
 __device__ __forceinline__ SplitG<R> split_g(R r, const SplitK<R> &K, const TabT<R> *tab)
 {
     SplitG<R> s;
     if constexpr (std::is_same<R, float>::value) {
         const float t = r * K.ct;
-        const V4<float> c = tab[(int)t];  // t >= 0
+        const int q = (int)t;  // t >= 0
         const float f = __builtin_amdgcn_fractf(t);
-        float d = c.w;
-        s.ec = fmaf(d, f, c.z);
-        d = fmaf(d, f, s.ec);
-        s.ec = fmaf(s.ec, f, c.y);
-        d = fmaf(d, f, s.ec);
-        s.ec = fmaf(s.ec, f, c.x);
-        s.g = fmaf(-t, d, s.ec);
+        s.ec = horner(tab[q], f);
+        s.g = horner(tab[kSplitEntries + q], f);
         if (CELL) {
-            const float u = r * K.i2rs;
-            const float u2 = 2.0f * u * u;
-            const float h = u2 * (-t * d);
-            s.g2 = fmaf(3.0f, s.g, h);
-            s.g3 = fmaf(15.0f, s.g, fmaf(5.0f, h, u2 * h));
+            s.g2 = horner(tab[2 * kSplitEntries + q], f);
+            s.g3 = horner(tab[3 * kSplitEntries + q], f);
         }
     } else {
         const R t = r * K.ct;

@@ -29,6 +29,18 @@ const V4<float> *guarded_table()
 
 extern "C" {
 
+// erfc(u), g, G2, G3 (out[4k ..]) at r[k] with the split scale rs[k], as the
+// FP32 kernels form them.
+void split_functions_f32(int n, const float *r, const double *rs, float *out)
+{
+    for (int k = 0; k < n; ++k) {
+        const SplitG<float> f = split_g<float, true>(r[k], split_k<float>(rs[k]),
+                                                     guarded_table());
+        const float o[4] = {f.ec, f.g, f.g2, f.g3};
+        std::memcpy(out + 4 * k, o, sizeof(o));
+    }
+}
+
 // n pairs, offsets xi, xj (FP64, from the group centre): the FP32 split
 // kernels' acceleration (a[4k .. 4k + 2]) and potential (negative, a[4k + 3])
 // of a unit mass at xj on xi, as a particle (cell 0) or as a cell without

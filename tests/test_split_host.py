@@ -62,3 +62,44 @@ def test_fp32_pairs_at_the_cutoff(host, cell, reach):
     err = np.abs(a[:, 0] / ref - 1.0).max()
     d = (2.0 * 2.5 ** 2 + 3.0) * 2.0 * reach * 2.0 ** -24
     assert err <= d + d * d + 3e-6, err
+
+
+def _functions(u):
+    """erfc(u), g, G2, G3 and their logarithmic derivatives d ln F / d ln u."""
+    c = 2.0 / np.sqrt(np.pi)
+    w = c * u * np.exp(-u * u)
+    ec = special.erfc(u)
+    h = 2.0 * u * u * w
+    k = 2.0 * u * u * h
+    val = np.stack([ec, ec + w, 3.0 * (ec + w) + h, 15.0 * (ec + w) + 5.0 * h + k])
+    # u d/du: erfc -> -w, w -> (1 - 2u^2) w, h -> (3 - 2u^2) h, k -> (5 - 2u^2) k
+    dw, dh, dk = (1.0 - 2.0 * u * u) * w, (3.0 - 2.0 * u * u) * h, (5.0 - 2.0 * u * u) * k
+    der = np.stack([-w, dw - w, 3.0 * (dw - w) + dh, 15.0 * (dw - w) + 5.0 * dh + dk])
+    return val, der / val
+
+
+def test_fp32_functions(host):
+    """The FP32 radial functions over 0 < u < 2.5 and r_s over three decades.
+    The table variable is r times a rounded scale, rounded: each rounding has
+    an r.m.s. of 0.42 units of 2^-24 (relative, over a decade of values), which
+    a function takes up by its logarithmic derivative.  A function's own cubic
+    adds its coefficients' and Horner's roundings, about 0.75 units together
+    for one that is read off directly; composing the functions from each other
+    takes several times that."""
+    g = np.random.default_rng(5)
+    n = 200000
+    rs = 10.0 ** g.uniform(-3.0, 0.0, n)
+    r = (g.uniform(0.0, 2.5, n) * 2.0 * rs * (1.0 - 1e-6)).astype(np.float32)
+    out = np.zeros((n, 4), np.float32)
+    P = ctypes.c_void_p
+    host.split_functions_f32(ctypes.c_int(n), P(r.ctypes.data), P(rs.ctypes.data),
+                             P(out.ctypes.data))
+    val, der = _functions(r.astype(np.float64) / (2.0 * rs))
+    unit = 2.0 ** -24
+    for j, name in enumerate(("erfc", "g", "G2", "G3")):
+        err = out[:, j] / val[j] - 1.0
+        want = unit * np.sqrt(2.0 * 0.42 ** 2 * np.mean(der[j] ** 2) + 0.75 ** 2)
+        rms = np.sqrt(np.mean(err ** 2))
+        assert rms <= want, (name, rms, want)
+        worst = unit * (2.0 * np.abs(der[j]) + 4.0)
+        assert np.all(np.abs(err) <= worst), (name, np.abs(err / worst).max())
