@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "bhq_terms.h"
+#include "split_erfc64.h"
 #include "split_table.h"
 #include "split_table64.h"
 
@@ -17,59 +18,54 @@ namespace bhq {
 __device__ __forceinline__ double erfc_r(double v) { return ::erfc(v); }
 __device__ __forceinline__ double exp_r(double v) { return ::exp(v); }
 
-// The FP64 kernels' table of erfc(u), likewise copied to LDS by each block of
-// an FP64 split kernel: on 128 intervals of 0 <= u < 4 a polynomial of degree
-// 9 in f = t - q, t = 32 u, whose derivative gives exp(-u^2) as well.  It is
-// made from split_table64.h (exp(-u^2) of degree 9 and erfcx on 64 intervals):
-// the integral of the exp polynomial from the interval's start, where erfc is
-// exp(-u^2) erfcx, taken about the start of each half and lowered from degree
-// 10 to 9 by the Chebyshev polynomial (the last coefficient over 2^19, below
-// 1e-16 of erfc everywhere).
-// A pair then reads 80 B from LDS in place of the 144 of the two polynomials;
-// LDS bound the kernel (busy 66 % of the time and 15 % more in bank
-// conflicts, VALU 72 %): the force kernel of a 60^3 lattice took 0.64 ms, now
-// 0.56.
-constexpr int kErfcDegree = 9;
-constexpr int kErfcIntervals = 2 * kTab64Intervals;
-constexpr int kErfcStride = kErfcDegree + 1;
-
+// The FP64 kernels' table of erfc(u) (split_erfc64.h), copied to LDS by each
+// block of an FP64 split kernel: on 128 intervals of 0 <= u < 4 a polynomial
+// of degree 9 in f = t - q, t = 32 u, whose derivative gives exp(-u^2) as well.
+// A pair then reads 80 B from LDS in place of the 144 of two polynomials
+// (exp(-u^2) and erfcx); LDS bound the kernel (busy 66 % of the time and 15 %
+// more in bank conflicts, VALU 72 %): the force kernel of a 60^3 lattice took
+// 0.64 ms, now 0.56.  The coefficients are rounded to FP64 once, from 50
+// digits: against 64 bits and more the functions' r.m.s. errors (absolute,
+// 1e-17, random r_s) are 2.9 (erfc), 5.3 (g), 7.5 / 3 (G2) and 8.9 / 15 (G3), those
+// of the two polynomials 5.8, 7.5, 9.4 and 10.5; coefficients formed in FP64
+// from the two polynomials gave 6.0, 8.1, 10.1 and 11.4.
 struct Tab64 {
     double v[kErfcIntervals * kErfcStride];
 };
 
 constexpr Tab64 make_tab64()
 {
-    constexpr double rsqpi2 = 1.12837916709551257389615890312;  // 2 / sqrt(pi)
-    constexpr double w = kTab64Domain / kTab64Intervals;
-    // T_10(2 s - 1)
-    constexpr double cheb[kErfcDegree + 2] = {1.0,        -200.0,    6600.0,   -84480.0,
-                                              549120.0,   -2050048.0, 4659200.0, -6553600.0,
-                                              5570560.0,  -2621440.0, 524288.0};
-    static_assert(kExpDegree == kErfcDegree, "the integral is one degree higher");
     Tab64 t{};
-    for (int q = 0; q < kTab64Intervals; ++q) {
-        double c[kErfcDegree + 2] = {};
-        c[0] = kTab64[q][0] * kTab64[q][kExpDegree + 1];
-        for (int k = 0; k <= kExpDegree; ++k) c[k + 1] = -rsqpi2 * w * kTab64[q][k] / (k + 1);
-        for (int b = 0; b < 2; ++b) {
-            double d[kErfcDegree + 2] = {};
-            for (int k = 0; k < kErfcDegree + 2; ++k) d[k] = c[k];
-            if (b == 1)  // about f = 1/2
-                for (int i = 0; i < kErfcDegree + 1; ++i)
-                    for (int k = kErfcDegree; k >= i; --k) d[k] += 0.5 * d[k + 1];
-            double scale = 1.0;
-            for (int k = 0; k < kErfcDegree + 2; ++k, scale *= 0.5) d[k] *= scale;
-            const double top = d[kErfcDegree + 1] / cheb[kErfcDegree + 1];
-            for (int k = 0; k < kErfcStride; ++k)
-                t.v[(2 * q + b) * kErfcStride + k] = d[k] - top * cheb[k];
-        }
-    }
+    for (int q = 0; q < kErfcIntervals; ++q)
+        for (int k = 0; k < kErfcStride; ++k) t.v[q * kErfcStride + k] = kErfc64[q][k];
     return t;
 }
 
-// The FP32 table of the split radial functions (split_table.h) in device
-// memory, one V4 {c0, c1, c2, c3} per function and interval; each block of
-// a split kernel copies it to LDS, where lanes read their own intervals.  One
+// The table agrees with exp(-u^2) and erfcx, interpolated by themselves
+// (split_table64.h): erfc = exp(-u^2) erfcx and erfc' = -2/sqrt(pi) exp(-u^2) at
+// the start and in the middle of their intervals.
+constexpr bool erfc_table_agrees()
+{
+    constexpr double rsqpi2 = 1.12837916709551257389615890312;  // 2 / sqrt(pi)
+    for (int q = 0; q < kErfcIntervals; ++q) {
+        const double *c = kTab64[q / 2];
+        const double f = 0.5 * (q % 2);
+        double e = 0.0, x = 0.0;
+        for (int k = kExpDegree; k >= 0; --k) e = e * f + c[k];
+        for (int k = kErfcxDegree; k >= 0; --k) x = x * f + c[kExpDegree + 1 + k];
+        const double v = kErfc64[q][0] / (e * x) - 1.0;
+        const double d = kErfc64[q][1] * (kErfcIntervals / kErfcDomain) / (-rsqpi2 * e) - 1.0;
+        if (!(v < 2e-15 && v > -2e-15 && d < 2e-15 && d > -2e-15)) return false;
+    }
+    return true;
+}
+static_assert(kErfcDomain == kTab64Domain && kErfcIntervals == 2 * kTab64Intervals &&
+                  erfc_table_agrees(),
+              "split_erfc64.h and split_table64.h: generate both again");
+
+// The FP32 table of the split radial functions (split_table.h), one V4
+// {c0, c1, c2, c3} per function and interval, likewise copied to LDS, where
+// lanes read their own intervals.  One
 // cubic of erfc on 641 intervals whose derivative gives the other functions
 // reads half as much from LDS (a cell a quarter) and was 2 to 4 % faster, but
 // its errors were larger: 1.1 (erfc) to 1.25 (G3) times these cubics' r.m.s.
@@ -104,7 +100,7 @@ __device__ __forceinline__ SplitK<R> split_k(double rs)
     K.i2rs = R(i2rs);
     K.ct = std::is_same<R, float>::value
                ? R(i2rs * (kSplitIntervals / (double)kSplitDomain))
-               : R(i2rs * (kErfcIntervals / kTab64Domain));
+               : R(i2rs * (kErfcIntervals / kErfcDomain));
     return K;
 }
 

@@ -1,6 +1,7 @@
-"""Generate split_table64.h: exp(-u^2) and the scaled complementary error
-function erfcx(u) = exp(u^2) erfc(u) as piecewise polynomials, for the FP64
-short-range kernels.
+"""Generate split_erfc64.h, the FP64 short-range kernels' table of erfc(u), and
+split_table64.h, exp(-u^2) and the scaled complementary error function
+erfcx(u) = exp(u^2) erfc(u), from which the kernels' table is checked when they
+are compiled; all as piecewise polynomials.
 
 The Gaussian-split radial functions (u = r / (2 r_s)) need E = exp(-u^2)
 and erfc(u) = E erfcx(u).  Both are smooth; erfcx varies slowly (1 at
@@ -17,6 +18,13 @@ interval (degree + 1 of them), computed with 50 significant digits (mpmath)
 and rounded to FP64 once, coefficient by coefficient.  A row of the table
 holds the interval's E coefficients followed by its erfcx coefficients.
 
+The kernels need E only as the derivative of erfc (u = t / 32):
+    erfc(u) = c0 + f (c1 + ... + f c9),  d erfc / dt = c1 + f (2 c2 + ... + 9 f^8 c9)
+on 128 intervals of the same domain.  The derivative is the polynomial of degree
+8 that interpolates it at the Chebyshev points of the interval, and c0 is erfc
+at the interval's start; both are within 1e-19 of the functions before the
+coefficients are rounded to FP64, once each.
+
     python paper_1812_07313_amd/csrc/gen_split_table64.py
 """
 import os
@@ -27,6 +35,8 @@ DOMAIN = 4
 INTERVALS = 64
 EXP_DEGREE = 9
 ERFCX_DEGREE = 7
+ERFC_INTERVALS = 128
+ERFC_DEGREE = 9
 
 
 def expm2(u):
@@ -56,6 +66,19 @@ def table(domain=DOMAIN, n=INTERVALS):
             for q in range(n)]
 
 
+def erfc_table(domain=DOMAIN, n=ERFC_INTERVALS):
+    """Rows c0..c9 of erfc per interval, rounded to FP64."""
+    rows = []
+    with mp.workdps(50):
+        h = mp.mpf(domain) / n
+        for q in range(n):
+            d = interval(lambda u: -2 * h / mp.sqrt(mp.pi) * expm2(u), q, ERFC_DEGREE - 1,
+                         domain, n)
+            rows.append([float(mp.erfc(q * h))] + [float(d[k] / (k + 1))
+                                                   for k in range(ERFC_DEGREE)])
+    return rows
+
+
 def main():
     tab = table()
     stride = EXP_DEGREE + ERFCX_DEGREE + 2
@@ -82,6 +105,27 @@ def main():
         lines.append("    {%s}," % ", ".join("%.17e" % v for v in row))
     lines += ["};", "", "}  // namespace bhq", ""]
     with open(os.path.join(here, "split_table64.h"), "w") as f:
+        f.write("\n".join(lines))
+    lines = [
+        "// split_erfc64.h -- generated by gen_split_table64.py; do not edit.",
+        "// erfc(u) on %d intervals of 0 <= u < %d: row q holds a polynomial's coefficients in" % (
+            ERFC_INTERVALS, DOMAIN),
+        "// increasing powers of f = t - q, t = u %d / %d, whose derivative is that of erfc too." % (
+            ERFC_INTERVALS, DOMAIN),
+        "#pragma once",
+        "",
+        "namespace bhq {",
+        "",
+        "constexpr double kErfcDomain = %d.0;" % DOMAIN,
+        "constexpr int kErfcIntervals = %d;" % ERFC_INTERVALS,
+        "constexpr int kErfcDegree = %d;" % ERFC_DEGREE,
+        "constexpr int kErfcStride = kErfcDegree + 1;",
+        "constexpr double kErfc64[kErfcIntervals][kErfcStride] = {",
+    ]
+    for row in erfc_table():
+        lines.append("    {%s}," % ", ".join("%.17e" % v for v in row))
+    lines += ["};", "", "}  // namespace bhq", ""]
+    with open(os.path.join(here, "split_erfc64.h"), "w") as f:
         f.write("\n".join(lines))
 
 

@@ -41,6 +41,36 @@ void split_functions_f32(int n, const float *r, const double *rs, float *out)
     }
 }
 
+// The same of the FP64 kernels.
+void split_functions_f64(int n, const double *r, const double *rs, double *out)
+{
+    static const Tab64 tab = make_tab64();
+    for (int k = 0; k < n; ++k) {
+        const SplitG<double> f = split_g<double, true>(r[k], split_k<double>(rs[k]), tab.v);
+        const double o[4] = {f.ec, f.g, f.g2, f.g3};
+        std::memcpy(out + 4 * k, o, sizeof(o));
+    }
+}
+
+// The same from the two polynomials of split_table64.h (exp(-u^2) and erfcx).
+void split_functions_two_polynomials(int n, const double *r, const double *rs, double *out)
+{
+    for (int k = 0; k < n; ++k) {
+        const double u = r[k] * (0.5 / rs[k]), u2 = u * u;
+        const double t = u * (kTab64Intervals / kTab64Domain);
+        const int q = (int)t;
+        const double f = t - q;
+        const double *c = kTab64[q], *cx = c + kExpDegree + 1;
+        double E = c[kExpDegree], x = cx[kErfcxDegree];
+        for (int i = kExpDegree - 1; i >= 0; --i) E = fma(E, f, c[i]);
+        for (int i = kErfcxDegree - 1; i >= 0; --i) x = fma(x, f, cx[i]);
+        const double e = E * 0.56418958354775628694807945156;
+        const double ec = E * x, g = fma(2 * u, e, ec), h = 4 * u * u2 * e;
+        const double o[4] = {ec, g, fma(3.0, g, h), fma(15.0, g, fma(5.0, h, 2 * u2 * h))};
+        std::memcpy(out + 4 * k, o, sizeof(o));
+    }
+}
+
 // n pairs, offsets xi, xj (FP64, from the group centre): the FP32 split
 // kernels' acceleration (a[4k .. 4k + 2]) and potential (negative, a[4k + 3])
 // of a unit mass at xj on xi, as a particle (cell 0) or as a cell without

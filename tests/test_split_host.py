@@ -1,7 +1,9 @@
 """The split kernels' device functions (csrc/bhq_split.h), compiled for the
 host with a stand-in for the HIP header, on inputs where they could go wrong."""
 import ctypes
+import importlib.util
 import os
+import re
 import subprocess
 
 import numpy as np
@@ -76,6 +78,49 @@ def _functions(u):
     dw, dh, dk = (1.0 - 2.0 * u * u) * w, (3.0 - 2.0 * u * u) * h, (5.0 - 2.0 * u * u) * k
     der = np.stack([-w, dw - w, 3.0 * (dw - w) + dh, 15.0 * (dw - w) + 5.0 * dh + dk])
     return val, der / val
+
+
+def test_fp64_functions(host):
+    """The FP64 radial functions over 0 < u < 4 at r_s = 1/2, where u and the
+    table variable are exact, against 30 digits: no further off than the two
+    polynomials of exp(-u^2) and erfcx (test_split_table.py) on the same points,
+    in absolute and in relative r.m.s. and in the largest absolute error."""
+    import mpmath as mp
+    g = np.random.default_rng(6)
+    u = np.concatenate([g.uniform(0.0, 4.0, 6000), np.arange(128) / 32.0,
+                        np.nextafter(np.arange(1, 129) / 32.0, 0.0)])
+    n = len(u)
+    rs = np.full(n, 0.5)
+    ref = []
+    with mp.workdps(30):
+        for v in u:
+            v = mp.mpf(float(v))
+            w = 2 / mp.sqrt(mp.pi) * v * mp.exp(-v * v)
+            a, h = mp.erfc(v) + w, 2 * v * v * w
+            ref.append((mp.erfc(v), a, 3 * a + h, 15 * a + 5 * h + 2 * v * v * h))
+        P = ctypes.c_void_p
+        stat = []
+        for call in (host.split_functions_f64, host.split_functions_two_polynomials):
+            out = np.zeros((n, 4))
+            call(ctypes.c_int(n), P(u.ctypes.data), P(rs.ctypes.data), P(out.ctypes.data))
+            err = np.array([[float(o - f) for o, f in zip(row, r)] for row, r in zip(out, ref)])
+            rel = err / np.array(ref, float)
+            stat.append((np.sqrt(np.mean(err ** 2, axis=0)), np.sqrt(np.mean(rel ** 2, axis=0)),
+                         np.abs(err).max(axis=0)))
+    for new, two in zip(*stat):
+        assert np.all(new <= two), (new, two)
+
+
+def test_fp64_table_matches_generator():
+    spec = importlib.util.spec_from_file_location("gen64",
+                                                  os.path.join(CSRC, "gen_split_table64.py"))
+    gen = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(gen)
+    with open(os.path.join(CSRC, "split_erfc64.h")) as f:
+        text = f.read()
+    text = text[text.index("kErfc64["):]
+    vals = [float(v) for v in re.findall(r"([-+0-9.]+e[-+0-9]+)", text[text.index("= {"):])]
+    assert np.array_equal(np.array(vals).reshape(128, 10), np.array(gen.erfc_table()))
 
 
 def test_fp32_functions(host):
