@@ -164,13 +164,14 @@ __global__ __launch_bounds__(kBlock) void k_cell_keys(int64_t np, const CellKeys
 // Sorted particle records (x, y, z, m) and first[c] = first sorted particle of
 // cell c or later (first[n3] = np), written by the particle at whose key the
 // range of cells ends.  Long ranges of empty cells are written by the whole
-// wave.
+// wave.  Also clears the count of k_rho's crowded blocks.
 __global__ __launch_bounds__(kBlock) void k_sorted(int64_t np, int64_t n3, const uint32_t *key,
                                                    const int32_t *idx, const double *x,
                                                    const double *m, double4 *xs,
-                                                   int32_t *first)
+                                                   int32_t *first, int32_t *crowded)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (k == 0) *crowded = 0;
     int64_t lo = 0, hi = -1;  // cells lo .. hi begin at k
     if (k <= np) {
         lo = k > 0 ? (int64_t)key[k - 1] + 1 : 0;
@@ -212,23 +213,52 @@ constexpr int kPlane = kPY * kPZ;
 constexpr int kPlaneCap = 448;
 static_assert(kRY * kRZ == kBlock, "a column per thread");
 
+//
+// A thread goes over the particles of its cells one by one, so a block is as
+// long as its fullest cells: a block with a cell of more than kCrowded
+// particles among those it looks at leaves its points to k_rho_crowded
+// (crowded[0] counts such blocks, their numbers follow).  Whole evaluations
+// (ms) with every block here, with 16, 24 and 32, and with a thread per mesh
+// point over its 27 cells: Plummer spheres of scale 0.05 in the box, 2,000,003
+// particles on 128^3 56 / 2.1 / 2.2 / 2.3 / 15; 0.1, 4,000,000 on 256^3 8.7 / 3.1 /
+// 3.3 / 3.7 / 5.1; uniform particles, 8 per point on 128^3 3.5 / 5.6 / 3.5 / 3.5 / 5.6, 16
+// on 64^3 1.33 / 1.12 / 1.12 / 1.41 / 1.42, 64 10.0 / 4.1 / 4.1 / 4.1 / 7.3.
+constexpr int kCrowded = 24;
+
 inline unsigned rho_blocks(int n, int len)
 {
     return (unsigned)(((n + kRY - 1) / kRY) * ((n + kRZ - 1) / kRZ) * ((n + len - 1) / len));
 }
 
+// Points per column and block: eight, or fewer where the blocks would not fill
+// the chip (each costs two planes more than it has points).
+inline int rho_len(int n)
+{
+    int len = 8;
+    while (len > 2 && rho_blocks(n, len) < 1024) len /= 2;
+    return len;
+}
+
+// First mesh point of block b.
+__device__ __forceinline__ void rho_origin(int b, int n, int len, int &x0, int &y0, int &z0)
+{
+    const int nz = (n + kRZ - 1) / kRZ, ny = (n + kRY - 1) / kRY;
+    z0 = (b % nz) * kRZ;
+    b /= nz;
+    y0 = (b % ny) * kRY;
+    x0 = (b / ny) * len;
+}
+
 __global__ __launch_bounds__(kBlock) void k_rho(int n, double ih, int len, const double4 *xs,
-                                                const int32_t *first, double *rho)
+                                                const int32_t *first, double *rho,
+                                                int32_t *crowded)
 {
     typedef hipcub::BlockScan<int, kBlock> Scan;
     __shared__ double mwx[3][kPlaneCap], wy[3][kPlaneCap], wz[3][kPlaneCap];
     __shared__ int32_t sfirst[kPlane + 1], sstart[kPlane];
     __shared__ typename Scan::TempStorage scan_tmp;
-    const int nz = (n + kRZ - 1) / kRZ, ny = (n + kRY - 1) / kRY;
-    int b = (int)blockIdx.x;
-    const int z0 = (b % nz) * kRZ;
-    b /= nz;
-    const int y0 = (b % ny) * kRY, x0 = (b / ny) * len;
+    int x0, y0, z0;
+    rho_origin((int)blockIdx.x, n, len, x0, y0, z0);
     const int t = threadIdx.x, tz = t % kRZ, ty = t / kRZ;
     const int xe = x0 + len < n ? x0 + len : n;
     constexpr int kPer = (kPlane + kBlock - 1) / kBlock;
@@ -246,6 +276,7 @@ __global__ __launch_bounds__(kBlock) void k_rho(int n, double ih, int len, const
     for (int px = x0 - 1; px <= xe; ++px) {
         const int64_t plane = (int64_t)pmod(px, n) * n;
         int cnt[kPer], part = 0;
+        bool full = false;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int h = kPer * t + u;
@@ -257,6 +288,7 @@ __global__ __launch_bounds__(kBlock) void k_rho(int n, double ih, int len, const
                 sstart[h] = f;
             }
             part += cnt[u];
+            full |= cnt[u] > kCrowded;
         }
         int at = 0, total = 0;
         Scan(scan_tmp).ExclusiveSum(part, at, total);
@@ -267,7 +299,10 @@ __global__ __launch_bounds__(kBlock) void k_rho(int n, double ih, int len, const
             at += cnt[u];
         }
         if (t == 0) sfirst[kPlane] = total;
-        __syncthreads();
+        if (__syncthreads_or(full)) {
+            if (t == 0) crowded[1 + atomicAdd(crowded, 1)] = (int32_t)blockIdx.x;
+            return;
+        }
         for (int c0 = 0; c0 < total; c0 += kPlaneCap) {
             const int c1 = total - c0 < kPlaneCap ? total : c0 + kPlaneCap;
             if (c0 > 0) __syncthreads();
@@ -320,6 +355,76 @@ __global__ __launch_bounds__(kBlock) void k_rho(int n, double ih, int len, const
     }
 }
 
+// TSC weight for offset o (-1, 0, +1) with o known only at run time; the
+// same operations as tsc_w (negating d is exact).
+__device__ __forceinline__ double tsc_w_var(double d, int o)
+{
+    const double s = o < 0 ? -d : d;
+    return o == 0 ? 0.75 - d * d : 0.5 * (0.5 + s) * (0.5 + s);
+}
+
+__device__ __forceinline__ double tsc_offset(double x, double ih)
+{
+    double i0;
+    return tsc_d(x, ih, i0);
+}
+
+// rho at the points of the crowded blocks, a wave per point: lane c < 27
+// finds the range of cell c around the point, the lanes go side by side over
+// the particles of all of them, and the lanes' sums are added in a fixed
+// order.  However the particles are concentrated, the work is spread over the
+// points that they reach.
+constexpr int kCrowdedBlocks = 1024;
+
+__global__ __launch_bounds__(kBlock) void k_rho_crowded(int n, double ih, int len,
+                                                        const double4 *xs, const int32_t *first,
+                                                        const int32_t *crowded, double *rho)
+{
+    const int lane = threadIdx.x & 63;
+    const int per = kBlock * len;  // points of a block of k_rho
+    const int64_t points = (int64_t)crowded[0] * per;
+    constexpr int kWaves = kCrowdedBlocks * (kBlock / 64);
+    for (int64_t i = blockIdx.x * (kBlock / 64) + threadIdx.x / 64; i < points; i += kWaves) {
+        int x0, y0, z0;
+        rho_origin(crowded[1 + i / per], n, len, x0, y0, z0);
+        const int r = (int)(i % per);
+        const int px = x0 + r / kBlock, py = y0 + r % kBlock / kRZ, pz = z0 + r % kRZ;
+        if (px >= n || py >= n || pz >= n) continue;
+        int32_t lo = 0, incl = 0;
+        if (lane < 27) {
+            const int64_t c = ((int64_t)wrap(px + lane / 9 - 1, n) * n +
+                               wrap(py + lane / 3 % 3 - 1, n)) * n + wrap(pz + lane % 3 - 1, n);
+            lo = first[c];
+            incl = first[c + 1] - lo;
+        }
+        const int own = incl;
+        for (int h = 1; h < 32; h *= 2) {
+            const int v = __shfl_up(incl, h);
+            if (lane >= h) incl += v;
+        }
+        lo -= incl - own;  // sorted index of cell c's particle j: lo + j
+        const int total = __shfl(incl, 26);
+        double s = 0.0;
+        for (int j = lane; j - lane < total; j += 64) {
+            int c = 0;  // cells that end at or before j
+            for (int h = 16; h > 0; h /= 2)
+                if (__shfl(incl, c + h - 1) <= j) c += h;
+            c = c < 26 ? c : 26;
+            const int64_t k = (int64_t)__shfl(lo, c) + j;
+            if (j < total) {
+                const double4 q = xs[k];
+                // a cell below the point is at offset +1 from its particles
+                const double wx = tsc_w_var(tsc_offset(q.x, ih), 1 - c / 9),
+                             wy = tsc_w_var(tsc_offset(q.y, ih), 1 - c / 3 % 3),
+                             wz = tsc_w_var(tsc_offset(q.z, ih), 1 - c % 3);
+                s = fma(q.w * wx, wy * wz, s);
+            }
+        }
+        for (int h = 32; h > 0; h /= 2) s += __shfl_xor(s, h);
+        if (lane == 0) rho[((int64_t)px * n + py) * n + pz] = s;
+    }
+}
+
 __device__ __forceinline__ double sinc_half(double kh)
 {
     // sin(kh/2) / (kh/2), 1 at k = 0
@@ -362,20 +467,6 @@ __global__ __launch_bounds__(kBlock) void k_green(const hipfftDoubleComplex *rk,
     fk[e] = make_hipDoubleComplex(gx * pi, -gx * pr);
     fk[nc + e] = make_hipDoubleComplex(gy * pi, -gy * pr);
     fk[2 * nc + e] = make_hipDoubleComplex(gz * pi, -gz * pr);
-}
-
-// TSC weight for offset o (-1, 0, +1) with o known only at run time; the
-// same operations as tsc_w (negating d is exact).
-__device__ __forceinline__ double tsc_w_var(double d, int o)
-{
-    const double s = o < 0 ? -d : d;
-    return o == 0 ? 0.75 - d * d : 0.5 * (0.5 + s) * (0.5 + s);
-}
-
-__device__ __forceinline__ double tsc_offset(double x, double ih)
-{
-    double i0;
-    return tsc_d(x, ih, i0);
 }
 
 // One term of the 27-point interpolation, in the order of the points.
@@ -516,6 +607,7 @@ struct bhq_pm {
     bhq::DevArray rho, rk, fk, mesh;  // fk, mesh: four fields each
     // per-particle sorting (grown to the largest n seen)
     bhq::DevArray key, key2, idx, idx2, xs, sort_tmp, first;
+    bhq::DevArray crowded;  // k_rho's crowded blocks: count, numbers
     hipfftHandle fwd = 0, inv = 0;
     int batch = 1;  // fields per inverse transform
     bool have_fwd = false, have_inv = false;
@@ -543,7 +635,7 @@ void pm_free(bhq_pm *p)
     if (p->have_fwd) (void)hipfftDestroy(p->fwd);
     if (p->have_inv) (void)hipfftDestroy(p->inv);
     for (bhq::DevArray *a : {&p->rho, &p->rk, &p->fk, &p->mesh, &p->key, &p->key2, &p->idx,
-                             &p->idx2, &p->xs, &p->sort_tmp, &p->first})
+                             &p->idx2, &p->xs, &p->sort_tmp, &p->first, &p->crowded})
         a->release();
     if (p->ev0) (void)hipEventDestroy(p->ev0);
     if (p->ev1) (void)hipEventDestroy(p->ev1);
@@ -604,6 +696,8 @@ int bhq_pm_create(bhq_pm **out, int device, int nmesh, double box, double rs)
     if (e == hipSuccess) e = p->fk.reserve(4 * nc * sizeof(hipfftDoubleComplex));
     if (e == hipSuccess) e = p->mesh.reserve(4 * n3 * sizeof(double));
     if (e == hipSuccess) e = p->first.reserve((n3 + 1) * sizeof(int32_t));
+    if (e == hipSuccess)
+        e = p->crowded.reserve((rho_blocks(nmesh, rho_len(nmesh)) + 1) * sizeof(int32_t));
     if (e == hipSuccess) e = hipEventCreate(&p->ev0);
     if (e == hipSuccess) e = hipEventCreate(&p->ev1);
     if (e != hipSuccess) {
@@ -705,14 +799,17 @@ int bhq_pm_compute(bhq_pm *pm, int64_t np, const double *x, const double *m, dou
     }
     hipLaunchKernelGGL(k_sorted, dim3(nblocks(np + 1)), dim3(kBlock), 0, s, np, (int64_t)n3,
                        pm->key2.as<uint32_t>(), pm->idx2.as<int32_t>(), x, m,
-                       pm->xs.as<double4>(), pm->first.as<int32_t>());
+                       pm->xs.as<double4>(), pm->first.as<int32_t>(),
+                       pm->crowded.as<int32_t>());
     if (!hipok(hipGetLastError(), "sorted records")) return BHQ_E_HIP;
-    // points per column and block: eight, or fewer where the blocks would not
-    // fill the chip (each costs two planes more than it has points)
-    int len = 8;
-    while (len > 2 && rho_blocks(n, len) < 1024) len /= 2;
+    const int len = rho_len(n);
     hipLaunchKernelGGL(k_rho, dim3(rho_blocks(n, len)), dim3(kBlock), 0, s, n, ih, len,
-                       pm->xs.as<double4>(), pm->first.as<int32_t>(), pm->rho.as<double>());
+                       pm->xs.as<double4>(), pm->first.as<int32_t>(), pm->rho.as<double>(),
+                       pm->crowded.as<int32_t>());
+    if (!hipok(hipGetLastError(), "assignment")) return BHQ_E_HIP;
+    hipLaunchKernelGGL(k_rho_crowded, dim3(kCrowdedBlocks), dim3(kBlock), 0, s, n, ih, len,
+                       pm->xs.as<double4>(), pm->first.as<int32_t>(),
+                       pm->crowded.as<int32_t>(), pm->rho.as<double>());
     if (!hipok(hipGetLastError(), "assignment")) return BHQ_E_HIP;
     if (!fftok(hipfftSetStream(pm->fwd, s), "set stream") ||
         !fftok(hipfftSetStream(pm->inv, s), "set stream"))
