@@ -194,19 +194,24 @@ __global__ __launch_bounds__(kBlock) void k_root(const double *part, const int *
     set_flags(bad, nb, flag);
 }
 
-// Several systems' root cubes, a block each (bound by its chain of loads: 256
-// systems of 15,000 on average took 103 us with 256 threads, 38 now).
-constexpr int kSysBlock = 1024;
+// Several systems' root cubes, a block each: bound by the largest system's chain
+// of loads where that is long (a quarter as long with 1024 threads), else by the
+// number of blocks (a quarter as many of 1024 at once).  256 / 1024 threads (us): 2^20
+// systems of 4 2090 / 9281, 65,536 of 64 136 / 594, 4096 of 500 16 / 43, 700 of 6000 18.7 /
+// 22.8, 512 of 8000 18.4 / 19.8, 256 of 15,000 25 / 18, 32 of 65,536 83 / 30; 65,535 of 16
+// and one of 10^6 1216 / 643.  The line lies where the largest system has ten
+// particles per system of the batch.
+constexpr int kSysBlock = 256, kSysBlockWide = 1024, kSysWide = 10;
 
-__global__ __launch_bounds__(kSysBlock) void k_root_sys(const double *x, const int64_t *sys_off,
-                                                        const int *bad, int nb, int *flag,
-                                                        double *roots)
+template <int BS>
+__global__ __launch_bounds__(BS) void k_root_sys(const double *x, const int64_t *sys_off,
+                                                 const int *bad, int nb, int *flag, double *roots)
 {
-    __shared__ double s[6][kSysBlock];
+    __shared__ double s[6][BS];
     const int64_t a = sys_off[blockIdx.x], e = sys_off[blockIdx.x + 1];
     double lo[3], hi[3];
     for (int k = 0; k < 3; ++k) lo[k] = hi[k] = x[3 * a + k];
-    for (int64_t p = a + threadIdx.x; p < e; p += kSysBlock)
+    for (int64_t p = a + threadIdx.x; p < e; p += BS)
         for (int k = 0; k < 3; ++k) {
             const double v = x[3 * p + k];
             lo[k] = v < lo[k] ? v : lo[k];
@@ -216,8 +221,8 @@ __global__ __launch_bounds__(kSysBlock) void k_root_sys(const double *x, const i
         s[k][threadIdx.x] = lo[k];
         s[3 + k][threadIdx.x] = hi[k];
     }
-    block_box<kSysBlock>(s);
-    if (threadIdx.x == 0) root_cube<kSysBlock>(s, roots + 4 * blockIdx.x);
+    block_box<BS>(s);
+    if (threadIdx.x == 0) root_cube<BS>(s, roots + 4 * blockIdx.x);
     if (blockIdx.x == 0) set_flags(bad, nb, flag);
 }
 
@@ -1602,13 +1607,24 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
             STEP(hipMemcpyAsync(B[T_SYSOFF].p, P.sys_off, (size_t)(nsys + 1) * 8,
                                 hipMemcpyHostToDevice, s),
                  "copy");
-            so32.assign(P.sys_off, P.sys_off + nsys + 1);
+            so32.resize((size_t)nsys + 1);
+            int64_t largest = 0;
+            for (int q = 0; q < nsys; ++q) {
+                so32[(size_t)q] = (int32_t)P.sys_off[q];
+                largest = std::max(largest, P.sys_off[q + 1] - P.sys_off[q]);
+            }
+            so32[(size_t)nsys] = (int32_t)P.sys_off[nsys];
             STEP(hipMemcpyAsync(B[T_SYSOFF32].p, so32.data(), (size_t)(nsys + 1) * 4,
                                 hipMemcpyHostToDevice, s),
                  "copy");
             sys_off = B[T_SYSOFF].as<int64_t>();
-            hipLaunchKernelGGL(k_root_sys, dim3((unsigned)nsys), dim3(kSysBlock), 0, s, P.x,
-                               sys_off, bad, nbox, flag, roots);
+            if (largest > kSysWide * P.nsys)
+                hipLaunchKernelGGL(k_root_sys<kSysBlockWide>, dim3((unsigned)nsys),
+                                   dim3(kSysBlockWide), 0, s, P.x, sys_off, bad, nbox, flag,
+                                   roots);
+            else
+                hipLaunchKernelGGL(k_root_sys<kSysBlock>, dim3((unsigned)nsys), dim3(kSysBlock),
+                                   0, s, P.x, sys_off, bad, nbox, flag, roots);
             LAUNCHED("root cubes");
         }
     }
