@@ -166,11 +166,7 @@ struct bhq_ctx {
     // device builds: slot sizes for the next one-walk build, and what the
     // last build did (one walk or not, longest particle and cell lists)
     int64_t walk_cap_p = 0, walk_cap_c = 0;
-    // cells a group may open in the next build's walk (0: unknown, -1: too
-    // many at walk_theta and walk_ncrit)
-    int walk_oct = 0;
-    double walk_theta = 0.0;
-    int walk_ncrit = 0;
+    bhq::OctMemory walk_oct;
     int tree_levels = 0;  // levels of the last device-built tree
     int64_t build_info[3] = {0, 0, 0};
     uint64_t args_version = 0;  // bumped when device pointers/params change
@@ -2012,10 +2008,7 @@ static int device_build(bhq_ctx *ctx, int64_t nsys, const int64_t *sys_off,
     // previous lists' memory plus 256 MiB.
     P.cap_p = ctx->walk_cap_p;
     P.cap_c = ctx->walk_cap_c;
-    // a group's opened cells in the walk's LDS: sized by the last build too,
-    // and not tried again for an opening criterion under which they outgrew it
-    const bool same = ctx->walk_theta == theta && ctx->walk_ncrit == ncrit;
-    P.cap_o = ctx->walk_oct >= 0 ? ctx->walk_oct : (same ? -1 : 0);
+    P.cap_o = ctx->walk_oct.capacity(theta, ncrit);
     P.spec_levels = ctx->tree_levels;
     P.slot_bytes = ctx->ng >= 0 ? bhq::slot_memory_bound(ctx->njp, ctx->njc) : 0;
     bhq::TreeOut O;
@@ -2058,12 +2051,7 @@ static int device_build(bhq_ctx *ctx, int64_t nsys, const int64_t *sys_off,
     ctx->off_stale = true;
     ctx->walk_cap_p = bhq::next_slot_cap(ctx->walk_cap_p, O.max_p);
     ctx->walk_cap_c = bhq::next_slot_cap(ctx->walk_cap_c, O.max_c);
-    if (O.oct_full)
-        ctx->walk_oct = ctx->walk_oct > 0 && ctx->walk_oct < bhq::kOctMost ? 0 : -1;
-    else if (P.cap_o >= 0)
-        ctx->walk_oct = (int)std::min<int64_t>(O.max_o + O.max_o / 4 + 8, bhq::kOctMost);
-    ctx->walk_theta = theta;
-    ctx->walk_ncrit = ncrit;
+    ctx->walk_oct.built(theta, ncrit, O.max_o);
     ctx->tree_levels = O.nlevels;
     ctx->build_info[0] = O.one_walk ? 1 : 0;
     ctx->build_info[1] = O.max_p;

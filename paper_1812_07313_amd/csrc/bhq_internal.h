@@ -292,8 +292,7 @@ struct TreeParams {
     // offsets.
     int64_t cap_p = 0, cap_c = 0;
     int64_t slot_bytes = 0;  // upper bound on the slot memory of that mode
-    // Cells a group may open in the level walk's LDS (0: unknown; < 0: a
-    // group of an earlier build of this kind opened too many)
+    // Cells a group may open in the level walk's LDS (0: octet walk)
     int cap_o = 0;
     // dispatch order planned with the build (window 0: none)
     int window = 0, tail = 0, xcds = 0;
@@ -320,8 +319,37 @@ inline int64_t slot_memory_bound(int64_t njp, int64_t njc)
 }
 
 // Cells a group may open in the level walk, whose LDS holds kOctBytes for
-// each: at a first build, and at most (64 KiB less the kernel's other LDS).
+// each: at a first build, and at most (64 KiB less the kernel's other LDS).  It
+// is the faster walk up to there: rebuilds with capacities of up to 2048, 3072
+// and 4080 cells, where larger needs go to the octet walk (us): Plummer sphere
+// of 131,072 at ncrit 256, theta = 0.2 6270 / 6273 / 743, 0.25 4118 / 491 / 496; cube of
+// as many, theta = 0.15 4712 / 606 / 743; Plummer sphere of 10^6, 0.3 2335 / 2338 / 2332.
 constexpr int kOctFirst = 1024, kOctMost = 4080, kOctBytes = 16;
+
+// What a context remembers of the cells that its last device build's groups
+// opened, and the capacity of the next build's level walk.  Both walks count
+// them, so that a build that outgrew its capacity sizes the next one.
+struct OctMemory {
+    int most = -1;  // cells opened by a group (-1: no build yet)
+    double theta = 0.0;
+    int ncrit = 0;
+
+    // 1.25 times the last build's; 0 (octet walk) where those did not fit, until
+    // the opening criterion changes.
+    constexpr int capacity(double th, int nc) const
+    {
+        if (most < 0) return kOctFirst;
+        if (most > kOctMost) return th == theta && nc == ncrit ? 0 : kOctFirst;
+        const int want = most + most / 4 + 8;
+        return want < kOctMost ? want : kOctMost;
+    }
+    constexpr void built(double th, int nc, int64_t opened)
+    {
+        most = opened < (1 << 30) ? (int)opened : 1 << 30;
+        theta = th;
+        ncrit = nc;
+    }
+};
 
 // Builder working memory, kept between builds of one context.
 enum TreeBuf {
@@ -352,9 +380,7 @@ struct TreeOut {
     int64_t ng = 0, njp = 0, njc = 0, ncell = 0;
     // longest particle and cell list of a group; whether one walk sufficed
     int64_t max_p = 0, max_c = 0;
-    // most cells opened by a group in the level walk; whether they outgrew it
-    int64_t max_o = 0;
-    bool oct_full = false;
+    int64_t max_o = 0;  // most cells opened by a group
     bool one_walk = false;
     // one walk: jp_idx / jc_idx hold the per-group slots of these sizes
     int64_t slot_p = 0, slot_c = 0;

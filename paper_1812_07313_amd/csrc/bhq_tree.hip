@@ -1038,7 +1038,7 @@ struct WalkArgs {
     int32_t *jp_idx, *jc_idx;
     int *flag;                         // set if a stack (1) or the level walk's
                                        // octets (2) would overflow
-    int *most;                         // most octets of a group in the level walk
+    int *most;                         // most cells that a group opens
     int64_t cap_p, cap_c;              // slot sizes of the one-walk mode
     int frames;                        // frame stack depth: levels of the tree
     const double *gbox;                // [6 ng] lo, hi of each group's particles
@@ -1304,8 +1304,8 @@ __global__ __launch_bounds__(64 * NW) void k_walk_level(const WalkArgs W, int ca
         if (MODE != kWalkFill) {
             W.jc_cnt[gi] = s_sum[0].x;
             W.jp_cnt[gi] = s_sum[0].y;
-            // most octets of a group, for the next build's LDS (the plain
-            // read spares most groups the atomic)
+            // most cells opened by a group (its octets), for the next
+            // build's LDS (the plain read spares most groups the atomic)
             if (*(volatile int *)W.most < hi) atomicMax(W.most, hi);
         }
         s_sum[0] = make_int2(0, 0);
@@ -1406,7 +1406,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
     }
     const WLink R = W.wl[W.groot ? W.groot[gi] : 0];
     const int below[3] = {k >= 1 ? -1 : 0, k >= 2 ? -1 : 0, k >= 4 ? -1 : 0};
-    int sp = 0, nch = 0, cur = 0;
+    int sp = 0, nch = 0, cur = 0, opened = 0;
     int2 e = make_int2(-1, 0);
     if (R.child0 < 0) {
         // a one-leaf tree: the root contains the group and is opened
@@ -1419,6 +1419,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
         e = k < nch ? classify<true>(W, R.child0 + k, G, GL, gb) : make_int2(-1, 0);
         s_ent[0][t] = e;
         sp = 1;
+        opened = 1;
     }
     // Each round: emit and return from frames (cheap) until the octet must
     // open a child or is done, then open it (loads and classification).
@@ -1480,10 +1481,12 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(const WalkArgs W)
         nch = n2;
         cur = 0;
         ++sp;
+        ++opened;
     }
     if (MODE != kWalkFill && k == 0) {
         W.jp_cnt[gi] = np;
         W.jc_cnt[gi] = nc;
+        if (*(volatile int *)W.most < opened) atomicMax(W.most, opened);  // as in k_walk_level
     }
 }
 
@@ -1919,7 +1922,7 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     W.frames = std::max(1, std::min(kFrames, nlevels));
     const size_t walk_lds = (size_t)W.frames * (kWalkBlock * sizeof(int2) + kWalkBlock / kOct * 4);
     // octets the level walk's LDS holds; 0: octet walk
-    int oct_cap = std::min(P.cap_o > 0 ? P.cap_o : (P.cap_o == 0 ? kOctFirst : 0), kOctMost);
+    int oct_cap = std::min(std::max(P.cap_o, 0), kOctMost);
     // Waves per group of the level walk: two, or four when there are too few
     // groups to fill the chip (2048: 16 waves per CU either way), where the
     // time is the chain of one group.  With one, two and four waves a rebuild's
@@ -2005,7 +2008,6 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         if (stats[kStatWalk] != 2) break;
         // a group opened more cells than the level walk's LDS holds
         oct_cap = 0;
-        O.oct_full = true;
         STEP(hipMemsetAsync(W.flag, 0, 16, s), "memset");
     }
     if (stats[kStatWalk]) {
