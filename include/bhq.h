@@ -269,12 +269,15 @@ int bhq_compute(bhq_ctx *ctx, void *stream);
  * evaluation of bhq_compute with the context's inputs and launch shape,
  * allocating nothing.  Results go straight to the caller's device arrays
  * a[ni][3] and pot[ni] (FP64, group order; pot may be NULL), which must lie
- * in device memory of the context's device.  The persistent queue counters
- * and the j-split parts live in a static array of the library (256 B plus
- * 16 MiB per device, held until the process ends), so jsplit * ni * 16 B
- * (FP32) or 32 B (FP64) must fit 16 MiB: BHQ_E_RANGE otherwise.  Every call
- * on one device shares that array: calls that overlap in time on one
- * device (two streams, or two host threads) race and give wrong results.
+ * in device memory of the context's device.  After bhq_set_tuning the
+ * persistent queue counters and the j-split parts live in a static array of
+ * the library (256 B plus 16 MiB per device, held until the process ends), so
+ * jsplit * ni * 16 B (FP32) or 32 B (FP64) must fit 16 MiB: BHQ_E_RANGE
+ * otherwise.  Every such call on one device shares that array: calls that
+ * overlap in time on one device (two streams, or two host threads) race and
+ * give wrong results.  A context that chooses its shape itself takes the parts'
+ * memory with its lists, apart from bhq_compute's: its calls may overlap with
+ * bhq_compute and with other contexts' calls, but not with each other.
  * No graph is recorded (use_graph is ignored).  Asynchronous on `stream`;
  * bhq_get_kernel_ms times it.  Errors as bhq_compute, plus BHQ_E_ARG / 
  * BHQ_E_RANGE for the output arrays. */
@@ -350,7 +353,7 @@ int bhq_clock_end(bhq_ctx *ctx, double *mhz);
  * chooses its shape at each compute, from the kernel, the precision, the group
  * sizes and the lists' costs (up to 2^21 i-particles; the same lists always
  * get the same shape): blocks of 256 or 512, one or two i-particles per thread,
- * up to eight parts with up to 16 MiB of the context's memory, taken when the
+ * up to eight parts with up to 32 MiB of the context's memory, taken when the
  * lists are set or built.  bhq_get_tuning returns the values above all the
  * same.  Errors: BHQ_E_ARG for values outside these sets, or
  * waves_per_eu != 0 with block 128. */

@@ -33,7 +33,7 @@ enum Arr {
     A_AX, A_AY, A_AZ, A_POT,
     A_QUEUE,
     A_POOLP, A_POOLC, A_JPIDX, A_JCIDX,
-    A_TORDER, A_ENERGY, A_OSCRATCH, A_SORTSCRATCH, A_PART, A_FLAG, A_LIVE, A_CLOCK,
+    A_TORDER, A_ENERGY, A_OSCRATCH, A_SORTSCRATCH, A_PART, A_PARTAUTO, A_FLAG, A_LIVE, A_CLOCK,
     A_COUNT
 };
 
@@ -327,8 +327,10 @@ struct bhq_ctx {
     // grid over 110 sets of lists (1000 to 700,000 particles).  The split
     // kernels have one part: what they compute is the same bits in every
     // default launch.
-    // The memory for the parts (up to 16 MiB) is taken here, so that a compute
-    // allocates nothing.
+    // The memory for the parts is taken here, so that a compute allocates
+    // nothing and a captured one keeps its address until the lists change: up to
+    // 16 MiB for bhq_compute and as much after it for bhq_compute_noalloc, whose
+    // calls may run beside each other.
     void plan_jsplit(double total, double largest)
     {
         auto_jsplit = 1;
@@ -341,10 +343,10 @@ struct bhq_ctx {
                (size_t)(2 * j) * (size_t)ni * 32 <= bhq::kScratchPartBytes)
             j *= 2;
         if (j > 1) {
-            const size_t bytes = (size_t)j * (size_t)ni * 32;
-            if (bytes > arr[A_PART].cap) {
+            const size_t bytes = 2 * (size_t)j * (size_t)ni * 32;
+            if (bytes > arr[A_PARTAUTO].cap) {
                 quiesce();
-                if (arr[A_PART].reserve(bytes) != hipSuccess) {
+                if (arr[A_PARTAUTO].reserve(bytes) != hipSuccess) {
                     (void)hipGetLastError();
                     j = 1;
                 }
@@ -895,7 +897,9 @@ int bhq_compute(bhq_ctx *ctx, void *stream)
     TRY(prepare_compute(ctx, A));
     const bhq::LaunchCfg cfg = ctx->shape();
 
-    if (cfg.jsplit > 1) {
+    if (!ctx->tuned) {
+        A.part = ctx->arr[A_PARTAUTO].p;
+    } else if (cfg.jsplit > 1) {
         // parts of every i-particle's sums (32 B per entry covers FP64)
         const size_t bytes = (size_t)cfg.jsplit * (size_t)ctx->ni * 32;
         if (bytes > ctx->arr[A_PART].cap) {
@@ -1000,7 +1004,8 @@ int bhq_compute_noalloc(bhq_ctx *ctx, double *a, double *pot, void *stream)
     A.pot = pot;
     A.out_stride = 3;
     A.queue = reinterpret_cast<unsigned int *>(sp);
-    A.part = own ? ctx->arr[A_PART].p : sp + bhq::kScratchQueueBytes;
+    A.part = own ? ctx->arr[A_PARTAUTO].as<char>() + (size_t)cfg.jsplit * (size_t)ctx->ni * 32
+                 : sp + bhq::kScratchQueueBytes;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = hipEventRecord(ctx->ev0, s);
     if (e != hipSuccess) return ctx->hip_fail(e, "hipEventRecord");
