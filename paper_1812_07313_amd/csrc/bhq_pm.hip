@@ -597,7 +597,7 @@ __global__ __launch_bounds__(kBlock) void k_interp(int n, const double4 *xs, con
 }  // namespace
 
 // Largest mesh whose inverse transforms are batched.
-constexpr int kBatchMesh = 128;
+constexpr int kBatchMesh = 224;
 
 struct bhq_pm {
     int device = 0;
@@ -712,10 +712,11 @@ int bhq_pm_create(bhq_pm **out, int device, int nmesh, double box, double rs)
         return BHQ_E_HIP;
     }
     p->have_fwd = true;
-    // The four inverse transforms go in one batch where their fields (67 MB
-    // at 128^3) stay in the caches between its passes: 145 us one after
-    // another at 128^3, 93 together, 53 and 17 at 60^3.  Larger ones run one
-    // after another.
+    // The four inverse transforms go in one batch as far as that is faster:
+    // whole evaluations with few particles, one after another / together (us),
+    // 60^3 141 / 108, 128^3 308 / 257, 130^3 403 / 333, 160^3 506 / 459, 192^3 834 / 782,
+    // 224^3 1183 / 1141, 256^3 1807 / 1808.  From there on they are equal within 2 %, and
+    // one after another they need a quarter of the work memory.
     p->batch = nmesh <= kBatchMesh ? 4 : 1;
     int dims[3] = {nmesh, nmesh, nmesh};
     if (hipfftPlanMany(&p->inv, 3, dims, nullptr, 1, 0, nullptr, 1, 0, HIPFFT_Z2D, p->batch) !=
