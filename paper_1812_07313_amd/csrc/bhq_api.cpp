@@ -215,7 +215,10 @@ struct bhq_ctx {
 
     bhq::LaunchCfg cfg;
     bool tuned = false;    // bhq_set_tuning was called: cfg as it is
-    int auto_jsplit = 1;   // of the current lists, where it was not
+    // of the current lists, where it was not: parts worth trying, and the lanes'
+    // work by shape (kStatWork, kStatMaxWork)
+    int auto_jsplit = 1;
+    double shape_work[bhq::kShapes] = {}, shape_most[bhq::kShapes] = {};
     int use_graph = 0;
     int order_mode = BHQ_ORDER_XCD, order_window = BHQ_ORDER_WINDOW,
         order_tail = BHQ_ORDER_TAIL;
@@ -388,8 +391,10 @@ struct bhq_ctx {
     // nothing and a captured one keeps its address until the lists change: up to
     // 16 MiB for bhq_compute and as much after it for bhq_compute_noalloc, whose
     // calls may run beside each other.
-    void plan_jsplit(double total, double largest)
+    void plan_shape(double total, double largest, const double *work, const double *most)
     {
+        std::copy(work, work + bhq::kShapes, shape_work);
+        std::copy(most, most + bhq::kShapes, shape_most);
         auto_jsplit = 1;
         if (ng < 1 || ni < 1 || !(total > 0.0)) return;
         const double tail = 2.0 * largest * cfg.num_cu / total;
@@ -411,6 +416,15 @@ struct bhq_ctx {
             }
         }
         auto_jsplit = j;
+    }
+    void plan_shape(const volatile int64_t *stats)
+    {
+        double work[bhq::kShapes], most[bhq::kShapes];
+        for (int q = 0; q < bhq::kShapes; ++q) {
+            work[q] = (double)stats[bhq::kStatWork + q];
+            most[q] = (double)stats[bhq::kStatMaxWork + q];
+        }
+        plan_shape((double)stats[bhq::kStatCost], (double)stats[bhq::kStatMaxCost], work, most);
     }
     // The launch shape of a compute: the caller's (bhq_set_tuning), or one
     // chosen by kernel, precision and mean group size.  One i-particle per
@@ -437,11 +451,41 @@ struct bhq_ctx {
     // thread: their results are held to that shape bit for bit (512 would not
     // gain there, clustered 2^22 9258 / 9435; one per thread would gain 2 to
     // 3 % on small groups, 256 systems 5452 / 5268).
+    // The mean says little where groups are uneven, so in FP32 the shape is then
+    // compared with the others by a model of the time (in us), linear in
+    //   the lanes' work on all groups' lists (kStatWork, per 10^12),
+    //   the longest block's (kStatMaxWork per thread, per 10^6) over the parts,
+    //   the blocks, ng times the parts (per 10^4), and a constant,
+    // with coefficients per kernel and shape: least-squares fits of relative
+    // errors to 418 lists of Plummer spheres, cubes, shells, disks, fractals and
+    // clumps of 700 to 2,000,000 particles at ncrit 12 to 1300, in one part and in the
+    // parts planned above (within 18 to 20 % r.m.s., the shapes' errors together).
+    // One that is 3 % faster by the model is taken.  Over the lists the quadrupole
+    // takes 0.980 of the time of the mean's choice (0.45 at best, 1.22 at worst) and
+    // the monopole 0.956 (0.58, 1.07), with coefficients from the other half of the
+    // lists the same; against (256, 2) in one part the worst lists take 1.11 of the
+    // time in place of 1.62 and 1.71 (60,000 particles of a Plummer sphere at ncrit
+    // 150, whose work is in groups of 75 to 150 but whose mean is 39: 231 us, (256, 2)
+    // 142, now 105 in blocks of 512).  In FP64 the model gained 1 % and lost as much
+    // elsewhere.
     // The split kernels keep two (in FP64 one per thread is half as fast); in
     // FP32 their six waves (80 registers) take 749 us against 807 (lattice
     // 96^3) and 4244 against 4550 (160^3).
+    struct ShapeTime {
+        int block, per, waves, shape;  // the shape whose lanes' work it does
+        double work, longest, blocks, fixed;
+    };
     bhq::LaunchCfg shape() const
     {
+        static constexpr ShapeTime kMono[] = {{256, 2, 0, 1, 996, 168, 62.4, 11},
+                                            {256, 1, 8, 0, 956, 206, 43.2, 11},
+                                            {256, 1, 6, 0, 929, 207, 44.6, 8.6},
+                                            {256, 2, 8, 1, 935, 171, 75.4, 15.8},
+                                            {}};
+        static constexpr ShapeTime kQuad[] = {{256, 2, 0, 1, 1720, 228, 77.9, 9.96},
+                                            {256, 1, 6, 0, 1600, 274, 50.8, 8.03},
+                                            {512, 1, 6, 1, 1630, 312, 111, 9.7},
+                                            {}};
         bhq::LaunchCfg c = cfg;
         if (tuned) return c;
         const double mean = ng > 0 ? (double)ni / (double)ng : 0.0;
@@ -464,6 +508,26 @@ struct bhq_ctx {
             c.i_per_thread = 1;
             c.waves_per_eu = 6;
         }
+        if (precision == BHQ_FP64) return c;
+        const ShapeTime *first = kernel == BHQ_MONO ? kMono : kQuad;
+        auto us = [&](const ShapeTime &t, int parts) {
+            return t.work * shape_work[t.shape] * 1e-12 +
+                   t.longest * shape_most[t.shape] * 1e-6 / (t.block * parts) +
+                   t.blocks * (double)ng * parts * 1e-4 + t.fixed;
+        };
+        double best = 0.0;  // none: a shape without a model stays
+        for (const ShapeTime *t = first; t->block > 0; ++t)
+            if (t->block == c.block && t->per == c.i_per_thread && t->waves == c.waves_per_eu)
+                best = 0.97 * us(*t, c.jsplit);
+        for (const ShapeTime *t = first; t->block > 0; ++t)
+            for (int parts : {1, auto_jsplit})
+                if (us(*t, parts) < best) {
+                    best = us(*t, parts);
+                    c.block = t->block;
+                    c.i_per_thread = t->per;
+                    c.waves_per_eu = t->waves;
+                    c.jsplit = parts;
+                }
         return c;
     }
     // Compute the slot table for the current groups and order mode and
@@ -487,15 +551,24 @@ struct bhq_ctx {
         if (e != hipSuccess) return hip_fail(e, "order upload");
         nslots = (int64_t)order.size();
         ++args_version;
-        double total = 0.0, largest = 0.0;
+        uint64_t total = 0, largest = 0, work[bhq::kShapes] = {}, most[bhq::kShapes] = {};
         for (int64_t g = 0; g < ng; ++g) {
-            const double c = (double)bhq::order_cost(i_off[(size_t)g + 1] - i_off[(size_t)g],
-                                                     jp_off[(size_t)g + 1] - jp_off[(size_t)g],
-                                                     jc_off[(size_t)g + 1] - jc_off[(size_t)g]);
-            total += c;
-            largest = std::max(largest, c);
+            const size_t h = (size_t)g;
+            const int64_t n = i_off[h + 1] - i_off[h];
+            const uint64_t e =
+                bhq::list_cost(jp_off[h + 1] - jp_off[h], jc_off[h + 1] - jc_off[h]);
+            total += (uint64_t)n * e;
+            largest = std::max(largest, (uint64_t)n * e);
+            for (int q = 0; q < bhq::kShapes; ++q) {
+                const uint64_t w = e * bhq::shape_lanes(n, q);
+                work[q] += w;
+                most[q] = std::max(most[q], w);
+            }
         }
-        plan_jsplit(total, largest);
+        double dw[bhq::kShapes], dm[bhq::kShapes];
+        std::copy(work, work + bhq::kShapes, dw);
+        std::copy(most, most + bhq::kShapes, dm);
+        plan_shape((double)total, (double)largest, dw, dm);
         return BHQ_OK;
     }
     // Turn lists kept in per-group slots into compact lists at the offsets
@@ -1820,7 +1893,7 @@ int bhq_set_groups_dev(bhq_ctx *ctx, int64_t ng, const int64_t *i_off,
         else
             ctx->fail(orc, "%s", msg.c_str());
         if (orc == BHQ_OK)
-            ctx->plan_jsplit((double)L.stats[bhq::kStatCost], (double)L.stats[bhq::kStatMaxCost]);
+            ctx->plan_shape(L.stats);
     } else {
         e = hipStreamSynchronize(s);
         orc = e == hipSuccess ? ctx->upload_order() : ctx->hip_fail(e, "set_groups_dev: copy");
@@ -2137,7 +2210,8 @@ static int device_build(bhq_ctx *ctx, int64_t nsys, const int64_t *sys_off,
     else if (ctx->eps_mode == 2)
         ctx->eps_mode = 0;
     ctx->nslots = O.nslots;
-    ctx->plan_jsplit(O.cost, O.max_cost);
+    ctx->plan_shape(reinterpret_cast<const int64_t *>(static_cast<char *>(ctx->build_host) +
+                                                      bhq::kBuildStats));
     if (!device_order) {
         const int orc = ctx->upload_order();
         if (orc != BHQ_OK) {

@@ -16,9 +16,30 @@ namespace bhq {
 // table).  Cost of a group in units of 1/100 of a particle term:
 // ni (100 njp + 265 njc + 100): a cell term costs about 53/20 of a particle
 // term, and the last term stands for loading and storing the i-particles.
+constexpr uint64_t list_cost(int64_t njp, int64_t njc)
+{
+    return 100u * (uint64_t)njp + 265u * (uint64_t)njc + 100u;
+}
 constexpr uint64_t order_cost(int64_t ni, int64_t njp, int64_t njc)
 {
-    return (uint64_t)ni * (100u * (uint64_t)njp + 265u * (uint64_t)njc + 100u);
+    return (uint64_t)ni * list_cost(njp, njc);
+}
+
+// Work of a group's launch with one and with two i-particles per thread of a
+// block of 256 (shape 0 and 1; 512 threads with one do the work of 256 with two):
+// lanes spent on a list entry by a group of ni, all of the block's (times the
+// i-particles per thread) for each full pass of i-particles and, in the last,
+// their S-th part, with S the slices of threads that share the entries.
+constexpr int kShapes = 2;
+constexpr uint64_t shape_lanes(int64_t ni, int shape)
+{
+    const int per = shape == 0 ? 1 : 2, bs = 256;
+    const int64_t full = ni / (bs * per);
+    const int left = (int)(ni - full * (bs * per));
+    if (left == 0) return (uint64_t)(full * (bs * per));
+    // quotients of integers up to 512, exact after truncation
+    const int slices = (int)((float)bs / (float)((left + per - 1) / per));
+    return (uint64_t)(full * (bs * per) + (int)((float)(bs * per) / (float)slices));
 }
 
 // XCD piece of group g: the piece holding the midpoint of the group's cost
@@ -249,7 +270,9 @@ enum ListStat {
     kStatMaxParts, kStatMaxCells,  // longest lists
     kStatWalk, kStatOpened,        // flag[0], flag[2] of the walk
     kStatCost, kStatMaxCost,       // order_cost: all groups', the largest
-    kStatSlots,                    // launch slots
+    // list_cost times the lanes of each shape: all groups', the largest
+    kStatWork, kStatMaxWork = kStatWork + kShapes,
+    kStatSlots = kStatMaxWork + kShapes,  // launch slots
     kStatCount
 };
 struct ListPlan {
@@ -385,13 +408,13 @@ struct TreeOut {
     // one walk: jp_idx / jc_idx hold the per-group slots of these sizes
     int64_t slot_p = 0, slot_c = 0;
     int nlevels = 0;  // levels of the tree (the root's included)
-    double cost = 0.0, max_cost = 0.0;  // order_cost of all groups, the largest
     int64_t nslots = 0;  // launch slots (where an order was asked for)
 };
 
 // What a build's kernels write for the host: 64 int32 (the level table), then
 // kStatCount int64.
-constexpr size_t kBuildHostBytes = 64 * 4 + 8 * kStatCount;
+constexpr size_t kBuildStats = 64 * 4;
+constexpr size_t kBuildHostBytes = kBuildStats + 8 * kStatCount;
 
 // Returns a BHQ_* code; on failure *err names the step.
 int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t stream,

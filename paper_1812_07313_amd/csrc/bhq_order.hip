@@ -34,9 +34,11 @@ constexpr int kTile = kBlock * kItems;  // groups per block of the sums
 constexpr int kSortMax = 1024;          // largest window sorted by one block
 constexpr int kMaxXcds = 64;
 
+// Sums over groups of the list entries, the cost and the shapes' work, and
+// the largest of each.
+constexpr int kTerms = 3 + kShapes;
 struct Sums {
-    uint64_t p, c, cost;  // list entries, cost
-    uint64_t mp, mc, mcost;  // longest lists, largest cost
+    uint64_t sum[kTerms], most[kTerms];
 };
 
 struct PlanArgs {
@@ -55,73 +57,100 @@ struct PlanArgs {
     int64_t *stats;
 };
 
-__device__ __forceinline__ void group_terms(const PlanArgs &A, int64_t g, uint64_t &p, uint64_t &c,
-                                            uint64_t &cost)
+// Entries and cost of group g (0 past the end).
+__device__ __forceinline__ void group_terms(const PlanArgs &A, int64_t g, uint64_t (&v)[3])
 {
-    p = c = cost = 0;
+    v[0] = v[1] = v[2] = 0;
     if (g >= A.ng) return;
-    p = (uint64_t)(A.jp_cnt ? A.jp_cnt[g] : A.jp_off[g + 1] - A.jp_off[g]);
-    c = (uint64_t)(A.jc_cnt ? A.jc_cnt[g] : A.jc_off[g + 1] - A.jc_off[g]);
-    cost = order_cost(A.i_off[g + 1] - A.i_off[g], (int64_t)p, (int64_t)c);
+    v[0] = (uint64_t)(A.jp_cnt ? A.jp_cnt[g] : A.jp_off[g + 1] - A.jp_off[g]);
+    v[1] = (uint64_t)(A.jc_cnt ? A.jc_cnt[g] : A.jc_off[g + 1] - A.jc_off[g]);
+    v[2] = order_cost(A.i_off[g + 1] - A.i_off[g], (int64_t)v[0], (int64_t)v[1]);
+}
+
+// Adds a group's terms, the shapes' work among them.
+__device__ __forceinline__ void add_group(const PlanArgs &A, int64_t g, Sums &s)
+{
+    uint64_t e[3], v[kTerms];
+    group_terms(A, g, e);
+    if (g >= A.ng) return;
+    const uint64_t entries = list_cost((int64_t)e[0], (int64_t)e[1]);
+    for (int k = 0; k < 3; ++k) v[k] = e[k];
+    for (int q = 0; q < kShapes; ++q)
+        v[3 + q] = entries * shape_lanes(A.i_off[g + 1] - A.i_off[g], q);
+    for (int k = 0; k < kTerms; ++k) {
+        s.sum[k] += v[k];
+        s.most[k] = v[k] > s.most[k] ? v[k] : s.most[k];
+    }
+}
+
+// Sums of s.sum and the largest of s.most over the block's threads, to all of
+// them.
+__device__ __forceinline__ void block_reduce(Sums &s)
+{
+    __shared__ Sums wave[kBlock / 64];
+    for (int h = 32; h > 0; h /= 2)
+        for (int k = 0; k < kTerms; ++k) {
+            s.sum[k] += __shfl_xor((unsigned long long)s.sum[k], h);
+            const uint64_t m = __shfl_xor((unsigned long long)s.most[k], h);
+            s.most[k] = m > s.most[k] ? m : s.most[k];
+        }
+    if (threadIdx.x % 64 == 0) wave[threadIdx.x / 64] = s;
+    __syncthreads();
+    s = wave[0];
+    for (int w = 1; w < kBlock / 64; ++w)
+        for (int k = 0; k < kTerms; ++k) {
+            s.sum[k] += wave[w].sum[k];
+            s.most[k] = wave[w].most[k] > s.most[k] ? wave[w].most[k] : s.most[k];
+        }
 }
 
 __global__ __launch_bounds__(kBlock) void k_tile_sums(const PlanArgs A)
 {
-    typedef hipcub::BlockReduce<uint64_t, kBlock> Reduce;
-    __shared__ typename Reduce::TempStorage tmp;
-    uint64_t v[6] = {0, 0, 0, 0, 0, 0};
-    for (int u = 0; u < kItems; ++u) {
-        uint64_t p, c, cost;
-        group_terms(A, (int64_t)blockIdx.x * kTile + u * kBlock + threadIdx.x, p, c, cost);
-        v[0] += p;
-        v[1] += c;
-        v[2] += cost;
-        v[3] = p > v[3] ? p : v[3];
-        v[4] = c > v[4] ? c : v[4];
-        v[5] = cost > v[5] ? cost : v[5];
-    }
-    uint64_t r[6];
-    for (int k = 0; k < 6; ++k) {
-        r[k] = k < 3 ? Reduce(tmp).Sum(v[k]) : Reduce(tmp).Reduce(v[k], hipcub::Max());
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) A.tile[blockIdx.x] = Sums{r[0], r[1], r[2], r[3], r[4], r[5]};
+    Sums s{};
+    for (int u = 0; u < kItems; ++u)
+        add_group(A, (int64_t)blockIdx.x * kTile + u * kBlock + threadIdx.x, s);
+    block_reduce(s);
+    if (threadIdx.x == 0) A.tile[blockIdx.x] = s;
 }
 
-// Exclusive sums of the tiles' sums, totals after them; one block.
+// Exclusive sums of the tiles' entries and costs (in sum[0..2]), totals after
+// them; one block.
 __global__ __launch_bounds__(kBlock) void k_tile_scan(const PlanArgs A, int tiles)
 {
     typedef hipcub::BlockScan<uint64_t, kBlock> Scan;
-    typedef hipcub::BlockReduce<uint64_t, kBlock> Reduce;
-    __shared__ union {
-        typename Scan::TempStorage scan;
-        typename Reduce::TempStorage reduce;
-    } tmp;
-    uint64_t at[3] = {0, 0, 0}, m[3] = {0, 0, 0};
+    __shared__ typename Scan::TempStorage tmp;
+    uint64_t at[3] = {0, 0, 0};
+    Sums all{};
     for (int b = 0; b < tiles; b += kBlock) {
         const int i = b + (int)threadIdx.x;
-        const Sums t = i < tiles ? A.tile[i] : Sums{0, 0, 0, 0, 0, 0};
-        const uint64_t v[3] = {t.p, t.c, t.cost};
-        uint64_t ex[3], tot[3];
+        const Sums t = i < tiles ? A.tile[i] : Sums{};
         for (int k = 0; k < 3; ++k) {
-            Scan(tmp.scan).ExclusiveSum(v[k], ex[k], tot[k]);
+            uint64_t ex, tot;
+            Scan(tmp).ExclusiveSum(t.sum[k], ex, tot);
             __syncthreads();
+            if (i < tiles) A.tile[i].sum[k] = at[k] + ex;
+            at[k] += tot;
         }
-        if (i < tiles) A.tile[i] = Sums{at[0] + ex[0], at[1] + ex[1], at[2] + ex[2], 0, 0, 0};
-        for (int k = 0; k < 3; ++k) at[k] += tot[k];
-        m[0] = t.mp > m[0] ? t.mp : m[0];
-        m[1] = t.mc > m[1] ? t.mc : m[1];
-        m[2] = t.mcost > m[2] ? t.mcost : m[2];
+        for (int k = 0; k < kTerms; ++k) {
+            all.sum[k] += t.sum[k];
+            all.most[k] = t.most[k] > all.most[k] ? t.most[k] : all.most[k];
+        }
     }
-    for (int k = 0; k < 3; ++k) {
-        m[k] = Reduce(tmp.reduce).Reduce(m[k], hipcub::Max());
-        __syncthreads();
+    block_reduce(all);
+    if (threadIdx.x == 0) A.tile[tiles] = all;
+}
+
+__device__ __forceinline__ void write_work(const PlanArgs &A, const Sums &s)
+{
+    for (int q = 0; q < kShapes; ++q) {
+        A.stats[kStatWork + q] = (int64_t)s.sum[3 + q];
+        A.stats[kStatMaxWork + q] = (int64_t)s.most[3 + q];
     }
-    if (threadIdx.x == 0) A.tile[tiles] = Sums{at[0], at[1], at[2], m[0], m[1], m[2]};
 }
 
 // A tile's offsets, costs and pieces; the statistics.  ONE: the only tile,
-// whose sums are the block's own.
+// whose sums are the block's own; a second block has the shapes' work (2 us more
+// in the first).
 template <bool ONE>
 __global__ __launch_bounds__(kBlock) void k_offsets(const PlanArgs A, int tiles)
 {
@@ -131,63 +160,76 @@ __global__ __launch_bounds__(kBlock) void k_offsets(const PlanArgs A, int tiles)
         typename Scan::TempStorage scan;
         typename Reduce::TempStorage reduce;
     } tmp;
+    if constexpr (ONE) {
+        if (blockIdx.x == 1) {
+            Sums s{};
+            for (int64_t g = threadIdx.x; g < A.ng; g += kBlock) add_group(A, g, s);
+            block_reduce(s);
+            if (threadIdx.x == 0) write_work(A, s);
+            return;
+        }
+    }
     const int64_t g0 = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
     uint64_t v[3][kItems], cost[kItems], mx[3] = {0, 0, 0};
     for (int u = 0; u < kItems; ++u) {
-        group_terms(A, g0 + u, v[0][u], v[1][u], v[2][u]);
-        cost[u] = v[2][u];
-        for (int k = 0; k < 3; ++k) mx[k] = v[k][u] > mx[k] ? v[k][u] : mx[k];
+        uint64_t x[3];
+        group_terms(A, g0 + u, x);
+        for (int k = 0; k < 3; ++k) {
+            v[k][u] = x[k];
+            mx[k] = x[k] > mx[k] ? x[k] : mx[k];
+        }
+        cost[u] = x[2];
     }
-    Sums before{0, 0, 0, 0, 0, 0}, all;
-    uint64_t tot[3];
+    Sums all{};
+    uint64_t before[3] = {0, 0, 0};
     for (int k = 0; k < 3; ++k) {
-        Scan(tmp.scan).ExclusiveSum(v[k], v[k], tot[k]);
+        Scan(tmp.scan).ExclusiveSum(v[k], v[k], all.sum[k]);
         __syncthreads();
     }
     if constexpr (ONE) {
         for (int k = 0; k < 3; ++k) {
-            mx[k] = Reduce(tmp.reduce).Reduce(mx[k], hipcub::Max());
+            all.most[k] = Reduce(tmp.reduce).Reduce(mx[k], hipcub::Max());  // (thread 0)
             __syncthreads();
         }
-        all = Sums{tot[0], tot[1], tot[2], mx[0], mx[1], mx[2]};  // (maxima: thread 0)
     } else {
-        before = A.tile[blockIdx.x];
+        for (int k = 0; k < 3; ++k) before[k] = A.tile[blockIdx.x].sum[k];
         all = A.tile[tiles];
     }
     // the piece of the group before this thread's first: its cost interval
     // ends where the first's begins
     int xp = -1;
     if (g0 > 0 && g0 < A.ng) {
-        uint64_t p, c, cc;
-        group_terms(A, g0 - 1, p, c, cc);
-        xp = order_piece(before.cost + v[2][0] - cc, cc, all.cost, A.xcds, g0 - 1, A.ng);
+        uint64_t x[3];
+        group_terms(A, g0 - 1, x);
+        xp = order_piece(before[2] + v[2][0] - x[2], x[2], all.sum[2], A.xcds, g0 - 1, A.ng);
     }
     for (int u = 0; u < kItems; ++u) {
         const int64_t g = g0 + u;
         if (g >= A.ng) break;
         if (A.jp_cnt) {
-            A.jp_off[g] = (int64_t)(before.p + v[0][u]);
-            A.jc_off[g] = (int64_t)(before.c + v[1][u]);
+            A.jp_off[g] = (int64_t)(before[0] + v[0][u]);
+            A.jc_off[g] = (int64_t)(before[1] + v[1][u]);
         }
         A.cost[g] = cost[u];
-        const int x = order_piece(before.cost + v[2][u], cost[u], all.cost, A.xcds, g, A.ng);
+        const int x = order_piece(before[2] + v[2][u], cost[u], all.sum[2], A.xcds, g, A.ng);
         for (int p = xp + 1; p <= x; ++p) A.start[p] = g;
         xp = x;
         if (g == A.ng - 1) {
             for (int p = x + 1; p <= A.xcds; ++p) A.start[p] = A.ng;
             if (A.jp_cnt) {
-                A.jp_off[A.ng] = (int64_t)all.p;
-                A.jc_off[A.ng] = (int64_t)all.c;
+                A.jp_off[A.ng] = (int64_t)all.sum[0];
+                A.jc_off[A.ng] = (int64_t)all.sum[1];
             }
         }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        A.stats[kStatParts] = (int64_t)all.p;
-        A.stats[kStatCells] = (int64_t)all.c;
-        A.stats[kStatMaxParts] = (int64_t)all.mp;
-        A.stats[kStatMaxCells] = (int64_t)all.mc;
-        A.stats[kStatCost] = (int64_t)all.cost;
-        A.stats[kStatMaxCost] = (int64_t)all.mcost;
+        A.stats[kStatParts] = (int64_t)all.sum[0];
+        A.stats[kStatCells] = (int64_t)all.sum[1];
+        A.stats[kStatMaxParts] = (int64_t)all.most[0];
+        A.stats[kStatMaxCells] = (int64_t)all.most[1];
+        A.stats[kStatCost] = (int64_t)all.sum[2];
+        A.stats[kStatMaxCost] = (int64_t)all.most[2];
+        if (!ONE) write_work(A, all);
         A.stats[kStatWalk] = A.flag ? A.flag[0] : 0;
         A.stats[kStatOpened] = A.flag ? A.flag[2] : 0;
     }
@@ -327,7 +369,7 @@ int plan_lists_launch(const ListPlan &P, hipStream_t s, std::string *what)
     if (e != hipSuccess) return fail(e);
     const PlanArgs A = plan_args(P);
     if (tiles == 1) {
-        hipLaunchKernelGGL(k_offsets<true>, dim3(1), dim3(kBlock), 0, s, A, 1);
+        hipLaunchKernelGGL(k_offsets<true>, dim3(2), dim3(kBlock), 0, s, A, 1);
     } else {
         hipLaunchKernelGGL(k_tile_sums, dim3((unsigned)tiles), dim3(kBlock), 0, s, A);
         if ((e = hipGetLastError()) != hipSuccess) return fail(e);

@@ -1996,7 +1996,7 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
     L.tail = P.tail;
     L.xcds = P.xcds;
     L.flag = W.flag;
-    L.stats = reinterpret_cast<int64_t *>(static_cast<char *>(O.host) + 64 * 4);
+    L.stats = reinterpret_cast<int64_t *>(static_cast<char *>(O.host) + kBuildStats);
     L.order = P.window > 0 ? O.slots : nullptr;
     L.scratch = O.scratch;
     volatile int64_t *stats = L.stats;
@@ -2021,8 +2021,6 @@ int build_tree_lists(const TreeParams &P, TreeOut &O, hipStream_t s, std::string
         O.nslots = stats[kStatSlots];
     }
     const int64_t most = stats[kStatOpened];
-    O.cost = (double)stats[kStatCost];
-    O.max_cost = (double)stats[kStatMaxCost];
     const int64_t njp = stats[kStatParts], njc = stats[kStatCells];
     const int64_t max_p = stats[kStatMaxParts], max_c = stats[kStatMaxCells];
     O.one_walk = slots && max_p <= P.cap_p && max_c <= P.cap_c;
