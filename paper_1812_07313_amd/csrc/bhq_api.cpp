@@ -468,9 +468,11 @@ struct bhq_ctx {
     // 150, whose work is in groups of 75 to 150 but whose mean is 39: 231 us, (256, 2)
     // 142, now 105 in blocks of 512).  In FP64 the model gained 1 % and lost as much
     // elsewhere.
-    // The split kernels keep two (in FP64 one per thread is half as fast); in
-    // FP32 their six waves (80 registers) take 749 us against 807 (lattice
-    // 96^3) and 4244 against 4550 (160^3).
+    // The split kernels keep two: FP64 quadrupole, ms, two per thread against
+    // one, 3.67 / 4.04 (lattice 128^3, ncrit 128) and 0.61 / 0.65 (48^3, 256),
+    // though 4.45 / 3.23 where groups have five (110^3, 32).  In FP32 their six
+    // waves (80 registers) take 749 us against 807 (lattice 96^3) and 4244
+    // against 4550 (160^3).
     struct ShapeTime {
         int block, per, waves, shape;  // the shape whose lanes' work it does
         double work, longest, blocks, fixed;

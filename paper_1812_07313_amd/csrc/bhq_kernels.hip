@@ -522,25 +522,22 @@ __device__ __forceinline__ void load_split_tab(TabT<R> *tab)
 }
 
 // Waves per SIMD the register allocation must allow: WPE > 0 asks for at
-// least WPE (registers capped to fit).  Otherwise the FP64 split kinds ask
-// for BHQ_F64_SPLIT_WAVES: left alone the compiler takes 188 VGPRs (2
-// waves); capped for 3, 4 and 5 waves (registers spilled to scratch) they
-// ran the 2^24 lattice in 49.2, 47.5 and 50.8 ms against 56.7, with exp
-// from the library.  A minimum of 1 leaves the compiler's choice.
-#ifndef BHQ_F64_SPLIT_WAVES
-#define BHQ_F64_SPLIT_WAVES 4
-#endif
+// least WPE (registers capped to fit); a minimum of 1 leaves the compiler's
+// choice.  That is 128 VGPRs, 4 waves, for the FP64 split quadrupole kernel.
+// The persistent one would take 140 (3 waves): held to 4 it runs the lattice
+// 128^3 in 3.70 ms against 3.93.
 template <typename R, int KIND, int WPE>
-constexpr int min_waves()
+constexpr int min_waves(bool persistent)
 {
     return WPE > 0 ? WPE
-                   : (std::is_same<R, double>::value && (KIND == kSplitQuad || KIND == kSplitMono)
-                          ? BHQ_F64_SPLIT_WAVES
+                   : (persistent && std::is_same<R, double>::value &&
+                              (KIND == kSplitQuad || KIND == kSplitMono)
+                          ? 4
                           : 1);
 }
 
 template <typename R, int KIND, bool PERIODIC, int BS, int IB, int WPE>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(min_waves<R, KIND, WPE>())))
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(min_waves<R, KIND, WPE>(false))))
 void force_kernel(const ForceArgs A)
 {
     constexpr bool kCellQ = Smem<R, KIND>::kCellQ;
@@ -574,7 +571,7 @@ __device__ __forceinline__ int xcd_id()
 // counter once it has passed that counter's slot count, so every block
 // exits.
 template <typename R, int KIND, bool PERIODIC, int BS, int IB, int WPE>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(min_waves<R, KIND, WPE>())))
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(min_waves<R, KIND, WPE>(true))))
 void force_kernel_persistent(const ForceArgs A, int nj)
 {
     constexpr bool kCellQ = Smem<R, KIND>::kCellQ;

@@ -138,6 +138,21 @@ __device__ __forceinline__ float horner(const V4<float> &c, float f)
     return fmaf(fmaf(fmaf(c.w, f, c.z), f, c.y), f, c.x);
 }
 
+// erfc(u) and e^{-u^2} past the FP64 table, from the library.  A function that
+// is not inlined: inlined, its constants were kept over the loops of lists
+// that never come here, in registers spilled to scratch memory by every block
+// (252 bytes a lane), and each unrolled pair had its copy.  FP64 quadrupole
+// kernel, ms, inlined / called: lattice 110^3 in 239,675 groups 10.5 / 4.5,
+// 60^3 in 4096 groups 0.52 / 0.44; cutoff 12 r_s, 48^3, 1.6 / 0.62.
+struct FarG {
+    double ec, e;
+};
+
+__device__ inline __attribute__((noinline)) FarG far_g(double u)
+{
+    return {erfc_r(u), exp_r(-u * u)};
+}
+
 template <typename R, bool CELL>
 __device__ __forceinline__ SplitG<R> split_g(R r, const SplitK<R> &K, const TabT<R> *tab)
 {
@@ -170,8 +185,9 @@ __device__ __forceinline__ SplitG<R> split_g(R r, const SplitK<R> &K, const TabT
             s.g = fma(-t, d, s.ec);
         } else {
             const R u = r * K.i2rs;
-            s.ec = erfc_r(u);
-            w = R(1.12837916709551257389615890312) * u * exp_r(-u * u);
+            const FarG far = far_g(u);
+            s.ec = far.ec;
+            w = R(1.12837916709551257389615890312) * u * far.e;
             s.g = s.ec + w;
         }
         if (CELL) {
