@@ -470,9 +470,25 @@ struct bhq_ctx {
     // elsewhere.
     // The split kernels keep two: FP64 quadrupole, ms, two per thread against
     // one, 3.67 / 4.04 (lattice 128^3, ncrit 128) and 0.61 / 0.65 (48^3, 256),
-    // though 4.45 / 3.23 where groups have five (110^3, 32).  In FP32 their six
-    // waves (80 registers) take 749 us against 807 (lattice 96^3) and 4244
-    // against 4550 (160^3).
+    // though 4.45 / 3.23 where groups have five (110^3, 32).  In FP32 a cap for
+    // their six waves (80 registers) pays where the blocks are many and the
+    // groups not too small; few blocks have the waves' room anyway, and small
+    // groups feel what the cap adds to each block.  us, uncapped / six waves, by
+    // blocks and mean group, quadrupole and monopole (the same bits):
+    //     512 of 8 19 / 25 and 19 / 21, 512 of 64 73 / 76 and 69 / 77, 2171 of 15
+    //     60 / 63 and 56 / 63, 2255 of 116 923 / 965 and 892 / 996;
+    //     4096 of 8 62 / 72 and 60 / 60, of 16 83 / 82 and 71 / 65, of 27 112 / 106
+    //     and 99 / 90, of 64 265 / 246 and 242 / 225, of 216 1379 / 1289 and 1267 /
+    //     1214; 7280 of 15.2 141 / 147 and 129 / 125;
+    //     31,557 of 3.5 352 / 393 and 336 / 340, 31,838 of 5.5 370 / 383 and 350 /
+    //     333, 32,765 of 8 407 / 403 and 372 / 344, 32,739 of 11 476 / 459 and
+    //     414 / 374, 139,361 of 15 2545 / 2406 and 2314 / 2105.
+    bool split_six_waves() const
+    {
+        const double least = ng >= 64 * (int64_t)cfg.num_cu ? 10.0 : 15.5;
+        return ng >= 12 * (int64_t)cfg.num_cu &&
+               (double)ni >= (double)ng * (kernel == BHQ_SPLIT_MONO ? 0.5 : 1.0) * least;
+    }
     struct ShapeTime {
         int block, per, waves, shape;  // the shape whose lanes' work it does
         double work, longest, blocks, fixed;
@@ -492,7 +508,7 @@ struct bhq_ctx {
         if (tuned) return c;
         const double mean = ng > 0 ? (double)ni / (double)ng : 0.0;
         if (kernel == BHQ_SPLIT_QUAD || kernel == BHQ_SPLIT_MONO) {
-            c.waves_per_eu = 6;
+            c.waves_per_eu = split_six_waves() ? 6 : 0;
             return c;
         }
         c.jsplit = auto_jsplit;
