@@ -90,7 +90,7 @@ enum Arr {
     A_AX, A_AY, A_AZ, A_POT,
     A_QUEUE,
     A_POOLP, A_POOLC, A_JPIDX, A_JCIDX,
-    A_TORDER, A_ENERGY, A_OSCRATCH, A_SORTSCRATCH, A_PART, A_PARTAUTO, A_FLAG, A_LIVE, A_CLOCK,
+    A_TORDER, A_ENERGY, A_OSCRATCH, A_SORTSCRATCH, A_PART, A_PARTAUTO, A_PARTAUTO64, A_FLAG, A_LIVE, A_CLOCK,
     A_COUNT
 };
 
@@ -387,10 +387,10 @@ struct bhq_ctx {
     // grid over 110 sets of lists (1000 to 700,000 particles).  The split
     // kernels have one part: what they compute is the same bits in every
     // default launch.
-    // The memory for the parts is taken here, so that a compute allocates
-    // nothing and a captured one keeps its address until the lists change: up to
-    // 16 MiB for bhq_compute and as much after it for bhq_compute_noalloc, whose
-    // calls may run beside each other.
+    // The memory for the parts is taken here (reserve_parts), so that a compute
+    // allocates nothing and a captured one keeps its address until the lists
+    // change: up to 16 MiB (8 in FP32) for bhq_compute and as much after it for
+    // bhq_compute_noalloc, whose calls may run beside each other.
     void plan_shape(double total, double largest, const double *work, const double *most)
     {
         std::copy(work, work + bhq::kShapes, shape_work);
@@ -404,18 +404,32 @@ struct bhq_ctx {
                total / (double)ng / (2 * j) >= 4.5e5 &&
                (size_t)(2 * j) * (size_t)ni * 32 <= bhq::kScratchPartBytes)
             j *= 2;
-        if (j > 1) {
-            const size_t bytes = 2 * (size_t)j * (size_t)ni * 32;
-            if (bytes > arr[A_PARTAUTO].cap) {
-                quiesce();
-                if (arr[A_PARTAUTO].reserve(bytes) != hipSuccess) {
-                    (void)hipGetLastError();
-                    j = 1;
-                }
-                ++args_version;
-            }
-        }
         auto_jsplit = j;
+        reserve_parts();
+    }
+    // The parts' memory, an array per precision: the current one's, and the
+    // other's once it was used, so that a change of precision moves nothing and
+    // at most takes an array that was empty.  (One array for both would be twice
+    // as long as FP32 needs; taking it is a fifth of the first call on a Plummer
+    // sphere of 100,003.)  Without the memory: one part.
+    static Arr part_array(int prec) { return prec == BHQ_FP64 ? A_PARTAUTO64 : A_PARTAUTO; }
+    size_t part_bytes(int prec, int parts) const
+    {
+        return (size_t)parts * (size_t)ni * (prec == BHQ_FP64 ? 32 : 16);
+    }
+    void reserve_parts()
+    {
+        for (int prec : {BHQ_FP32_OFS64, BHQ_FP64}) {
+            DevArray &d = arr[part_array(prec)];
+            const size_t bytes = 2 * part_bytes(prec, auto_jsplit);
+            if (auto_jsplit <= 1 || bytes <= d.cap || (prec != precision && d.cap == 0)) continue;
+            if (d.cap > 0) quiesce();
+            if (d.reserve(bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                auto_jsplit = 1;
+            }
+            ++args_version;
+        }
     }
     void plan_shape(const volatile int64_t *stats)
     {
@@ -752,7 +766,15 @@ int bhq_set_kernel(bhq_ctx *ctx, int kernel, int precision)
         return ctx->fail(BHQ_E_ARG, "bhq_set_kernel: unknown kernel %d or "
                                     "precision %d", kernel, precision);
     ctx->kernel = kernel;
-    ctx->precision = precision;
+    if (precision != ctx->precision) {
+        ctx->precision = precision;
+        TRY(ctx->select());
+        // the caller may be capturing a stream
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        ctx->reserve_parts();
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
     return BHQ_OK;
 }
 
@@ -1047,7 +1069,7 @@ int bhq_compute(bhq_ctx *ctx, void *stream)
     const bhq::LaunchCfg cfg = ctx->shape();
 
     if (!ctx->tuned) {
-        A.part = ctx->arr[A_PARTAUTO].p;
+        A.part = ctx->arr[bhq_ctx::part_array(ctx->precision)].p;
     } else if (cfg.jsplit > 1) {
         // parts of every i-particle's sums (32 B per entry covers FP64)
         const size_t bytes = (size_t)cfg.jsplit * (size_t)ctx->ni * 32;
@@ -1153,7 +1175,8 @@ int bhq_compute_noalloc(bhq_ctx *ctx, double *a, double *pot, void *stream)
     A.pot = pot;
     A.out_stride = 3;
     A.queue = reinterpret_cast<unsigned int *>(sp);
-    A.part = own ? ctx->arr[A_PARTAUTO].as<char>() + (size_t)cfg.jsplit * (size_t)ctx->ni * 32
+    A.part = own ? ctx->arr[bhq_ctx::part_array(ctx->precision)].as<char>() +
+                       ctx->part_bytes(ctx->precision, cfg.jsplit)
                  : sp + bhq::kScratchQueueBytes;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = hipEventRecord(ctx->ev0, s);
