@@ -52,9 +52,8 @@ FLOPS_PP = 20
 FLOPS_PC = {bhq.QUAD: 53, bhq.MONO: 20, bhq.QUAD_SOFT: 55}
 # FP32 split kernels, per term inside the cutoff (FMA = 2, rsqrt and fract 1,
 # the table index conversion 0): particle term 36 (separation 8, rsqrt 1,
-# r 1, table variable and fraction 2, erfc, its derivative and g 12, the rest
-# 12);
-# quadrupole cell term 97 (the same start, erfc to k and G2, G3 24, D1..D3,
+# r 1, table variable and fraction 2, erfc and g by Horner 12, the rest 12);
+# quadrupole cell term 97 (the same start, four Horner functions 24, D1..D3,
 # Q d and d.Q.d, the trace terms and the accumulation); monopole cell 37.
 # Masked terms (beyond the cutoff) do no work of the method and are not
 # counted: the split roofline is priced on the pairs bhq_count_live finds.
@@ -67,7 +66,8 @@ FLOPS_SPLIT_PC = {bhq.SPLIT_QUAD: 97, bhq.SPLIT_MONO: 37}
 # term 123 (the particle term's radial part plus u^2, h, k, G2 and G3 12,
 # and the FP32 cell term's other 71); monopole cell 63.  The price is kept:
 # the kernels now spend two operations fewer (one polynomial and its
-# derivative).
+# derivative: 60, 121 and 61), so FP64 split rates are stated about 3 % above
+# the arithmetic done.
 FLOPS_SPLIT64_PP = 62
 FLOPS_SPLIT64_PC = {bhq.SPLIT_QUAD: 123, bhq.SPLIT_MONO: 63}
 # the paper's convention for one particle-cell quadrupole interaction

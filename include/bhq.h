@@ -105,7 +105,7 @@ int bhq_destroy(bhq_ctx *ctx);
  * quadrupole cells (Sec. 3, eqs. 1, 4-7), monopole cells (the monopole
  * program of Secs. 4-5), the complete softened quadrupole, or the split
  * kinds (no counterpart in the paper); FP32 with FP64 offsets or FP64.
- * Errors: BHQ_E_ARG for an unknown kernel or precision. */
+ * Errors: BHQ_E_ARG for an unknown kernel or precision, BHQ_E_HIP. */
 int bhq_set_kernel(bhq_ctx *ctx, int kernel, int precision);
 
 /* One softening length for every i-particle: eps^2 = eps * eps (the
@@ -131,7 +131,8 @@ int bhq_set_eps2_i(bhq_ctx *ctx, int64_t ni, const double *eps2);
  * r / (2 r_s) <= 2.5 only, so bhq_compute returns BHQ_E_ARG for FP32 with
  * rcut > 5 r_s (FP64 has no such limit: it takes erfc(u) and, as its
  * derivative, exp(-u^2) from a table of polynomials up to u = 4 and calls the
- * library's exp and erfc beyond).  In a periodic box every group cell plus 2 rcut must stay below half the box. */
+ * library's exp and erfc beyond).  In a periodic box every group cell plus
+ * 2 rcut must stay below half the box. */
 int bhq_set_split(bhq_ctx *ctx, double rs, double rcut, double box);
 
 /* Define the groups and the list sizes; must precede set_i / set_jp /

@@ -10,7 +10,8 @@
 //      at integer multiples of h): the particles are radix-sorted by their
 //      nearest mesh point, and a thread per column of mesh points sums, in a
 //      fixed order, the particles of the 27 cells around each (no atomics:
-//      the result is the same bits every run);
+//      the result is the same bits every run); a wave per mesh point does so
+//      around crowded cells;
 //   2. forward real-to-complex FFT (hipFFT);
 //   3. one thread per complex mode: phi(k) = G(k) rho(k) with
 //      G = -4 pi exp(-k^2 r_s^2) / k^2 / W(k)^2, W = prod_a sinc(k_a h/2)^3
@@ -20,7 +21,7 @@
 //   5. one thread per particle, in the sorted order, interpolates the four
 //      meshes with the same TSC weights and writes its result at the
 //      particle's input position.  A block takes the particles of a tile of
-//      2 x 8 x 16 cells, with the fields at the tile's mesh points and their
+//      4 x 8 x 16 cells, with the fields at the tile's mesh points and their
 //      neighbours in LDS.
 // All FP64.
 #include <hip/hip_runtime.h>
@@ -213,7 +214,6 @@ constexpr int kPlane = kPY * kPZ;
 constexpr int kPlaneCap = 448;
 static_assert(kRY * kRZ == kBlock, "a column per thread");
 
-//
 // A thread goes over the particles of its cells one by one, so a block is as
 // long as its fullest cells: a block with a cell of more than kCrowded
 // particles among those it looks at leaves its points to k_rho_crowded

@@ -1,8 +1,8 @@
 // bhq_sort.h -- stable sort of up to kRankSortMost (key, index) pairs by key
 // bits (device code), for the sizes at which a device sort's time is its
 // launches: blocks sort tiles of 1024 to 4096 keys, which they read or form
-// themselves, and one or two launches merge up to eight sorted runs each, every element finding its place by its rank in the other
-// runs.
+// themselves, and one or two launches merge up to eight sorted runs each,
+// every element finding its place by its rank in the other runs.
 //
 // Bound by the chain of dependent loads of the ranks' binary searches; the
 // up to eight searches of an element go side by side (one after another they

@@ -24,7 +24,7 @@ __device__ __forceinline__ double exp_r(double v) { return ::exp(v); }
 // A pair then reads 80 B from LDS in place of the 144 of two polynomials
 // (exp(-u^2) and erfcx); LDS bound the kernel (busy 66 % of the time and 15 %
 // more in bank conflicts, VALU 72 %): the force kernel of a 60^3 lattice took
-// 0.64 ms, now 0.56.  The coefficients are rounded to FP64 once, from 50
+// 0.64 ms, then 0.56 (0.48 with far_g below).  The coefficients are rounded to FP64 once, from 50
 // digits: against 64 bits and more the functions' r.m.s. errors (absolute,
 // 1e-17, random r_s) are 2.9 (erfc), 5.3 (g), 7.5 / 3 (G2) and 8.9 / 15 (G3), those
 // of the two polynomials 5.8, 7.5, 9.4 and 10.5; coefficients formed in FP64
@@ -65,11 +65,10 @@ static_assert(kErfcDomain == kTab64Domain && kErfcIntervals == 2 * kTab64Interva
 
 // The FP32 table of the split radial functions (split_table.h), one V4
 // {c0, c1, c2, c3} per function and interval, likewise copied to LDS, where
-// lanes read their own intervals.  One
-// cubic of erfc on 641 intervals whose derivative gives the other functions
-// reads half as much from LDS (a cell a quarter) and was 2 to 4 % faster, but
-// its errors were larger: 1.1 (erfc) to 1.25 (G3) times these cubics' r.m.s.
-// over random r_s.
+// lanes read their own intervals.  One cubic of erfc on 641 intervals whose
+// derivative gives the other functions reads half as much from LDS (a cell a
+// quarter) and was 2 to 4 % faster, but its errors were larger: 1.1 (erfc) to
+// 1.25 (G3) times these cubics' r.m.s. over random r_s.
 struct SplitTab {
     V4<float> v[kSplitFuncs * kSplitEntries];
 };

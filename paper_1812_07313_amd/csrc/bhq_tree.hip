@@ -336,8 +336,12 @@ __global__ __launch_bounds__(kBlock) void k_keys_root(const double *x, int64_t n
 // chip (Plummer spheres of 2048 and 16,384: 28 and 31 us for both with four).
 constexpr int kPerLarge = 4;
 constexpr int64_t kSmallTree = 65536;
-constexpr int kWinMost = 4096;         // longest window k_split holds in LDS
-constexpr int kRows = kMaxDepth + 2;   // depths 0 .. 21 and the groups
+// Longest window k_split holds in LDS.  With leaves of more particles (up to
+// nleaf) each particle's window is read from memory: a build of 10^6 particles
+// takes 11.5 ms at nleaf 5000, 16.3 at 8000 and 88 at 50,000 (1530 and 2750 at
+// the first two with a pass per level).
+constexpr int kWinMost = 4096;
+constexpr int kRows = kMaxDepth + 2;  // depths 0 .. 21 and the groups
 
 // What the build needs of a sorted key array: key(k) = (v[k] & mask) << lo.
 struct SortedKeys {
@@ -1170,9 +1174,9 @@ enum WalkMode { kWalkCount = 0, kWalkFill = 1, kWalkSlots = 2 };
 // LDS keeps 16 B per octet, so that occupancy is not bound by it: the first
 // child's id, the number of the first octet opened (16 bits) over the
 // children's kinds (2 bits each), and the totals (summed by one lane per
-// octet), replaced by the octet's position on the way down.  `cap` octets fit: a group that opens more sets
-// *W.flag = 2 (its other cells are left out) and the host walks again with
-// the octet walk.
+// octet), replaced by the octet's position on the way down.  `cap` octets fit:
+// a group that opens more sets *W.flag = 2 (its other cells are left out) and
+// the host walks again with the octet walk.
 // A rebuild's walk took 0.75 ms on the cube of 10^6, 4.6 on the 2^24 lattice
 // at ncrit 128 and 0.65 on a Plummer sphere of 16,384 (989 groups, each a
 // chain of about 200 openings) with the octet walk, and 0.20, 3.3 and 0.042
